@@ -215,6 +215,8 @@ void Batch::init(int n, const kfbi_interface *ifaces, const kfbi_grid *grids, co
       for (int a = 0; a < 3; ++a) m.D0[a] = m.D1[a] = p.D[0][a];
       m.kappa = p.kappa;
       m.norm = p.lam_scale;
+      m.h2 = p.h * p.h;
+      g.direct = g.direct && p.direct;
       ms.push_back(m);
     }
     g.msv = balloc<ModeParams>(ms.size());
@@ -327,8 +329,8 @@ void Batch::init(int n, const kfbi_interface *ifaces, const kfbi_grid *grids, co
   for (Group &g : groups) {
     const DevProblem &p0 = *probs[g.members[0]];
     const int G = (int)g.members.size();
-    autotune_group<double>(g.Mfft, G, g.work64, g.cs, g.msv, p0.f64.tw, p0.f64.sp, g.tile_w[0], cap);
-    autotune_group<float>(g.Mfft, G, g.work32, g.cs, g.msv, p0.f32.tw, p0.f32.sp, g.tile_w[1], cap);
+    autotune_group<double>(g.Mfft, G, g.work64, g.cs, g.msv, p0.f64.tw, p0.f64.sp, g.tile_w[0], g.direct, cap);
+    autotune_group<float>(g.Mfft, G, g.work32, g.cs, g.msv, p0.f32.tw, p0.f32.sp, g.tile_w[1], g.direct, cap);
   }
 }
 
@@ -386,17 +388,19 @@ void Batch::box_all(bool from_fpad, hipStream_t st) {
   if (merged && mergeable()) {
     MultiGroupDesc d[kMaxMultiGroups];
     int k = 0;
+    bool direct = true;
     for (const Group &g : groups) {
+      direct = direct && g.direct;
       const PrecTables<T> &tb = const_cast<DevProblem &>(*probs[g.members[0]]).tab<T>();
       d[k++] = MultiGroupDesc{g.Mfft, (int)g.members.size(), g.cs, src_of(g), g.work<T>(), g.msv, tb.tw, tb.sp};
     }
-    box_solve_multi<T>(d, k, st);
+    box_solve_multi<T>(d, k, direct, st);
     return;
   }
   for (const Group &g : groups) {
     const PrecTables<T> &tb = const_cast<DevProblem &>(*probs[g.members[0]]).tab<T>();
     box_solve_group<T>(g.Mfft, (int)g.members.size(), src_of(g), g.work<T>(), g.cs, g.msv, tb.tw, tb.sp,
-                       g.tile_w[sizeof(T) == 8 ? 0 : 1], st);
+                       g.tile_w[sizeof(T) == 8 ? 0 : 1], g.direct, st);
   }
 }
 

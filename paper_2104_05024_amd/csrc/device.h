@@ -114,6 +114,7 @@ struct DevProblem {
   // sparse matvec box solve (3D): rows of the flattened [comp][z][y] row list that carry
   // irregular nodes (in) / extrapolation-stencil nodes (out), and their [z][y] byte masks
   bool sparse = true;
+  bool direct = false;         // last axis as tridiagonal systems (column_direct) instead of DSTs
   int32_t *rows_in = nullptr, *rows_out = nullptr;
   int64_t n_rows_in = 0, n_rows_out = 0;
   uint64_t *mask_in = nullptr, *mask_out = nullptr;     // [z][16] bit rows: y rows with rhs / stencil nodes
@@ -152,6 +153,7 @@ inline PrecTables<float> &DevProblem::tab<float>() { return f32; }
 struct ModeParams {
   const double *lam;
   double D0[3], D1[3], kappa, norm;   // conductivity per axis of component 0 and 1
+  double h2;                          // h^2 (the direct last-axis solve)
 };
 
 // One two-dimensional, one-component problem of a batch as the batched interface kernels see
@@ -299,10 +301,10 @@ template <typename T>
 void launch_batch_gather(const BatchItem<T> *items, const BatchCounts &c, bool with_jumps, double *out,
                          hipStream_t st);
 // Grouped 2D box solve of G equal-size problems (padded layout, stride cs, msv on the device).
-// w: tile widths of the x and last-axis passes (w[0], w[2]).
+// w: tile widths of the x and last-axis passes (w[0], w[2]); direct: the last axis solved directly.
 template <typename T>
 void box_solve_group(int Mfft, int G, const T *src, T *dst, int64_t cs, const ModeParams *msv, const T *tw,
-                     const T *sp, const int *w, hipStream_t st);
+                     const T *sp, const int *w, bool direct, hipStream_t st);
 // Merged 2D box solve of several such groups (each with its own size): one launch per pass for
 // all groups together, so the tiles of small grids run beside those of large ones instead of in
 // launches of their own that cannot fill the GPU.  Sizes 64..1024, tile width 1; the groups are
@@ -317,14 +319,44 @@ struct MultiGroupDesc {
   const void *tw = nullptr, *sp = nullptr;
 };
 constexpr int kMaxMultiGroups = 8;
+// direct: the last axis of every group is solved directly (last_axis_direct_multi).
 template <typename T>
-void box_solve_multi(const MultiGroupDesc *groups, int ngroups, hipStream_t st);
+void box_solve_multi(const MultiGroupDesc *groups, int ngroups, bool direct, hipStream_t st);
+
+// The last axis of a box solve as tridiagonal systems along its columns (lastaxis.hip): in -> out
+// (may alias), padded layout.  Forms as in the DST pass: 0-2 by the plane sets given (none; both;
+// zout alone), 3-5 those of a bidomain step.
+template <typename T>
+struct LastAxis {
+  const T *in = nullptr;
+  T *out = nullptr;
+  int dim = 3, ncomp = 1, M = 0;
+  int64_t cs = 0;                       // component stride
+  ModeParams ms{};
+  const ModeParams *msv = nullptr;      // 2D: per-problem parameters of nprob fields at stride pstride
+  int nprob = 1;
+  int64_t pstride = 0;
+  const PlaneBits *zin = nullptr, *zout = nullptr;
+  int form = 0;
+  const T *in2 = nullptr;
+};
+// Whether the columns are solved directly: where the slowest mode decays across the box,
+// s M^2 >= 2 (the isotropic boxes have 9.9 in 2D and 19.7 in 3D).  Below that the direct solve's
+// starting values come out of a difference of nearly equal sums (relative error in the lowest
+// mode about 2e-15 at s M^2 = 2 and 6e-14 at 0.1, against the DST's 5e-16), so boxes whose
+// conductivity along the last axis is more than five (2D) or ten (3D) times the others' keep the
+// DST; so do reaction terms so large (s >= 1e12) that mu drops out of the recursions.
+bool column_direct(int dim, int ncomp, int M, double h, const double D[2][3], double kappa);
+template <typename T>
+void last_axis_direct(const LastAxis<T> &l, hipStream_t st);
+template <typename T>
+void last_axis_direct_multi(const MultiGroupDesc *groups, int ngroups, hipStream_t st);
 // Autotuner: time each dense pass at both tile widths and keep the faster (cached per process
 // by dimension, grid size, components and precision); clears the work buffers afterwards.
 void autotune_tiles(DevProblem &p, hipStream_t st);
 template <typename T>
 void autotune_group(int Mfft, int G, T *a, int64_t cs, const ModeParams *msv, const T *tw, const T *sp, int *w,
-                    hipStream_t st);
+                    bool direct, hipStream_t st);
 
 void upload_tables(DevProblem &p);
 void free_tables(DevProblem &p);

@@ -1419,7 +1419,34 @@ ModeScale mode_of(const DevProblem &p) {
   }
   m.kappa = p.kappa;
   m.norm = p.lam_scale;
+  m.h2 = p.h * p.h;
   return m;
+}
+
+// The last axis of one problem, from in (null: a itself) to a: as tridiagonal systems, or by the
+// fused DST pass where those would be less accurate (column_direct).
+template <typename T, int M>
+void solve_last(DevProblem &p, T *a, hipStream_t st, const T *in = nullptr, const PlaneBits *zin = nullptr,
+                const PlaneBits *zout = nullptr, int form = 0, const T *in2 = nullptr) {
+  PrecTables<T> &tb = p.tab<T>();
+  if (p.direct) {
+    LastAxis<T> l;
+    l.in = in ? in : a;
+    l.out = a;
+    l.dim = p.dim;
+    l.ncomp = p.ncomp;
+    l.M = M;
+    l.cs = p.comp_stride;
+    l.ms = mode_of<T>(p);
+    l.zin = zin;
+    l.zout = zout;
+    l.form = form;
+    l.in2 = in2;
+    last_axis_direct<T>(l, st);
+    return;
+  }
+  pass_last<T, M>(p.tile_w[prec_index<T>()][2], a, p.dim, p.ncomp, p.P, p.comp_stride, mode_of<T>(p),
+                  reinterpret_cast<const C2<T> *>(tb.tw), tb.sp, nullptr, 1, 0, st, in, zin, zout, form, in2);
 }
 
 // skip & 1: work already holds the forward x pass of the source (src unused); skip & 2: stop
@@ -1434,7 +1461,6 @@ void run_box(DevProblem &p, const T *src, bool src_plain, T *dst, bool dst_plain
   const int64_t P = p.P, cs = p.comp_stride;
   const int64_t rows = (int64_t)p.ncomp * (p.dim == 3 ? (int64_t)N * N : N);
   const int *w = p.tile_w[prec_index<T>()];
-  const ModeScale ms = mode_of<T>(p);
   auto tic = [&](Timer &t) { t.tic(p.profile, st); };
   auto toc = [&](Timer &t) { t.toc(p.profile, st); };
   if (!(skip & 1)) {
@@ -1448,7 +1474,7 @@ void run_box(DevProblem &p, const T *src, bool src_plain, T *dst, bool dst_plain
     toc(p.t_dst_y);
   }
   tic(p.t_dst_last);
-  pass_last<T, M>(w[2], A, p.dim, p.ncomp, P, cs, ms, tw, sp, nullptr, 1, 0, st);
+  solve_last<T, M>(p, A, st);
   toc(p.t_dst_last);
   if (p.dim == 3) {
     tic(p.t_dst_y);
@@ -1478,7 +1504,6 @@ void run_box_stencils(DevProblem &p, const T *src, hipStream_t st, bool skip_x =
   const int64_t P = p.P, cs = p.comp_stride;
   const int64_t rows = (int64_t)p.ncomp * N * N;
   const int *w = p.tile_w[prec_index<T>()];
-  const ModeScale ms = mode_of<T>(p);
   auto tic = [&](Timer &t) { t.tic(p.profile, st); };
   auto toc = [&](Timer &t) { t.toc(p.profile, st); };
   if (!skip_x) {
@@ -1496,14 +1521,14 @@ void run_box_stencils(DevProblem &p, const T *src, hipStream_t st, bool skip_x =
     pass_y<T, M>(w[1], G, G, P, cs, 1, nullptr, nullptr, tw, sp, st);
     toc(p.t_dst_y1);
     tic(p.t_dst_last_anti);
-    pass_last<T, M>(w[2], A, 3, p.ncomp, P, cs, ms, tw, sp, nullptr, 1, 0, st, G, nullptr, &p.planes_out_bits, 3);
+    solve_last<T, M>(p, A, st, G, nullptr, &p.planes_out_bits, 3);
     toc(p.t_dst_last_anti);
   } else {
     tic(p.t_dst_y);
     pass_y<T, M>(w[1], A, A, P, cs, p.ncomp, nullptr, nullptr, tw, sp, st);
     toc(p.t_dst_y);
     tic(p.t_dst_last_out);
-    pass_last<T, M>(w[2], A, 3, p.ncomp, P, cs, ms, tw, sp, nullptr, 1, 0, st, nullptr, nullptr, &p.planes_out_bits);
+    solve_last<T, M>(p, A, st, nullptr, nullptr, &p.planes_out_bits);
     toc(p.t_dst_last_out);
   }
   tic(p.t_dst_y_sparse);
@@ -1589,8 +1614,7 @@ void run_bidomain_final(DevProblem &p, const FhnArgs &a, bool fuse_be, hipStream
         pass_y<double, M>(w[1], X, Y, P, cs, 2, p.mask_in, nullptr, tw, tb.sp, st, p.planes_in);
         p.t_dst_y_sparse.toc(p.profile, st);
         p.t_dst_last_comb.tic(p.profile, st);
-        pass_last<double, M>(w[2], A, 3, 2, P, cs, mode_of<double>(p), tw, tb.sp, nullptr, 1, 0, st, tb.gbuf,
-                             &p.planes_in_bits, nullptr, 5, Y);
+        solve_last<double, M>(p, A, st, tb.gbuf, &p.planes_in_bits, nullptr, 5, Y);
         p.t_dst_last_comb.toc(p.profile, st);
       } else {
         launch_x_fhn<M, FHN_SRC>(p, a, st);
@@ -1598,8 +1622,7 @@ void run_bidomain_final(DevProblem &p, const FhnArgs &a, bool fuse_be, hipStream
         pass_y<double, M>(w[1], A, A, P, cs, 2, nullptr, nullptr, tw, tb.sp, st);
         p.t_dst_y.toc(p.profile, st);
         p.t_dst_last_diff.tic(p.profile, st);
-        pass_last<double, M>(w[2], A, 3, 2, P, cs, mode_of<double>(p), tw, tb.sp, nullptr, 1, 0, st, nullptr, nullptr,
-                             nullptr, 4);
+        solve_last<double, M>(p, A, st, nullptr, nullptr, nullptr, 4);
         p.t_dst_last_diff.toc(p.profile, st);
       }
       p.t_dst_y1.tic(p.profile, st);
@@ -1634,7 +1657,6 @@ void run_box_sparse(DevProblem &p, hipStream_t st) {
   const T *sp = tb.sp;
   const int64_t P = p.P, cs = p.comp_stride;
   const int *w = p.tile_w[prec_index<T>()];
-  const ModeScale ms = mode_of<T>(p);
   auto tic = [&](Timer &t) { t.tic(p.profile, st); };
   auto toc = [&](Timer &t) { t.toc(p.profile, st); };
   const unsigned gin = (unsigned)((p.n_rows_in + 2 * Sh::NP - 1) / (2 * Sh::NP));
@@ -1650,7 +1672,7 @@ void run_box_sparse(DevProblem &p, hipStream_t st) {
   tic(p.t_dst_last_sparse);
   // planes without rhs rows are zero in Y (not read); only planes with stencil rows are used
   // by the inverse passes (only those are written)
-  pass_last<T, M>(w[2], A, 3, p.ncomp, P, cs, ms, tw, sp, nullptr, 1, 0, st, Y, &p.planes_in_bits, &p.planes_out_bits);
+  solve_last<T, M>(p, A, st, Y, &p.planes_in_bits, &p.planes_out_bits);
   toc(p.t_dst_last_sparse);
   tic(p.t_dst_y_sparse);
   pass_y<T, M>(w[1], A, A, P, cs, p.ncomp, nullptr, p.mask_out, tw, sp, st, p.planes_out);
@@ -1665,13 +1687,24 @@ void run_box_sparse(DevProblem &p, hipStream_t st) {
 // padded layout: one launch per pass for the whole group.
 template <typename T, int M>
 void run_box_group(int G, const T *src, T *dst, int64_t cs, const ModeParams *msv, const T *tw_, const T *sp,
-                   const int *w, hipStream_t st) {
+                   const int *w, bool direct, hipStream_t st) {
   constexpr int N = M - 1;
   const C2<T> *tw = reinterpret_cast<const C2<T> *>(tw_);
   const int64_t rows = (int64_t)G * N;
   if (cs != (int64_t)N * M) throw std::invalid_argument("group stride");
   pass_x<T, M>(w[0], src, false, dst, false, rows, tw, sp, st);
-  pass_last<T, M>(w[2], dst, 2, 1, M, cs, ModeParams{}, tw, sp, msv, G, cs, st);
+  if (direct) {
+    LastAxis<T> l;
+    l.in = l.out = dst;
+    l.dim = 2;
+    l.M = M;
+    l.msv = msv;
+    l.nprob = G;
+    l.pstride = cs;
+    last_axis_direct<T>(l, st);
+  } else {
+    pass_last<T, M>(w[2], dst, 2, 1, M, cs, ModeParams{}, tw, sp, msv, G, cs, st);
+  }
   pass_x<T, M>(w[0], dst, false, dst, false, rows, tw, sp, st);
 }
 
@@ -1803,13 +1836,13 @@ float time_pass(int pass, int w, T *a, int dim, int ncomp, int64_t P, int64_t cs
 // that clock and cache drift affect both alike; the median of each decides.
 template <typename T, int M>
 void tune(int *w, T *a, int dim, int ncomp, int64_t P, int64_t cs, int64_t rows, const ModeScale &ms,
-          const C2<T> *tw, const T *sp, const ModeScale *msv, int nprob, hipStream_t st) {
+          const C2<T> *tw, const T *sp, const ModeScale *msv, int nprob, bool direct, hipStream_t st) {
   constexpr int kRounds = 7;
   hipEvent_t e0, e1;
   KFBI_HIP(hipEventCreate(&e0));
   KFBI_HIP(hipEventCreate(&e1));
   for (int pass = 0; pass < 3; ++pass) {
-    if (pass == 1 && dim != 3) continue;
+    if ((pass == 1 && dim != 3) || (pass == 2 && direct)) continue;   // not run by these solves
     float t[2][kRounds];
     for (int r = -2; r < kRounds; ++r)
       for (int k = 0; k < 2; ++k) {
@@ -1835,7 +1868,7 @@ void autotune_prec(DevProblem &p, hipStream_t st) {
   int *w = p.tile_w[prec_index<T>()];
   switch (p.Mfft) {
 #define KFBI_TUNE_CASE(MM) \
-    case MM: tune<T, MM>(w, A, p.dim, p.ncomp, p.P, p.comp_stride, rows, ms, tw, tb.sp, nullptr, 1, st); break;
+    case MM: tune<T, MM>(w, A, p.dim, p.ncomp, p.P, p.comp_stride, rows, ms, tw, tb.sp, nullptr, 1, p.direct, st); break;
     KFBI_TUNE_CASE(16) KFBI_TUNE_CASE(32) KFBI_TUNE_CASE(64) KFBI_TUNE_CASE(128) KFBI_TUNE_CASE(256)
     KFBI_TUNE_CASE(512) KFBI_TUNE_CASE(1024)
 #undef KFBI_TUNE_CASE
@@ -1848,9 +1881,9 @@ void autotune_prec(DevProblem &p, hipStream_t st) {
 // Tile widths per (dimension, grid size, components, precision): measured once per process.
 void autotune_tiles(DevProblem &p, hipStream_t st) {
   static std::mutex mu;
-  static std::map<std::array<int, 4>, std::array<int, 3>> cache;
+  static std::map<std::array<int, 5>, std::array<int, 3>> cache;
   for (int prec = 0; prec < 2; ++prec) {
-    const std::array<int, 4> key{p.dim, (int)p.Mfft, p.ncomp, prec};
+    const std::array<int, 5> key{p.dim, (int)p.Mfft, p.ncomp, prec, p.direct};
     {
       std::lock_guard<std::mutex> lk(mu);
       auto it = cache.find(key);
@@ -1874,12 +1907,12 @@ void autotune_tiles(DevProblem &p, hipStream_t st) {
 // Batched groups: widths of the x and last-axis passes for one group, timed on its buffers.
 template <typename T>
 void autotune_group(int Mfft, int G, T *a, int64_t cs, const ModeParams *msv, const T *tw_, const T *sp, int *w,
-                    hipStream_t st) {
+                    bool direct, hipStream_t st) {
   const C2<T> *tw = reinterpret_cast<const C2<T> *>(tw_);
   const int64_t rows = (int64_t)G * (Mfft - 1);
   switch (Mfft) {
 #define KFBI_TUNE_CASE(MM) \
-    case MM: tune<T, MM>(w, a, 2, 1, MM, cs, rows, ModeParams{}, tw, sp, msv, G, st); break;
+    case MM: tune<T, MM>(w, a, 2, 1, MM, cs, rows, ModeParams{}, tw, sp, msv, G, direct, st); break;
     KFBI_TUNE_CASE(16) KFBI_TUNE_CASE(32) KFBI_TUNE_CASE(64) KFBI_TUNE_CASE(128) KFBI_TUNE_CASE(256)
     KFBI_TUNE_CASE(512) KFBI_TUNE_CASE(1024)
 #undef KFBI_TUNE_CASE
@@ -1889,26 +1922,26 @@ void autotune_group(int Mfft, int G, T *a, int64_t cs, const ModeParams *msv, co
   KFBI_HIP(hipStreamSynchronize(st));
 }
 template void autotune_group<double>(int, int, double *, int64_t, const ModeParams *, const double *,
-                                     const double *, int *, hipStream_t);
+                                     const double *, int *, bool, hipStream_t);
 template void autotune_group<float>(int, int, float *, int64_t, const ModeParams *, const float *, const float *,
-                                    int *, hipStream_t);
+                                    int *, bool, hipStream_t);
 
 template <typename T>
 void box_solve_group(int Mfft, int G, const T *src, T *dst, int64_t cs, const ModeParams *msv, const T *tw,
-                     const T *sp, const int *w, hipStream_t st) {
+                     const T *sp, const int *w, bool direct, hipStream_t st) {
   switch (Mfft) {
-    case 16: run_box_group<T, 16>(G, src, dst, cs, msv, tw, sp, w, st); break;
-    case 32: run_box_group<T, 32>(G, src, dst, cs, msv, tw, sp, w, st); break;
-    case 64: run_box_group<T, 64>(G, src, dst, cs, msv, tw, sp, w, st); break;
-    case 128: run_box_group<T, 128>(G, src, dst, cs, msv, tw, sp, w, st); break;
-    case 256: run_box_group<T, 256>(G, src, dst, cs, msv, tw, sp, w, st); break;
-    case 512: run_box_group<T, 512>(G, src, dst, cs, msv, tw, sp, w, st); break;
-    case 1024: run_box_group<T, 1024>(G, src, dst, cs, msv, tw, sp, w, st); break;
+    case 16: run_box_group<T, 16>(G, src, dst, cs, msv, tw, sp, w, direct, st); break;
+    case 32: run_box_group<T, 32>(G, src, dst, cs, msv, tw, sp, w, direct, st); break;
+    case 64: run_box_group<T, 64>(G, src, dst, cs, msv, tw, sp, w, direct, st); break;
+    case 128: run_box_group<T, 128>(G, src, dst, cs, msv, tw, sp, w, direct, st); break;
+    case 256: run_box_group<T, 256>(G, src, dst, cs, msv, tw, sp, w, direct, st); break;
+    case 512: run_box_group<T, 512>(G, src, dst, cs, msv, tw, sp, w, direct, st); break;
+    case 1024: run_box_group<T, 1024>(G, src, dst, cs, msv, tw, sp, w, direct, st); break;
     default: throw std::invalid_argument("unsupported grid size");
   }
 }
 template <typename T>
-void box_solve_multi(const MultiGroupDesc *gd, int ng, hipStream_t st) {
+void box_solve_multi(const MultiGroupDesc *gd, int ng, bool direct, hipStream_t st) {
   if (ng < 1 || ng > kMaxMultiGroups) throw std::invalid_argument("merged passes take 1 to 8 groups");
   // largest grids first: their long-running tiles start first, the small ones fill in after
   int order[kMaxMultiGroups];
@@ -1938,18 +1971,19 @@ void box_solve_multi(const MultiGroupDesc *gd, int ng, hipStream_t st) {
   constexpr int NT = Shape<T, 64>::NT;
   k_dst_x_multi<T><<<bx, NT, 0, st>>>(x1);
   KFBI_HIP(hipGetLastError());
-  k_dst_last_multi<T><<<bl, NT, 0, st>>>(la);
+  if (direct) last_axis_direct_multi<T>(gd, ng, st);
+  else k_dst_last_multi<T><<<bl, NT, 0, st>>>(la);
   KFBI_HIP(hipGetLastError());
   k_dst_x_multi<T><<<bx, NT, 0, st>>>(x2);
   KFBI_HIP(hipGetLastError());
 }
-template void box_solve_multi<double>(const MultiGroupDesc *, int, hipStream_t);
-template void box_solve_multi<float>(const MultiGroupDesc *, int, hipStream_t);
+template void box_solve_multi<double>(const MultiGroupDesc *, int, bool, hipStream_t);
+template void box_solve_multi<float>(const MultiGroupDesc *, int, bool, hipStream_t);
 
 template void box_solve_group<double>(int, int, const double *, double *, int64_t, const ModeParams *,
-                                      const double *, const double *, const int *, hipStream_t);
+                                      const double *, const double *, const int *, bool, hipStream_t);
 template void box_solve_group<float>(int, int, const float *, float *, int64_t, const ModeParams *, const float *,
-                                     const float *, const int *, hipStream_t);
+                                     const float *, const int *, bool, hipStream_t);
 
 template <typename T>
 void box_solve(DevProblem &p, const T *src, bool src_plain, T *dst, bool dst_plain, hipStream_t st) {
