@@ -37,8 +37,6 @@ struct PrecTables {          // per-precision device copies of the numeric table
   T *arm_d = nullptr, *arm_s = nullptr;  // arm offsets [narm]; s D_{c,a} / h^2 [comp][narm]
   T *tw = nullptr, *sp = nullptr;        // DST twiddles exp(-2 pi i m/M) (complex) and sin(pi n/M)
   T *rhs = nullptr, *work = nullptr;     // matvec right-hand side (zero off irregular nodes), work field
-  T *xbuf = nullptr;                     // sparse matvec: x-forward output, zero outside the rhs rows
-  T *ybuf = nullptr;                     // sparse matvec: y-forward output, zero in planes without rhs rows
   T *gbuf = nullptr;                     // coupled 3D FP64: x-y transform of kappa V1 (one component),
                                          // kept from a step's volume solve for its final solve
   T *jz = nullptr;                       // jumps at crossings [comp][2][nc] (written in this precision)

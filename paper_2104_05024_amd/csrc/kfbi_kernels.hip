@@ -473,10 +473,6 @@ void upload_prec(DevProblem &p, PrecTables<T> &tb, const NumTables &h) {
   KFBI_HIP(hipMemset(tb.rhs, 0, field * sizeof(T)));
   KFBI_HIP(hipMemset(tb.work, 0, field * sizeof(T)));
   if (p.dim == 3) {
-    tb.xbuf = dalloc<T>(field);
-    KFBI_HIP(hipMemset(tb.xbuf, 0, field * sizeof(T)));
-    tb.ybuf = dalloc<T>(field);
-    KFBI_HIP(hipMemset(tb.ybuf, 0, field * sizeof(T)));
     if (fits && p.ncomp == 2) {
       tb.gbuf = dalloc<T>((size_t)p.comp_stride);
       KFBI_HIP(hipMemset(tb.gbuf, 0, (size_t)p.comp_stride * sizeof(T)));
@@ -490,7 +486,7 @@ void upload_prec(DevProblem &p, PrecTables<T> &tb, const NumTables &h) {
 template <typename T>
 void free_prec(PrecTables<T> &tb) {
   T **all[] = {&tb.z_A, &tb.z_B, &tb.q_wg, &tb.q_c, &tb.q_G, &tb.arm_d, &tb.arm_s, &tb.st_nw, &tb.st_r,
-               &tb.tw, &tb.sp, &tb.rhs, &tb.work, &tb.xbuf, &tb.ybuf, &tb.gbuf, &tb.jz, &tb.jq};
+               &tb.tw, &tb.sp, &tb.rhs, &tb.work, &tb.gbuf, &tb.jz, &tb.jq};
   for (T **q : all) {
     if (*q) (void)hipFree(*q);
     *q = nullptr;
