@@ -154,9 +154,9 @@ int kfbi_table(kfbi_problem p, const char *name, void *dst, int64_t *count, int3
  * nodes (Sec. 5.3 eq. correct), DST-I box solve, and n.D grad u+ at the nodes by
  * jump-corrected quadratic extrapolation (Sec. 5.4).  psi, out: device [ncomp][M]
  * in `dtype`.  KFBI_F64: the whole product in FP64.  KFBI_F32 (the reduced-precision product of
- * the mixed-precision solves): the correction and the box solve run in FP32, while the jumps and
+ * the mixed-precision solves): the box solve runs in FP32, while the jumps, the correction and
  * the extrapolation fits keep FP64 weights and FP64 sums (psi is widened to FP64 on entry, the
- * result rounded to FP32 on exit). */
+ * correction rounded to the FP32 grid, the result to FP32 on exit).  psi and out may overlap. */
 int kfbi_apply(kfbi_problem p, const void *psi, void *out, int32_t dtype, void *stream);
 
 /* kfbi_box_solve: u = S f, the fast box solve alone (Sec. 5.2 eq. FDE with u = 0 on the box
@@ -375,7 +375,7 @@ const char *kfbi_last_error(void);
  * update over that one field; its inverse y pass counts under "dst_y1"), "dst_last_comb" (that
  * z pass when the step also has no stimulus current: it adds the transform of C psi, taken
  * through the masked row and plane passes, to the volume solve's transform of kappa V1 as it
- * loads), "correct", "gather", "jumps").
+ * loads), "correct", "gather", "jumps" (no launches: the jumps are part of "correct" and "gather")).
  * Returns KFBI_EINVAL if the name is unknown. */
 int kfbi_kernel_time(kfbi_problem p, const char *kernel, double *avg_us, int64_t *launches);
 /* DST tile widths (1 or 2: multiples of the base pencil pairs per workgroup) of the x, y and

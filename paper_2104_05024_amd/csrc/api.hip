@@ -162,17 +162,28 @@ int kfbi_table(kfbi_problem p, const char *name, void *dst, int64_t *count, int3
   return KFBI_OK;
 }
 
+// The product reads psi until its last kernel, which writes out: when the caller's arrays overlap,
+// psi is taken from a copy in scratch.
+static const void *apart(const void *psi, const void *out, int64_t n, int32_t dtype, double *scratch,
+                         hipStream_t st) {
+  const size_t bytes = (size_t)n * (dtype == KFBI_F64 ? sizeof(double) : sizeof(float));
+  const char *a = (const char *)psi, *b = (const char *)out;
+  if (a + bytes <= b || b + bytes <= a) return psi;
+  KFBI_HIP(hipMemcpyAsync(scratch, psi, bytes, hipMemcpyDeviceToDevice, st));
+  return scratch;
+}
+
 int kfbi_apply(kfbi_problem p, const void *psi, void *out, int32_t dtype, void *stream) {
   return guard([&]() -> int {
     if (!p || !psi || !out) return fail(KFBI_EINVAL, "null argument");
     if (!p->p.on_device) return fail(KFBI_ENODEV, "problem set up host-only");
+    if (dtype != KFBI_F64 && dtype != KFBI_F32) return fail(KFBI_EINVAL, "dtype");
     hipStream_t st = (hipStream_t)stream;
+    psi = apart(psi, out, p->solver.L, dtype, p->solver.t, st);
     if (dtype == KFBI_F64)
       p->solver.apply<double>(p->p, (const double *)psi, (double *)out, st);
-    else if (dtype == KFBI_F32)
-      p->solver.apply_f32(p->p, (const float *)psi, (float *)out, st);
     else
-      return fail(KFBI_EINVAL, "dtype");
+      p->solver.apply<float>(p->p, (const float *)psi, (float *)out, st);
     return KFBI_OK;
   });
 }
@@ -285,10 +296,11 @@ int kfbi_batch_query(kfbi_batch b, int32_t i, int64_t *M, int64_t *N, int64_t *i
 int kfbi_batch_apply(kfbi_batch b, const void *psi, void *out, int32_t dtype, void *stream) {
   return guard([&]() -> int {
     if (!b || !psi || !out) return fail(KFBI_EINVAL, "argument");
+    if (dtype != KFBI_F64 && dtype != KFBI_F32) return fail(KFBI_EINVAL, "dtype");
     const hipStream_t st = (hipStream_t)stream;
+    psi = apart(psi, out, b->b.L, dtype, b->b.t, st);
     if (dtype == KFBI_F64) b->b.matvec<double>((const double *)psi, (double *)out, st);
-    else if (dtype == KFBI_F32) b->b.apply_f32((const float *)psi, (float *)out, st);
-    else return fail(KFBI_EINVAL, "dtype");
+    else b->b.matvec<float>((const float *)psi, (float *)out, st);
     KFBI_HIP(hipStreamSynchronize(st));
     return KFBI_OK;
   });

@@ -46,8 +46,8 @@ struct Batch {
   std::vector<int64_t> off, goff;      // prefix sums of M_p (interface) and N_p^2 (grid)
   int64_t L = 0;                       // total interface nodes
   int16_t *pid = nullptr;              // problem of every concatenated interface entry
-  int64_t *off_dev = nullptr, *goff_dev = nullptr, *cum_nc = nullptr, *cum_irr = nullptr;
-  BatchCounts counts;
+  int64_t *off_dev = nullptr, *goff_dev = nullptr;
+  BatchBlocks correct_bl, gather_bl, pack_bl;
   BatchItem<double> *items64 = nullptr;
   BatchItem<float> *items32 = nullptr;
   PackItem *packs = nullptr;
@@ -76,11 +76,9 @@ struct Batch {
   BatchItem<T> *items() const;
   // A psi for every problem with the grid side (correction, box solve) in T; the density side
   // (jumps, extrapolation fits) is FP64 in both, and so are the vectors
-  template <typename T>
-  void matvec(const double *in, double *out, hipStream_t st);
+  template <typename T, typename TP>
+  void matvec(const TP *in, TP *out, hipStream_t st);
   void apply_vec(int prec, const double *in, double *out, hipStream_t st);
-  // FP32 vectors at the boundary (converted to and from FP64 around the FP32 product)
-  void apply_f32(const float *in, float *out, hipStream_t st);
   void seg_norms(const double *v, std::vector<double> &out, hipStream_t st);
   void arnoldi_step(int prec, int m, hipStream_t st);
   void run_step(int prec, int m, hipStream_t st);

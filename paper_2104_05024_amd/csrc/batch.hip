@@ -4,8 +4,8 @@
 //   * size groups: problems with the same grid size share padded field buffers (stride
 //     N * M), so each DST pass of a group is one launch (blockIdx.y = problem for the fused
 //     last-axis pass, with per-problem mode parameters);
-//   * work lists: the jump, correction and gather kernels of all problems run as one launch
-//     each over the concatenated items, the problem found by a binary search over prefix sums;
+//   * work lists: the correction and gather kernels of all problems run as one launch
+//     each, a table naming the problem of every block;
 //   * GMRES(m) for all problems in lockstep on concatenated vectors [problem][M_p]: per-problem
 //     dot products, Gram-Schmidt (two passes), norms and basis updates are segment kernels;
 //     the Givens least-squares updates run on the host, one synchronisation per iteration.
@@ -27,6 +27,7 @@ namespace kfbi {
 namespace {
 
 constexpr int kB = 256;
+constexpr int kPackRows = 16;
 inline unsigned nb(int64_t n) { return (unsigned)((n + kB - 1) / kB); }
 
 template <typename T>
@@ -123,12 +124,6 @@ __global__ __launch_bounds__(kB) void k_axpby(double *__restrict__ z, double a, 
   if (i < n) z[i] = a * x[i] + (y ? b * y[i] : 0.0);
 }
 
-template <typename A, typename B>
-__global__ __launch_bounds__(kB) void k_cast(const A *__restrict__ a, B *__restrict__ b, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x;
-  if (i < n) b[i] = (B)a[i];
-}
-
 // zero the segments of problems whose mask entry is 0
 __global__ __launch_bounds__(kB) void k_seg_mask(double *__restrict__ v, const int16_t *__restrict__ pid,
                                                  const double *__restrict__ keep, int64_t L) {
@@ -136,31 +131,25 @@ __global__ __launch_bounds__(kB) void k_seg_mask(double *__restrict__ v, const i
   if (e < L && keep[pid[e]] == 0.0) v[e] = 0.0;
 }
 
-__device__ __forceinline__ int find_seg(const int64_t *__restrict__ cum, int n, int64_t i) {
-  int lo = 0, hi = n;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (cum[mid] <= i) lo = mid;
-    else hi = mid;
-  }
-  return lo;
-}
-
 // caller layout (concatenated [problem][N_p^2]) <-> padded group buffers
-__global__ __launch_bounds__(kB) void k_pack(double *__restrict__ plain, const int64_t *__restrict__ gcum,
-                                             const PackItem *__restrict__ it, int n, int64_t tot, int which,
-                                             int to_padded) {
-  const int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x;
-  if (i >= tot) return;
-  const int p = find_seg(gcum, n, i);
-  const PackItem &q = it[p];
-  const int64_t lin = i - gcum[p];
+// block b takes kPackRows grid rows of problem blocks[b].x from row blocks[b].y * kPackRows on, a
+// wavefront per row at a time
+__global__ __launch_bounds__(kB) void k_pack(double *__restrict__ plain, const int64_t *__restrict__ goff,
+                                             const PackItem *__restrict__ it, const int2 *__restrict__ blocks,
+                                             int which, int to_padded) {
+  const int2 b = blocks[blockIdx.x];
+  const PackItem &q = it[b.x];
   double *pad = which == 0 ? q.fpad : q.work;
-  const int64_t pos = (lin % q.N) + q.P * (lin / q.N);
-  if (to_padded)
-    pad[pos] = plain[i];
-  else
-    plain[i] = pad[pos];
+  double *pl = plain + goff[b.x];
+  const int64_t N = q.N;
+  for (int r = threadIdx.x / 64; r < kPackRows; r += kB / 64) {
+    const int64_t y = (int64_t)b.y * kPackRows + r;
+    if (y >= N) break;
+    for (int64_t x = threadIdx.x % 64; x < N; x += 64) {
+      if (to_padded) pad[y * q.P + x] = pl[y * N + x];
+      else pl[y * N + x] = pad[y * q.P + x];
+    }
+  }
 }
 
 }  // namespace
@@ -226,13 +215,14 @@ void Batch::init(int n, const kfbi_interface *ifaces, const kfbi_grid *grids, co
   // concatenated interface vectors and work lists
   off.assign(n + 1, 0);
   goff.assign(n + 1, 0);
-  std::vector<int64_t> cnc(n + 1, 0), cirr(n + 1, 0);
+  std::vector<int2> cb, gb, pb;   // blocks of the correction, gather and packing launches
   for (int i = 0; i < n; ++i) {
     const DevProblem &p = *probs[i];
     off[i + 1] = off[i] + p.M;
     goff[i + 1] = goff[i] + p.N * p.N;
-    cnc[i + 1] = cnc[i] + p.nc;
-    cirr[i + 1] = cirr[i] + p.nirr;
+    for (int k = 0; k < correct_blocks(p); ++k) cb.push_back(make_int2(i, k));
+    for (int k = 0; k < gather_blocks(p); ++k) gb.push_back(make_int2(i, k));
+    for (int k = 0; k < (int)((p.N + kPackRows - 1) / kPackRows); ++k) pb.push_back(make_int2(i, k));
   }
   L = off[n];
   if (L == 0) throw std::invalid_argument("no interface nodes");
@@ -245,55 +235,32 @@ void Batch::init(int n, const kfbi_interface *ifaces, const kfbi_grid *grids, co
   KFBI_HIP(hipMemcpy(off_dev, off.data(), (n + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
   goff_dev = balloc<int64_t>(n + 1);
   KFBI_HIP(hipMemcpy(goff_dev, goff.data(), (n + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-  cum_nc = balloc<int64_t>(n + 1);
-  cum_irr = balloc<int64_t>(n + 1);
-  KFBI_HIP(hipMemcpy(cum_nc, cnc.data(), (n + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-  KFBI_HIP(hipMemcpy(cum_irr, cirr.data(), (n + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-  counts.cum_nc = cum_nc;
-  counts.cum_M = off_dev;
-  counts.cum_nirr = cum_irr;
-  counts.n = n;
-  counts.tot_nc = cnc[n];
-  counts.tot_M = L;
-  counts.tot_nirr = cirr[n];
+  auto blocks_of = [&](const std::vector<int2> &v, BatchBlocks &bl) {
+    int2 *q = balloc<int2>(v.size());
+    KFBI_HIP(hipMemcpy(q, v.data(), v.size() * sizeof(int2), hipMemcpyHostToDevice));
+    bl.ref = q;
+    bl.n = (int)v.size();
+  };
+  blocks_of(cb, correct_bl);
+  blocks_of(gb, gather_bl);
+  blocks_of(pb, pack_bl);
   std::vector<BatchItem<double>> i64(n);
   std::vector<BatchItem<float>> i32(n);
   std::vector<PackItem> pk(n);
-  // fits (transfer, jump and extrapolation weights, node jumps) from the FP64 tables in both precisions
-  auto fill = [&](auto &it, auto &tb, auto *rhs, auto *fpad, auto *work, const DevProblem &p, int i) {
-    const PrecTables<double> &t64 = p.f64;
-    it.z_idx = p.z_idx;
-    it.z_A = t64.z_A;
-    it.z_B = t64.z_B;
-    it.irr_pos = p.irr_pos;
-    it.irr_ptr = p.irr_ptr;
-    it.arm_cross = p.arm_cross;
-    it.arm_d = tb.arm_d;
-    it.arm_s = tb.arm_s;
-    it.narm = p.narm;
-    it.q_idx = p.q_idx;
-    it.q_wg = t64.q_wg;
-    it.q_c = t64.q_c;
-    it.q_G = t64.q_G;
-    it.st_pos = p.st_pos;
-    it.st_nw = t64.st_nw;
-    it.st_r = t64.st_r;
-    it.jz = tb.jz;
-    it.jq = t64.jq;
+  auto fill = [&](auto &it, auto *rhs, auto *fpad, auto *work, const DevProblem &p, int i) {
+    it.tab = p.itab;
     it.rhs = rhs;
     it.fpad = fpad;
     it.work = work;
     it.M = p.M;
-    it.nc = p.nc;
-    it.nirr = p.nirr;
     it.ioff = off[i];
   };
   for (int i = 0; i < n; ++i) {
     const DevProblem &p = *probs[i];
     const Group &g = groups[group_of[i]];
     const int64_t o = (int64_t)slot_of[i] * g.cs;
-    fill(i64[i], probs[i]->f64, g.rhs64 + o, g.fpad64 + o, g.work64 + o, p, i);
-    fill(i32[i], probs[i]->f32, g.rhs32 + o, g.fpad32 + o, g.work32 + o, p, i);
+    fill(i64[i], g.rhs64 + o, g.fpad64 + o, g.work64 + o, p, i);
+    fill(i32[i], g.rhs32 + o, g.fpad32 + o, g.work32 + o, p, i);
     pk[i] = PackItem{g.fpad64 + o, g.work64 + o, p.N, (int64_t)g.Mfft};
   }
   items64 = balloc<BatchItem<double>>(n);
@@ -329,8 +296,8 @@ void Batch::init(int n, const kfbi_interface *ifaces, const kfbi_grid *grids, co
   for (Group &g : groups) {
     const DevProblem &p0 = *probs[g.members[0]];
     const int G = (int)g.members.size();
-    autotune_group<double>(g.Mfft, G, g.work64, g.cs, g.msv, p0.f64.tw, p0.f64.sp, g.tile_w[0], g.direct, cap);
-    autotune_group<float>(g.Mfft, G, g.work32, g.cs, g.msv, p0.f32.tw, p0.f32.sp, g.tile_w[1], g.direct, cap);
+    autotune_group<double>(g.Mfft, G, g.work64, g.cs, p0.f64.tw, p0.f64.sp, g.tile_w[0], cap);
+    autotune_group<float>(g.Mfft, G, g.work32, g.cs, p0.f32.tw, p0.f32.sp, g.tile_w[1], cap);
   }
 }
 
@@ -346,7 +313,8 @@ void Batch::release() {
       if (q) (void)hipFree(q);
   }
   groups.clear();
-  void *ps[] = {pid, off_dev, goff_dev, cum_nc, cum_irr, items64, items32, packs, V, vin, w, r, d, t, gp, x, dx,
+  void *ps[] = {pid, off_dev, goff_dev, const_cast<int2 *>(correct_bl.ref), const_cast<int2 *>(gather_bl.ref),
+                const_cast<int2 *>(pack_bl.ref), items64, items32, packs, V, vin, w, r, d, t, gp, x, dx,
                 hcols, ydev, sdev, nrm, jdev, seqdev};
   for (void *q : ps)
     if (q) (void)hipFree(q);
@@ -366,7 +334,7 @@ void Batch::release() {
 bool Batch::mergeable() const {
   if (groups.empty() || (int)groups.size() > kMaxMultiGroups) return false;
   for (const Group &g : groups)
-    if (g.Mfft < 64 || g.Mfft > 1024) return false;
+    if (g.Mfft < 64 || g.Mfft > 1024 || !g.direct) return false;
   return true;
 }
 
@@ -388,13 +356,11 @@ void Batch::box_all(bool from_fpad, hipStream_t st) {
   if (merged && mergeable()) {
     MultiGroupDesc d[kMaxMultiGroups];
     int k = 0;
-    bool direct = true;
     for (const Group &g : groups) {
-      direct = direct && g.direct;
       const PrecTables<T> &tb = const_cast<DevProblem &>(*probs[g.members[0]]).tab<T>();
       d[k++] = MultiGroupDesc{g.Mfft, (int)g.members.size(), g.cs, src_of(g), g.work<T>(), g.msv, tb.tw, tb.sp};
     }
-    box_solve_multi<T>(d, k, direct, st);
+    box_solve_multi<T>(d, k, st);
     return;
   }
   for (const Group &g : groups) {
@@ -404,26 +370,18 @@ void Batch::box_all(bool from_fpad, hipStream_t st) {
   }
 }
 
-template <typename T>
-void Batch::matvec(const double *in, double *out, hipStream_t st) {
-  launch_batch_jumps<T>(items<T>(), counts, in, st);
-  launch_batch_correct<T>(items<T>(), counts, 0, st);
+template <typename T, typename TP>
+void Batch::matvec(const TP *in, TP *out, hipStream_t st) {
+  launch_batch_correct<T, TP>(items<T>(), correct_bl, in, false, st);
   box_all<T>(false, st);
-  launch_batch_gather<T>(items<T>(), counts, true, out, st);
+  launch_batch_gather<T, TP>(items<T>(), gather_bl, in, out, st);
 }
-template void Batch::matvec<double>(const double *, double *, hipStream_t);
-template void Batch::matvec<float>(const double *, double *, hipStream_t);
+template void Batch::matvec<double, double>(const double *, double *, hipStream_t);
+template void Batch::matvec<float, float>(const float *, float *, hipStream_t);
 
 void Batch::apply_vec(int prec, const double *in, double *out, hipStream_t st) {
   if (prec == 0) matvec<double>(in, out, st);
   else matvec<float>(in, out, st);
-}
-
-void Batch::apply_f32(const float *in, float *out, hipStream_t st) {
-  k_cast<float, double><<<nb(L), kB, 0, st>>>(in, t, L);
-  matvec<float>(t, w, st);
-  k_cast<double, float><<<nb(L), kB, 0, st>>>(w, out, L);
-  KFBI_HIP(hipGetLastError());
 }
 
 // per-problem squared norms of v into nrm (device) and hhost[0..np) (host)
@@ -589,9 +547,9 @@ void Batch::gmres(int prec, const double *b, double *xv, bool x_zero, const std:
 }
 
 void Batch::pack(const double *plain, int which, bool to_padded, hipStream_t st) {
-  const int64_t tot = goff[np];
   // the caller's array is only read when packing into the padded buffers
-  k_pack<<<nb(tot), kB, 0, st>>>(const_cast<double *>(plain), goff_dev, packs, np, tot, which, to_padded ? 1 : 0);
+  k_pack<<<(unsigned)pack_bl.n, kB, 0, st>>>(const_cast<double *>(plain), goff_dev, packs, pack_bl.ref, which,
+                                             to_padded ? 1 : 0);
   KFBI_HIP(hipGetLastError());
 }
 
@@ -600,7 +558,7 @@ int Batch::solve(const double *g, const double *f, double *u, double *psi, const
   // volume part: u_V = S f, g' = g - n.D grad u_V+
   pack(f, 0, true, st);
   box_all<double>(true, st);
-  launch_batch_gather<double>(items64, counts, false, t, st);
+  launch_batch_gather<double, double>(items64, gather_bl, nullptr, t, st);
   if (g) k_axpby<<<nb(L), kB, 0, st>>>(gp, 1.0, g, -1.0, t, L);
   else k_axpby<<<nb(L), kB, 0, st>>>(gp, -1.0, t, 0.0, nullptr, L);
   KFBI_HIP(hipGetLastError());
@@ -659,8 +617,7 @@ int Batch::solve(const double *g, const double *f, double *u, double *psi, const
     }
   }
   // u = S(f + C psi)
-  launch_batch_jumps<double>(items64, counts, psi, st);
-  launch_batch_correct<double>(items64, counts, 1, st);
+  launch_batch_correct<double, double>(items64, correct_bl, psi, true, st);
   box_all<double>(true, st);
   pack(u, 1, false, st);
   KFBI_HIP(hipStreamSynchronize(st));

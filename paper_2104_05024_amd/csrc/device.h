@@ -26,21 +26,11 @@ struct HipError {
 // Caller-visible fields use the unpadded layout (pitch N).
 
 template <typename T>
-struct PrecTables {          // per-precision device copies of the numeric tables
-  // density-side tables, FP64 only (null in the FP32 set): every product takes its jumps and its
-  // extrapolation fits in FP64
-  T *z_A = nullptr, *z_B = nullptr;      // crossing jumps [comp][K][nc]: [u_a] = sum A psi, [u_aa] = sum B psi
-  T *q_wg = nullptr;                     // node surface-gradient weights [Kn][d][M]
-  T *q_c = nullptr, *q_G = nullptr;      // node jumps [comp][d + NH][M] on psi_q, [comp][d + NH][d][M] on g
-  T *st_nw = nullptr, *st_r = nullptr;   // gather weights n.D_c grad [comp][S][M]; offsets [S][d][M]
-  // grid-side tables, one copy per precision
-  T *arm_d = nullptr, *arm_s = nullptr;  // arm offsets [narm]; s D_{c,a} / h^2 [comp][narm]
+struct PrecTables {          // per-precision device copies of the DST tables, and the fields
   T *tw = nullptr, *sp = nullptr;        // DST twiddles exp(-2 pi i m/M) (complex) and sin(pi n/M)
   T *rhs = nullptr, *work = nullptr;     // matvec right-hand side (zero off irregular nodes), work field
   T *gbuf = nullptr;                     // coupled 3D FP64: x-y transform of kappa V1 (one component),
                                          // kept from a step's volume solve for its final solve
-  T *jz = nullptr;                       // jumps at crossings [comp][2][nc] (written in this precision)
-  T *jq = nullptr;                       // jumps at nodes [comp][d+nh][M] (FP64 set only)
 };
 
 // Per-kernel-class launch timer: HIP events recorded around each launch on the launch
@@ -93,21 +83,27 @@ struct PlaneBits {
   uint64_t w[16] = {};
 };
 
+// Device tables of the interface kernels (kfbi_kernels.hip), FP64 weights in every precision.
+struct InterfaceTables {
+  int64_t n_slots = 0;                               // arms of the irregular nodes, padded to 64s
+  int32_t *arm_idx = nullptr, *arm_head = nullptr;   // density points [K][slot]; (position, arms of the node) [slot]
+  double *arm_w = nullptr;                           // [comp][K][slot]
+  int32_t *st_pos = nullptr, *q_idx = nullptr;       // grid and density points of the nodes [M][S], [M][Kn]
+  double *st_nw = nullptr, *q_w = nullptr;           // their weights [comp][M][S], [comp][M][Kn]
+};
+
 struct DevProblem {
   HostTables ht;
   bool on_device = false;
   int dev = 0;
   int dim = 0, ncomp = 1, Mfft = 0;
-  int64_t N = 0, M = 0, P = 0, nc = 0, nirr = 0, narm = 0;
+  int64_t N = 0, M = 0, P = 0;
   int64_t comp_stride = 0;     // padded elements per component
-  int K = 0, Kn = 0, S = 0;
+  int S = 0;                   // extrapolation stencil size
   double h = 0, kappa = 0, D[2][3] = {{1, 1, 1}, {1, 1, 1}};   // diagonal conductivity per component
   double lam_scale = 1;        // (2/M)^d normalisation of the inverse transforms
 
-  // integer tables
-  int32_t *z_idx = nullptr, *z_axis = nullptr, *q_idx = nullptr;
-  int32_t *irr_pos = nullptr, *irr_ptr = nullptr, *arm_cross = nullptr;
-  int32_t *st_pos = nullptr;   // padded index, negative (-pos-1) for stencil nodes outside the tissue
+  InterfaceTables itab;
   int8_t *inside_pad = nullptr;  // padded-layout tissue mask
   // sparse matvec box solve (3D): rows of the flattened [comp][z][y] row list that carry
   // irregular nodes (in) / extrapolation-stencil nodes (out), and their [z][y] byte masks
@@ -157,29 +153,17 @@ struct ModeParams {
 // One two-dimensional, one-component problem of a batch as the batched interface kernels see
 // it: its tables, its fields inside the size-group buffers, and its offset in the
 // concatenated interface vectors.
-// The density-side tables and node jumps are FP64 for both precisions (as in PrecTables).
 template <typename T>
 struct BatchItem {
-  const int32_t *z_idx;
-  const double *z_A, *z_B;
-  const int32_t *irr_pos, *irr_ptr, *arm_cross;
-  const T *arm_d, *arm_s;
-  int64_t narm;
-  const int32_t *q_idx;
-  const double *q_wg, *q_c, *q_G;
-  const int32_t *st_pos;
-  const double *st_nw, *st_r;
-  T *jz;
-  double *jq;
+  InterfaceTables tab;
   T *rhs, *fpad, *work;        // padded fields inside the group buffers
-  int64_t M, nc, nirr, ioff;
+  int64_t M, ioff;
 };
 
-// Prefix sums over the problems of a batch (device arrays of n + 1 entries) and totals.
-struct BatchCounts {
-  const int64_t *cum_nc = nullptr, *cum_M = nullptr, *cum_nirr = nullptr;
+// The blocks of one batched launch: (problem, block within the problem), on the device.
+struct BatchBlocks {
+  const int2 *ref = nullptr;
   int n = 0;
-  int64_t tot_nc = 0, tot_M = 0, tot_nirr = 0;
 };
 
 // ---- launchers (defined in dst.hip / kfbi_kernels.hip)
@@ -277,29 +261,26 @@ struct FhnArgs {
 void bidomain_volume_solve(DevProblem &p, const FhnArgs &a, hipStream_t st);
 void bidomain_final_solve(DevProblem &p, const FhnArgs &a, bool fuse_be, hipStream_t st);
 
-// Jumps from the FP64 density (FP64 weights and arithmetic); the crossing jumps are stored in T
-// for the correction of a T product, the node jumps in FP64.
-template <typename T>
-void launch_jumps(DevProblem &p, const double *psi, hipStream_t st);
-template <typename T>
-void launch_correct(DevProblem &p, hipStream_t st);
-// n.D grad u+ at the nodes from the T grid values u: FP64 fit weights, jumps and sums, FP64 out.
-template <typename T>
-void launch_gather(DevProblem &p, const T *u, bool with_jumps, double *out, hipStream_t st);
-template <typename T>
-void launch_add_correction(DevProblem &p, T *field_padded, hipStream_t st);
+// The correction C psi into the product's right-hand side (overwritten at the irregular nodes), or
+// added to a padded field; T the grid side's precision, TP the density's.
+template <typename T, typename TP>
+void launch_correct(DevProblem &p, const TP *psi, hipStream_t st);
+void launch_add_correction(DevProblem &p, const double *psi, double *field_padded, hipStream_t st);
+// n.D grad u+ at the nodes from the T grid values u and the jumps of psi (null: none).
+template <typename T, typename TP>
+void launch_gather(DevProblem &p, const T *u, const TP *psi, TP *out, hipStream_t st);
 
-// Batched 2D launches: jumps of every problem (crossings and nodes) in one launch; the
-// correction into rhs (overwrite, target 0) or fpad (accumulate, target 1); the gather from work.
-template <typename T>
-void launch_batch_jumps(const BatchItem<T> *items, const BatchCounts &c, const double *psi, hipStream_t st);
-template <typename T>
-void launch_batch_correct(const BatchItem<T> *items, const BatchCounts &c, int target, hipStream_t st);
-template <typename T>
-void launch_batch_gather(const BatchItem<T> *items, const BatchCounts &c, bool with_jumps, double *out,
-                         hipStream_t st);
+// Batched 2D launches over all problems: the correction into rhs (overwrite) or fpad (accumulate),
+// and the gather from work; psi and out concatenated.
+int correct_blocks(const DevProblem &p);   // blocks of one problem in those launches
+int gather_blocks(const DevProblem &p);
+template <typename T, typename TP>
+void launch_batch_correct(const BatchItem<T> *items, const BatchBlocks &b, const TP *psi, bool into_fpad,
+                          hipStream_t st);
+template <typename T, typename TP>
+void launch_batch_gather(const BatchItem<T> *items, const BatchBlocks &b, const TP *psi, TP *out, hipStream_t st);
 // Grouped 2D box solve of G equal-size problems (padded layout, stride cs, msv on the device).
-// w: tile widths of the x and last-axis passes (w[0], w[2]); direct: the last axis solved directly.
+// w[0]: tile width of the x passes; direct: the last axis solved directly.
 template <typename T>
 void box_solve_group(int Mfft, int G, const T *src, T *dst, int64_t cs, const ModeParams *msv, const T *tw,
                      const T *sp, const int *w, bool direct, hipStream_t st);
@@ -317,9 +298,9 @@ struct MultiGroupDesc {
   const void *tw = nullptr, *sp = nullptr;
 };
 constexpr int kMaxMultiGroups = 8;
-// direct: the last axis of every group is solved directly (last_axis_direct_multi).
+// The last axis is solved directly (every group's problems must qualify, column_direct).
 template <typename T>
-void box_solve_multi(const MultiGroupDesc *groups, int ngroups, bool direct, hipStream_t st);
+void box_solve_multi(const MultiGroupDesc *groups, int ngroups, hipStream_t st);
 
 // The last axis of a box solve as tridiagonal systems along its columns (lastaxis.hip): in -> out
 // (may alias), padded layout.  Forms as in the DST pass: 0-2 by the plane sets given (none; both;
@@ -353,8 +334,7 @@ void last_axis_direct_multi(const MultiGroupDesc *groups, int ngroups, hipStream
 // by dimension, grid size, components and precision); clears the work buffers afterwards.
 void autotune_tiles(DevProblem &p, hipStream_t st);
 template <typename T>
-void autotune_group(int Mfft, int G, T *a, int64_t cs, const ModeParams *msv, const T *tw, const T *sp, int *w,
-                    bool direct, hipStream_t st);
+void autotune_group(int Mfft, int G, T *a, int64_t cs, const T *tw, const T *sp, int *w, hipStream_t st);
 
 void upload_tables(DevProblem &p);
 void free_tables(DevProblem &p);

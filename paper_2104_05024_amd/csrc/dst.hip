@@ -802,7 +802,7 @@ struct ModeHook {
 // component 0 plus the pair read from ain2 on the planes in zin.
 // One tile of the pass: tile number id of total (gx tiles per row of the grid of tiles), LDS
 // buffers sbuf (NP * PADM values), slam (M) and ssin (M / 2 + 1).
-template <typename T, int M, int NC, int DIM, int W = 1, int ZM = 0>
+template <typename T, int M, int NC, int DIM, int ZM = 0>
 __device__ __forceinline__ void dst_last_tile(const T *__restrict__ ain, T *__restrict__ a, int64_t P,
                                               int64_t comp_stride, const ModeScale &ms0,
                                               const C2<T> *__restrict__ tw, const T *__restrict__ sp,
@@ -810,13 +810,13 @@ __device__ __forceinline__ void dst_last_tile(const T *__restrict__ ain, T *__re
                                               const PlaneBits &zin, const PlaneBits &zout, C2<T> *sbuf, T *slam,
                                               T *ssin, int64_t id, int64_t total, int gx,
                                               const T *__restrict__ ain2 = nullptr) {
-  using Sh = Shape<T, M, W>;
+  using Sh = Shape<T, M>;
   constexpr int N = Sh::N, NP = Sh::NP, NT = Sh::NT, PADM = Sh::PADM;
   constexpr int TX = NC == 2 ? NP : 2 * NP;          // columns per tile
   constexpr int64_t LS = DIM == 3 ? (int64_t)N : 1;  // rows of the last axis step by LS * P
-  using Tl = StridedTile<T, M, TX, NC, W>;
+  using Tl = StridedTile<T, M, TX, NC>;
   const int tid = threadIdx.x;
-  // At W = 1 a tile row of TX columns is half of a 128-byte line; the tile sharing the line is
+  // A tile row of TX columns is half of a 128-byte line; the tile sharing the line is
   // given to the workgroup dispatched 8 later, i.e. on the same XCD (round-robin dispatch), so
   // the second half of the line comes from that XCD's L2 instead of a second HBM fetch.
   if (id < (total & ~int64_t(15))) id = (id & ~int64_t(15)) + 2 * (id & 7) + ((id >> 3) & 1);
@@ -869,8 +869,8 @@ __device__ __forceinline__ void dst_last_tile(const T *__restrict__ ain, T *__re
   else Tl::store(base, LS * P, comp_stride, x0, sbuf, tid);
 }
 
-template <typename T, int M, int NC, int DIM, int W = 1, int ZM = 0>
-__global__ __launch_bounds__((Shape<T, M, W>::NT)) void k_dst_last(const T *__restrict__ ain, T *__restrict__ a,
+template <typename T, int M, int NC, int DIM, int ZM = 0>
+__global__ __launch_bounds__((Shape<T, M>::NT)) void k_dst_last(const T *__restrict__ ain, T *__restrict__ a,
                                                                      int64_t P, int64_t comp_stride,
                                                                   ModeScale ms0, const C2<T> *__restrict__ tw,
                                                                   const T *__restrict__ sp,
@@ -878,11 +878,11 @@ __global__ __launch_bounds__((Shape<T, M, W>::NT)) void k_dst_last(const T *__re
                                                                   int64_t pstride = 0, PlaneBits zin = {},
                                                                   PlaneBits zout = {},
                                                                   const T *__restrict__ ain2 = nullptr) {
-  using Sh = Shape<T, M, W>;
+  using Sh = Shape<T, M>;
   __shared__ C2<T> sbuf[Sh::NP * Sh::PADM];
   __shared__ T slam[M];
   __shared__ T ssin[M / 2 + 1];
-  dst_last_tile<T, M, NC, DIM, W, ZM>(ain, a, P, comp_stride, ms0, tw, sp, msv, pstride, zin, zout, sbuf, slam, ssin,
+  dst_last_tile<T, M, NC, DIM, ZM>(ain, a, P, comp_stride, ms0, tw, sp, msv, pstride, zin, zout, sbuf, slam, ssin,
                                       blockIdx.x + (int64_t)gridDim.x * blockIdx.y,
                                       (int64_t)gridDim.x * gridDim.y, (int)gridDim.x, ain2);
 }
@@ -1344,12 +1344,12 @@ void launch_y(const T *in, T *out, int64_t P, int64_t cs, int ncomp, const uint6
 }
 
 // fused last-axis pass; nprob > 1 only in 2D (batched groups with per-problem msv)
-template <typename T, int M, int W>
+template <typename T, int M>
 void launch_last(const T *in, T *a, int dim, int ncomp, int64_t P, int64_t cs, const ModeScale &ms,
                  const C2<T> *tw, const T *sp, const ModeScale *msv, int nprob, int64_t pstride, hipStream_t st,
                  const PlaneBits *zin = nullptr, const PlaneBits *zout = nullptr, int form = 0,
                  const T *in2 = nullptr) {
-  using Sh = Shape<T, M, W>;
+  using Sh = Shape<T, M>;
   const int tx = ncomp == 2 ? Sh::NP : 2 * Sh::NP;
   const dim3 g((Sh::N + tx - 1) / tx, dim == 3 ? Sh::N : nprob, 1);
   // form 3: antisymmetric source (needs zout); form 4: the difference of the pair (no masks);
@@ -1362,27 +1362,27 @@ void launch_last(const T *in, T *a, int dim, int ncomp, int64_t P, int64_t cs, c
     throw std::invalid_argument("the combined z pass takes the coupled 3D pair, a second input and its plane mask");
   if (dim == 3) {
     if (form >= 3) {
-      if constexpr (StridedTile<T, M, Sh::NP, 2, W>::VEC) {
-        if (form == 3) k_dst_last<T, M, 2, 3, W, 3><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp, nullptr, 0, {}, *zout);
-        else if (form == 4) k_dst_last<T, M, 2, 3, W, 4><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp);
-        else k_dst_last<T, M, 2, 3, W, 5><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp, nullptr, 0, *zin, {}, in2);
+      if constexpr (StridedTile<T, M, Sh::NP, 2>::VEC) {
+        if (form == 3) k_dst_last<T, M, 2, 3, 3><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp, nullptr, 0, {}, *zout);
+        else if (form == 4) k_dst_last<T, M, 2, 3, 4><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp);
+        else k_dst_last<T, M, 2, 3, 5><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp, nullptr, 0, *zin, {}, in2);
       } else {
         throw std::invalid_argument("the z passes of forms 3 to 5 need tiles of whole 16-byte vectors (M >= 64)");
       }
     } else if (zin && zout) {
-      if (ncomp == 2) k_dst_last<T, M, 2, 3, W, 1><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp, nullptr, 0, *zin, *zout);
-      else k_dst_last<T, M, 1, 3, W, 1><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp, nullptr, 0, *zin, *zout);
+      if (ncomp == 2) k_dst_last<T, M, 2, 3, 1><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp, nullptr, 0, *zin, *zout);
+      else k_dst_last<T, M, 1, 3, 1><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp, nullptr, 0, *zin, *zout);
     } else if (zout) {
-      if (ncomp == 2) k_dst_last<T, M, 2, 3, W, 2><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp, nullptr, 0, {}, *zout);
-      else k_dst_last<T, M, 1, 3, W, 2><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp, nullptr, 0, {}, *zout);
+      if (ncomp == 2) k_dst_last<T, M, 2, 3, 2><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp, nullptr, 0, {}, *zout);
+      else k_dst_last<T, M, 1, 3, 2><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp, nullptr, 0, {}, *zout);
     } else {
       if (zin) throw std::invalid_argument("an input plane mask needs an output plane mask");
-      if (ncomp == 2) k_dst_last<T, M, 2, 3, W><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp);
-      else k_dst_last<T, M, 1, 3, W><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp);
+      if (ncomp == 2) k_dst_last<T, M, 2, 3><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp);
+      else k_dst_last<T, M, 1, 3><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp);
     }
   } else {
-    if (ncomp == 2) k_dst_last<T, M, 2, 2, W><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp, msv, pstride);
-    else k_dst_last<T, M, 1, 2, W><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp, msv, pstride);
+    if (ncomp == 2) k_dst_last<T, M, 2, 2><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp, msv, pstride);
+    else k_dst_last<T, M, 1, 2><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp, msv, pstride);
   }
   KFBI_HIP(hipGetLastError());
 }
@@ -1399,16 +1399,6 @@ void pass_y(int w, const T *in, T *out, int64_t P, int64_t cs, int ncomp, const 
   if (w == 2) launch_y<T, M, 2>(in, out, P, cs, ncomp, mi, mo, planes, tw, sp, st);
   else launch_y<T, M, 1>(in, out, P, cs, ncomp, mi, mo, planes, tw, sp, st);
 }
-template <typename T, int M>
-void pass_last(int w, T *a, int dim, int ncomp, int64_t P, int64_t cs, const ModeScale &ms, const C2<T> *tw,
-               const T *sp, const ModeScale *msv, int nprob, int64_t pstride, hipStream_t st,
-               const T *in = nullptr, const PlaneBits *zin = nullptr, const PlaneBits *zout = nullptr,
-               int form = 0, const T *in2 = nullptr) {
-  if (!in) in = a;
-  if (w == 2) launch_last<T, M, 2>(in, a, dim, ncomp, P, cs, ms, tw, sp, msv, nprob, pstride, st, zin, zout, form, in2);
-  else launch_last<T, M, 1>(in, a, dim, ncomp, P, cs, ms, tw, sp, msv, nprob, pstride, st, zin, zout, form, in2);
-}
-
 template <typename T>
 ModeScale mode_of(const DevProblem &p) {
   ModeScale m{};
@@ -1445,8 +1435,8 @@ void solve_last(DevProblem &p, T *a, hipStream_t st, const T *in = nullptr, cons
     last_axis_direct<T>(l, st);
     return;
   }
-  pass_last<T, M>(p.tile_w[prec_index<T>()][2], a, p.dim, p.ncomp, p.P, p.comp_stride, mode_of<T>(p),
-                  reinterpret_cast<const C2<T> *>(tb.tw), tb.sp, nullptr, 1, 0, st, in, zin, zout, form, in2);
+  launch_last<T, M>(in ? in : a, a, p.dim, p.ncomp, p.P, p.comp_stride, mode_of<T>(p),
+                    reinterpret_cast<const C2<T> *>(tb.tw), tb.sp, nullptr, 1, 0, st, zin, zout, form, in2);
 }
 
 // skip & 1: work already holds the forward x pass of the source (src unused); skip & 2: stop
@@ -1704,7 +1694,7 @@ void run_box_group(int G, const T *src, T *dst, int64_t cs, const ModeParams *ms
     l.pstride = cs;
     last_axis_direct<T>(l, st);
   } else {
-    pass_last<T, M>(w[2], dst, 2, 1, M, cs, ModeParams{}, tw, sp, msv, G, cs, st);
+    launch_last<T, M>(dst, dst, 2, 1, M, cs, ModeParams{}, tw, sp, msv, G, cs, st);
   }
   pass_x<T, M>(w[0], dst, false, dst, false, rows, tw, sp, st);
 }
@@ -1725,19 +1715,6 @@ struct MultiX {
     const C2<T> *tw;
     const T *sp;
     int M, begin;
-  } g[kMaxMultiGroups];
-  int ng;
-};
-
-template <typename T>
-struct MultiLast {
-  struct G {
-    T *a;
-    int64_t cs;
-    const ModeScale *msv;
-    const C2<T> *tw;
-    const T *sp;
-    int M, begin, gx, nprob;
   } g[kMaxMultiGroups];
   int ng;
 };
@@ -1776,31 +1753,6 @@ __global__ __launch_bounds__((Shape<T, 64>::NT)) void k_dst_x_multi(MultiX<T> mp
 }
 
 template <typename T>
-__global__ __launch_bounds__((Shape<T, 64>::NT)) void k_dst_last_multi(MultiLast<T> mp) {
-  __shared__ C2<T> sbuf[multi_sbuf<T>()];
-  __shared__ T slam[1024];
-  __shared__ T ssin[1024 / 2 + 1];
-  const int k = multi_group<T>(mp);
-  const auto &g = mp.g[k];
-  const int64_t b = (int64_t)blockIdx.x - g.begin, total = (int64_t)g.gx * g.nprob;
-  const ModeScale none{};
-  const PlaneBits nob{};
-  switch (g.M) {
-#define KFBI_MULTI_LAST(MM)                                                                                    \
-    case MM:                                                                                                   \
-      dst_last_tile<T, MM, 1, 2>(g.a, g.a, MM, g.cs, none, g.tw, g.sp, g.msv, g.cs, nob, nob, sbuf, slam, ssin, b, \
-                                 total, g.gx);                                                                 \
-      break;
-    KFBI_MULTI_LAST(64) KFBI_MULTI_LAST(128) KFBI_MULTI_LAST(256) KFBI_MULTI_LAST(512)
-    default:
-      dst_last_tile<T, 1024, 1, 2>(g.a, g.a, 1024, g.cs, none, g.tw, g.sp, g.msv, g.cs, nob, nob, sbuf, slam, ssin,
-                                   b, total, g.gx);
-      break;
-#undef KFBI_MULTI_LAST
-  }
-}
-
-template <typename T>
 int tile_rows(int M) {   // rows per x-pass tile at width 1
   return 2 * ((sizeof(T) == 8 ? 2048 : 4096) / M);
 }
@@ -1815,8 +1767,8 @@ __global__ void k_fill_pattern(T *__restrict__ a, int64_t n) {
 
 // One launch of a pass at width w, in place on `a`, timed with events.
 template <typename T, int M>
-float time_pass(int pass, int w, T *a, int dim, int ncomp, int64_t P, int64_t cs, int64_t rows, const ModeScale &ms,
-                const C2<T> *tw, const T *sp, const ModeScale *msv, int nprob, hipEvent_t e0, hipEvent_t e1,
+float time_pass(int pass, int w, T *a, int dim, int ncomp, int64_t P, int64_t cs, int64_t rows,
+                const C2<T> *tw, const T *sp, int nprob, hipEvent_t e0, hipEvent_t e1,
                 hipStream_t st) {
   // fresh data for every launch (the unnormalised passes would otherwise grow it without bound)
   const int64_t nfill = dim == 3 ? (int64_t)ncomp * cs : (int64_t)nprob * cs;
@@ -1824,8 +1776,7 @@ float time_pass(int pass, int w, T *a, int dim, int ncomp, int64_t P, int64_t cs
   KFBI_HIP(hipGetLastError());
   KFBI_HIP(hipEventRecord(e0, st));
   if (pass == 0) pass_x<T, M>(w, a, false, a, false, rows, tw, sp, st);
-  else if (pass == 1) pass_y<T, M>(w, a, a, P, cs, ncomp, nullptr, nullptr, tw, sp, st);
-  else pass_last<T, M>(w, a, dim, ncomp, P, cs, ms, tw, sp, msv, nprob, cs, st);
+  else pass_y<T, M>(w, a, a, P, cs, ncomp, nullptr, nullptr, tw, sp, st);
   KFBI_HIP(hipEventRecord(e1, st));
   KFBI_HIP(hipEventSynchronize(e1));
   float ms_ = 0;
@@ -1836,18 +1787,18 @@ float time_pass(int pass, int w, T *a, int dim, int ncomp, int64_t P, int64_t cs
 // Both widths are launched alternately (after warm-up launches that bring the clocks up), so
 // that clock and cache drift affect both alike; the median of each decides.
 template <typename T, int M>
-void tune(int *w, T *a, int dim, int ncomp, int64_t P, int64_t cs, int64_t rows, const ModeScale &ms,
-          const C2<T> *tw, const T *sp, const ModeScale *msv, int nprob, bool direct, hipStream_t st) {
+void tune(int *w, T *a, int dim, int ncomp, int64_t P, int64_t cs, int64_t rows,
+          const C2<T> *tw, const T *sp, int nprob, hipStream_t st) {
   constexpr int kRounds = 7;
   hipEvent_t e0, e1;
   KFBI_HIP(hipEventCreate(&e0));
   KFBI_HIP(hipEventCreate(&e1));
-  for (int pass = 0; pass < 3; ++pass) {
-    if ((pass == 1 && dim != 3) || (pass == 2 && direct)) continue;   // not run by these solves
+  for (int pass = 0; pass < 2; ++pass) {
+    if (pass == 1 && dim != 3) continue;
     float t[2][kRounds];
     for (int r = -2; r < kRounds; ++r)
       for (int k = 0; k < 2; ++k) {
-        const float v = time_pass<T, M>(pass, k + 1, a, dim, ncomp, P, cs, rows, ms, tw, sp, msv, nprob, e0, e1, st);
+        const float v = time_pass<T, M>(pass, k + 1, a, dim, ncomp, P, cs, rows, tw, sp, nprob, e0, e1, st);
         if (r >= 0) t[k][r] = v;
       }
     std::sort(t[0], t[0] + kRounds);
@@ -1865,11 +1816,10 @@ void autotune_prec(DevProblem &p, hipStream_t st) {
   const C2<T> *tw = reinterpret_cast<const C2<T> *>(tb.tw);
   const int64_t N = p.N;
   const int64_t rows = (int64_t)p.ncomp * (p.dim == 3 ? N * N : N);
-  const ModeScale ms = mode_of<T>(p);
   int *w = p.tile_w[prec_index<T>()];
   switch (p.Mfft) {
 #define KFBI_TUNE_CASE(MM) \
-    case MM: tune<T, MM>(w, A, p.dim, p.ncomp, p.P, p.comp_stride, rows, ms, tw, tb.sp, nullptr, 1, p.direct, st); break;
+    case MM: tune<T, MM>(w, A, p.dim, p.ncomp, p.P, p.comp_stride, rows, tw, tb.sp, 1, st); break;
     KFBI_TUNE_CASE(16) KFBI_TUNE_CASE(32) KFBI_TUNE_CASE(64) KFBI_TUNE_CASE(128) KFBI_TUNE_CASE(256)
     KFBI_TUNE_CASE(512) KFBI_TUNE_CASE(1024)
 #undef KFBI_TUNE_CASE
@@ -1882,9 +1832,9 @@ void autotune_prec(DevProblem &p, hipStream_t st) {
 // Tile widths per (dimension, grid size, components, precision): measured once per process.
 void autotune_tiles(DevProblem &p, hipStream_t st) {
   static std::mutex mu;
-  static std::map<std::array<int, 5>, std::array<int, 3>> cache;
+  static std::map<std::array<int, 4>, std::array<int, 3>> cache;
   for (int prec = 0; prec < 2; ++prec) {
-    const std::array<int, 5> key{p.dim, (int)p.Mfft, p.ncomp, prec, p.direct};
+    const std::array<int, 4> key{p.dim, (int)p.Mfft, p.ncomp, prec};
     {
       std::lock_guard<std::mutex> lk(mu);
       auto it = cache.find(key);
@@ -1907,13 +1857,12 @@ void autotune_tiles(DevProblem &p, hipStream_t st) {
 
 // Batched groups: widths of the x and last-axis passes for one group, timed on its buffers.
 template <typename T>
-void autotune_group(int Mfft, int G, T *a, int64_t cs, const ModeParams *msv, const T *tw_, const T *sp, int *w,
-                    bool direct, hipStream_t st) {
+void autotune_group(int Mfft, int G, T *a, int64_t cs, const T *tw_, const T *sp, int *w, hipStream_t st) {
   const C2<T> *tw = reinterpret_cast<const C2<T> *>(tw_);
   const int64_t rows = (int64_t)G * (Mfft - 1);
   switch (Mfft) {
 #define KFBI_TUNE_CASE(MM) \
-    case MM: tune<T, MM>(w, a, 2, 1, MM, cs, rows, ModeParams{}, tw, sp, msv, G, direct, st); break;
+    case MM: tune<T, MM>(w, a, 2, 1, MM, cs, rows, tw, sp, G, st); break;
     KFBI_TUNE_CASE(16) KFBI_TUNE_CASE(32) KFBI_TUNE_CASE(64) KFBI_TUNE_CASE(128) KFBI_TUNE_CASE(256)
     KFBI_TUNE_CASE(512) KFBI_TUNE_CASE(1024)
 #undef KFBI_TUNE_CASE
@@ -1922,10 +1871,8 @@ void autotune_group(int Mfft, int G, T *a, int64_t cs, const ModeParams *msv, co
   KFBI_HIP(hipMemsetAsync(a, 0, (size_t)G * cs * sizeof(T), st));
   KFBI_HIP(hipStreamSynchronize(st));
 }
-template void autotune_group<double>(int, int, double *, int64_t, const ModeParams *, const double *,
-                                     const double *, int *, bool, hipStream_t);
-template void autotune_group<float>(int, int, float *, int64_t, const ModeParams *, const float *, const float *,
-                                    int *, bool, hipStream_t);
+template void autotune_group<double>(int, int, double *, int64_t, const double *, const double *, int *, hipStream_t);
+template void autotune_group<float>(int, int, float *, int64_t, const float *, const float *, int *, hipStream_t);
 
 template <typename T>
 void box_solve_group(int Mfft, int G, const T *src, T *dst, int64_t cs, const ModeParams *msv, const T *tw,
@@ -1942,44 +1889,38 @@ void box_solve_group(int Mfft, int G, const T *src, T *dst, int64_t cs, const Mo
   }
 }
 template <typename T>
-void box_solve_multi(const MultiGroupDesc *gd, int ng, bool direct, hipStream_t st) {
+void box_solve_multi(const MultiGroupDesc *gd, int ng, hipStream_t st) {
   if (ng < 1 || ng > kMaxMultiGroups) throw std::invalid_argument("merged passes take 1 to 8 groups");
   // largest grids first: their long-running tiles start first, the small ones fill in after
   int order[kMaxMultiGroups];
   for (int k = 0; k < ng; ++k) order[k] = k;
   std::sort(order, order + ng, [&](int a, int b) { return gd[a].Mfft > gd[b].Mfft; });
   MultiX<T> x1{}, x2{};
-  MultiLast<T> la{};
-  int bx = 0, bl = 0;
+  int bx = 0;
   for (int j = 0; j < ng; ++j) {
     const MultiGroupDesc &d = gd[order[j]];
     const int M = d.Mfft, N = M - 1;
     if (M < 64 || M > 1024 || (M & (M - 1)) || d.G < 1 || d.cs != (int64_t)N * M)
       throw std::invalid_argument("merged passes: sizes 64..1024, padded groups");
     const int64_t rows = (int64_t)d.G * N;
-    const int tr = tile_rows<T>(M), np = tr / 2;
+    const int tr = tile_rows<T>(M);
     const C2<T> *tw = reinterpret_cast<const C2<T> *>(d.tw);
     const T *sp = static_cast<const T *>(d.sp);
     T *dst = static_cast<T *>(d.dst);
     x1.g[j] = {static_cast<const T *>(d.src), dst, rows, tw, sp, M, bx};
     x2.g[j] = {dst, dst, rows, tw, sp, M, bx};
     bx += (int)((rows + tr - 1) / tr);
-    const int gx = (N + 2 * np - 1) / (2 * np);
-    la.g[j] = {dst, d.cs, d.msv, tw, sp, M, bl, gx, d.G};
-    bl += gx * d.G;
   }
-  x1.ng = x2.ng = la.ng = ng;
+  x1.ng = x2.ng = ng;
   constexpr int NT = Shape<T, 64>::NT;
   k_dst_x_multi<T><<<bx, NT, 0, st>>>(x1);
   KFBI_HIP(hipGetLastError());
-  if (direct) last_axis_direct_multi<T>(gd, ng, st);
-  else k_dst_last_multi<T><<<bl, NT, 0, st>>>(la);
-  KFBI_HIP(hipGetLastError());
+  last_axis_direct_multi<T>(gd, ng, st);
   k_dst_x_multi<T><<<bx, NT, 0, st>>>(x2);
   KFBI_HIP(hipGetLastError());
 }
-template void box_solve_multi<double>(const MultiGroupDesc *, int, bool, hipStream_t);
-template void box_solve_multi<float>(const MultiGroupDesc *, int, bool, hipStream_t);
+template void box_solve_multi<double>(const MultiGroupDesc *, int, hipStream_t);
+template void box_solve_multi<float>(const MultiGroupDesc *, int, hipStream_t);
 
 template void box_solve_group<double>(int, int, const double *, double *, int64_t, const ModeParams *,
                                       const double *, const double *, const int *, bool, hipStream_t);

@@ -1,23 +1,25 @@
 // Interface-side kernels of the KFBI matrix-vector product and the table upload.
 //
-//  k_jumps_nc     : density -> jumps [u_a], [u_aa] at every grid-line intersection
-//                   (single-layer interface problem, Sec. 5.1 eq. single; jump relations
-//                   from [u] = 0 and [n.D grad u] = psi for diagonal D_c), and
-//                   [grad u], [Hess u] at every interface node, in one launch.
-//  k_correct_nc   : right-hand-side correction at irregular grid nodes (Sec. 5.3, eq.
-//                   correct): rhs_p = sum_arms s_p D_{c,a}/h^2 ([u_a] d + [u_aa] d^2 / 2).
-//                   One thread owns one irregular node, so no atomics are needed.
-//  k_gather_coop  : n.D grad u+ at every interface node from its 6/10-node quadratic fit,
-//                   adding the Taylor-expanded jump to values on the "-" side
-//                   (Sec. 5.4, eqs. taylor-i-po, taylor-i-co, ji).
-// The single-problem gather is wavefront-cooperative (a group of lanes per node, one stencil
-// point per lane, a DPP butterfly for the sums); the jumps and the correction keep one thread
-// per item, as do the batched kernels (each choice measured).
+//  k_correct : density -> right-hand-side correction at irregular grid nodes (Sec. 5.3, eq.
+//              correct): rhs_p = sum_arms s_p D_{c,a}/h^2 ([u_a] d + [u_aa] d^2 / 2).  The jumps at
+//              the arm's grid-line intersection (single-layer interface problem, Sec. 5.1 eq.
+//              single; jump relations from [u] = 0 and [n.D grad u] = psi for diagonal D_c) are
+//              weighted sums of the density values of the crossing's transfer stencil, so an arm's
+//              whole term is one weighted sum, its weights formed at setup.
+//  k_gather  : n.D grad u+ at every interface node from its 6/10-node quadratic fit with the
+//              Taylor-expanded jump added to values on the "-" side (Sec. 5.4, eqs. taylor-i-po,
+//              taylor-i-co, ji).  The jumps at the node are linear in the density values of its
+//              transfer stencil, so the fit is a weighted sum of grid values plus one of density
+//              values, the second's weights formed at setup.
 //
-// Precision: the density, the transfer and jump weights, the node jumps and the extrapolation
-// fits are FP64 in every product.  Only the grid side follows the product's precision T: the
-// crossing jumps are stored in T for the correction, which writes the T right-hand side that
-// the T box solve transforms, and the gather reads the T grid values into its FP64 fit.
+// Folding the jumps into these weights takes the product of the 256^3 shell from 760 bytes of
+// tables per crossing and 1,500 per node to 400 per crossing (200 per arm) and 400 per node, and
+// from three launches with two intermediate arrays to two without.
+//
+// Precision: the density, the weights and the sums are FP64 in every product.  Only the grid side
+// follows the product's precision T: the correction is rounded to the T right-hand side that the T
+// box solve transforms, and the gather reads the T grid values into its FP64 fit.  The density and
+// the result are TP at the boundary (FP32 callers pass theirs, widened and rounded here).
 #include <cmath>
 #include <type_traits>
 #include <stdexcept>
@@ -29,193 +31,48 @@ namespace {
 
 constexpr int kBlock = 256;
 
-// All stencil sizes are compile-time constants so that every index load of a thread is
-// issued before the dependent gathers (the per-item forms are latency-bound).
-// The jump relations enter through per-point weights built at setup (linear in the density
-// values of the transfer stencil), so these kernels hold no geometry and serve any diagonal D.
-
-// [u_a], [u_aa] at one crossing for every component: two weighted sums of the density values.
-template <typename TZ, int K>
-__device__ __forceinline__ void jumps_cross_at(int64_t c, const double *__restrict__ psi, int64_t M, int64_t nc,
-                                               const int32_t *__restrict__ z_idx, const double *__restrict__ zA,
-                                               const double *__restrict__ zB, int ncomp, TZ *__restrict__ jz) {
-  int32_t j[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k) j[k] = z_idx[k * nc + c];
-  for (int comp = 0; comp < ncomp; ++comp) {
-    const double *ps = psi + comp * M;
-    const double *A = zA + (int64_t)comp * K * nc, *B = zB + (int64_t)comp * K * nc;
-    double v[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = ps[j[k]];
-    double ju = 0, juu = 0;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      ju += A[k * nc + c] * v[k];
-      juu += B[k * nc + c] * v[k];
-    }
-    jz[(2 * comp) * nc + c] = (TZ)ju;
-    jz[(2 * comp + 1) * nc + c] = (TZ)juu;
-  }
-}
-
-// One irregular node per thread (batched kernels); at most 2D arms, loaded predicated and all at once.
-// arm_s[comp][arm] = s_p D_{c,a} / h^2 for the arm's axis a.
-template <typename T, int D>
-__device__ __forceinline__ void correct_at(int64_t r, const int32_t *__restrict__ irr_pos,
-                                           const int32_t *__restrict__ irr_ptr, const int32_t *__restrict__ arm_cross,
-                                           const T *__restrict__ arm_d, const T *__restrict__ arm_s, int64_t narm,
-                                           const T *__restrict__ jz, int64_t nc, int ncomp, T *__restrict__ rhs,
-                                           int64_t comp_stride, int accumulate) {
-  constexpr int MAXA = 2 * D;
-  const int32_t b = irr_ptr[r], e = irr_ptr[r + 1];
-  const int64_t pos = irr_pos[r];
-  int32_t cr[MAXA];
-  T d[MAXA];
-#pragma unroll
-  for (int i = 0; i < MAXA; ++i) {
-    const bool ok = b + i < e;
-    cr[i] = ok ? arm_cross[b + i] : 0;
-    d[i] = ok ? arm_d[b + i] : T(0);
-  }
-  for (int comp = 0; comp < ncomp; ++comp) {
-    T du[MAXA], duu[MAXA], sg[MAXA];
-#pragma unroll
-    for (int i = 0; i < MAXA; ++i) {
-      const bool ok = b + i < e;
-      du[i] = jz[(2 * comp) * nc + cr[i]];
-      duu[i] = jz[(2 * comp + 1) * nc + cr[i]];
-      sg[i] = ok ? arm_s[comp * narm + b + i] : T(0);
-    }
-    T acc = 0;
-#pragma unroll
-    for (int i = 0; i < MAXA; ++i) acc += sg[i] * (du[i] * d[i] + (T)0.5 * duu[i] * d[i] * d[i]);
-    T *o = rhs + comp * comp_stride + pos;
-    if (accumulate)
-      *o += acc;
-    else
-      *o = acc;
-  }
-}
-
-template <int D>
-struct NH {
-  static constexpr int v = D == 2 ? 3 : 6;   // symmetric entries: xx yy (zz) xy (xz yz)
-};
-
-template <int D>
-__device__ __forceinline__ void sym_index(int e, int &a, int &b) {
-  if (D == 2) {
-    a = e == 1 ? 1 : 0;
-    b = e == 0 ? 0 : 1;
-  } else {
-    a = e < 3 ? e : (e == 5 ? 1 : 0);
-    b = e < 3 ? e : (e == 3 ? 1 : 2);
-  }
-}
-
-// [grad u] (D entries) and [Hess u] (NH entries) at one node for every component:
-// out_j = psi_q qc[j] + sum_f g_f qG[j][f], g = surface gradient of psi from the transfer fit.
-template <int D, int KN>
-__device__ __forceinline__ void jumps_nodes_at(int64_t q, const double *__restrict__ psi, int64_t M,
-                                               const int32_t *__restrict__ q_idx, const double *__restrict__ q_wg,
-                                               const double *__restrict__ q_c, const double *__restrict__ q_G,
-                                               int ncomp, double *__restrict__ jq) {
-  constexpr int J = D + NH<D>::v;
-  int32_t j[KN];
-#pragma unroll
-  for (int k = 0; k < KN; ++k) j[k] = q_idx[k * M + q];
-  for (int comp = 0; comp < ncomp; ++comp) {
-    const double *ps = psi + comp * M;
-    double v[KN];
-#pragma unroll
-    for (int k = 0; k < KN; ++k) v[k] = ps[j[k]];
-    double g[D];
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-      g[a] = 0;
-#pragma unroll
-      for (int k = 0; k < KN; ++k) g[a] += q_wg[(k * D + a) * M + q] * v[k];
-    }
-    const double pq = ps[q];
-    const double *C = q_c + (int64_t)comp * J * M, *G = q_G + (int64_t)comp * J * D * M;
-    double *o = jq + (int64_t)comp * J * M;
-#pragma unroll
-    for (int e = 0; e < J; ++e) {
-      double acc = pq * C[e * M + q];
-#pragma unroll
-      for (int f = 0; f < D; ++f) acc += g[f] * G[(e * D + f) * M + q];
-      o[e * M + q] = acc;
-    }
-  }
-}
-
-// n.D_c grad u+ at one node: st_nw[comp][j] = sum_a n_a D_{c,a} (gradient weight of node j)_a.
-template <typename TU, int D, int S>
-__device__ __forceinline__ void gather_at(int64_t q, const TU *__restrict__ u, int64_t comp_stride, int64_t M,
-                                          const int32_t *__restrict__ st_pos, const double *__restrict__ st_nw,
-                                          const double *__restrict__ st_r, const double *__restrict__ jq, int ncomp,
-                                          int with_jumps, double *__restrict__ out) {
-  constexpr int NHv = NH<D>::v, STR = D + NHv;
-  int32_t pe[S];
-#pragma unroll
-  for (int j = 0; j < S; ++j) pe[j] = st_pos[j * M + q];
-  for (int comp = 0; comp < ncomp; ++comp) {
-    const TU *uc = u + comp * comp_stride;
-    double val[S];
-#pragma unroll
-    for (int j = 0; j < S; ++j) val[j] = (double)uc[pe[j] < 0 ? -pe[j] - 1 : pe[j]];
-    if (with_jumps) {
-      const double *o = jq + (int64_t)comp * STR * M;
-      double du[D], H[D][D];
-#pragma unroll
-      for (int a = 0; a < D; ++a) du[a] = o[a * M + q];
-#pragma unroll
-      for (int e = 0; e < NHv; ++e) {
-        int a, b;
-        sym_index<D>(e, a, b);
-        H[a][b] = H[b][a] = o[(D + e) * M + q];
-      }
-#pragma unroll
-      for (int j = 0; j < S; ++j) {
-        if (pe[j] >= 0) continue;
-        double r[D];
-#pragma unroll
-        for (int a = 0; a < D; ++a) r[a] = st_r[(j * D + a) * M + q];
-        double Jv = 0;
-#pragma unroll
-        for (int a = 0; a < D; ++a) {
-          double hr = 0;
-#pragma unroll
-          for (int b = 0; b < D; ++b) hr += H[a][b] * r[b];
-          Jv += r[a] * (du[a] + 0.5 * hr);
-        }
-        val[j] += Jv;
-      }
-    }
-    const double *nw = st_nw + (int64_t)comp * S * M;
-    double acc = 0;
-#pragma unroll
-    for (int j = 0; j < S; ++j) acc += nw[j * M + q] * val[j];
-    out[comp * M + q] = acc;
-  }
-}
-
 inline unsigned nblk(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
-// ---------------------------------------------------------------- wavefront-cooperative gather
-//
-// One thread per node leaves the single-problem gather short of parallelism: 40,960 nodes of a
-// 3D problem are 640 wavefronts for 1024 SIMDs, each a chain of dependent loads (stencil index
-// -> grid value -> weighted sum).  Here a group of G consecutive lanes (4, 8 or 16, the next
-// power of two at or above the stencil size) shares one node: lane k takes stencil point k, and
-// the weighted sum is finished by a butterfly across the group.  Tables keep their
-// [point][node] layout.  The summation order differs from the one-thread form (a fixed tree
-// instead of a left-to-right sum), deterministically.
+// One arm per thread: all of its loads are independent of each other's results but for the
+// density values behind their indices.  The arms of a node are consecutive slots within 64 (setup
+// pads), and the first of them (count > 0) adds up the others' terms, at most 2D in all.
+// One thread per node instead would walk its arms one after the other.
+template <typename T, typename TP, int D, int K, int NC>
+__device__ __forceinline__ void correct_slot(const InterfaceTables &t, int64_t s, const TP *__restrict__ psi,
+                                             int64_t M, T *__restrict__ field, int64_t comp_stride, int accumulate) {
+  const int64_t ns = t.n_slots;
+  int32_t j[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) j[k] = t.arm_idx[k * ns + s];
+  const int2 head = reinterpret_cast<const int2 *>(t.arm_head)[s];   // padded position, arms of the node
+  double v[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const double *w = t.arm_w + (int64_t)c * K * ns;
+    v[c] = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[c] += w[k * ns + s] * (double)psi[c * M + j[k]];
+  }
+  double sum[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) sum[c] = v[c];
+#pragma unroll
+  for (int i = 1; i < 2 * D; ++i)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const double o = __shfl_down(v[c], i, 64);
+      sum[c] += i < head.y ? o : 0.0;
+    }
+  if (head.y > 0) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      T *o = field + c * comp_stride + head.x;
+      *o = accumulate ? (T)(*o + (T)sum[c]) : (T)sum[c];
+    }
+  }
+}
 
-constexpr int coop_group(int S) { return S <= 4 ? 4 : (S <= 8 ? 8 : 16); }
-
-// Sum over the G lanes of a group (G = 4, 8 or 16, aligned); every lane receives the total.
+// Sum over the G lanes of a group (G = 8 or 16, aligned); every lane receives the total.
 // A butterfly of DPP moves within a row of 16 lanes: swap neighbours, swap pairs (quad
 // permutes 1,0,3,2 and 2,3,0,1), then mirror within half rows and within the row, each step
 // pairing every lane with one of the other half of its current block.  VALU moves only, so the
@@ -227,202 +84,81 @@ __device__ __forceinline__ double dpp_f64(double v) {
   return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_update_dpp(0, w.x, CTRL, 0xF, 0xF, false),
                                               __builtin_amdgcn_update_dpp(0, w.y, CTRL, 0xF, 0xF, false)));
 }
-template <int CTRL>
-__device__ __forceinline__ float dpp_f32(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
-}
-template <int G, typename T>
-__device__ __forceinline__ T group_sum(T v) {
-  static_assert(G == 4 || G == 8 || G == 16, "group of 4, 8 or 16 lanes");
-  auto mv = [](T x, auto ctrl) {
-    if constexpr (sizeof(T) == 8) return dpp_f64<decltype(ctrl)::value>(x);
-    else return dpp_f32<decltype(ctrl)::value>(x);
-  };
-  v += mv(v, std::integral_constant<int, 0xB1>{});   // quad_perm 1,0,3,2
-  v += mv(v, std::integral_constant<int, 0x4E>{});   // quad_perm 2,3,0,1
-  if constexpr (G >= 8) v += mv(v, std::integral_constant<int, 0x141>{});   // row_half_mirror
-  if constexpr (G >= 16) v += mv(v, std::integral_constant<int, 0x140>{});  // row_mirror
+template <int G>
+__device__ __forceinline__ double group_sum(double v) {
+  static_assert(G == 8 || G == 16, "group of 8 or 16 lanes");
+  v += dpp_f64<0xB1>(v);                           // quad_perm 1,0,3,2
+  v += dpp_f64<0x4E>(v);                           // quad_perm 2,3,0,1
+  v += dpp_f64<0x141>(v);                          // row_half_mirror
+  if constexpr (G >= 16) v += dpp_f64<0x140>(v);   // row_mirror
   return v;
 }
 
-// [u_a], [u_aa] at crossing c for NC components, one thread per crossing: at 154,210 crossings
-// of a 3D problem that is 2.4 wavefronts per SIMD already, and a lane group per crossing (one
-// density point per lane, lane-shuffle sums) was measured slower, 28 -> 51 us for the launch.
-template <typename TZ, int K, int NC>
-__device__ __forceinline__ void jumps_cross_nc(int64_t c, const double *__restrict__ psi, int64_t M, int64_t nc,
-                                               const int32_t *__restrict__ z_idx, const double *__restrict__ zA,
-                                               const double *__restrict__ zB, TZ *__restrict__ jz) {
-  int32_t j[K];
+constexpr int gather_group(int S) { return S <= 8 ? 8 : 16; }
+
+// n.D_c grad u+ at node q by a group of consecutive lanes: lane k takes stencil point k and
+// density point k.  One thread per node leaves the GPU short of parallelism (40,960 nodes are 640
+// wavefronts for 1024 SIMDs, each a chain of index, value and sum).  Tables are [node][point], so
+// that a group's loads are contiguous.  psi null: the jumps are zero (volume solve).
+template <typename TU, typename TP, int S, int KN, int NC>
+__device__ __forceinline__ void gather_node(const InterfaceTables &t, int64_t q, int k, const TU *__restrict__ u,
+                                            int64_t comp_stride, const TP *__restrict__ psi, int64_t M,
+                                            TP *__restrict__ out) {
+  const bool us = k < S, ps = psi && k < KN;
+  const int32_t pos = us ? t.st_pos[q * S + k] : 0, j = ps ? t.q_idx[q * KN + k] : 0;
+  double v[NC];
 #pragma unroll
-  for (int k = 0; k < K; ++k) j[k] = z_idx[k * nc + c];
+  for (int c = 0; c < NC; ++c) {
+    const double nw = us ? t.st_nw[(c * M + q) * S + k] : 0.0, qw = ps ? t.q_w[(c * M + q) * KN + k] : 0.0;
+    v[c] = us ? nw * (double)u[c * comp_stride + pos] : 0.0;
+    if (ps) v[c] += qw * (double)psi[c * M + j];
+  }
 #pragma unroll
-  for (int comp = 0; comp < NC; ++comp) {
-    const double *ps = psi + comp * M;
-    const double *A = zA + (int64_t)comp * K * nc, *B = zB + (int64_t)comp * K * nc;
-    double ju = 0, juu = 0;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const double v = ps[j[k]];
-      ju += A[k * nc + c] * v;
-      juu += B[k * nc + c] * v;
-    }
-    jz[(2 * comp) * nc + c] = (TZ)ju;
-    jz[(2 * comp + 1) * nc + c] = (TZ)juu;
+  for (int c = 0; c < NC; ++c) {
+    const double sum = group_sum<gather_group(S)>(v[c]);
+    if (k == c) out[c * M + q] = (TP)sum;
   }
 }
 
-// Both jump sets in one launch (they are independent): blocks [0, nbc) take the crossings,
-// the others the interface nodes, one thread per item with the components unrolled.  A lane
-// group per node (one transfer point per lane, then butterflies over the group) was measured
-// slower: with the tables in [point][node] order each load of a group touches a separate line
-// per point, where a thread per node reads whole lines.
-template <typename TZ, int D, int K, int KN, int NC>
-__global__ __launch_bounds__(kBlock) void k_jumps_nc(const double *__restrict__ psi, int64_t M, int64_t nc,
-                                                     int64_t nbc, const int32_t *__restrict__ z_idx,
-                                                     const double *__restrict__ zA, const double *__restrict__ zB,
-                                                     const int32_t *__restrict__ q_idx, const double *__restrict__ q_wg,
-                                                     const double *__restrict__ q_c, const double *__restrict__ q_G,
-                                                     TZ *__restrict__ jz, double *__restrict__ jq) {
-  if ((int64_t)blockIdx.x < nbc) {
-    const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (c < nc) jumps_cross_nc<TZ, K, NC>(c, psi, M, nc, z_idx, zA, zB, jz);
-  } else {
-    const int64_t q = ((int64_t)blockIdx.x - nbc) * kBlock + threadIdx.x;
-    if (q < M) jumps_nodes_at<D, KN>(q, psi, M, q_idx, q_wg, q_c, q_G, NC, jq);
-  }
+template <typename T, typename TP, int D, int K, int NC>
+__global__ __launch_bounds__(kBlock) void k_correct(InterfaceTables t, const TP *__restrict__ psi, int64_t M,
+                                                    T *__restrict__ field, int64_t comp_stride, int accumulate) {
+  const int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (s < t.n_slots) correct_slot<T, TP, D, K, NC>(t, s, psi, M, field, comp_stride, accumulate);
 }
 
-// n.D_c grad u+ at node q, lane k < S taking stencil point k (its value, its jump term on the
-// "-" side, its flux weight).
-template <typename TU, int D, int S, int NC, int G>
-__device__ __forceinline__ void gather_coop(int64_t q, int k, const TU *__restrict__ u, int64_t comp_stride,
-                                            int64_t M, const int32_t *__restrict__ st_pos,
-                                            const double *__restrict__ st_nw, const double *__restrict__ st_r,
-                                            const double *__restrict__ jq, int with_jumps,
-                                            double *__restrict__ out) {
-  constexpr int NHv = NH<D>::v, STR = D + NHv;
-  const bool act = k < S;
-  const int32_t pe = act ? st_pos[k * M + q] : 0;
-  const int64_t pu = pe < 0 ? -(int64_t)pe - 1 : pe;
-  const bool minus = act && pe < 0 && with_jumps;
-  double val[NC], nw[NC], r[D];
-#pragma unroll
-  for (int comp = 0; comp < NC; ++comp) {
-    val[comp] = act ? (double)u[comp * comp_stride + pu] : 0.0;
-    nw[comp] = act ? st_nw[((int64_t)comp * S + k) * M + q] : 0.0;
-  }
-  if (minus) {
-#pragma unroll
-    for (int a = 0; a < D; ++a) r[a] = st_r[(k * D + a) * M + q];
-#pragma unroll
-    for (int comp = 0; comp < NC; ++comp) {
-      const double *o = jq + (int64_t)comp * STR * M;
-      double du[D], H[D][D];
-#pragma unroll
-      for (int a = 0; a < D; ++a) du[a] = o[a * M + q];
-#pragma unroll
-      for (int e = 0; e < NHv; ++e) {
-        int a, b;
-        sym_index<D>(e, a, b);
-        H[a][b] = H[b][a] = o[(D + e) * M + q];
-      }
-      double Jv = 0;
-#pragma unroll
-      for (int a = 0; a < D; ++a) {
-        double hr = 0;
-#pragma unroll
-        for (int b = 0; b < D; ++b) hr += H[a][b] * r[b];
-        Jv += r[a] * (du[a] + 0.5 * hr);
-      }
-      val[comp] += Jv;
-    }
-  }
-#pragma unroll
-  for (int comp = 0; comp < NC; ++comp) {
-    const double acc = group_sum<G>(nw[comp] * val[comp]);
-    if (k == comp) out[comp * M + q] = acc;
-  }
+template <typename TU, typename TP, int S, int KN, int NC>
+__global__ __launch_bounds__(kBlock) void k_gather(InterfaceTables t, const TU *__restrict__ u, int64_t comp_stride,
+                                                   const TP *__restrict__ psi, int64_t M, TP *__restrict__ out) {
+  constexpr int G = gather_group(S);
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x, q = i / G;
+  if (q < M) gather_node<TU, TP, S, KN, NC>(t, q, (int)(i % G), u, comp_stride, psi, M, out);
 }
 
-template <typename TU, int D, int S, int NC>
-__global__ __launch_bounds__(kBlock) void k_gather_coop(const TU *__restrict__ u, int64_t comp_stride, int64_t M,
-                                                        const int32_t *__restrict__ st_pos,
-                                                        const double *__restrict__ st_nw,
-                                                        const double *__restrict__ st_r,
-                                                        const double *__restrict__ jq, int with_jumps,
-                                                        double *__restrict__ out) {
-  constexpr int G = coop_group(S);
-  const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const int64_t q = t / G;
-  if (q < M) gather_coop<TU, D, S, NC, G>(q, (int)(t % G), u, comp_stride, M, st_pos, st_nw, st_r, jq, with_jumps,
-                                          out);
+// Batched 2D forms: block b of the launch is block blocks[b].y of problem blocks[b].x (a table, read
+// with one scalar load, where a search over prefix sums was a chain of loads per thread).
+template <typename T, typename TP>
+__global__ __launch_bounds__(kBlock) void k_batch_correct(const BatchItem<T> *__restrict__ items,
+                                                          const int2 *__restrict__ blocks,
+                                                          const TP *__restrict__ psi, int into_fpad) {
+  const int2 b = blocks[blockIdx.x];
+  const BatchItem<T> &it = items[b.x];
+  const int64_t s = (int64_t)b.y * kBlock + threadIdx.x;
+  if (s < it.tab.n_slots)
+    correct_slot<T, TP, 2, 4, 1>(it.tab, s, psi + it.ioff, it.M, into_fpad ? it.fpad : it.rhs, 0, into_fpad);
 }
 
-// Correction at irregular node r, one thread per node with the components unrolled (a lane
-// per arm was measured slower: at most six arms give little to share).
-template <typename T, int D, int NC>
-__global__ __launch_bounds__(kBlock) void k_correct_nc(int64_t nirr, const int32_t *__restrict__ irr_pos,
-                                                       const int32_t *__restrict__ irr_ptr,
-                                                       const int32_t *__restrict__ arm_cross,
-                                                       const T *__restrict__ arm_d, const T *__restrict__ arm_s,
-                                                       int64_t narm, const T *__restrict__ jz, int64_t nc,
-                                                       T *__restrict__ rhs, int64_t comp_stride, int accumulate) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < nirr)
-    correct_at<T, D>(r, irr_pos, irr_ptr, arm_cross, arm_d, arm_s, narm, jz, nc, NC, rhs, comp_stride, accumulate);
-}
-
-inline unsigned nblk_g(int64_t n, int G) { return (unsigned)((n * G + kBlock - 1) / kBlock); }
-
-// Problem of a flattened batch item: the largest p with cum[p] <= i (cum[0] = 0 <= i < cum[n]).
-__device__ __forceinline__ int batch_problem(const int64_t *__restrict__ cum, int n, int64_t i) {
-  int lo = 0, hi = n;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (cum[mid] <= i) lo = mid;
-    else hi = mid;
-  }
-  return lo;
-}
-
-// Work list of one launch: all crossings of all problems, then all their nodes.
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_batch_jumps(const BatchItem<T> *__restrict__ items, BatchCounts c,
-                                                        const double *__restrict__ psi) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < c.tot_nc) {
-    const int p = batch_problem(c.cum_nc, c.n, i);
-    const BatchItem<T> &it = items[p];
-    jumps_cross_at<T, 4>(i - c.cum_nc[p], psi + it.ioff, it.M, it.nc, it.z_idx, it.z_A, it.z_B, 1, it.jz);
-    return;
-  }
-  i -= c.tot_nc;
-  if (i >= c.tot_M) return;
-  const int p = batch_problem(c.cum_M, c.n, i);
-  const BatchItem<T> &it = items[p];
-  jumps_nodes_at<2, 5>(i - c.cum_M[p], psi + it.ioff, it.M, it.q_idx, it.q_wg, it.q_c, it.q_G, 1, it.jq);
-}
-
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_batch_correct(const BatchItem<T> *__restrict__ items, BatchCounts c,
-                                                          int target) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= c.tot_nirr) return;
-  const int p = batch_problem(c.cum_nirr, c.n, i);
-  const BatchItem<T> &it = items[p];
-  correct_at<T, 2>(i - c.cum_nirr[p], it.irr_pos, it.irr_ptr, it.arm_cross, it.arm_d, it.arm_s, it.narm, it.jz,
-                   it.nc, 1, target ? it.fpad : it.rhs, 0, target);
-}
-
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_batch_gather(const BatchItem<T> *__restrict__ items, BatchCounts c,
-                                                         int with_jumps, double *__restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= c.tot_M) return;
-  const int p = batch_problem(c.cum_M, c.n, i);
-  const BatchItem<T> &it = items[p];
-  gather_at<T, 2, 6>(i - c.cum_M[p], it.work, 0, it.M, it.st_pos, it.st_nw, it.st_r, it.jq, 1, with_jumps,
-                     out + it.ioff);
+template <typename T, typename TP>
+__global__ __launch_bounds__(kBlock) void k_batch_gather(const BatchItem<T> *__restrict__ items,
+                                                         const int2 *__restrict__ blocks,
+                                                         const TP *__restrict__ psi, TP *__restrict__ out) {
+  const int2 b = blocks[blockIdx.x];
+  const BatchItem<T> &it = items[b.x];
+  constexpr int G = gather_group(6);
+  const int64_t i = (int64_t)b.y * kBlock + threadIdx.x, q = i / G;
+  if (q < it.M)
+    gather_node<T, TP, 6, 5, 1>(it.tab, q, (int)(i % G), it.work, 0, psi ? psi + it.ioff : nullptr, it.M,
+                                out + it.ioff);
 }
 
 template <typename T>
@@ -443,28 +179,13 @@ std::vector<T> cast_vec(const std::vector<double> &v) {
   return std::vector<T>(v.begin(), v.end());
 }
 
-// Numeric tables in FP64 (as built on the host) and their device copies in one precision.
+// DST tables in FP64 as built on the host; every precision keeps its copy, its fields and its rhs.
 struct NumTables {
-  std::vector<double> z_A, z_B, q_wg, q_c, q_G, arm_d, arm_s, st_nw, st_r, tw, sp;
+  std::vector<double> tw, sp;
 };
 
-// The density-side tables (transfer and jump weights, extrapolation fits) and the node jumps
-// exist in FP64 only; every precision keeps its correction weights, DST tables, fields and
-// crossing jumps.
 template <typename T>
 void upload_prec(DevProblem &p, PrecTables<T> &tb, const NumTables &h) {
-  const bool fits = sizeof(T) == sizeof(double);
-  if (fits) {
-    tb.z_A = dupload(cast_vec<T>(h.z_A));
-    tb.z_B = dupload(cast_vec<T>(h.z_B));
-    tb.q_wg = dupload(cast_vec<T>(h.q_wg));
-    tb.q_c = dupload(cast_vec<T>(h.q_c));
-    tb.q_G = dupload(cast_vec<T>(h.q_G));
-    tb.st_nw = dupload(cast_vec<T>(h.st_nw));
-    tb.st_r = dupload(cast_vec<T>(h.st_r));
-  }
-  tb.arm_d = dupload(cast_vec<T>(h.arm_d));
-  tb.arm_s = dupload(cast_vec<T>(h.arm_s));
   tb.tw = dupload(cast_vec<T>(h.tw));
   tb.sp = dupload(cast_vec<T>(h.sp));
   const size_t field = (size_t)p.ncomp * p.comp_stride;
@@ -473,20 +194,16 @@ void upload_prec(DevProblem &p, PrecTables<T> &tb, const NumTables &h) {
   KFBI_HIP(hipMemset(tb.rhs, 0, field * sizeof(T)));
   KFBI_HIP(hipMemset(tb.work, 0, field * sizeof(T)));
   if (p.dim == 3) {
-    if (fits && p.ncomp == 2) {
+    if (sizeof(T) == sizeof(double) && p.ncomp == 2) {
       tb.gbuf = dalloc<T>((size_t)p.comp_stride);
       KFBI_HIP(hipMemset(tb.gbuf, 0, (size_t)p.comp_stride * sizeof(T)));
     }
   }
-  const int nh = p.dim == 2 ? 3 : 6;
-  tb.jz = dalloc<T>((size_t)p.ncomp * 2 * std::max<int64_t>(p.nc, 1));
-  if (fits) tb.jq = dalloc<T>((size_t)p.ncomp * (p.dim + nh) * p.M);
 }
 
 template <typename T>
 void free_prec(PrecTables<T> &tb) {
-  T **all[] = {&tb.z_A, &tb.z_B, &tb.q_wg, &tb.q_c, &tb.q_G, &tb.arm_d, &tb.arm_s, &tb.st_nw, &tb.st_r,
-               &tb.tw, &tb.sp, &tb.rhs, &tb.work, &tb.gbuf, &tb.jz, &tb.jq};
+  T **all[] = {&tb.tw, &tb.sp, &tb.rhs, &tb.work, &tb.gbuf};
   for (T **q : all) {
     if (*q) (void)hipFree(*q);
     *q = nullptr;
@@ -495,113 +212,75 @@ void free_prec(PrecTables<T> &tb) {
 
 }  // namespace
 
-template <typename T, int D, int K, int KN, int NC>
-static void jumps_nc(DevProblem &p, const double *psi, hipStream_t st) {
-  const PrecTables<double> &tb = p.f64;
-  const int64_t nbc = p.nc > 0 ? nblk(p.nc) : 0;
-  const unsigned g = (unsigned)(nbc + nblk(p.M));
-  k_jumps_nc<T, D, K, KN, NC><<<g, kBlock, 0, st>>>(psi, p.M, p.nc, nbc, p.z_idx, tb.z_A, tb.z_B, p.q_idx, tb.q_wg,
-                                                    tb.q_c, tb.q_G, p.tab<T>().jz, tb.jq);
-}
-
-template <typename T>
-void launch_jumps(DevProblem &p, const double *psi, hipStream_t st) {
+template <typename T, typename TP>
+static void correct_into(DevProblem &p, const TP *psi, T *field, int accumulate, hipStream_t st) {
+  const InterfaceTables &t = p.itab;
+  if (t.n_slots == 0) return;
+  const unsigned g = nblk(t.n_slots);
+  const int64_t cs = p.comp_stride;
   if (p.dim == 2) {
-    if (p.ncomp == 2) jumps_nc<T, 2, 4, 5, 2>(p, psi, st);
-    else jumps_nc<T, 2, 4, 5, 1>(p, psi, st);
+    if (p.ncomp == 2) k_correct<T, TP, 2, 4, 2><<<g, kBlock, 0, st>>>(t, psi, p.M, field, cs, accumulate);
+    else k_correct<T, TP, 2, 4, 1><<<g, kBlock, 0, st>>>(t, psi, p.M, field, cs, accumulate);
   } else {
-    if (p.ncomp == 2) jumps_nc<T, 3, kLsqNodes, kLsqNodes, 2>(p, psi, st);
-    else jumps_nc<T, 3, kLsqNodes, kLsqNodes, 1>(p, psi, st);
+    if (p.ncomp == 2) k_correct<T, TP, 3, kLsqNodes, 2><<<g, kBlock, 0, st>>>(t, psi, p.M, field, cs, accumulate);
+    else k_correct<T, TP, 3, kLsqNodes, 1><<<g, kBlock, 0, st>>>(t, psi, p.M, field, cs, accumulate);
   }
   KFBI_HIP(hipGetLastError());
 }
 
-template <typename T, int D, int NC>
-static void correct_nc(DevProblem &p, T *field, int accumulate, hipStream_t st) {
-  PrecTables<T> &tb = p.tab<T>();
-  k_correct_nc<T, D, NC><<<nblk(p.nirr), kBlock, 0, st>>>(
-      p.nirr, p.irr_pos, p.irr_ptr, p.arm_cross, tb.arm_d, tb.arm_s, p.narm, tb.jz, p.nc, field, p.comp_stride,
-      accumulate);
+template <typename T, typename TP>
+void launch_correct(DevProblem &p, const TP *psi, hipStream_t st) {
+  correct_into<T, TP>(p, psi, p.tab<T>().rhs, 0, st);
+}
+template void launch_correct<double, double>(DevProblem &, const double *, hipStream_t);
+template void launch_correct<float, double>(DevProblem &, const double *, hipStream_t);
+template void launch_correct<float, float>(DevProblem &, const float *, hipStream_t);
+
+void launch_add_correction(DevProblem &p, const double *psi, double *field_padded, hipStream_t st) {
+  correct_into<double, double>(p, psi, field_padded, 1, st);
 }
 
-template <typename T>
-static void correct_into(DevProblem &p, T *field, int accumulate, hipStream_t st) {
-  if (p.nirr == 0) return;
+template <typename T, typename TP>
+void launch_gather(DevProblem &p, const T *u, const TP *psi, TP *out, hipStream_t st) {
+  const unsigned g = nblk(p.M * gather_group(p.S));
+  const InterfaceTables &t = p.itab;
+  const int64_t cs = p.comp_stride;
   if (p.dim == 2) {
-    if (p.ncomp == 2) correct_nc<T, 2, 2>(p, field, accumulate, st);
-    else correct_nc<T, 2, 1>(p, field, accumulate, st);
+    if (p.ncomp == 2) k_gather<T, TP, 6, 5, 2><<<g, kBlock, 0, st>>>(t, u, cs, psi, p.M, out);
+    else k_gather<T, TP, 6, 5, 1><<<g, kBlock, 0, st>>>(t, u, cs, psi, p.M, out);
   } else {
-    if (p.ncomp == 2) correct_nc<T, 3, 2>(p, field, accumulate, st);
-    else correct_nc<T, 3, 1>(p, field, accumulate, st);
+    if (p.ncomp == 2) k_gather<T, TP, 10, kLsqNodes, 2><<<g, kBlock, 0, st>>>(t, u, cs, psi, p.M, out);
+    else k_gather<T, TP, 10, kLsqNodes, 1><<<g, kBlock, 0, st>>>(t, u, cs, psi, p.M, out);
   }
   KFBI_HIP(hipGetLastError());
 }
+template void launch_gather<double, double>(DevProblem &, const double *, const double *, double *, hipStream_t);
+template void launch_gather<float, double>(DevProblem &, const float *, const double *, double *, hipStream_t);
+template void launch_gather<float, float>(DevProblem &, const float *, const float *, float *, hipStream_t);
 
-template <typename T>
-void launch_correct(DevProblem &p, hipStream_t st) {
-  correct_into<T>(p, p.tab<T>().rhs, 0, st);
-}
+int correct_blocks(const DevProblem &p) { return (int)nblk(p.itab.n_slots); }
+int gather_blocks(const DevProblem &p) { return (int)nblk(p.M * gather_group(p.S)); }
 
-template <typename T>
-void launch_add_correction(DevProblem &p, T *field_padded, hipStream_t st) {
-  correct_into<T>(p, field_padded, 1, st);
-}
-
-template <typename T, int D, int S, int NC>
-static void gather_coop_launch(DevProblem &p, const T *u, bool with_jumps, double *out, hipStream_t st) {
-  const PrecTables<double> &tb = p.f64;
-  k_gather_coop<T, D, S, NC><<<nblk_g(p.M, coop_group(S)), kBlock, 0, st>>>(
-      u, p.comp_stride, p.M, p.st_pos, tb.st_nw, tb.st_r, tb.jq, with_jumps ? 1 : 0, out);
-}
-
-template <typename T>
-void launch_gather(DevProblem &p, const T *u, bool with_jumps, double *out, hipStream_t st) {
-  if (p.dim == 2) {
-    if (p.ncomp == 2) gather_coop_launch<T, 2, 6, 2>(p, u, with_jumps, out, st);
-    else gather_coop_launch<T, 2, 6, 1>(p, u, with_jumps, out, st);
-  } else {
-    if (p.ncomp == 2) gather_coop_launch<T, 3, 10, 2>(p, u, with_jumps, out, st);
-    else gather_coop_launch<T, 3, 10, 1>(p, u, with_jumps, out, st);
-  }
+template <typename T, typename TP>
+void launch_batch_correct(const BatchItem<T> *items, const BatchBlocks &b, const TP *psi, bool into_fpad,
+                          hipStream_t st) {
+  if (b.n == 0) return;
+  k_batch_correct<T, TP><<<(unsigned)b.n, kBlock, 0, st>>>(items, b.ref, psi, into_fpad ? 1 : 0);
   KFBI_HIP(hipGetLastError());
 }
-
-template <typename T>
-void launch_batch_jumps(const BatchItem<T> *items, const BatchCounts &c, const double *psi, hipStream_t st) {
-  const int64_t n = c.tot_nc + c.tot_M;
-  if (n == 0) return;
-  k_batch_jumps<T><<<nblk(n), kBlock, 0, st>>>(items, c, psi);
+template <typename T, typename TP>
+void launch_batch_gather(const BatchItem<T> *items, const BatchBlocks &b, const TP *psi, TP *out, hipStream_t st) {
+  if (b.n == 0) return;
+  k_batch_gather<T, TP><<<(unsigned)b.n, kBlock, 0, st>>>(items, b.ref, psi, out);
   KFBI_HIP(hipGetLastError());
 }
-template <typename T>
-void launch_batch_correct(const BatchItem<T> *items, const BatchCounts &c, int target, hipStream_t st) {
-  if (c.tot_nirr == 0) return;
-  k_batch_correct<T><<<nblk(c.tot_nirr), kBlock, 0, st>>>(items, c, target);
-  KFBI_HIP(hipGetLastError());
-}
-template <typename T>
-void launch_batch_gather(const BatchItem<T> *items, const BatchCounts &c, bool with_jumps, double *out,
-                         hipStream_t st) {
-  if (c.tot_M == 0) return;
-  k_batch_gather<T><<<nblk(c.tot_M), kBlock, 0, st>>>(items, c, with_jumps ? 1 : 0, out);
-  KFBI_HIP(hipGetLastError());
-}
-template void launch_batch_jumps<double>(const BatchItem<double> *, const BatchCounts &, const double *, hipStream_t);
-template void launch_batch_jumps<float>(const BatchItem<float> *, const BatchCounts &, const double *, hipStream_t);
-template void launch_batch_correct<double>(const BatchItem<double> *, const BatchCounts &, int, hipStream_t);
-template void launch_batch_correct<float>(const BatchItem<float> *, const BatchCounts &, int, hipStream_t);
-template void launch_batch_gather<double>(const BatchItem<double> *, const BatchCounts &, bool, double *,
-                                          hipStream_t);
-template void launch_batch_gather<float>(const BatchItem<float> *, const BatchCounts &, bool, double *, hipStream_t);
-
-template void launch_jumps<double>(DevProblem &, const double *, hipStream_t);
-template void launch_jumps<float>(DevProblem &, const double *, hipStream_t);
-template void launch_correct<double>(DevProblem &, hipStream_t);
-template void launch_correct<float>(DevProblem &, hipStream_t);
-template void launch_add_correction<double>(DevProblem &, double *, hipStream_t);
-template void launch_add_correction<float>(DevProblem &, float *, hipStream_t);
-template void launch_gather<double>(DevProblem &, const double *, bool, double *, hipStream_t);
-template void launch_gather<float>(DevProblem &, const float *, bool, double *, hipStream_t);
+#define KFBI_BATCH_LAUNCH(T, TP)                                                                                 \
+  template void launch_batch_correct<T, TP>(const BatchItem<T> *, const BatchBlocks &, const TP *, bool, hipStream_t); \
+  template void launch_batch_gather<T, TP>(const BatchItem<T> *, const BatchBlocks &, const TP *, TP *, hipStream_t);
+KFBI_BATCH_LAUNCH(double, double)
+KFBI_BATCH_LAUNCH(float, double)
+KFBI_BATCH_LAUNCH(float, float)
+#undef KFBI_BATCH_LAUNCH
 
 // Jump-relation coefficients of one component at a point with normal n and shape operator W
 // (diagonal conductivity Dv): with a = psi / (n.D n),
@@ -651,10 +330,6 @@ void upload_tables(DevProblem &p) {
   p.Mfft = t.cells;
   p.P = t.cells;
   p.comp_stride = p.P * (d == 3 ? p.N * p.N : p.N);
-  p.nc = t.nc;
-  p.nirr = (int64_t)t.irregular.size();
-  p.K = t.K;
-  p.Kn = t.Kn;
   p.S = t.S;
   p.h = t.h;
   p.kappa = t.kappa;
@@ -663,32 +338,16 @@ void upload_tables(DevProblem &p) {
   p.lam_scale = 1.0;
   for (int a = 0; a < d; ++a) p.lam_scale *= 2.0 / (double)t.cells;
   p.direct = column_direct(d, nc_, t.cells, t.h, p.D, t.kappa);
-  const int64_t N = p.N, M = p.M, nc = p.nc, P = p.P, K = t.K, Kn = t.Kn, S = t.S;
+  const int64_t N = p.N, M = p.M, nc = t.nc, P = p.P, K = t.K, Kn = t.Kn, S = t.S;
   auto padpos = [&](int64_t lin) { return (lin % N) + P * (lin / N); };
   if (padpos(N * (d == 3 ? N * N : N) - 1) >= (int64_t)1 << 31) throw std::invalid_argument("grid too large");
   NumTables h;
 
-  // crossings: [u_a] and [u_aa] (a = the arm's axis) as weights on the transfer stencil
-  std::vector<int32_t> z_idx(nc * K), z_axis(nc);
-  h.z_A.assign((size_t)nc_ * K * nc, 0.0);
-  h.z_B.assign((size_t)nc_ * K * nc, 0.0);
-  for (int64_t c = 0; c < nc; ++c) {
-    const int a = (int)t.c_axis[c];
-    z_axis[c] = a;
-    for (int k = 0; k < K; ++k) z_idx[k * nc + c] = (int32_t)t.z_idx[c * K + k];
-    for (int comp = 0; comp < nc_; ++comp) {
-      const JumpCoef jc(d, &t.c_n[c * d], &t.c_W[c * d * d], t.D[comp]);
-      const double al = jc.alpha(a, a);
-      for (int k = 0; k < K; ++k) {
-        const double w0 = t.z_w0[c * K + k];
-        double bk = w0 * al;
-        for (int f = 0; f < d; ++f) bk += t.z_wg[(c * K + k) * d + f] * jc.beta(a, a, f);
-        h.z_A[((size_t)comp * K + k) * nc + c] = w0 * jc.grad(a);
-        h.z_B[((size_t)comp * K + k) * nc + c] = bk;
-      }
-    }
-  }
-  // correction records: CSR over irregular nodes; arm_s[comp][arm] = s D_{comp,a} / h^2
+  // Correction records.  The arm of a crossing at node p (tissue side: s = +1) adds
+  //   s D_{c,a} / h^2 ([u_a] d + [u_aa] d^2 / 2),  [u_a] = sum_k w0_k grad_a psi_k,
+  //   [u_aa] = sum_k (w0_k alpha_aa + sum_f wg_kf beta_aa,f) psi_k,
+  // a = the crossing's axis, so it is one weight per density point of the crossing's stencil.
+  // Arms of a node take consecutive slots that do not straddle a multiple of 64.
   std::vector<std::vector<int64_t>> arms_of(t.irregular.size());
   auto rank = [&](int64_t lin) {
     return (int64_t)(std::lower_bound(t.irregular.begin(), t.irregular.end(), lin) - t.irregular.begin());
@@ -697,72 +356,87 @@ void upload_tables(DevProblem &p) {
     arms_of[rank(t.c_pin[c])].push_back(2 * c);       // tissue-side node, s = +1
     arms_of[rank(t.c_pout[c])].push_back(2 * c + 1);  // "-"-side node, s = -1
   }
-  std::vector<int32_t> irr_pos(t.irregular.size()), irr_ptr(t.irregular.size() + 1, 0), arm_cross;
-  std::vector<int> arm_axis;
-  std::vector<double> arm_sign;
   const double ih2 = 1.0 / (t.h * t.h);
   auto coord = [&](int64_t lin, int a) {
     int64_t r = lin;
     for (int b = 0; b < a; ++b) r /= N;
     return t.lo + t.h * (double)(r % N + 1);
   };
+  std::vector<int64_t> slot_of(t.irregular.size());
+  int64_t ns = 0;
   for (size_t r = 0; r < t.irregular.size(); ++r) {
-    irr_pos[r] = (int32_t)padpos(t.irregular[r]);
-    for (int64_t code : arms_of[r]) {
-      const int64_t c = code / 2;
-      const bool plus = (code % 2) == 0;
-      const int a = (int)t.c_axis[c];
-      const int64_t nb = plus ? t.c_pout[c] : t.c_pin[c];
-      arm_cross.push_back((int32_t)c);
-      h.arm_d.push_back(coord(nb, a) - t.c_z[c * d + a]);
-      arm_axis.push_back(a);
-      arm_sign.push_back(plus ? ih2 : -ih2);
-    }
-    irr_ptr[r + 1] = (int32_t)arm_cross.size();
+    const int64_t n = (int64_t)arms_of[r].size();
+    if (n > 2 * d) throw std::logic_error("a grid node with more arms than directions");
+    if (ns % 64 + n > 64) ns = (ns + 63) / 64 * 64;
+    slot_of[r] = ns;
+    ns += n;
   }
-  p.narm = (int64_t)arm_cross.size();
-  h.arm_s.assign((size_t)nc_ * std::max<int64_t>(p.narm, 1), 0.0);
-  for (int comp = 0; comp < nc_; ++comp)
-    for (int64_t i = 0; i < p.narm; ++i) h.arm_s[comp * p.narm + i] = arm_sign[i] * t.D[comp][arm_axis[i]];
-  // node jumps: [grad u] and [Hess u] from psi at the node and the surface gradient g
-  const int nh = d == 2 ? 3 : 6, J = d + nh;
-  const int SA[6] = {0, 1, 2, 0, 0, 1}, SB[6] = {0, 1, 2, 1, 2, 2};
-  const int SA2[3] = {0, 1, 0}, SB2[3] = {0, 1, 1};
-  std::vector<int32_t> q_idx(M * Kn);
-  h.q_wg.assign((size_t)M * Kn * d, 0.0);
-  h.q_c.assign((size_t)nc_ * J * M, 0.0);
-  h.q_G.assign((size_t)nc_ * J * d * M, 0.0);
-  for (int64_t q = 0; q < M; ++q) {
-    for (int k = 0; k < Kn; ++k) {
-      q_idx[k * M + q] = (int32_t)t.q_idx[q * Kn + k];
-      for (int a = 0; a < d; ++a) h.q_wg[(k * d + a) * M + q] = t.q_wg[(q * Kn + k) * d + a];
+  ns = (ns + 63) / 64 * 64;
+  std::vector<int32_t> arm_idx((size_t)K * ns, 0), arm_head((size_t)2 * ns, 0);
+  std::vector<double> arm_w((size_t)nc_ * K * ns, 0.0);
+  for (size_t r = 0; r < t.irregular.size(); ++r) {
+    arm_head[2 * slot_of[r]] = (int32_t)padpos(t.irregular[r]);
+    arm_head[2 * slot_of[r] + 1] = (int32_t)arms_of[r].size();
+    for (size_t i = 0; i < arms_of[r].size(); ++i) {
+      const int64_t c = arms_of[r][i] / 2, s = slot_of[r] + (int64_t)i;
+      const bool plus = (arms_of[r][i] % 2) == 0;
+      const int a = (int)t.c_axis[c];
+      const double dist = coord(plus ? t.c_pout[c] : t.c_pin[c], a) - t.c_z[c * d + a];
+      for (int k = 0; k < K; ++k) arm_idx[k * ns + s] = (int32_t)t.z_idx[c * K + k];
+      for (int comp = 0; comp < nc_; ++comp) {
+        const JumpCoef jc(d, &t.c_n[c * d], &t.c_W[c * d * d], t.D[comp]);
+        const double al = jc.alpha(a, a), sc = (plus ? ih2 : -ih2) * t.D[comp][a];
+        for (int k = 0; k < K; ++k) {
+          const double w0 = t.z_w0[c * K + k];
+          double bk = w0 * al;
+          for (int f = 0; f < d; ++f) bk += t.z_wg[(c * K + k) * d + f] * jc.beta(a, a, f);
+          arm_w[((size_t)comp * K + k) * ns + s] = sc * (w0 * jc.grad(a) * dist + 0.5 * bk * dist * dist);
+        }
+      }
     }
+  }
+  // Gather tables [node][point]: st_nw[comp] = n . D_comp (gradient weights of the stencil node), and
+  // the jumps the fit adds on its "-" side points r_j,  sum_j nw_j (r.[grad u] + r.[Hess u] r / 2),
+  // as one weight q_w per density point of the node's stencil.
+  std::vector<int32_t> st_pos(M * S), q_idx(M * Kn);
+  std::vector<double> st_nw((size_t)nc_ * M * S), q_w((size_t)nc_ * M * Kn);
+  for (int64_t q = 0; q < M; ++q) {
+    int self = -1;
+    for (int k = 0; k < Kn; ++k) {
+      q_idx[q * Kn + k] = (int32_t)t.q_idx[q * Kn + k];
+      if (t.q_idx[q * Kn + k] == q && self < 0) self = k;
+    }
+    if (self < 0) throw std::logic_error("a node's transfer stencil without the node");
+    for (int j = 0; j < S; ++j) st_pos[q * S + j] = (int32_t)padpos(t.st_lin[q * S + j]);
     for (int comp = 0; comp < nc_; ++comp) {
       const JumpCoef jc(d, &t.nrm[q * d], &t.W[q * d * d], t.D[comp]);
-      double *C = &h.q_c[(size_t)comp * J * M], *G = &h.q_G[(size_t)comp * J * d * M];
-      for (int a = 0; a < d; ++a) C[a * M + q] = jc.grad(a);
-      for (int e = 0; e < nh; ++e) {
-        const int a = d == 2 ? SA2[e] : SA[e], b = d == 2 ? SB2[e] : SB[e];
-        C[(d + e) * M + q] = jc.alpha(a, b);
-        for (int f = 0; f < d; ++f) G[((d + e) * d + f) * M + q] = jc.beta(a, b, f);
+      double rg[3] = {0, 0, 0}, rh[3][3] = {};
+      for (int j = 0; j < S; ++j) {
+        double nw = 0;
+        for (int a = 0; a < d; ++a) nw += t.nrm[q * d + a] * t.D[comp][a] * t.st_wgrad[(q * S + j) * d + a];
+        st_nw[((size_t)comp * M + q) * S + j] = nw;
+        if (!t.st_chi[q * S + j]) continue;
+        const double *r = &t.st_r[(q * S + j) * d];
+        for (int a = 0; a < d; ++a) {
+          rg[a] += nw * r[a];
+          for (int b = 0; b < d; ++b) rh[a][b] += 0.5 * nw * r[a] * r[b];
+        }
+      }
+      double cq = 0, cg[3] = {0, 0, 0};
+      for (int a = 0; a < d; ++a) {
+        cq += rg[a] * jc.grad(a);
+        for (int b = 0; b < d; ++b) {
+          cq += rh[a][b] * jc.alpha(a, b);
+          for (int f = 0; f < d; ++f) cg[f] += rh[a][b] * jc.beta(a, b, f);
+        }
+      }
+      for (int k = 0; k < Kn; ++k) {
+        double w = k == self ? cq : 0.0;
+        for (int f = 0; f < d; ++f) w += cg[f] * t.q_wg[(q * Kn + k) * d + f];
+        q_w[((size_t)comp * M + q) * Kn + k] = w;
       }
     }
   }
-  // gather stencils: st_nw[comp][j] = n . D_comp (gradient weights of stencil node j)
-  std::vector<int32_t> st_pos(M * S);
-  h.st_nw.assign((size_t)nc_ * S * M, 0.0);
-  h.st_r.assign((size_t)M * S * d, 0.0);
-  for (int64_t q = 0; q < M; ++q)
-    for (int j = 0; j < S; ++j) {
-      const int64_t pos = padpos(t.st_lin[q * S + j]);
-      st_pos[j * M + q] = t.st_chi[q * S + j] ? (int32_t)(-pos - 1) : (int32_t)pos;
-      for (int a = 0; a < d; ++a) h.st_r[(j * d + a) * M + q] = t.st_r[(q * S + j) * d + a];
-      for (int comp = 0; comp < nc_; ++comp) {
-        double nw = 0;
-        for (int a = 0; a < d; ++a) nw += t.nrm[q * d + a] * t.D[comp][a] * t.st_wgrad[(q * S + j) * d + a];
-        h.st_nw[((size_t)comp * S + j) * M + q] = nw;
-      }
-    }
   // DST tables
   const int Mf = p.Mfft;
   h.tw.resize(2 * Mf);
@@ -819,13 +493,14 @@ void upload_tables(DevProblem &p) {
       if (pout[z]) p.planes_out_bits.w[z >> 6] |= uint64_t(1) << (z & 63);
     }
   }
-  p.z_idx = dupload(z_idx);
-  p.z_axis = dupload(z_axis);
-  p.q_idx = dupload(q_idx);
-  p.irr_pos = dupload(irr_pos);
-  p.irr_ptr = dupload(irr_ptr);
-  p.arm_cross = dupload(arm_cross);
-  p.st_pos = dupload(st_pos);
+  p.itab.n_slots = ns;
+  p.itab.arm_idx = dupload(arm_idx);
+  p.itab.arm_head = dupload(arm_head);
+  p.itab.arm_w = dupload(arm_w);
+  p.itab.st_pos = dupload(st_pos);
+  p.itab.st_nw = dupload(st_nw);
+  p.itab.q_idx = dupload(q_idx);
+  p.itab.q_w = dupload(q_w);
   p.inside_pad = dupload(ins_pad);
   p.lam = dupload(lam);
   upload_prec<double>(p, p.f64, h);
@@ -839,8 +514,13 @@ void upload_tables(DevProblem &p) {
 }
 
 void free_tables(DevProblem &p) {
-  int32_t **ip[] = {&p.z_idx, &p.z_axis, &p.q_idx, &p.irr_pos, &p.irr_ptr, &p.arm_cross, &p.st_pos,
-                    &p.rows_in, &p.rows_out};
+  int32_t **ip[] = {&p.itab.arm_idx, &p.itab.arm_head, &p.itab.st_pos, &p.itab.q_idx, &p.rows_in, &p.rows_out};
+  double **wp[] = {&p.itab.arm_w, &p.itab.st_nw, &p.itab.q_w};
+  for (double **q : wp) {
+    if (*q) (void)hipFree(*q);
+    *q = nullptr;
+  }
+  p.itab.n_slots = 0;
   uint8_t **up[] = {&p.planes_in, &p.planes_out};
   for (uint8_t **q : up) {
     if (*q) (void)hipFree(*q);

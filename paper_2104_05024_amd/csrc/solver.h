@@ -42,15 +42,12 @@ struct Solver {
   void init(DevProblem &p);
   void release();
 
-  // out = A psi with FP64 vectors; T is the precision of the grid side (correction and box solve),
-  // the density side (jumps, extrapolation fits) is FP64 in both
-  template <typename T>
-  void apply(DevProblem &p, const double *psi, double *out, hipStream_t st);
+  // out = A psi; T is the precision of the grid side (correction and box solve), the weights and
+  // sums of the density side are FP64 in both; TP the vectors' type at the boundary
+  template <typename T, typename TP>
+  void apply(DevProblem &p, const TP *psi, TP *out, hipStream_t st);
   // y = A x; prec 1 runs the grid side in FP32
   void apply_vec(DevProblem &p, int prec, const double *x, double *y, hipStream_t st);
-  // FP32 vectors at the boundary, converted to and from FP64 around the FP32 product
-  void apply_f32(DevProblem &p, const float *psi, float *out, hipStream_t st);
-
   double dot(const double *a, const double *b, hipStream_t st);
   double residual_norm(const double *b, const double *Ax, hipStream_t st);   // ||b - Ax||_2 (uses d)
   // GMRES(m) with FP64 Arnoldi (CGS2) and Givens rotations on A x = b (stops at ||b - A x|| <= tol_abs);

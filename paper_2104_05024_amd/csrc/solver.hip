@@ -209,12 +209,6 @@ __global__ __launch_bounds__(kB) void k_end_step(double *__restrict__ gp_prev, c
   psi_last[i] = v;
 }
 
-template <typename A, typename B>
-__global__ __launch_bounds__(kB) void k_cast(const A *__restrict__ x, B *__restrict__ y, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x;
-  if (i < n) y[i] = (B)x[i];
-}
-
 // plain [comp][N^d] -> padded [comp][..][P]
 __global__ __launch_bounds__(kB) void k_to_padded(const double *__restrict__ f, double *__restrict__ fp,
                                                   int64_t nplain, int64_t N, int64_t P, int64_t cs, int ncomp) {
@@ -338,33 +332,22 @@ void Solver::release() {
   hhost = nullptr;
 }
 
-template <typename T>
-void Solver::apply(DevProblem &p, const double *psi, double *out, hipStream_t st) {
-  PrecTables<T> &tb = p.tab<T>();
-  p.t_jumps.tic(p.profile, st);
-  launch_jumps<T>(p, psi, st);
-  p.t_jumps.toc(p.profile, st);
+template <typename T, typename TP>
+void Solver::apply(DevProblem &p, const TP *psi, TP *out, hipStream_t st) {
   p.t_correct.tic(p.profile, st);
-  launch_correct<T>(p, st);
+  launch_correct<T, TP>(p, psi, st);
   p.t_correct.toc(p.profile, st);
   box_solve_matvec<T>(p, st);
   p.t_gather.tic(p.profile, st);
-  launch_gather<T>(p, tb.work, true, out, st);
+  launch_gather<T, TP>(p, p.tab<T>().work, psi, out, st);
   p.t_gather.toc(p.profile, st);
 }
-template void Solver::apply<double>(DevProblem &, const double *, double *, hipStream_t);
-template void Solver::apply<float>(DevProblem &, const double *, double *, hipStream_t);
+template void Solver::apply<double, double>(DevProblem &, const double *, double *, hipStream_t);
+template void Solver::apply<float, float>(DevProblem &, const float *, float *, hipStream_t);
 
 void Solver::apply_vec(DevProblem &p, int prec, const double *x, double *y, hipStream_t st) {
   if (prec == 0) apply<double>(p, x, y, st);
   else apply<float>(p, x, y, st);
-}
-
-void Solver::apply_f32(DevProblem &p, const float *psi, float *out, hipStream_t st) {
-  k_cast<float, double><<<nblk(L), kB, 0, st>>>(psi, t, L);
-  apply<float>(p, t, w, st);
-  k_cast<double, float><<<nblk(L), kB, 0, st>>>(w, out, L);
-  KFBI_HIP(hipGetLastError());
 }
 
 double Solver::residual_norm(const double *b, const double *Ax, hipStream_t st) {
@@ -617,7 +600,7 @@ void Solver::bie_rhs(DevProblem &p, const double *g, hipStream_t st, const FhnAr
   // u_V is needed only at the extrapolation stencils of the interface nodes
   if (fa) bidomain_volume_solve(p, *fa, st);
   else box_solve_stencils<double>(p, fpad, st);
-  launch_gather<double>(p, p.f64.work, false, t, st);
+  launch_gather<double, double>(p, p.f64.work, nullptr, t, st);
   if (g)
     k_axpby<<<nblk(L), kB, 0, st>>>(gp, 1.0, g, -1.0, t, L);
   else
@@ -750,13 +733,12 @@ void Solver::reconstruct(DevProblem &p, const double *psi, hipStream_t st, const
     KFBI_HIP(hipGetLastError());
     psi = nullp;
   }
-  launch_jumps<double>(p, psi, st);
   if (fa) {
-    launch_correct<double>(p, st);
+    launch_correct<double>(p, psi, st);
     bidomain_final_solve(p, *fa, fuse_be, st);
     return;
   }
-  launch_add_correction<double>(p, fpad, st);
+  launch_add_correction(p, psi, fpad, st);
   box_solve<double>(p, fpad, false, p.f64.work, false, st);
 }
 
