@@ -122,7 +122,7 @@ typedef struct {
 typedef struct kfbi_problem_s *kfbi_problem;
 
 #define KFBI_SETUP_HOST_ONLY 1u   /* build the host tables only (no GPU calls) */
-#define KFBI_SETUP_NO_AUTOTUNE 2u /* keep the default DST tile widths (no timed launches at setup) */
+#define KFBI_SETUP_NO_AUTOTUNE 2u /* accepted, no effect: the passes have one tile shape, none is timed at setup */
 
 /* kfbi_setup: build every static table of the method for (interface, grid, coeffs)
  * -- interface nodes, normals, shape operators; grid-node sides; grid-line
@@ -351,8 +351,7 @@ int kfbi_batch_solve_neumann(kfbi_batch b, const double *g, const double *f, dou
 int kfbi_batch_graph(kfbi_batch b, int32_t enable);
 /* enable != 0 (default): when every grid size of the batch is 64..1024 cells, each DST pass of
  * the box solves is one launch over all size groups together (the tiles of small grids run
- * beside those of large ones); 0: one launch per size group and pass, at the tile widths timed
- * for that group.  Results are identical.  Waits for the batch's capture stream; the captured
+ * beside those of large ones); 0: one launch per size group and pass.  Results are identical.  Waits for the batch's capture stream; the captured
  * Arnoldi steps are captured again at their next use. */
 int kfbi_batch_merge(kfbi_batch b, int32_t enable);
 
@@ -378,10 +377,9 @@ const char *kfbi_last_error(void);
  * loads), "correct", "gather", "jumps" (no launches: the jumps are part of "correct" and "gather")).
  * Returns KFBI_EINVAL if the name is unknown. */
 int kfbi_kernel_time(kfbi_problem p, const char *kernel, double *avg_us, int64_t *launches);
-/* DST tile widths (1 or 2: multiples of the base pencil pairs per workgroup) of the x, y and
- * last-axis passes for dtype KFBI_F64 / KFBI_F32, as chosen by the autotuner at setup (each
- * dense pass timed at both widths on the problem's own buffers); kfbi_set_tiles overrides them.
- * Results do not depend on the widths (each pencil is transformed the same way). */
+/* DST tile widths (1 or 2) of the x, y and last-axis passes for dtype KFBI_F64 / KFBI_F32: 1 after
+ * setup, or what kfbi_set_tiles stored.  Every pass has one tile shape (the wider one was within 3%
+ * of it at best), so the widths have no effect. */
 int kfbi_get_tiles(kfbi_problem p, int32_t dtype, int32_t widths[3]);
 /* GMRES iterations of kfbi_solve_neumann / bidomain_step replay one captured Arnoldi step
  * (a hipGraph holding the product, both Gram-Schmidt passes, the norm and the next basis

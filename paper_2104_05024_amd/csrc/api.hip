@@ -93,7 +93,6 @@ int kfbi_setup(const kfbi_interface *iface, const kfbi_grid *grid, const kfbi_co
       try {
         upload_tables(h->p);
         h->solver.init(h->p);
-        if (!(flags & KFBI_SETUP_NO_AUTOTUNE)) autotune_tiles(h->p, nullptr);
       } catch (...) {
         h->solver.release();
         free_tables(h->p);

@@ -22,7 +22,6 @@ struct Group {
   float *rhs32 = nullptr, *fpad32 = nullptr, *work32 = nullptr;
   ModeParams *msv = nullptr;   // per-slot mode parameters (device)
   bool direct = true;                          // every member's last axis is solved directly
-  int tile_w[2][3] = {{1, 1, 1}, {1, 1, 1}};   // autotuned tile widths [FP64 / FP32][x, -, last]
   template <typename T>
   T *rhs() const;
   template <typename T>

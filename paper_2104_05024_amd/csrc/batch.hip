@@ -292,13 +292,6 @@ void Batch::init(int n, const kfbi_interface *ifaces, const kfbi_grid *grids, co
   seqdev = balloc<int>(1);
   KFBI_HIP(hipMemset(seqdev, 0, sizeof(int)));
   KFBI_HIP(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
-  // tile widths of every size group, timed on the group's own buffers
-  for (Group &g : groups) {
-    const DevProblem &p0 = *probs[g.members[0]];
-    const int G = (int)g.members.size();
-    autotune_group<double>(g.Mfft, G, g.work64, g.cs, p0.f64.tw, p0.f64.sp, g.tile_w[0], cap);
-    autotune_group<float>(g.Mfft, G, g.work32, g.cs, p0.f32.tw, p0.f32.sp, g.tile_w[1], cap);
-  }
 }
 
 void Batch::release() {
@@ -365,8 +358,7 @@ void Batch::box_all(bool from_fpad, hipStream_t st) {
   }
   for (const Group &g : groups) {
     const PrecTables<T> &tb = const_cast<DevProblem &>(*probs[g.members[0]]).tab<T>();
-    box_solve_group<T>(g.Mfft, (int)g.members.size(), src_of(g), g.work<T>(), g.cs, g.msv, tb.tw, tb.sp,
-                       g.tile_w[sizeof(T) == 8 ? 0 : 1], g.direct, st);
+    box_solve_group<T>(g.Mfft, (int)g.members.size(), src_of(g), g.work<T>(), g.cs, g.msv, tb.tw, tb.sp, g.direct, st);
   }
 }
 

@@ -112,7 +112,8 @@ struct DevProblem {
   int32_t *rows_in = nullptr, *rows_out = nullptr;
   int64_t n_rows_in = 0, n_rows_out = 0;
   uint64_t *mask_in = nullptr, *mask_out = nullptr;     // [z][16] bit rows: y rows with rhs / stencil nodes
-  uint8_t *planes_in = nullptr, *planes_out = nullptr;   // [z]: plane holds any rhs / stencil row
+  int32_t *zlist_in = nullptr, *zlist_out = nullptr;     // planes that hold any rhs / stencil row
+  int n_planes_in = 0, n_planes_out = 0;
   PlaneBits planes_in_bits, planes_out_bits;             // the same sets as bits
   double *lam = nullptr;       // (4/h^2) sin^2(k pi / 2M), k = 1..N
 
@@ -123,7 +124,7 @@ struct DevProblem {
   double *red = nullptr;       // small device scratch for dot products
   double *host_red = nullptr;  // pinned host mirror
 
-  // tile width multiplier (1 or 2) per precision (0: FP64, 1: FP32) and pass (x, y, last axis)
+  // kept for kfbi_get_tiles / kfbi_set_tiles: every pass has one tile shape
   int tile_w[2][3] = {{1, 1, 1}, {1, 1, 1}};
 
   bool profile = false;
@@ -280,13 +281,13 @@ void launch_batch_correct(const BatchItem<T> *items, const BatchBlocks &b, const
 template <typename T, typename TP>
 void launch_batch_gather(const BatchItem<T> *items, const BatchBlocks &b, const TP *psi, TP *out, hipStream_t st);
 // Grouped 2D box solve of G equal-size problems (padded layout, stride cs, msv on the device).
-// w[0]: tile width of the x passes; direct: the last axis solved directly.
+// direct: the last axis solved directly.
 template <typename T>
 void box_solve_group(int Mfft, int G, const T *src, T *dst, int64_t cs, const ModeParams *msv, const T *tw,
-                     const T *sp, const int *w, bool direct, hipStream_t st);
+                     const T *sp, bool direct, hipStream_t st);
 // Merged 2D box solve of several such groups (each with its own size): one launch per pass for
 // all groups together, so the tiles of small grids run beside those of large ones instead of in
-// launches of their own that cannot fill the GPU.  Sizes 64..1024, tile width 1; the groups are
+// launches of their own that cannot fill the GPU.  Sizes 64..1024; the groups are
 // those of one precision, src -> dst per group as in box_solve_group.  Results are identical to
 // box_solve_group's.
 struct MultiGroupDesc {
@@ -330,12 +331,6 @@ template <typename T>
 void last_axis_direct(const LastAxis<T> &l, hipStream_t st);
 template <typename T>
 void last_axis_direct_multi(const MultiGroupDesc *groups, int ngroups, hipStream_t st);
-// Autotuner: time each dense pass at both tile widths and keep the faster (cached per process
-// by dimension, grid size, components and precision); clears the work buffers afterwards.
-void autotune_tiles(DevProblem &p, hipStream_t st);
-template <typename T>
-void autotune_group(int Mfft, int G, T *a, int64_t cs, const T *tw, const T *sp, int *w, hipStream_t st);
-
 void upload_tables(DevProblem &p);
 void free_tables(DevProblem &p);
 

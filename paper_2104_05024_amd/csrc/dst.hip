@@ -20,9 +20,6 @@
 //   scaling and the inverse z transform -> y inverse -> x inverse.
 // Each pass reads and writes its tile once; y and z passes work in place.
 #include <algorithm>
-#include <array>
-#include <map>
-#include <mutex>
 
 #include "device.h"
 
@@ -150,14 +147,13 @@ __device__ __forceinline__ void pair_sync() {
 }
 
 
-// W: tile-width multiplier picked by the autotuner (1 or 2 times the base pairs per workgroup)
-template <typename T, int M, int W = 1>
+template <typename T, int M>
 struct Shape {
   static constexpr int N = M - 1;
   static constexpr int TPP = M / 16;                          // threads per pencil pair
   static_assert(TPP <= 64 && 64 % TPP == 0, "a pencil pair must lie inside one wavefront");
-  static constexpr int NP = W * (sizeof(T) == 8 ? 2048 : 4096) / M;  // pencil pairs per workgroup
-  static constexpr int NT = NP * TPP;                         // threads per workgroup (W x 128 / 256)
+  static constexpr int NP = (sizeof(T) == 8 ? 2048 : 4096) / M;  // pencil pairs per workgroup
+  static constexpr int NT = NP * TPP;                         // threads per workgroup (128 / 256)
   static constexpr int PADM = M + (M >> KFBI_LDS_PAD_SHIFT) + KFBI_LDS_PAIR_SKEW;                  // padded LDS length of one pair (odd:
                                                               // pairs start on different banks)
 };
@@ -329,11 +325,11 @@ struct alignas(16) V16 {
 // DST along contiguous rows: pairs of consecutive rows of the flattened [comp][..][x] list.
 // PIN / POUT: input / output in the padded layout (row pitch M) instead of pitch N.
 // One tile (2 NP rows, tile index blk) in the LDS buffer sbuf of NP * PADM values.
-template <typename T, int M, bool PIN, bool POUT, int W = 1>
+template <typename T, int M, bool PIN, bool POUT>
 __device__ __forceinline__ void dst_x_tile(const T *__restrict__ in, T *__restrict__ out, int64_t nrows,
                                            const C2<T> *__restrict__ tw, const T *__restrict__ sp, C2<T> *sbuf,
                                            int64_t blk) {
-  using Sh = Shape<T, M, W>;
+  using Sh = Shape<T, M>;
   constexpr int N = Sh::N, NP = Sh::NP, NT = Sh::NT, PADM = Sh::PADM, VW = 16 / sizeof(T);
   constexpr int ROWS = 2 * NP;
   const int tid = threadIdx.x;
@@ -470,13 +466,13 @@ __device__ __forceinline__ void dst_x_tile(const T *__restrict__ in, T *__restri
   }
 }
 
-template <typename T, int M, bool PIN, bool POUT, int W = 1>
-__global__ __launch_bounds__((Shape<T, M, W>::NT)) void k_dst_x(const T *__restrict__ in, T *__restrict__ out,
+template <typename T, int M, bool PIN, bool POUT>
+__global__ __launch_bounds__((Shape<T, M>::NT)) void k_dst_x(const T *__restrict__ in, T *__restrict__ out,
                                                              int64_t nrows, const C2<T> *__restrict__ tw,
                                                              const T *__restrict__ sp) {
-  using Sh = Shape<T, M, W>;
+  using Sh = Shape<T, M>;
   __shared__ C2<T> sbuf[Sh::NP * Sh::PADM];
-  dst_x_tile<T, M, PIN, POUT, W>(in, out, nrows, tw, sp, sbuf, blockIdx.x);
+  dst_x_tile<T, M, PIN, POUT>(in, out, nrows, tw, sp, sbuf, blockIdx.x);
 }
 
 // Row predicates of the strided tile mover: every row; rows in a bit set read once from memory
@@ -513,9 +509,9 @@ struct BitRows {
 // Tile mover for the strided passes: a tile is NR rows (stride RS elements) of TX consecutive
 // columns starting at column x0, for NC components (stride CS); element (row r, column xo,
 // component c) lives at LDS pair PAIR(xo, c), lane LANE(xo, c), position r + 1.
-template <typename T, int M, int TX, int NC, int W = 1>
+template <typename T, int M, int TX, int NC>
 struct StridedTile {
-  using Sh = Shape<T, M, W>;
+  using Sh = Shape<T, M>;
   static constexpr int N = Sh::N, NT = Sh::NT, PADM = Sh::PADM, VW = 16 / sizeof(T);
   static constexpr bool VEC = (TX % VW == 0) && (TX <= M);
   static constexpr int NE = VEC ? N * NC * (TX / VW) : N * NC * TX;
@@ -734,22 +730,21 @@ struct StridedTile {
 
 // DST along y (3D): tile = 2 NP consecutive x columns of one (comp, z) plane.  in and out
 // may alias.  mask_in / mask_out (optional, [z][16] bit rows, bit y of plane z): rows known to
-// be zero on input are not read; only rows flagged on output are written.  planes (optional, [z] bytes): planes
-// flagged 0 are skipped altogether (no reads, no writes).
-template <typename T, int M, int W = 1>
-__global__ __launch_bounds__((Shape<T, M, W>::NT)) void k_dst_y(const T *__restrict__ in, T *__restrict__ out,
+// be zero on input are not read; only rows flagged on output are written.  planes (optional): the list of
+// planes to take, one per blockIdx.y; the others are neither read nor written.
+template <typename T, int M>
+__global__ __launch_bounds__((Shape<T, M>::NT)) void k_dst_y(const T *__restrict__ in, T *__restrict__ out,
                                                                int64_t P, int64_t comp_stride,
                                                                const uint64_t *__restrict__ mask_in,
                                                                const uint64_t *__restrict__ mask_out,
-                                                               const uint8_t *__restrict__ planes,
+                                                               const int32_t *__restrict__ planes,
                                                                const C2<T> *__restrict__ tw, const T *__restrict__ sp) {
-  using Sh = Shape<T, M, W>;
-  using Tl = StridedTile<T, M, 2 * Sh::NP, 1, W>;
+  using Sh = Shape<T, M>;
+  using Tl = StridedTile<T, M, 2 * Sh::NP, 1>;
   __shared__ C2<T> sbuf[Sh::NP * Sh::PADM];
   const int tid = threadIdx.x;
-  const int x0 = blockIdx.x * 2 * Sh::NP, z = blockIdx.y, c = blockIdx.z;
+  const int x0 = blockIdx.x * 2 * Sh::NP, z = planes ? planes[blockIdx.y] : (int)blockIdx.y, c = blockIdx.z;
   const int64_t off = c * comp_stride + (int64_t)z * Sh::N * P;
-  if (planes && !planes[z]) return;   // nothing to read or write in this plane (whole workgroup)
   constexpr int NW = (Sh::N + 63) / 64;
   const Sines<T, M> sn(sp, tid % Sh::TPP);
   Tl::load(in + off, P, 0, x0, sbuf, tid, BitRowsMem<NW>(mask_in ? mask_in + (int64_t)z * 16 : nullptr));
@@ -900,17 +895,6 @@ __global__ __launch_bounds__((Shape<T, M>::NT)) void k_dst_x_rows(const T *__res
   __shared__ C2<T> sbuf[NP * PADM];
   const int tid = threadIdx.x;
   const int64_t r0 = (int64_t)blockIdx.x * ROWS;
-  // the tile's row indices through uniform (scalar) loads, then picked per thread from
-  // registers: no data load waits on a per-thread index load
-  int32_t ri[ROWS];
-#pragma unroll
-  for (int k = 0; k < ROWS; ++k) ri[k] = r0 + k < nlist ? rows[r0 + k] : 0;
-  auto row_of = [&](int rr) {
-    int32_t v = 0;
-#pragma unroll
-    for (int k = 0; k < ROWS; ++k) v = rr == k ? ri[k] : v;
-    return v;
-  };
   const Sines<T, M> sn(sp, tid % Sh::TPP);
   if constexpr (M >= 64) {
     // one pencil pair per wave at a time (pair index uniform in the wave, so its two rows are
@@ -918,12 +902,19 @@ __global__ __launch_bounds__((Shape<T, M>::NT)) void k_dst_x_rows(const T *__res
     // per 16-byte LDS word, unit stride, no bank conflicts
     constexpr int NWV = NT / 64, PPW = NP / NWV, KS = M / 64;
     const int wv = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
+    // the wave's row indices, one per lane (its pair pp takes rows 2 (wv + NWV pp) and the next), read
+    // back as uniform values; a chain of selects over all the tile's rows instead, as long as
+    // they fill scalar registers, took 45 us against 8 us at 64^3 FP32 (128 rows per tile)
+    static_assert(2 * PPW <= 64, "a lane per row of the wave");
+    const int64_t il = r0 + 2 * (wv + NWV * (lane >> 1)) + (lane & 1);
+    const int32_t mine = lane < 2 * PPW && il < nlist ? rows[il] : 0;
+    auto row_of = [&](int pp, int h) { return (int64_t)__builtin_amdgcn_readlane(mine, 2 * pp + h); };
     C2<T> v[PPW][KS];
 #pragma unroll
     for (int pp = 0; pp < PPW; ++pp) {
       const int rr = wv + NWV * pp;
       const bool oka = r0 + 2 * rr < nlist, okb = r0 + 2 * rr + 1 < nlist;
-      const T *ra = in + (int64_t)row_of(2 * rr) * M, *rb = in + (int64_t)row_of(2 * rr + 1) * M;
+      const T *ra = in + row_of(pp, 0) * M, *rb = in + row_of(pp, 1) * M;
 #pragma unroll
       for (int k = 0; k < KS; ++k) {
         const int n = lane + 64 * k;
@@ -943,7 +934,7 @@ __global__ __launch_bounds__((Shape<T, M>::NT)) void k_dst_x_rows(const T *__res
     for (int pp = 0; pp < PPW; ++pp) {
       const int rr = wv + NWV * pp;
       const bool oka = r0 + 2 * rr < nlist, okb = r0 + 2 * rr + 1 < nlist;
-      T *ra = out + (int64_t)row_of(2 * rr) * M, *rb = out + (int64_t)row_of(2 * rr + 1) * M;
+      T *ra = out + row_of(pp, 0) * M, *rb = out + row_of(pp, 1) * M;
 #pragma unroll
       for (int k = 0; k < KS; ++k) {
         const int n = lane + 64 * k;   // n = N is the pad column: written as zero
@@ -959,7 +950,7 @@ __global__ __launch_bounds__((Shape<T, M>::NT)) void k_dst_x_rows(const T *__res
       const int e = tid + i * NT;
       const int rr = e / VPR, s = e - rr * VPR;
       if (e < NV && r0 + rr < nlist)
-        reg[i] = *reinterpret_cast<const V16<T> *>(in + (int64_t)row_of(rr) * M + s * VW);
+        reg[i] = *reinterpret_cast<const V16<T> *>(in + (int64_t)rows[r0 + rr] * M + s * VW);
       else
 #pragma unroll
         for (int j = 0; j < VW; ++j) reg[i].v[j] = T(0);
@@ -992,7 +983,7 @@ __global__ __launch_bounds__((Shape<T, M>::NT)) void k_dst_x_rows(const T *__res
     for (int i = 0; i < PER; ++i) {
       const int e = tid + i * NT;
       const int rr = e / VPR, s = e - rr * VPR;
-      if (e < NV && r0 + rr < nlist) *reinterpret_cast<V16<T> *>(out + (int64_t)row_of(rr) * M + s * VW) = reg[i];
+      if (e < NV && r0 + rr < nlist) *reinterpret_cast<V16<T> *>(out + (int64_t)rows[r0 + rr] * M + s * VW) = reg[i];
     }
   }
 }
@@ -1316,30 +1307,26 @@ __global__ __launch_bounds__((Shape<double, M>::NT)) void k_dst_x_be1(FhnArgs a,
 
 // ---------------------------------------------------------------- launchers
 //
-// Every dense pass exists at two tile widths (W = 1, 2: pencil pairs per workgroup); the
-// width per (grid size, precision, pass) is picked by autotune_tiles() from timed launches.
-
-template <typename T>
-constexpr int prec_index() { return sizeof(T) == 8 ? 0 : 1; }
-
 // x pass over `rows` contiguous rows (padded in/out unless stated)
-template <typename T, int M, int W>
-void launch_x(const T *in, bool in_plain, T *out, bool out_plain, int64_t rows, const C2<T> *tw, const T *sp,
-              hipStream_t st) {
-  using Sh = Shape<T, M, W>;
+template <typename T, int M>
+void pass_x(const T *in, bool in_plain, T *out, bool out_plain, int64_t rows, const C2<T> *tw, const T *sp,
+            hipStream_t st) {
+  using Sh = Shape<T, M>;
   const dim3 g((unsigned)((rows + 2 * Sh::NP - 1) / (2 * Sh::NP)));
-  if (in_plain) k_dst_x<T, M, false, true, W><<<g, Sh::NT, 0, st>>>(in, out, rows, tw, sp);
-  else if (out_plain) k_dst_x<T, M, true, false, W><<<g, Sh::NT, 0, st>>>(in, out, rows, tw, sp);
-  else k_dst_x<T, M, true, true, W><<<g, Sh::NT, 0, st>>>(in, out, rows, tw, sp);
+  if (in_plain) k_dst_x<T, M, false, true><<<g, Sh::NT, 0, st>>>(in, out, rows, tw, sp);
+  else if (out_plain) k_dst_x<T, M, true, false><<<g, Sh::NT, 0, st>>>(in, out, rows, tw, sp);
+  else k_dst_x<T, M, true, true><<<g, Sh::NT, 0, st>>>(in, out, rows, tw, sp);
   KFBI_HIP(hipGetLastError());
 }
 
-template <typename T, int M, int W>
-void launch_y(const T *in, T *out, int64_t P, int64_t cs, int ncomp, const uint64_t *mask_in,
-              const uint64_t *mask_out, const uint8_t *planes, const C2<T> *tw, const T *sp, hipStream_t st) {
-  using Sh = Shape<T, M, W>;
-  const dim3 g((Sh::N + 2 * Sh::NP - 1) / (2 * Sh::NP), Sh::N, ncomp);
-  k_dst_y<T, M, W><<<g, Sh::NT, 0, st>>>(in, out, P, cs, mask_in, mask_out, planes, tw, sp);
+// y pass over every plane, or over the nz planes listed
+template <typename T, int M>
+void pass_y(const T *in, T *out, int64_t P, int64_t cs, int ncomp, const uint64_t *mask_in, const uint64_t *mask_out,
+            const C2<T> *tw, const T *sp, hipStream_t st, const int32_t *planes = nullptr, int nz = -1) {
+  using Sh = Shape<T, M>;
+  if (nz == 0) return;
+  const dim3 g((Sh::N + 2 * Sh::NP - 1) / (2 * Sh::NP), planes ? nz : Sh::N, ncomp);
+  k_dst_y<T, M><<<g, Sh::NT, 0, st>>>(in, out, P, cs, mask_in, mask_out, planes, tw, sp);
   KFBI_HIP(hipGetLastError());
 }
 
@@ -1387,18 +1374,6 @@ void launch_last(const T *in, T *a, int dim, int ncomp, int64_t P, int64_t cs, c
   KFBI_HIP(hipGetLastError());
 }
 
-template <typename T, int M>
-void pass_x(int w, const T *in, bool in_plain, T *out, bool out_plain, int64_t rows, const C2<T> *tw, const T *sp,
-            hipStream_t st) {
-  if (w == 2) launch_x<T, M, 2>(in, in_plain, out, out_plain, rows, tw, sp, st);
-  else launch_x<T, M, 1>(in, in_plain, out, out_plain, rows, tw, sp, st);
-}
-template <typename T, int M>
-void pass_y(int w, const T *in, T *out, int64_t P, int64_t cs, int ncomp, const uint64_t *mi, const uint64_t *mo,
-            const C2<T> *tw, const T *sp, hipStream_t st, const uint8_t *planes = nullptr) {
-  if (w == 2) launch_y<T, M, 2>(in, out, P, cs, ncomp, mi, mo, planes, tw, sp, st);
-  else launch_y<T, M, 1>(in, out, P, cs, ncomp, mi, mo, planes, tw, sp, st);
-}
 template <typename T>
 ModeScale mode_of(const DevProblem &p) {
   ModeScale m{};
@@ -1450,17 +1425,16 @@ void run_box(DevProblem &p, const T *src, bool src_plain, T *dst, bool dst_plain
   const T *sp = tb.sp;
   const int64_t P = p.P, cs = p.comp_stride;
   const int64_t rows = (int64_t)p.ncomp * (p.dim == 3 ? (int64_t)N * N : N);
-  const int *w = p.tile_w[prec_index<T>()];
   auto tic = [&](Timer &t) { t.tic(p.profile, st); };
   auto toc = [&](Timer &t) { t.toc(p.profile, st); };
   if (!(skip & 1)) {
     tic(p.t_dst_x);
-    pass_x<T, M>(w[0], src, src_plain, A, false, rows, tw, sp, st);
+    pass_x<T, M>(src, src_plain, A, false, rows, tw, sp, st);
     toc(p.t_dst_x);
   }
   if (p.dim == 3) {
     tic(p.t_dst_y);
-    pass_y<T, M>(w[1], A, A, P, cs, p.ncomp, nullptr, nullptr, tw, sp, st);
+    pass_y<T, M>(A, A, P, cs, p.ncomp, nullptr, nullptr, tw, sp, st);
     toc(p.t_dst_y);
   }
   tic(p.t_dst_last);
@@ -1468,12 +1442,12 @@ void run_box(DevProblem &p, const T *src, bool src_plain, T *dst, bool dst_plain
   toc(p.t_dst_last);
   if (p.dim == 3) {
     tic(p.t_dst_y);
-    pass_y<T, M>(w[1], A, A, P, cs, p.ncomp, nullptr, nullptr, tw, sp, st);
+    pass_y<T, M>(A, A, P, cs, p.ncomp, nullptr, nullptr, tw, sp, st);
     toc(p.t_dst_y);
   }
   if (!(skip & 2)) {
     tic(p.t_dst_x);
-    pass_x<T, M>(w[0], A, false, dst, dst_plain, rows, tw, sp, st);
+    pass_x<T, M>(A, false, dst, dst_plain, rows, tw, sp, st);
     toc(p.t_dst_x);
   }
 }
@@ -1493,12 +1467,11 @@ void run_box_stencils(DevProblem &p, const T *src, hipStream_t st, bool skip_x =
   const T *sp = tb.sp;
   const int64_t P = p.P, cs = p.comp_stride;
   const int64_t rows = (int64_t)p.ncomp * N * N;
-  const int *w = p.tile_w[prec_index<T>()];
   auto tic = [&](Timer &t) { t.tic(p.profile, st); };
   auto toc = [&](Timer &t) { t.toc(p.profile, st); };
   if (!skip_x) {
     tic(p.t_dst_x);
-    pass_x<T, M>(w[0], src, false, A, false, rows, tw, sp, st);
+    pass_x<T, M>(src, false, A, false, rows, tw, sp, st);
     toc(p.t_dst_x);
   }
   if (anti) {
@@ -1508,21 +1481,21 @@ void run_box_stencils(DevProblem &p, const T *src, hipStream_t st, bool skip_x =
     T *G = tb.gbuf;
     if (!G) throw std::logic_error("antisymmetric volume solve without its buffer");
     tic(p.t_dst_y1);
-    pass_y<T, M>(w[1], G, G, P, cs, 1, nullptr, nullptr, tw, sp, st);
+    pass_y<T, M>(G, G, P, cs, 1, nullptr, nullptr, tw, sp, st);
     toc(p.t_dst_y1);
     tic(p.t_dst_last_anti);
     solve_last<T, M>(p, A, st, G, nullptr, &p.planes_out_bits, 3);
     toc(p.t_dst_last_anti);
   } else {
     tic(p.t_dst_y);
-    pass_y<T, M>(w[1], A, A, P, cs, p.ncomp, nullptr, nullptr, tw, sp, st);
+    pass_y<T, M>(A, A, P, cs, p.ncomp, nullptr, nullptr, tw, sp, st);
     toc(p.t_dst_y);
     tic(p.t_dst_last_out);
     solve_last<T, M>(p, A, st, nullptr, nullptr, &p.planes_out_bits);
     toc(p.t_dst_last_out);
   }
   tic(p.t_dst_y_sparse);
-  pass_y<T, M>(w[1], A, A, P, cs, p.ncomp, nullptr, p.mask_out, tw, sp, st, p.planes_out);
+  pass_y<T, M>(A, A, P, cs, p.ncomp, nullptr, p.mask_out, tw, sp, st, p.zlist_out, p.n_planes_out);
   toc(p.t_dst_y_sparse);
   const unsigned gout = (unsigned)((p.n_rows_out + 2 * Sh::NP - 1) / (2 * Sh::NP));
   tic(p.t_dst_x_rows);
@@ -1589,7 +1562,6 @@ void run_bidomain_final(DevProblem &p, const FhnArgs &a, bool fuse_be, hipStream
       double *A = tb.work;
       const C2<double> *tw = reinterpret_cast<const C2<double> *>(tb.tw);
       const int64_t P = p.P, cs = p.comp_stride;
-      const int *w = p.tile_w[0];
       if (p.sparse && !a.stim && tb.gbuf) {
         // f + C psi with f = (g, -g) antisymmetric: the volume solve left g's x-y transform in
         // gbuf, so only C psi is transformed, on the rows and planes holding irregular nodes as
@@ -1600,7 +1572,7 @@ void run_bidomain_final(DevProblem &p, const FhnArgs &a, bool fuse_be, hipStream
         KFBI_HIP(hipGetLastError());
         p.t_dst_x_rows.toc(p.profile, st);
         p.t_dst_y_sparse.tic(p.profile, st);
-        pass_y<double, M>(w[1], A, A, P, cs, 2, p.mask_in, nullptr, tw, tb.sp, st, p.planes_in);
+        pass_y<double, M>(A, A, P, cs, 2, p.mask_in, nullptr, tw, tb.sp, st, p.zlist_in, p.n_planes_in);
         p.t_dst_y_sparse.toc(p.profile, st);
         p.t_dst_last_comb.tic(p.profile, st);
         solve_last<double, M>(p, A, st, tb.gbuf, &p.planes_in_bits, nullptr, 5, A);
@@ -1608,14 +1580,14 @@ void run_bidomain_final(DevProblem &p, const FhnArgs &a, bool fuse_be, hipStream
       } else {
         launch_x_fhn<M, FHN_SRC>(p, a, st);
         p.t_dst_y.tic(p.profile, st);
-        pass_y<double, M>(w[1], A, A, P, cs, 2, nullptr, nullptr, tw, tb.sp, st);
+        pass_y<double, M>(A, A, P, cs, 2, nullptr, nullptr, tw, tb.sp, st);
         p.t_dst_y.toc(p.profile, st);
         p.t_dst_last_diff.tic(p.profile, st);
         solve_last<double, M>(p, A, st, nullptr, nullptr, nullptr, 4);
         p.t_dst_last_diff.toc(p.profile, st);
       }
       p.t_dst_y1.tic(p.profile, st);
-      pass_y<double, M>(w[1], A, A, P, cs, 1, nullptr, nullptr, tw, tb.sp, st);
+      pass_y<double, M>(A, A, P, cs, 1, nullptr, nullptr, tw, tb.sp, st);
       p.t_dst_y1.toc(p.profile, st);
       const int64_t rows = p.N * p.N;
       p.t_dst_x_be1.tic(p.profile, st);
@@ -1648,7 +1620,6 @@ void run_box_sparse(DevProblem &p, hipStream_t st) {
   const C2<T> *tw = reinterpret_cast<const C2<T> *>(tb.tw);
   const T *sp = tb.sp;
   const int64_t P = p.P, cs = p.comp_stride;
-  const int *w = p.tile_w[prec_index<T>()];
   auto tic = [&](Timer &t) { t.tic(p.profile, st); };
   auto toc = [&](Timer &t) { t.toc(p.profile, st); };
   const unsigned gin = (unsigned)((p.n_rows_in + 2 * Sh::NP - 1) / (2 * Sh::NP));
@@ -1658,7 +1629,7 @@ void run_box_sparse(DevProblem &p, hipStream_t st) {
   KFBI_HIP(hipGetLastError());
   toc(p.t_dst_x_rows);
   tic(p.t_dst_y_sparse);
-  pass_y<T, M>(w[1], A, A, P, cs, p.ncomp, p.mask_in, nullptr, tw, sp, st, p.planes_in);
+  pass_y<T, M>(A, A, P, cs, p.ncomp, p.mask_in, nullptr, tw, sp, st, p.zlist_in, p.n_planes_in);
   toc(p.t_dst_y_sparse);
   tic(p.t_dst_last_sparse);
   // planes without rhs rows are zero (not read, whatever they hold); only planes with stencil rows are used
@@ -1666,7 +1637,7 @@ void run_box_sparse(DevProblem &p, hipStream_t st) {
   solve_last<T, M>(p, A, st, A, &p.planes_in_bits, &p.planes_out_bits);
   toc(p.t_dst_last_sparse);
   tic(p.t_dst_y_sparse);
-  pass_y<T, M>(w[1], A, A, P, cs, p.ncomp, nullptr, p.mask_out, tw, sp, st, p.planes_out);
+  pass_y<T, M>(A, A, P, cs, p.ncomp, nullptr, p.mask_out, tw, sp, st, p.zlist_out, p.n_planes_out);
   toc(p.t_dst_y_sparse);
   tic(p.t_dst_x_rows);
   if (gout) k_dst_x_rows<T, M><<<gout, Sh::NT, 0, st>>>(A, A, p.rows_out, p.n_rows_out, tw, sp);
@@ -1678,12 +1649,12 @@ void run_box_sparse(DevProblem &p, hipStream_t st) {
 // padded layout: one launch per pass for the whole group.
 template <typename T, int M>
 void run_box_group(int G, const T *src, T *dst, int64_t cs, const ModeParams *msv, const T *tw_, const T *sp,
-                   const int *w, bool direct, hipStream_t st) {
+                   bool direct, hipStream_t st) {
   constexpr int N = M - 1;
   const C2<T> *tw = reinterpret_cast<const C2<T> *>(tw_);
   const int64_t rows = (int64_t)G * N;
   if (cs != (int64_t)N * M) throw std::invalid_argument("group stride");
-  pass_x<T, M>(w[0], src, false, dst, false, rows, tw, sp, st);
+  pass_x<T, M>(src, false, dst, false, rows, tw, sp, st);
   if (direct) {
     LastAxis<T> l;
     l.in = l.out = dst;
@@ -1696,7 +1667,7 @@ void run_box_group(int G, const T *src, T *dst, int64_t cs, const ModeParams *ms
   } else {
     launch_last<T, M>(dst, dst, 2, 1, M, cs, ModeParams{}, tw, sp, msv, G, cs, st);
   }
-  pass_x<T, M>(w[0], dst, false, dst, false, rows, tw, sp, st);
+  pass_x<T, M>(dst, false, dst, false, rows, tw, sp, st);
 }
 
 // ---------------------------------------------------------------- merged 2D group passes
@@ -1719,7 +1690,7 @@ struct MultiX {
   int ng;
 };
 
-// largest tile buffer over the sizes 64..1024 at width 1 (NP * PADM, in complex values)
+// largest tile buffer over the sizes 64..1024 (NP * PADM, in complex values)
 template <typename T>
 constexpr int multi_sbuf() {
   return std::max({Shape<T, 64>::NP * Shape<T, 64>::PADM, Shape<T, 128>::NP * Shape<T, 128>::PADM,
@@ -1753,138 +1724,23 @@ __global__ __launch_bounds__((Shape<T, 64>::NT)) void k_dst_x_multi(MultiX<T> mp
 }
 
 template <typename T>
-int tile_rows(int M) {   // rows per x-pass tile at width 1
+int tile_rows(int M) {   // rows per x-pass tile
   return 2 * ((sizeof(T) == 8 ? 2048 : 4096) / M);
-}
-
-// Timing data: a fixed pseudo-random pattern in [-0.5, 0.5) (all-zero data runs at a higher
-// clock than real data under the power limit, which would bias the choice).
-template <typename T>
-__global__ void k_fill_pattern(T *__restrict__ a, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) a[i] = (T)((((uint32_t)i * 2654435761u) >> 8) & 0xffffu) * (T)(1.0 / 65536.0) - (T)0.5;
-}
-
-// One launch of a pass at width w, in place on `a`, timed with events.
-template <typename T, int M>
-float time_pass(int pass, int w, T *a, int dim, int ncomp, int64_t P, int64_t cs, int64_t rows,
-                const C2<T> *tw, const T *sp, int nprob, hipEvent_t e0, hipEvent_t e1,
-                hipStream_t st) {
-  // fresh data for every launch (the unnormalised passes would otherwise grow it without bound)
-  const int64_t nfill = dim == 3 ? (int64_t)ncomp * cs : (int64_t)nprob * cs;
-  k_fill_pattern<T><<<(unsigned)((nfill + 255) / 256), 256, 0, st>>>(a, nfill);
-  KFBI_HIP(hipGetLastError());
-  KFBI_HIP(hipEventRecord(e0, st));
-  if (pass == 0) pass_x<T, M>(w, a, false, a, false, rows, tw, sp, st);
-  else pass_y<T, M>(w, a, a, P, cs, ncomp, nullptr, nullptr, tw, sp, st);
-  KFBI_HIP(hipEventRecord(e1, st));
-  KFBI_HIP(hipEventSynchronize(e1));
-  float ms_ = 0;
-  KFBI_HIP(hipEventElapsedTime(&ms_, e0, e1));
-  return ms_;
-}
-
-// Both widths are launched alternately (after warm-up launches that bring the clocks up), so
-// that clock and cache drift affect both alike; the median of each decides.
-template <typename T, int M>
-void tune(int *w, T *a, int dim, int ncomp, int64_t P, int64_t cs, int64_t rows,
-          const C2<T> *tw, const T *sp, int nprob, hipStream_t st) {
-  constexpr int kRounds = 7;
-  hipEvent_t e0, e1;
-  KFBI_HIP(hipEventCreate(&e0));
-  KFBI_HIP(hipEventCreate(&e1));
-  for (int pass = 0; pass < 2; ++pass) {
-    if (pass == 1 && dim != 3) continue;
-    float t[2][kRounds];
-    for (int r = -2; r < kRounds; ++r)
-      for (int k = 0; k < 2; ++k) {
-        const float v = time_pass<T, M>(pass, k + 1, a, dim, ncomp, P, cs, rows, tw, sp, nprob, e0, e1, st);
-        if (r >= 0) t[k][r] = v;
-      }
-    std::sort(t[0], t[0] + kRounds);
-    std::sort(t[1], t[1] + kRounds);
-    w[pass] = t[1][kRounds / 2] < 0.97f * t[0][kRounds / 2] ? 2 : 1;   // the wider tile must win clearly
-  }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
-}
-
-template <typename T>
-void autotune_prec(DevProblem &p, hipStream_t st) {
-  PrecTables<T> &tb = p.tab<T>();
-  T *A = tb.work;
-  const C2<T> *tw = reinterpret_cast<const C2<T> *>(tb.tw);
-  const int64_t N = p.N;
-  const int64_t rows = (int64_t)p.ncomp * (p.dim == 3 ? N * N : N);
-  int *w = p.tile_w[prec_index<T>()];
-  switch (p.Mfft) {
-#define KFBI_TUNE_CASE(MM) \
-    case MM: tune<T, MM>(w, A, p.dim, p.ncomp, p.P, p.comp_stride, rows, tw, tb.sp, 1, st); break;
-    KFBI_TUNE_CASE(16) KFBI_TUNE_CASE(32) KFBI_TUNE_CASE(64) KFBI_TUNE_CASE(128) KFBI_TUNE_CASE(256)
-    KFBI_TUNE_CASE(512) KFBI_TUNE_CASE(1024)
-#undef KFBI_TUNE_CASE
-    default: throw std::invalid_argument("unsupported grid size");
-  }
 }
 
 }  // namespace
 
-// Tile widths per (dimension, grid size, components, precision): measured once per process.
-void autotune_tiles(DevProblem &p, hipStream_t st) {
-  static std::mutex mu;
-  static std::map<std::array<int, 4>, std::array<int, 3>> cache;
-  for (int prec = 0; prec < 2; ++prec) {
-    const std::array<int, 4> key{p.dim, (int)p.Mfft, p.ncomp, prec};
-    {
-      std::lock_guard<std::mutex> lk(mu);
-      auto it = cache.find(key);
-      if (it != cache.end()) {
-        for (int k = 0; k < 3; ++k) p.tile_w[prec][k] = it->second[k];
-        continue;
-      }
-    }
-    if (prec == 0) autotune_prec<double>(p, st);
-    else autotune_prec<float>(p, st);
-    std::lock_guard<std::mutex> lk(mu);
-    cache[key] = {p.tile_w[prec][0], p.tile_w[prec][1], p.tile_w[prec][2]};
-  }
-  // the timing launches ran in place on the work buffers: leave them zeroed
-  const size_t field = (size_t)p.ncomp * p.comp_stride;
-  KFBI_HIP(hipMemsetAsync(p.f64.work, 0, field * sizeof(double), st));
-  KFBI_HIP(hipMemsetAsync(p.f32.work, 0, field * sizeof(float), st));
-  KFBI_HIP(hipStreamSynchronize(st));
-}
-
-// Batched groups: widths of the x and last-axis passes for one group, timed on its buffers.
-template <typename T>
-void autotune_group(int Mfft, int G, T *a, int64_t cs, const T *tw_, const T *sp, int *w, hipStream_t st) {
-  const C2<T> *tw = reinterpret_cast<const C2<T> *>(tw_);
-  const int64_t rows = (int64_t)G * (Mfft - 1);
-  switch (Mfft) {
-#define KFBI_TUNE_CASE(MM) \
-    case MM: tune<T, MM>(w, a, 2, 1, MM, cs, rows, tw, sp, G, st); break;
-    KFBI_TUNE_CASE(16) KFBI_TUNE_CASE(32) KFBI_TUNE_CASE(64) KFBI_TUNE_CASE(128) KFBI_TUNE_CASE(256)
-    KFBI_TUNE_CASE(512) KFBI_TUNE_CASE(1024)
-#undef KFBI_TUNE_CASE
-    default: throw std::invalid_argument("unsupported grid size");
-  }
-  KFBI_HIP(hipMemsetAsync(a, 0, (size_t)G * cs * sizeof(T), st));
-  KFBI_HIP(hipStreamSynchronize(st));
-}
-template void autotune_group<double>(int, int, double *, int64_t, const double *, const double *, int *, hipStream_t);
-template void autotune_group<float>(int, int, float *, int64_t, const float *, const float *, int *, hipStream_t);
-
 template <typename T>
 void box_solve_group(int Mfft, int G, const T *src, T *dst, int64_t cs, const ModeParams *msv, const T *tw,
-                     const T *sp, const int *w, bool direct, hipStream_t st) {
+                     const T *sp, bool direct, hipStream_t st) {
   switch (Mfft) {
-    case 16: run_box_group<T, 16>(G, src, dst, cs, msv, tw, sp, w, direct, st); break;
-    case 32: run_box_group<T, 32>(G, src, dst, cs, msv, tw, sp, w, direct, st); break;
-    case 64: run_box_group<T, 64>(G, src, dst, cs, msv, tw, sp, w, direct, st); break;
-    case 128: run_box_group<T, 128>(G, src, dst, cs, msv, tw, sp, w, direct, st); break;
-    case 256: run_box_group<T, 256>(G, src, dst, cs, msv, tw, sp, w, direct, st); break;
-    case 512: run_box_group<T, 512>(G, src, dst, cs, msv, tw, sp, w, direct, st); break;
-    case 1024: run_box_group<T, 1024>(G, src, dst, cs, msv, tw, sp, w, direct, st); break;
+    case 16: run_box_group<T, 16>(G, src, dst, cs, msv, tw, sp, direct, st); break;
+    case 32: run_box_group<T, 32>(G, src, dst, cs, msv, tw, sp, direct, st); break;
+    case 64: run_box_group<T, 64>(G, src, dst, cs, msv, tw, sp, direct, st); break;
+    case 128: run_box_group<T, 128>(G, src, dst, cs, msv, tw, sp, direct, st); break;
+    case 256: run_box_group<T, 256>(G, src, dst, cs, msv, tw, sp, direct, st); break;
+    case 512: run_box_group<T, 512>(G, src, dst, cs, msv, tw, sp, direct, st); break;
+    case 1024: run_box_group<T, 1024>(G, src, dst, cs, msv, tw, sp, direct, st); break;
     default: throw std::invalid_argument("unsupported grid size");
   }
 }
@@ -1923,9 +1779,9 @@ template void box_solve_multi<double>(const MultiGroupDesc *, int, hipStream_t);
 template void box_solve_multi<float>(const MultiGroupDesc *, int, hipStream_t);
 
 template void box_solve_group<double>(int, int, const double *, double *, int64_t, const ModeParams *,
-                                      const double *, const double *, const int *, bool, hipStream_t);
+                                      const double *, const double *, bool, hipStream_t);
 template void box_solve_group<float>(int, int, const float *, float *, int64_t, const ModeParams *, const float *,
-                                     const float *, const int *, bool, hipStream_t);
+                                     const float *, bool, hipStream_t);
 
 template <typename T>
 void box_solve(DevProblem &p, const T *src, bool src_plain, T *dst, bool dst_plain, hipStream_t st) {

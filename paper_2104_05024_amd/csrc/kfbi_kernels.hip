@@ -484,8 +484,15 @@ void upload_tables(DevProblem &p) {
       if (min_[r]) pin[r / N] = 1;
       if (mout[r]) pout[r / N] = 1;
     }
-    p.planes_in = dupload(pin);
-    p.planes_out = dupload(pout);
+    auto listed = [&](const std::vector<uint8_t> &f, int &n) {
+      std::vector<int32_t> zs;
+      for (int64_t z = 0; z < N; ++z)
+        if (f[z]) zs.push_back((int32_t)z);
+      n = (int)zs.size();
+      return dupload(zs);
+    };
+    p.zlist_in = listed(pin, p.n_planes_in);
+    p.zlist_out = listed(pout, p.n_planes_out);
     p.planes_in_bits = PlaneBits{};
     p.planes_out_bits = PlaneBits{};
     for (int64_t z = 0; z < N; ++z) {
@@ -514,18 +521,14 @@ void upload_tables(DevProblem &p) {
 }
 
 void free_tables(DevProblem &p) {
-  int32_t **ip[] = {&p.itab.arm_idx, &p.itab.arm_head, &p.itab.st_pos, &p.itab.q_idx, &p.rows_in, &p.rows_out};
+  int32_t **ip[] = {&p.itab.arm_idx, &p.itab.arm_head, &p.itab.st_pos, &p.itab.q_idx,
+                    &p.rows_in,      &p.rows_out,      &p.zlist_in,    &p.zlist_out};
   double **wp[] = {&p.itab.arm_w, &p.itab.st_nw, &p.itab.q_w};
   for (double **q : wp) {
     if (*q) (void)hipFree(*q);
     *q = nullptr;
   }
   p.itab.n_slots = 0;
-  uint8_t **up[] = {&p.planes_in, &p.planes_out};
-  for (uint8_t **q : up) {
-    if (*q) (void)hipFree(*q);
-    *q = nullptr;
-  }
   uint64_t **bp[] = {&p.mask_in, &p.mask_out};
   for (uint64_t **q : bp) {
     if (*q) (void)hipFree(*q);

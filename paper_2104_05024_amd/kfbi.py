@@ -310,7 +310,7 @@ class Problem:
         _check(lib().kfbi_use_graph(self._h, 1 if enable else 0))
 
     def tiles(self, dtype=KFBI_F64):
-        """Autotuned DST tile widths (x, y, last-axis pass) for KFBI_F64 / KFBI_F32."""
+        """DST tile widths (x, y, last-axis pass) for KFBI_F64 / KFBI_F32, as stored (no effect)."""
         w = (C.c_int32 * 3)()
         _check(lib().kfbi_get_tiles(self._h, dtype, w))
         return tuple(w)
