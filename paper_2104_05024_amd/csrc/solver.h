@@ -17,14 +17,14 @@ struct Solver {
   double *npart = nullptr;     // [block] partials of ||w||^2 from the last Gram-Schmidt pass
   double *hdev = nullptr;      // device dot results (3 * (kMaxRestart + 2))
   double *hhost = nullptr;     // pinned host mirror
-  double *ydev = nullptr;      // least-squares coefficients uploaded for the update
-  double *ypin = nullptr;      // pinned staging of those coefficients [2][kMaxRestart + 2]
+  static constexpr int kMeanBlocks = 512;   // most block partials of one sum
+  double *meandev = nullptr;   // gauge mean of the last solve
   int64_t n_inside = 0;
   int8_t *inside_plain = nullptr;
   // captured Arnoldi step (per precision of the product), replayed every GMRES iteration
   bool use_graph = true;
   double *vin = nullptr, *wv = nullptr;
-  int *jdev = nullptr, *jhost = nullptr;
+  int *jdev = nullptr;
   // step counter: each replayed step ends by storing its number in pinned host memory, which
   // the host polls instead of sleeping in a stream synchronisation between steps
   int *seqdev = nullptr, *seqhost = nullptr;
@@ -37,6 +37,9 @@ struct Solver {
   hipGraphExec_t graph[2] = {nullptr, nullptr};
   int graph_m[2] = {0, 0};
   void arnoldi_step(DevProblem &p, int prec, int m, hipStream_t st);
+  void orthogonalise(double *w, const int *jd, int j, int m, double *vnext, hipStream_t st);
+  void orthogonalise_small(const double *w, bool step, int j, double *vnext, hipStream_t st);
+  void finish_host(int K, hipStream_t st);
   void run_step(DevProblem &p, int prec, int m, hipStream_t st);
 
   void init(DevProblem &p);
@@ -93,7 +96,7 @@ struct Solver {
   // by a constant pair (which the gauge removes); outside Omega, where V is evolved too, it
   // removes the field of a component that the near-zero eigenvalue makes large and
   // step-dependent, and that would otherwise feed back through the extended source.
-  double *nullz = nullptr, *nully = nullptr, *nullp = nullptr, *nullc = nullptr;
+  double *nullz = nullptr, *nully = nullptr, *nullp = nullptr;
   bool null_ready = false;
   void null_init(DevProblem &p, hipStream_t st);
   // u = S(fpad + C psi) into the padded work buffer (fpad gets the correction added); for the
@@ -102,7 +105,7 @@ struct Solver {
   // (midpoint update and backward Euler half step), leaving no potentials in work
   void reconstruct(DevProblem &p, const double *psi, hipStream_t st, const FhnArgs *fa = nullptr,
                    bool fuse_be = false);
-  double gauge_mean(DevProblem &p, hipStream_t st);   // mean over tissue nodes of comp 1 of work
+  const double *gauge_mean(DevProblem &p, hipStream_t st);   // mean over tissue nodes of comp 1 of work (device)
   int solve_neumann(DevProblem &p, const double *g, const double *f, double *u, double *psi,
                     const kfbi_solve_opts &o, kfbi_solve_info &info, hipStream_t st);
 };

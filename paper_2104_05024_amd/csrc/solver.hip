@@ -15,6 +15,14 @@ namespace kfbi {
 namespace {
 
 constexpr int kB = 256;
+struct Coefs {
+  double v[Solver::kMaxRestart + 2];
+};
+Coefs coefs(const double *v, int n) {
+  Coefs c;
+  std::copy(v, v + n, c.v);
+  return c;
+}
 inline unsigned nblk(int64_t n) { return (unsigned)((n + kB - 1) / kB); }
 
 template <typename T>
@@ -45,30 +53,37 @@ __global__ __launch_bounds__(kB) void k_multidot(const double *__restrict__ A, i
   if (threadIdx.x == 0) partials[(int64_t)k * gridDim.x + blockIdx.x] = s[0];
 }
 
-__global__ __launch_bounds__(kB) void k_finish(const double *__restrict__ partials, int nb,
-                                               double *__restrict__ out, const int *__restrict__ jlim = nullptr) {
+// out = scale * (sum of nb block partials)
+__global__ __launch_bounds__(kB) void k_finish(const double *__restrict__ partials, int nb, double scale,
+                                               double *__restrict__ out) {
   __shared__ double s[kB];
-  const int k = blockIdx.x;
-  if (jlim && k > *jlim) return;
   double acc = 0;
-  for (int i = threadIdx.x; i < nb; i += kB) acc += partials[(int64_t)k * nb + i];
+  for (int i = threadIdx.x; i < nb; i += kB) acc += partials[i];
   s[threadIdx.x] = acc;
   __syncthreads();
   for (int off = kB / 2; off > 0; off >>= 1) {
     if ((int)threadIdx.x < off) s[threadIdx.x] += s[threadIdx.x + off];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[k] = s[0];
+  if (threadIdx.x == 0) *out = scale * s[0];
 }
 
-// w -= sum_k h[k] V_k   (sign = -1)   or   x += sum_k h[k] V_k   (sign = +1)
+// x += sign sum_k c[k] V_k, or (out) out = sum_k c[k] V_k; the coefficients ride in the kernel arguments.
 __global__ __launch_bounds__(kB) void k_combine(double *__restrict__ w, const double *__restrict__ V, int64_t ldv,
-                                                const double *__restrict__ h, int K, double sign, int64_t n) {
+                                                Coefs c, int K, double sign, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x;
   if (i >= n) return;
   double acc = 0;
-  for (int k = 0; k < K; ++k) acc += h[k] * V[(int64_t)k * ldv + i];
+  for (int k = 0; k < K; ++k) acc += c.v[k] * V[(int64_t)k * ldv + i];
   w[i] += sign * acc;
+}
+__global__ __launch_bounds__(kB) void k_expand(double *__restrict__ out, const double *__restrict__ V, int64_t ldv,
+                                               Coefs c, int K, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x;
+  if (i >= n) return;
+  double acc = 0;
+  for (int k = 0; k < K; ++k) acc += c.v[k] * V[(int64_t)k * ldv + i];
+  out[i] = acc;
 }
 
 // Sum of the nb block partials of row k by one wave: lane-strided sums, then a butterfly (every
@@ -154,6 +169,138 @@ __global__ void k_inc_j(int *j, int *seq, int *seq_host) {
   }
 }
 
+// Sums of the block partials of K rows straight into pinned host memory, then the step counter: the
+// end of a dot product whose value the host waits for.
+__global__ __launch_bounds__(kB) void k_finish_host(const double *__restrict__ partials, int nb, int K,
+                                                    double *__restrict__ host, int *seq, int *seq_host) {
+  __shared__ double sums[Solver::kMaxRestart + 2];
+  for (int k = threadIdx.x >> 6; k < K; k += kB / 64) {
+    const double s = wave_sum_partials(partials, nb, k);
+    if ((threadIdx.x & 63) == 0) sums[k] = s;
+  }
+  __syncthreads();
+  if (threadIdx.x >= 64) return;   // one wavefront stores and fences: a system fence writes back the L2
+  for (int k = threadIdx.x; k < K; k += 64) host[k] = sums[k];
+  __threadfence_system();
+  if (threadIdx.x == 0) {
+    const int s = *seq + 1;
+    *seq = s;
+    __hip_atomic_store(seq_host, s, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
+// The orthogonalisation of one Arnoldi step for short vectors (n <= 1024 E), by one workgroup: both
+// classical Gram-Schmidt passes of w against V_0..V_j, the norm, V_{j+1} = w / ||w|| (also into vnext),
+// and the Hessenberg column straight into pinned host memory ([pass][kMaxRestart + 2], then
+// ||w||^2).  With seq it also ends the captured step: j <- j + 1 and the step counter.
+// Seven launches of 2-4 us each (and the gaps between them) become one: 8.7 us instead of 20 for the
+// 256 densities of a 128^2 pair, 18.0 instead of 27 for the 4,098 of a 64^3 one.  Bound by latency, then
+// by what one workgroup reads (the basis four times): at 10 basis vectors and about 5,000
+// entries it meets the many-block kernels.  With few vectors several wavefronts share one; only one
+// wavefront stores to the host and fences, since a system fence writes back the L2 (10.5 us with all).
+constexpr int kSmallThreads = 1024, kSmallMax = 5 * kSmallThreads;
+template <int E>
+__global__ __launch_bounds__(kSmallThreads) void k_orthogonalise_small(double *V, const double *w_in, int64_t n,
+                                                                       int *jdev, int jh, double *vnext,
+                                                                       double *__restrict__ host, int *seq,
+                                                                       int *seq_host) {
+  constexpr int NT = kSmallThreads, NW = NT / 64, HS = Solver::kMaxRestart + 2;
+  __shared__ double ws[E * NT];
+  __shared__ double hp[HS + NW];   // partial dots: P parts of each of the K vectors
+  __shared__ double hcol[2][HS];
+  __shared__ double red[NW];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int j = jdev ? *jdev : jh, K = j + 1;
+  double w[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int i = tid + NT * e;
+    w[e] = i < n ? w_in[i] : 0.0;
+    ws[i] = w[e];
+  }
+  const int P = K < NW ? NW / K : 1;   // wavefronts sharing one vector
+  for (int pass = 0; pass < 2; ++pass) {
+    __syncthreads();
+    for (int t = wave; t < K * P; t += NW) {
+      const int k = t / P, part = t - k * P;
+      const double *v = V + (int64_t)k * n;
+      double acc = 0;
+#pragma unroll 16
+      for (int i = lane + 64 * part; i < n; i += 64 * P) acc += v[i] * ws[i];
+      for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+      if (lane == 0) hp[t] = acc;
+    }
+    __syncthreads();
+    if (tid < K) {
+      double h = hp[tid * P];
+      for (int part = 1; part < P; ++part) h += hp[tid * P + part];
+      hcol[pass][tid] = h;
+    }
+    __syncthreads();
+    double acc[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[e] = 0;
+#pragma unroll 4
+    for (int k = 0; k < K; ++k) {
+      const double h = hcol[pass][k];
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int i = tid + NT * e;
+        acc[e] += i < n ? h * V[(int64_t)k * n + i] : 0.0;
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      w[e] -= acc[e];
+      if (pass == 0) ws[tid + NT * e] = w[e];
+    }
+  }
+  double sq = 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) sq += w[e] * w[e];
+  for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
+  if (lane == 0) red[wave] = sq;
+  __syncthreads();
+  double nrm2 = 0;
+#pragma unroll
+  for (int k = 0; k < NW; ++k) nrm2 += red[k];
+  const double sc = nrm2 > 0 ? 1.0 / sqrt(nrm2) : 0.0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int i = tid + NT * e;
+    if (i < n) {
+      V[(int64_t)K * n + i] = w[e] * sc;
+      if (vnext) vnext[i] = w[e] * sc;
+    }
+  }
+  if (wave > 0) return;   // one wavefront stores and fences: a system fence writes back the L2
+  for (int k = lane; k < K; k += 64) {
+    host[k] = hcol[0][k];
+    host[HS + k] = hcol[1][k];
+  }
+  if (lane == 0) host[2 * HS] = nrm2;
+  if (!seq) return;
+  __threadfence_system();
+  if (lane == 0) {
+    *jdev = j + 1;
+    const int s = *seq + 1;
+    *seq = s;
+    __hip_atomic_store(seq_host, s, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
+// Start of a restart cycle: V_0 = r / beta, also into vin, and j <- 0.
+__global__ __launch_bounds__(kB) void k_start_cycle(double *__restrict__ V, double *__restrict__ vin,
+                                                    const double *__restrict__ r, double s, int *__restrict__ j,
+                                                    int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x;
+  if (i == 0) *j = 0;
+  if (i >= n) return;
+  const double v = s * r[i];
+  V[i] = v;
+  vin[i] = v;
+}
+
 __global__ __launch_bounds__(kB) void k_axpby(double *__restrict__ z, double a, const double *__restrict__ x,
                                               double b, const double *__restrict__ y, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x;
@@ -166,12 +313,18 @@ __global__ __launch_bounds__(kB) void k_fill(double *__restrict__ z, double v, i
   if (i < n) z[i] = v;
 }
 
-// out = psi - c z with the coefficient c = <z, psi> read from device memory (out may be psi)
+// out = psi - c z, c = <z, psi> summed by every block from k_multidot's partials (out may be psi)
 __global__ __launch_bounds__(kB) void k_remove_along(double *out, const double *psi,
-                                                     const double *__restrict__ z, const double *__restrict__ c,
-                                                     int64_t n) {
+                                                     const double *__restrict__ z,
+                                                     const double *__restrict__ partials, int nb, int64_t n) {
+  __shared__ double c;
+  if (threadIdx.x < 64) {
+    const double s = wave_sum_partials(partials, nb, 0);
+    if (threadIdx.x == 0) c = s;
+  }
+  __syncthreads();
   const int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x;
-  if (i < n) out[i] = psi[i] - c[0] * z[i];
+  if (i < n) out[i] = psi[i] - c * z[i];
 }
 
 // Starting residual of psi^{n-1} without a product: (g'^n - g'^{n-1}) + (g'^{n-1} - A psi^{n-1}).
@@ -273,23 +426,20 @@ void Solver::init(DevProblem &p) {
   d = dalloc<double>(L);
   fpad = dalloc<double>((size_t)p.ncomp * p.comp_stride);
   KFBI_HIP(hipMemset(fpad, 0, (size_t)p.ncomp * p.comp_stride * sizeof(double)));
-  partials = dalloc<double>((size_t)(kMaxRestart + 2) * 512);
+  partials = dalloc<double>((size_t)(kMaxRestart + 2) * kMeanBlocks);
   npart = dalloc<double>((size_t)nblk(L));
   hdev = dalloc<double>(3 * (kMaxRestart + 2));
-  ydev = dalloc<double>(kMaxRestart + 2);
+  meandev = dalloc<double>(1);
   KFBI_HIP(hipHostMalloc(&hhost, 3 * (kMaxRestart + 2) * sizeof(double), hipHostMallocDefault));
-  KFBI_HIP(hipHostMalloc(&ypin, 2 * (kMaxRestart + 2) * sizeof(double), hipHostMallocDefault));
   vin = dalloc<double>(L);
   wv = dalloc<double>(L);
   if (p.ncomp == 2) {
     nullz = dalloc<double>(L);
     nully = dalloc<double>(L);
     nullp = dalloc<double>(L);
-    nullc = dalloc<double>(1);
   }
   null_ready = false;
   jdev = dalloc<int>(1);
-  KFBI_HIP(hipHostMalloc(&jhost, sizeof(int), hipHostMallocDefault));
   seqdev = dalloc<int>(1);
   KFBI_HIP(hipMemset(seqdev, 0, sizeof(int)));
   KFBI_HIP(hipHostMalloc(&seqhost, sizeof(int), hipHostMallocDefault));
@@ -311,23 +461,19 @@ void Solver::release() {
   if (cap) (void)hipStreamDestroy(cap);
   cap = nullptr;
   if (jdev) (void)hipFree(jdev);
-  if (jhost) (void)hipHostFree(jhost);
   jdev = nullptr;
-  jhost = nullptr;
   if (seqdev) (void)hipFree(seqdev);
   if (seqhost) (void)hipHostFree(seqhost);
   seqdev = nullptr;
   seqhost = nullptr;
   double **dp[] = {&V,    &r,    &w,  &t,   &gp,    &d,     &fpad,  &partials, &npart,
-                   &hdev, &ydev, &vin, &wv, &nullz, &nully, &nullp, &nullc};
+                   &hdev, &meandev, &vin, &wv, &nullz, &nully, &nullp};
   for (double **q : dp) {
     if (*q) (void)hipFree(*q);
     *q = nullptr;
   }
   if (inside_plain) (void)hipFree(inside_plain);
   if (hhost) (void)hipHostFree(hhost);
-  if (ypin) (void)hipHostFree(ypin);
-  ypin = nullptr;
   inside_plain = nullptr;
   hhost = nullptr;
 }
@@ -358,10 +504,44 @@ double Solver::residual_norm(const double *b, const double *Ax, hipStream_t st) 
 
 double Solver::dot(const double *a, const double *b, hipStream_t st) {
   k_multidot<<<dim3(nb, 1), kB, 0, st>>>(a, L, b, L, partials);
-  k_finish<<<1, kB, 0, st>>>(partials, nb, hdev);
-  KFBI_HIP(hipMemcpyAsync(hhost, hdev, sizeof(double), hipMemcpyDeviceToHost, st));
-  host_wait(st);
+  finish_host(1, st);
   return hhost[0];
+}
+
+// The sums of k_multidot's K rows of partials in hhost, waited for.
+void Solver::finish_host(int K, hipStream_t st) {
+  k_finish_host<<<1, kB, 0, st>>>(partials, nb, K, hhost, seqdev, seqhost);
+  KFBI_HIP(hipGetLastError());
+  wait_step(st);
+}
+
+// Both Gram-Schmidt passes of w against V_0..V_j, the norm and V_{j+1} (also into vnext), the Hessenberg column
+// on its way to hhost.  j from device memory when jd is given (the captured step).
+void Solver::orthogonalise(double *w, const int *jd, int j, int m, double *vnext, hipStream_t st) {
+  const int K = jd ? m : j + 1;
+  for (int pass = 0; pass < 2; ++pass) {
+    k_multidot<<<dim3(nb, K), kB, 0, st>>>(V, L, w, L, partials, jd);
+    k_cgs_combine<<<nblk(L), kB, 0, st>>>(w, V, L, partials, nb, hdev + pass * (kMaxRestart + 2), jd, j + 1, L,
+                                          pass == 1 ? npart : nullptr);
+  }
+  k_normalize<<<nblk(L), kB, 0, st>>>(V, L, w, npart, (int)nblk(L), hdev + 2 * (kMaxRestart + 2), jd, j, vnext, L);
+  KFBI_HIP(hipGetLastError());
+  KFBI_HIP(hipMemcpyAsync(hhost, hdev, 3 * (kMaxRestart + 2) * sizeof(double), hipMemcpyDeviceToHost, st));
+}
+
+// The same for short vectors in one launch; step: also the end of the captured step.
+void Solver::orthogonalise_small(const double *w, bool step, int j, double *vnext, hipStream_t st) {
+  int *jd = step ? jdev : nullptr, *sq = step ? seqdev : nullptr;
+  switch ((L + kSmallThreads - 1) / kSmallThreads) {
+#define KFBI_SMALL(EE)                                                                                           \
+  case EE:                                                                                                       \
+    k_orthogonalise_small<EE><<<1, kSmallThreads, 0, st>>>(V, w, L, jd, j, vnext, hhost, sq, seqhost);           \
+    break;
+    KFBI_SMALL(1) KFBI_SMALL(2) KFBI_SMALL(3) KFBI_SMALL(4)
+    default: k_orthogonalise_small<5><<<1, kSmallThreads, 0, st>>>(V, w, L, jd, j, vnext, hhost, sq, seqhost); break;
+#undef KFBI_SMALL
+  }
+  KFBI_HIP(hipGetLastError());
 }
 
 // One Arnoldi step with j read from device memory (so one captured graph serves every j):
@@ -369,15 +549,11 @@ double Solver::dot(const double *a, const double *b, hipStream_t st) {
 // norm, V_{j+1} (also into vin), the Hessenberg column to pinned host memory, j <- j + 1.
 void Solver::arnoldi_step(DevProblem &p, int prec, int m, hipStream_t st) {
   apply_vec(p, prec, vin, wv, st);
-  for (int pass = 0; pass < 2; ++pass) {
-    k_multidot<<<dim3(nb, m), kB, 0, st>>>(V, L, wv, L, partials, jdev);
-    k_cgs_combine<<<nblk(L), kB, 0, st>>>(wv, V, L, partials, nb, hdev + pass * (kMaxRestart + 2), jdev, 0, L,
-                                          pass == 1 ? npart : nullptr);
+  if (L <= kSmallMax) {
+    orthogonalise_small(wv, true, 0, vin, st);
+    return;
   }
-  k_normalize<<<nblk(L), kB, 0, st>>>(V, L, wv, npart, (int)nblk(L), hdev + 2 * (kMaxRestart + 2), jdev, 0, vin,
-                                      L);
-  KFBI_HIP(hipGetLastError());
-  KFBI_HIP(hipMemcpyAsync(hhost, hdev, 3 * (kMaxRestart + 2) * sizeof(double), hipMemcpyDeviceToHost, st));
+  orthogonalise(wv, jdev, 0, m, vin, st);
   k_inc_j<<<1, 1, 0, st>>>(jdev, seqdev, seqhost);
   KFBI_HIP(hipGetLastError());
 }
@@ -441,17 +617,18 @@ int Solver::gmres(DevProblem &p, const double *b, double bnorm, double *x, bool 
   };
   // the product of a restart residual: FP64 in a relaxed solve, else the solve's own precision
   const int prec_res = a.relax ? 0 : a.prec;
-  // r = b - A x
+  // rs: where the current residual b - A x is held
+  const double *rs = r;
   if (x_zero) {
-    KFBI_HIP(hipMemcpyAsync(r, b, L * sizeof(double), hipMemcpyDeviceToDevice, st));
+    rs = b;
   } else if (a.r0) {
-    KFBI_HIP(hipMemcpyAsync(r, a.r0, L * sizeof(double), hipMemcpyDeviceToDevice, st));
+    rs = a.r0;
   } else {
     apply_vec(p, prec_res, x, t, st);
     count(prec_res);
     k_axpby<<<nblk(L), kB, 0, st>>>(r, 1.0, b, -1.0, t, L);
   }
-  double beta = std::sqrt(dot(r, r, st));
+  double beta = x_zero ? bnorm : std::sqrt(dot(rs, rs, st));
   s.beta0 = beta;
   std::vector<double> H((size_t)(m + 1) * m), Hc((size_t)(m + 1) * m), cs(m), sn(m), g(m + 1), y(m), z(m + 1);
   while (beta > tol_abs && s.its < maxit) {
@@ -460,15 +637,11 @@ int Solver::gmres(DevProblem &p, const double *b, double bnorm, double *x, bool 
     std::fill(g.begin(), g.end(), 0.0);
     g[0] = beta;
     const double beta_cycle = beta;
-    k_axpby<<<nblk(L), kB, 0, st>>>(V, 1.0 / beta, r, 0.0, nullptr, L);
+    k_start_cycle<<<nblk(L), kB, 0, st>>>(V, vin, rs, 1.0 / beta, jdev, L);
+    KFBI_HIP(hipGetLastError());
     int jend = 0;
     bool breakdown = false, any32 = false;
     const bool graphed = use_graph && !p.profile;
-    if (graphed) {
-      *jhost = 0;
-      KFBI_HIP(hipMemcpyAsync(jdev, jhost, sizeof(int), hipMemcpyHostToDevice, st));
-      KFBI_HIP(hipMemcpyAsync(vin, V, L * sizeof(double), hipMemcpyDeviceToDevice, st));
-    }
     double target = tol_abs;
     for (int j = 0; j < m; ++j) {
       // relaxed: FP32 products once the current (Givens) residual is below sw_abs
@@ -480,16 +653,8 @@ int Solver::gmres(DevProblem &p, const double *b, double bnorm, double *x, bool 
         const double *vj = V + (int64_t)j * L;
         double *vn = V + (int64_t)(j + 1) * L;
         apply_vec(p, pj, vj, vn, st);
-        // classical Gram-Schmidt, twice; then the norm
-        for (int pass = 0; pass < 2; ++pass) {
-          k_multidot<<<dim3(nb, j + 1), kB, 0, st>>>(V, L, vn, L, partials);
-          k_cgs_combine<<<nblk(L), kB, 0, st>>>(vn, V, L, partials, nb, hdev + pass * (kMaxRestart + 2), nullptr,
-                                                j + 1, L, pass == 1 ? npart : nullptr);
-        }
-        k_normalize<<<nblk(L), kB, 0, st>>>(V, L, vn, npart, (int)nblk(L), hdev + 2 * (kMaxRestart + 2), nullptr, j,
-                                            nullptr, L);
-        KFBI_HIP(hipGetLastError());
-        KFBI_HIP(hipMemcpyAsync(hhost, hdev, 3 * (kMaxRestart + 2) * sizeof(double), hipMemcpyDeviceToHost, st));
+        if (L <= kSmallMax) orthogonalise_small(vn, false, j, nullptr, st);
+        else orthogonalise(vn, nullptr, j, m, nullptr, st);
       }
       count(pj);
       ++s.its;
@@ -529,9 +694,7 @@ int Solver::gmres(DevProblem &p, const double *b, double bnorm, double *x, bool 
       y[i] = acc / H[(size_t)i * m + i];
     }
     // x += V y
-    std::copy(y.begin(), y.begin() + jend, ypin);
-    KFBI_HIP(hipMemcpyAsync(ydev, ypin, jend * sizeof(double), hipMemcpyHostToDevice, st));
-    k_combine<<<nblk(L), kB, 0, st>>>(x, V, L, ydev, jend, 1.0, L);
+    k_combine<<<nblk(L), kB, 0, st>>>(x, V, L, coefs(y.data(), jend), jend, 1.0, L);
     KFBI_HIP(hipGetLastError());
     const bool converged = std::fabs(g[jend]) <= target && !breakdown;
     if (converged && !(any32 && a.relax)) {
@@ -547,14 +710,9 @@ int Solver::gmres(DevProblem &p, const double *b, double bnorm, double *x, bool 
         for (int k = 0; k < jend; ++k) acc -= Hc[(size_t)i * m + k] * y[k];
         z[i] = acc;
       }
-      std::copy(z.begin(), z.begin() + jend + 1, ypin + (kMaxRestart + 2));
-      KFBI_HIP(hipMemcpyAsync(ydev, ypin + (kMaxRestart + 2), (jend + 1) * sizeof(double), hipMemcpyHostToDevice,
-                              st));
-      k_axpby<<<nblk(L), kB, 0, st>>>(r, 0.0, r, 0.0, nullptr, L);
-      k_combine<<<nblk(L), kB, 0, st>>>(r, V, L, ydev, jend + 1, 1.0, L);
+      k_expand<<<nblk(L), kB, 0, st>>>(r, V, L, coefs(z.data(), jend + 1), jend + 1, L);
       KFBI_HIP(hipGetLastError());
       beta = std::fabs(g[jend]);
-      host_wait(st);
       break;
     }
     // the true residual: the FP64 certificate of a relaxed solve, else a restart
@@ -563,8 +721,11 @@ int Solver::gmres(DevProblem &p, const double *b, double bnorm, double *x, bool 
     count(pr);
     if (a.relax && any32) ++s.certs;
     k_axpby<<<nblk(L), kB, 0, st>>>(r, 1.0, b, -1.0, t, L);
+    rs = r;
     beta = std::sqrt(dot(r, r, st));
   }
+  if (s.its == 0 && rs != r)   // converged at the start: callers read the residual from r
+    KFBI_HIP(hipMemcpyAsync(r, rs, L * sizeof(double), hipMemcpyDeviceToDevice, st));
   s.resid = beta;
   return beta <= tol_abs ? KFBI_OK : KFBI_ENOCONV;
 }
@@ -728,8 +889,7 @@ void Solver::reconstruct(DevProblem &p, const double *psi, hipStream_t st, const
     // the coupled pair: the density without its component along the null density
     if (!null_ready) throw std::logic_error("reconstruct: null density not initialised");
     k_multidot<<<dim3(nb, 1), kB, 0, st>>>(nullz, L, psi, L, partials);
-    k_finish<<<1, kB, 0, st>>>(partials, nb, nullc);
-    k_remove_along<<<nblk(L), kB, 0, st>>>(nullp, psi, nullz, nullc, L);
+    k_remove_along<<<nblk(L), kB, 0, st>>>(nullp, psi, nullz, partials, nb, L);
     KFBI_HIP(hipGetLastError());
     psi = nullp;
   }
@@ -742,24 +902,23 @@ void Solver::reconstruct(DevProblem &p, const double *psi, hipStream_t st, const
   box_solve<double>(p, fpad, false, p.f64.work, false, st);
 }
 
-double Solver::gauge_mean(DevProblem &p, hipStream_t st) {
-  // mean over tissue nodes of comp 1 in the padded work field (mask in padded layout)
-  k_masked_sum<<<nb, kB, 0, st>>>(p.f64.work + p.comp_stride, p.inside_pad, p.comp_stride, partials);
-  k_finish<<<1, kB, 0, st>>>(partials, nb, hdev);
+const double *Solver::gauge_mean(DevProblem &p, hipStream_t st) {
+  // mean over tissue nodes of comp 1 in the padded work field (mask in padded layout), blocks by the field
+  const int blocks = (int)std::min<int64_t>(kMeanBlocks, (p.comp_stride + 4 * kB - 1) / (4 * kB));
+  k_masked_sum<<<blocks, kB, 0, st>>>(p.f64.work + p.comp_stride, p.inside_pad, p.comp_stride, partials);
+  k_finish<<<1, kB, 0, st>>>(partials, blocks, n_inside > 0 ? 1.0 / (double)n_inside : 0.0, meandev);
   KFBI_HIP(hipGetLastError());
-  KFBI_HIP(hipMemcpyAsync(hhost, hdev, sizeof(double), hipMemcpyDeviceToHost, st));
-  host_wait(st);
-  return n_inside > 0 ? hhost[0] / (double)n_inside : 0.0;
+  return meandev;
 }
 
 namespace {
 __global__ __launch_bounds__(kB) void k_from_padded(const double *__restrict__ fp, double *__restrict__ f,
                                                     int64_t nplain, int64_t N, int64_t P, int64_t cs, int ncomp,
-                                                    double shift) {
+                                                    const double *__restrict__ mean) {
   const int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x;
   if (i >= nplain * ncomp) return;
   const int64_t c = i / nplain, lin = i - c * nplain;
-  f[i] = fp[c * cs + (lin % N) + P * (lin / N)] - shift;
+  f[i] = fp[c * cs + (lin % N) + P * (lin / N)] - (mean ? mean[0] : 0.0);
 }
 }  // namespace
 
@@ -773,9 +932,9 @@ int Solver::solve_neumann(DevProblem &p, const double *g, const double *f, doubl
   bie_rhs(p, g, st);
   const int rc = solve_density(p, psi, o, o.x0 != 0, info, st);
   reconstruct(p, psi, st);
-  const double shift = p.ncomp == 2 ? gauge_mean(p, st) : 0.0;
+  const double *mean = p.ncomp == 2 ? gauge_mean(p, st) : nullptr;
   k_from_padded<<<nblk(nplain * p.ncomp), kB, 0, st>>>(p.f64.work, u, nplain, p.N, p.P, p.comp_stride, p.ncomp,
-                                                       shift);
+                                                       mean);
   KFBI_HIP(hipGetLastError());
   KFBI_HIP(hipStreamSynchronize(st));
   return rc;
@@ -815,10 +974,7 @@ void bidomain_s::proj_start(double *out_psi, double *out_r, hipStream_t st) {
   const int64_t L = sv.L;
   const int k = proj_n;
   k_multidot<<<dim3(sv.nb, k), kB, 0, st>>>(proj_b, L, sv.gp, L, sv.partials);
-  k_finish<<<k, kB, 0, st>>>(sv.partials, sv.nb, sv.hdev);
-  KFBI_HIP(hipGetLastError());
-  KFBI_HIP(hipMemcpyAsync(sv.hhost, sv.hdev, k * sizeof(double), hipMemcpyDeviceToHost, st));
-  sv.host_wait(st);
+  sv.finish_host(k, st);
   double A[kProj][kProj + 1];
   double dmax = 0;
   for (int i = 0; i < k; ++i) dmax = std::max(dmax, proj_G[i][i]);
@@ -843,12 +999,10 @@ void bidomain_s::proj_start(double *out_psi, double *out_r, hipStream_t st) {
     for (int j = i + 1; j < k; ++j) acc -= A[i][j] * cvec[j];
     cvec[i] = A[i][i] != 0.0 ? acc / A[i][i] : 0.0;
   }
-  std::copy(cvec.begin(), cvec.begin() + k, sv.ypin);
-  KFBI_HIP(hipMemcpyAsync(sv.ydev, sv.ypin, k * sizeof(double), hipMemcpyHostToDevice, st));
-  k_axpby<<<nblk(L), kB, 0, st>>>(out_psi, 0.0, out_psi, 0.0, nullptr, L);
-  k_combine<<<nblk(L), kB, 0, st>>>(out_psi, proj_psi, L, sv.ydev, k, 1.0, L);
+  const Coefs c = coefs(cvec.data(), k);
+  k_expand<<<nblk(L), kB, 0, st>>>(out_psi, proj_psi, L, c, k, L);
   KFBI_HIP(hipMemcpyAsync(out_r, sv.gp, L * sizeof(double), hipMemcpyDeviceToDevice, st));
-  k_combine<<<nblk(L), kB, 0, st>>>(out_r, proj_b, L, sv.ydev, k, -1.0, L);
+  k_combine<<<nblk(L), kB, 0, st>>>(out_r, proj_b, L, c, k, -1.0, L);
   KFBI_HIP(hipGetLastError());
 }
 
@@ -863,10 +1017,7 @@ void bidomain_s::proj_record(const double *psi, hipStream_t st) {
   proj_head = (proj_head + 1) % kProj;
   proj_n = std::min(proj_n + 1, kProj);
   k_multidot<<<dim3(sv.nb, proj_n), kB, 0, st>>>(proj_b, L, bs, L, sv.partials);
-  k_finish<<<proj_n, kB, 0, st>>>(sv.partials, sv.nb, sv.hdev);
-  KFBI_HIP(hipGetLastError());
-  KFBI_HIP(hipMemcpyAsync(sv.hhost, sv.hdev, proj_n * sizeof(double), hipMemcpyDeviceToHost, st));
-  sv.host_wait(st);
+  sv.finish_host(proj_n, st);
   for (int i = 0; i < proj_n; ++i) proj_G[slot][i] = proj_G[i][slot] = sv.hhost[i];
 }
 
@@ -1007,8 +1158,7 @@ int bidomain_s::step(bidomain_state &s, double dt, kfbi_solve_info &info, hipStr
       // without its component along the null density: the network also predicts the density's
       // step-dependent null component, which A hardly sees, and the step would scale it freely
       k_multidot<<<dim3(sv.nb, 1), kB, 0, st>>>(sv.nullz, L, zdir, L, sv.partials);
-      k_finish<<<1, kB, 0, st>>>(sv.partials, sv.nb, sv.nullc);
-      k_remove_along<<<nblk(L), kB, 0, st>>>(zdir, zdir, sv.nullz, sv.nullc, L);
+      k_remove_along<<<nblk(L), kB, 0, st>>>(zdir, zdir, sv.nullz, sv.partials, sv.nb, L);
     }
     KFBI_HIP(hipGetLastError());
     sv.apply_vec(p, 0, zdir, sv.t, st);
@@ -1036,10 +1186,8 @@ int bidomain_s::step(bidomain_state &s, double dt, kfbi_solve_info &info, hipStr
   // in its inverse x pass unless the potentials are returned as well
   sv.reconstruct(p, psi0, st, &fa, s.phi == nullptr);
   if (s.phi) {
-    const double mu = sv.gauge_mean(p, st);
-    sv.hhost[0] = mu;
-    KFBI_HIP(hipMemcpyAsync(sv.ydev, sv.hhost, sizeof(double), hipMemcpyHostToDevice, st));
-    k_mid_be<<<nblk(n), kB, 0, st>>>(p.f64.work, s.V, s.q, s.phi, sv.ydev, n, p.N, p.P, p.comp_stride, dth, m);
+    const double *mean = sv.gauge_mean(p, st);
+    k_mid_be<<<nblk(n), kB, 0, st>>>(p.f64.work, s.V, s.q, s.phi, mean, n, p.N, p.P, p.comp_stride, dth, m);
     KFBI_HIP(hipGetLastError());
   }
   // record (features, target) once two earlier densities and g'^{n-1} exist
