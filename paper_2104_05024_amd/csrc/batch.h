@@ -22,6 +22,7 @@ struct Group {
   float *rhs32 = nullptr, *fpad32 = nullptr, *work32 = nullptr;
   ModeParams *msv = nullptr;   // per-slot mode parameters (device)
   bool direct = true;                          // every member's last axis is solved directly
+  RowSet rows_in, rows_out;                    // rows of the members that hold irregular / stencil nodes
   template <typename T>
   T *rhs() const;
   template <typename T>
@@ -63,7 +64,9 @@ struct Batch {
   bool merged = true;
   bool mergeable() const;
   template <typename T>
-  void box_all(bool from_fpad, hipStream_t st);   // every group: src (rhs, or fpad if from_fpad) -> work
+  // every group: src (rhs, or fpad if from_fpad) -> work; stencils: only the rows holding stencil nodes are
+  // read afterwards.  rhs is zero outside the rows holding irregular nodes.
+  void box_all(bool from_fpad, bool stencils, hipStream_t st);
   void drop_graphs();                              // the captured steps are captured again when next used
   hipStream_t cap = nullptr;           // capture stream (the caller's stream may be the null stream)
   hipGraphExec_t graph[2] = {nullptr, nullptr};

@@ -208,6 +208,28 @@ void Batch::init(int n, const kfbi_interface *ifaces, const kfbi_grid *grids, co
       g.direct = g.direct && p.direct;
       ms.push_back(m);
     }
+    // rows of the members that matter to a product: the members' lists at their slots, their bits in slot order
+    auto set_of = [&](bool out) {
+      std::vector<int32_t> list;
+      std::vector<uint64_t> bits;
+      for (size_t k = 0; k < g.members.size(); ++k) {
+        const DevProblem &p = *probs[g.members[k]];
+        const RowSet rs = out ? p.set_out() : p.set_in();
+        std::vector<int32_t> l((size_t)rs.n);
+        std::vector<uint64_t> w(16);
+        if (rs.n) KFBI_HIP(hipMemcpy(l.data(), rs.list, l.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+        KFBI_HIP(hipMemcpy(w.data(), rs.bits, 16 * sizeof(uint64_t), hipMemcpyDeviceToHost));
+        for (int32_t r : l) list.push_back((int32_t)(k * (size_t)g.N) + r);
+        bits.insert(bits.end(), w.begin(), w.end());
+      }
+      int32_t *dl = balloc<int32_t>(list.size());
+      uint64_t *db = balloc<uint64_t>(bits.size());
+      KFBI_HIP(hipMemcpy(dl, list.data(), list.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+      KFBI_HIP(hipMemcpy(db, bits.data(), bits.size() * sizeof(uint64_t), hipMemcpyHostToDevice));
+      return RowSet{dl, (int64_t)list.size(), db};
+    };
+    g.rows_in = set_of(false);
+    g.rows_out = set_of(true);
     g.msv = balloc<ModeParams>(ms.size());
     KFBI_HIP(hipMemcpy(g.msv, ms.data(), ms.size() * sizeof(ModeParams), hipMemcpyHostToDevice));
     groups.push_back(g);
@@ -301,7 +323,9 @@ void Batch::release() {
       graph[k] = nullptr;
     }
   for (Group &g : groups) {
-    void *ps[] = {g.rhs64, g.fpad64, g.work64, g.rhs32, g.fpad32, g.work32, g.msv};
+    void *ps[] = {g.rhs64, g.fpad64, g.work64, g.rhs32, g.fpad32, g.work32, g.msv,
+                  const_cast<int32_t *>(g.rows_in.list),   const_cast<uint64_t *>(g.rows_in.bits),
+                  const_cast<int32_t *>(g.rows_out.list),  const_cast<uint64_t *>(g.rows_out.bits)};
     for (void *q : ps)
       if (q) (void)hipFree(q);
   }
@@ -341,31 +365,34 @@ void Batch::drop_graphs() {
 }
 
 template <typename T>
-void Batch::box_all(bool from_fpad, hipStream_t st) {
-  auto src_of = [&](const Group &g) -> const T * {
-    if constexpr (sizeof(T) == 8) return from_fpad ? g.fpad64 : g.rhs64;
-    else return from_fpad ? g.fpad32 : g.rhs32;
+void Batch::box_all(bool from_fpad, bool stencils, hipStream_t st) {
+  int64_t bytes = 0;
+  for (const Group &g : groups) bytes += (int64_t)g.members.size() * g.cs * (int64_t)sizeof(T);
+  const bool sets = row_sets_pay(bytes);
+  auto desc = [&](const Group &g) {
+    const PrecTables<T> &tb = const_cast<DevProblem &>(*probs[g.members[0]]).tab<T>();
+    const T *src;
+    if constexpr (sizeof(T) == 8) src = from_fpad ? g.fpad64 : g.rhs64;
+    else src = from_fpad ? g.fpad32 : g.rhs32;
+    return MultiGroupDesc{g.Mfft,   (int)g.members.size(), g.cs,
+                          src,      g.work<T>(),           g.msv,
+                          tb.tw,    tb.sp,                 !from_fpad && sets ? g.rows_in : RowSet{},
+                          stencils && sets ? g.rows_out : RowSet{}};
   };
   if (merged && mergeable()) {
     MultiGroupDesc d[kMaxMultiGroups];
     int k = 0;
-    for (const Group &g : groups) {
-      const PrecTables<T> &tb = const_cast<DevProblem &>(*probs[g.members[0]]).tab<T>();
-      d[k++] = MultiGroupDesc{g.Mfft, (int)g.members.size(), g.cs, src_of(g), g.work<T>(), g.msv, tb.tw, tb.sp};
-    }
+    for (const Group &g : groups) d[k++] = desc(g);
     box_solve_multi<T>(d, k, st);
     return;
   }
-  for (const Group &g : groups) {
-    const PrecTables<T> &tb = const_cast<DevProblem &>(*probs[g.members[0]]).tab<T>();
-    box_solve_group<T>(g.Mfft, (int)g.members.size(), src_of(g), g.work<T>(), g.cs, g.msv, tb.tw, tb.sp, g.direct, st);
-  }
+  for (const Group &g : groups) box_solve_group<T>(desc(g), g.direct, st);
 }
 
 template <typename T, typename TP>
 void Batch::matvec(const TP *in, TP *out, hipStream_t st) {
   launch_batch_correct<T, TP>(items<T>(), correct_bl, in, false, st);
-  box_all<T>(false, st);
+  box_all<T>(false, true, st);
   launch_batch_gather<T, TP>(items<T>(), gather_bl, in, out, st);
 }
 template void Batch::matvec<double, double>(const double *, double *, hipStream_t);
@@ -549,7 +576,7 @@ int Batch::solve(const double *g, const double *f, double *u, double *psi, const
                  kfbi_solve_info *info, hipStream_t st) {
   // volume part: u_V = S f, g' = g - n.D grad u_V+
   pack(f, 0, true, st);
-  box_all<double>(true, st);
+  box_all<double>(true, true, st);
   launch_batch_gather<double, double>(items64, gather_bl, nullptr, t, st);
   if (g) k_axpby<<<nb(L), kB, 0, st>>>(gp, 1.0, g, -1.0, t, L);
   else k_axpby<<<nb(L), kB, 0, st>>>(gp, -1.0, t, 0.0, nullptr, L);
@@ -610,7 +637,7 @@ int Batch::solve(const double *g, const double *f, double *u, double *psi, const
   }
   // u = S(f + C psi)
   launch_batch_correct<double, double>(items64, correct_bl, psi, true, st);
-  box_all<double>(true, st);
+  box_all<double>(true, false, st);
   pack(u, 1, false, st);
   KFBI_HIP(hipStreamSynchronize(st));
   bool ok = true;

@@ -92,6 +92,22 @@ struct InterfaceTables {
   double *st_nw = nullptr, *q_w = nullptr;           // their weights [comp][M][S], [comp][M][Kn]
 };
 
+// Rows of padded fields: the indices of some rows (null: every row) and their bits, 16 words per field
+// (2D) or plane (3D).
+struct RowSet {
+  const int32_t *list = nullptr;
+  int64_t n = 0;
+  const uint64_t *bits = nullptr;
+};
+
+// Whether the passes of a 2D product take row sets, by the bytes of its fields (a batch: of all its
+// problems).  Below, a pass fits on the GPU at once and the list's load only lengthens it; above, about 30% of
+// the rows of the closed curves here are left out.  One product, every row / row sets (us): FP64 128 21.5 /
+// 22.9, 256 22.9 / 23.9, 512 (2.1 MB) 27.0 / 27.4, coupled 512 (4.2 MB) 31.6 / 31.0, 1024 35.3 / 33.8, coupled
+// 1024 53.4 / 49.5; FP32 coupled 512 (2.1 MB) 29.2 / 29.5, 1024 (4.2 MB) 31.3 / 30.8.
+// A batch of 64 (64..1024 cells): x pass 38 -> 30 us and last axis 45 -> 37 in FP32, 72 -> 61 and 60 -> 54 in FP64.
+inline bool row_sets_pay(int64_t bytes) { return bytes >= 4000000; }
+
 struct DevProblem {
   HostTables ht;
   bool on_device = false;
@@ -105,8 +121,8 @@ struct DevProblem {
 
   InterfaceTables itab;
   int8_t *inside_pad = nullptr;  // padded-layout tissue mask
-  // sparse matvec box solve (3D): rows of the flattened [comp][z][y] row list that carry
-  // irregular nodes (in) / extrapolation-stencil nodes (out), and their [z][y] byte masks
+  // sparse matvec box solve: rows of the flattened [comp][z][y] row list that carry irregular
+  // nodes (in) / extrapolation-stencil nodes (out), and their [z][y] bits
   bool sparse = true;
   bool direct = false;         // last axis as tridiagonal systems (column_direct) instead of DSTs
   int32_t *rows_in = nullptr, *rows_out = nullptr;
@@ -115,6 +131,8 @@ struct DevProblem {
   int32_t *zlist_in = nullptr, *zlist_out = nullptr;     // planes that hold any rhs / stencil row
   int n_planes_in = 0, n_planes_out = 0;
   PlaneBits planes_in_bits, planes_out_bits;             // the same sets as bits
+  RowSet set_in() const { return {rows_in, n_rows_in, mask_in}; }
+  RowSet set_out() const { return {rows_out, n_rows_out, mask_out}; }
   double *lam = nullptr;       // (4/h^2) sin^2(k pi / 2M), k = 1..N
 
   PrecTables<double> f64;
@@ -280,16 +298,12 @@ void launch_batch_correct(const BatchItem<T> *items, const BatchBlocks &b, const
                           hipStream_t st);
 template <typename T, typename TP>
 void launch_batch_gather(const BatchItem<T> *items, const BatchBlocks &b, const TP *psi, TP *out, hipStream_t st);
-// Grouped 2D box solve of G equal-size problems (padded layout, stride cs, msv on the device).
-// direct: the last axis solved directly.
-template <typename T>
-void box_solve_group(int Mfft, int G, const T *src, T *dst, int64_t cs, const ModeParams *msv, const T *tw,
-                     const T *sp, bool direct, hipStream_t st);
-// Merged 2D box solve of several such groups (each with its own size): one launch per pass for
-// all groups together, so the tiles of small grids run beside those of large ones instead of in
-// launches of their own that cannot fill the GPU.  Sizes 64..1024; the groups are
-// those of one precision, src -> dst per group as in box_solve_group.  Results are identical to
-// box_solve_group's.
+// Grouped 2D box solve of G equal-size problems (padded layout, stride cs, msv on the device), one
+// launch per pass; direct: the last axis solved directly.  Where it is, `in` and `out` may name the rows
+// outside which the source is zero and the rows the result is read on (row sets of the whole group).
+// Merged: several such groups (each with its own size) in one launch per pass, so the tiles of small grids
+// run beside those of large ones instead of in launches of their own that cannot fill the GPU.
+// Sizes 64..1024, last axis direct; the groups are those of one precision.  Same results.
 struct MultiGroupDesc {
   int Mfft = 0, G = 0;
   int64_t cs = 0;
@@ -297,9 +311,11 @@ struct MultiGroupDesc {
   void *dst = nullptr;
   const ModeParams *msv = nullptr;
   const void *tw = nullptr, *sp = nullptr;
+  RowSet in, out;
 };
 constexpr int kMaxMultiGroups = 8;
-// The last axis is solved directly (every group's problems must qualify, column_direct).
+template <typename T>
+void box_solve_group(const MultiGroupDesc &d, bool direct, hipStream_t st);
 template <typename T>
 void box_solve_multi(const MultiGroupDesc *groups, int ngroups, hipStream_t st);
 
@@ -316,6 +332,7 @@ struct LastAxis {
   const ModeParams *msv = nullptr;      // 2D: per-problem parameters of nprob fields at stride pstride
   int nprob = 1;
   int64_t pstride = 0;
+  const uint64_t *bin = nullptr, *bout = nullptr;   // 2D: row bits per problem (null: every row)
   const PlaneBits *zin = nullptr, *zout = nullptr;
   int form = 0;
   const T *in2 = nullptr;

@@ -325,8 +325,10 @@ struct alignas(16) V16 {
 // DST along contiguous rows: pairs of consecutive rows of the flattened [comp][..][x] list.
 // PIN / POUT: input / output in the padded layout (row pitch M) instead of pitch N.
 // One tile (2 NP rows, tile index blk) in the LDS buffer sbuf of NP * PADM values.
-template <typename T, int M, bool PIN, bool POUT>
+// LIST (M >= 64): row i of the pass is row list[i] of both fields (row i itself where list is null).
+template <typename T, int M, bool PIN, bool POUT, bool LIST = false>
 __device__ __forceinline__ void dst_x_tile(const T *__restrict__ in, T *__restrict__ out, int64_t nrows,
+                                           const int32_t *__restrict__ list,
                                            const C2<T> *__restrict__ tw, const T *__restrict__ sp, C2<T> *sbuf,
                                            int64_t blk) {
   using Sh = Shape<T, M>;
@@ -341,12 +343,25 @@ __device__ __forceinline__ void dst_x_tile(const T *__restrict__ in, T *__restri
     constexpr int NWV = NT / 64, PPW = NP / NWV, KS = M / 64;
     constexpr int64_t PI = PIN ? M : N, PO = POUT ? M : N;
     const int wv = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
+    // LIST: the wave's row indices, one per lane (its pair pp takes rows 2 (wv + NWV pp) and the next),
+    // read back as uniform values; a chain of selects over all the tile's rows instead took 45 us
+    // against 8 us at 64^3 FP32 (128 rows per tile)
+    static_assert(!LIST || 2 * PPW <= 64, "a lane per row of the wave");
+    int32_t held = 0;
+    if constexpr (LIST) {
+      const int64_t il = r0 + 2 * (wv + NWV * (lane >> 1)) + (lane & 1);
+      if (lane < 2 * PPW && il < nrows) held = list ? list[il] : (int32_t)il;
+    }
+    auto row_of = [&](int pp, int h) -> int64_t {
+      if constexpr (LIST) return __builtin_amdgcn_readlane(held, 2 * pp + h);
+      else return r0 + 2 * (wv + NWV * pp) + h;
+    };
     C2<T> v[PPW][KS];
 #pragma unroll
     for (int pp = 0; pp < PPW; ++pp) {
-      const int64_t rowa = r0 + 2 * (wv + NWV * pp);
-      const bool oka = rowa < nrows, okb = rowa + 1 < nrows;
-      const T *ra = in + rowa * PI, *rb = ra + PI;
+      const int64_t ia = r0 + 2 * (wv + NWV * pp);
+      const bool oka = ia < nrows, okb = ia + 1 < nrows;
+      const T *ra = in + row_of(pp, 0) * PI, *rb = in + row_of(pp, 1) * PI;
 #pragma unroll
       for (int k = 0; k < KS; ++k) {
         const int n = lane + 64 * k;
@@ -365,9 +380,9 @@ __device__ __forceinline__ void dst_x_tile(const T *__restrict__ in, T *__restri
 #pragma unroll
     for (int pp = 0; pp < PPW; ++pp) {
       const int rr = wv + NWV * pp;
-      const int64_t rowa = r0 + 2 * rr;
-      const bool oka = rowa < nrows, okb = rowa + 1 < nrows;
-      T *oa = out + rowa * PO, *ob = oa + PO;
+      const int64_t ia = r0 + 2 * rr;
+      const bool oka = ia < nrows, okb = ia + 1 < nrows;
+      T *oa = out + row_of(pp, 0) * PO, *ob = out + row_of(pp, 1) * PO;
 #pragma unroll
       for (int k = 0; k < KS; ++k) {
         const int n = lane + 64 * k;   // n = N: the pad column of the padded layout, zero
@@ -472,7 +487,7 @@ __global__ __launch_bounds__((Shape<T, M>::NT)) void k_dst_x(const T *__restrict
                                                              const T *__restrict__ sp) {
   using Sh = Shape<T, M>;
   __shared__ C2<T> sbuf[Sh::NP * Sh::PADM];
-  dst_x_tile<T, M, PIN, POUT>(in, out, nrows, tw, sp, sbuf, blockIdx.x);
+  dst_x_tile<T, M, PIN, POUT>(in, out, nrows, nullptr, tw, sp, sbuf, blockIdx.x);
 }
 
 // Row predicates of the strided tile mover: every row; rows in a bit set read once from memory
@@ -893,57 +908,12 @@ __global__ __launch_bounds__((Shape<T, M>::NT)) void k_dst_x_rows(const T *__res
   constexpr int N = Sh::N, NP = Sh::NP, NT = Sh::NT, PADM = Sh::PADM, VW = 16 / sizeof(T);
   constexpr int ROWS = 2 * NP, VPR = M / VW, NV = ROWS * VPR, PER = (NV + NT - 1) / NT;
   __shared__ C2<T> sbuf[NP * PADM];
-  const int tid = threadIdx.x;
-  const int64_t r0 = (int64_t)blockIdx.x * ROWS;
-  const Sines<T, M> sn(sp, tid % Sh::TPP);
   if constexpr (M >= 64) {
-    // one pencil pair per wave at a time (pair index uniform in the wave, so its two rows are
-    // picked by scalar selects); a lane moves whole complex values: two 8-byte row elements
-    // per 16-byte LDS word, unit stride, no bank conflicts
-    constexpr int NWV = NT / 64, PPW = NP / NWV, KS = M / 64;
-    const int wv = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
-    // the wave's row indices, one per lane (its pair pp takes rows 2 (wv + NWV pp) and the next), read
-    // back as uniform values; a chain of selects over all the tile's rows instead, as long as
-    // they fill scalar registers, took 45 us against 8 us at 64^3 FP32 (128 rows per tile)
-    static_assert(2 * PPW <= 64, "a lane per row of the wave");
-    const int64_t il = r0 + 2 * (wv + NWV * (lane >> 1)) + (lane & 1);
-    const int32_t mine = lane < 2 * PPW && il < nlist ? rows[il] : 0;
-    auto row_of = [&](int pp, int h) { return (int64_t)__builtin_amdgcn_readlane(mine, 2 * pp + h); };
-    C2<T> v[PPW][KS];
-#pragma unroll
-    for (int pp = 0; pp < PPW; ++pp) {
-      const int rr = wv + NWV * pp;
-      const bool oka = r0 + 2 * rr < nlist, okb = r0 + 2 * rr + 1 < nlist;
-      const T *ra = in + row_of(pp, 0) * M, *rb = in + row_of(pp, 1) * M;
-#pragma unroll
-      for (int k = 0; k < KS; ++k) {
-        const int n = lane + 64 * k;
-        v[pp][k] = {oka && n < N ? ra[n] : T(0), okb && n < N ? rb[n] : T(0)};
-      }
-    }
-#pragma unroll
-    for (int pp = 0; pp < PPW; ++pp)
-#pragma unroll
-      for (int k = 0; k < KS; ++k) {
-        const int n = lane + 64 * k;
-        if (n < N) sbuf[(wv + NWV * pp) * PADM + pad(n + 1)] = v[pp][k];
-      }
-    __syncthreads();
-    dst_pair<T, M>(sbuf + (tid / Sh::TPP) * PADM, tid % Sh::TPP, tw, sn);
-#pragma unroll
-    for (int pp = 0; pp < PPW; ++pp) {
-      const int rr = wv + NWV * pp;
-      const bool oka = r0 + 2 * rr < nlist, okb = r0 + 2 * rr + 1 < nlist;
-      T *ra = out + row_of(pp, 0) * M, *rb = out + row_of(pp, 1) * M;
-#pragma unroll
-      for (int k = 0; k < KS; ++k) {
-        const int n = lane + 64 * k;   // n = N is the pad column: written as zero
-        const C2<T> c = n < N ? sbuf[rr * PADM + pad(n + 1)] : C2<T>{T(0), T(0)};
-        if (oka) ra[n] = c.x;
-        if (okb) rb[n] = c.y;
-      }
-    }
+    dst_x_tile<T, M, true, true, true>(in, out, nlist, rows, tw, sp, sbuf, blockIdx.x);
   } else {
+    const int tid = threadIdx.x;
+    const int64_t r0 = (int64_t)blockIdx.x * ROWS;
+    const Sines<T, M> sn(sp, tid % Sh::TPP);
     V16<T> reg[PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
@@ -1645,29 +1615,74 @@ void run_box_sparse(DevProblem &p, hipStream_t st) {
   toc(p.t_dst_x_rows);
 }
 
+// x pass over the rows of a set (all `rows` rows where it has no list), padded in and out
+template <typename T, int M>
+void pass_x_set(const T *in, T *out, const RowSet &set, int64_t rows, const C2<T> *tw, const T *sp, hipStream_t st) {
+  using Sh = Shape<T, M>;
+  if (!set.list) {
+    pass_x<T, M>(in, false, out, false, rows, tw, sp, st);
+    return;
+  }
+  const unsigned g = (unsigned)((set.n + 2 * Sh::NP - 1) / (2 * Sh::NP));
+  if (g) k_dst_x_rows<T, M><<<g, Sh::NT, 0, st>>>(in, out, set.list, set.n, tw, sp);
+  KFBI_HIP(hipGetLastError());
+}
+
 // Grouped 2D box solve of G one-component problems of equal size, stored at stride cs in
 // padded layout: one launch per pass for the whole group.
 template <typename T, int M>
-void run_box_group(int G, const T *src, T *dst, int64_t cs, const ModeParams *msv, const T *tw_, const T *sp,
-                   bool direct, hipStream_t st) {
+void run_box_group(const MultiGroupDesc &d, bool direct, hipStream_t st) {
   constexpr int N = M - 1;
-  const C2<T> *tw = reinterpret_cast<const C2<T> *>(tw_);
-  const int64_t rows = (int64_t)G * N;
-  if (cs != (int64_t)N * M) throw std::invalid_argument("group stride");
-  pass_x<T, M>(src, false, dst, false, rows, tw, sp, st);
+  const C2<T> *tw = static_cast<const C2<T> *>(d.tw);
+  const T *sp = static_cast<const T *>(d.sp), *src = static_cast<const T *>(d.src);
+  T *dst = static_cast<T *>(d.dst);
+  const int64_t rows = (int64_t)d.G * N;
+  if (d.cs != (int64_t)N * M) throw std::invalid_argument("group stride");
   if (direct) {
+    pass_x_set<T, M>(src, dst, d.in, rows, tw, sp, st);
     LastAxis<T> l;
     l.in = l.out = dst;
     l.dim = 2;
     l.M = M;
-    l.msv = msv;
-    l.nprob = G;
-    l.pstride = cs;
+    l.msv = d.msv;
+    l.nprob = d.G;
+    l.pstride = d.cs;
+    l.bin = d.in.bits;
+    l.bout = d.out.bits;
     last_axis_direct<T>(l, st);
+    pass_x_set<T, M>(dst, dst, d.out, rows, tw, sp, st);
   } else {
-    launch_last<T, M>(dst, dst, 2, 1, M, cs, ModeParams{}, tw, sp, msv, G, cs, st);
+    pass_x<T, M>(src, false, dst, false, rows, tw, sp, st);
+    launch_last<T, M>(dst, dst, 2, 1, M, d.cs, ModeParams{}, tw, sp, d.msv, d.G, d.cs, st);
+    pass_x<T, M>(dst, false, dst, false, rows, tw, sp, st);
   }
-  pass_x<T, M>(dst, false, dst, false, rows, tw, sp, st);
+}
+
+// 2D box solve whose right-hand side is zero outside the rows of `in` and whose result is read only on the rows
+// of `out` (sets without a list: every row), padded, into work: the other rows are neither read nor written.
+template <typename T, int M>
+void run_box_rows2d(DevProblem &p, const T *src, const RowSet &in, const RowSet &out, hipStream_t st) {
+  PrecTables<T> &tb = p.tab<T>();
+  const C2<T> *tw = reinterpret_cast<const C2<T> *>(tb.tw);
+  const int64_t rows = (int64_t)p.ncomp * (M - 1);
+  p.t_dst_x.tic(p.profile, st);
+  pass_x_set<T, M>(src, tb.work, in, rows, tw, tb.sp, st);
+  p.t_dst_x.toc(p.profile, st);
+  p.t_dst_last.tic(p.profile, st);
+  LastAxis<T> l;
+  l.in = l.out = tb.work;
+  l.dim = 2;
+  l.ncomp = p.ncomp;
+  l.M = M;
+  l.cs = p.comp_stride;
+  l.ms = mode_of<T>(p);
+  l.bin = in.bits;
+  l.bout = out.bits;
+  last_axis_direct<T>(l, st);
+  p.t_dst_last.toc(p.profile, st);
+  p.t_dst_x.tic(p.profile, st);
+  pass_x_set<T, M>(tb.work, tb.work, out, rows, tw, tb.sp, st);
+  p.t_dst_x.toc(p.profile, st);
 }
 
 // ---------------------------------------------------------------- merged 2D group passes
@@ -1683,6 +1698,7 @@ struct MultiX {
     const T *in;
     T *out;
     int64_t rows;
+    const int32_t *list;
     const C2<T> *tw;
     const T *sp;
     int M, begin;
@@ -1715,11 +1731,12 @@ __global__ __launch_bounds__((Shape<T, 64>::NT)) void k_dst_x_multi(MultiX<T> mp
   const auto &g = mp.g[k];
   const int64_t b = (int64_t)blockIdx.x - g.begin;
   switch (g.M) {
-    case 64: dst_x_tile<T, 64, true, true>(g.in, g.out, g.rows, g.tw, g.sp, sbuf, b); break;
-    case 128: dst_x_tile<T, 128, true, true>(g.in, g.out, g.rows, g.tw, g.sp, sbuf, b); break;
-    case 256: dst_x_tile<T, 256, true, true>(g.in, g.out, g.rows, g.tw, g.sp, sbuf, b); break;
-    case 512: dst_x_tile<T, 512, true, true>(g.in, g.out, g.rows, g.tw, g.sp, sbuf, b); break;
-    default: dst_x_tile<T, 1024, true, true>(g.in, g.out, g.rows, g.tw, g.sp, sbuf, b); break;
+#define KFBI_MULTI_ROWS(MM)                                                                       \
+    case MM:                                                                                      \
+      dst_x_tile<T, MM, true, true, true>(g.in, g.out, g.rows, g.list, g.tw, g.sp, sbuf, b);      \
+      break;
+    KFBI_MULTI_ROWS(64) KFBI_MULTI_ROWS(128) KFBI_MULTI_ROWS(256) KFBI_MULTI_ROWS(512) KFBI_MULTI_ROWS(1024)
+#undef KFBI_MULTI_ROWS
   }
 }
 
@@ -1731,16 +1748,15 @@ int tile_rows(int M) {   // rows per x-pass tile
 }  // namespace
 
 template <typename T>
-void box_solve_group(int Mfft, int G, const T *src, T *dst, int64_t cs, const ModeParams *msv, const T *tw,
-                     const T *sp, bool direct, hipStream_t st) {
-  switch (Mfft) {
-    case 16: run_box_group<T, 16>(G, src, dst, cs, msv, tw, sp, direct, st); break;
-    case 32: run_box_group<T, 32>(G, src, dst, cs, msv, tw, sp, direct, st); break;
-    case 64: run_box_group<T, 64>(G, src, dst, cs, msv, tw, sp, direct, st); break;
-    case 128: run_box_group<T, 128>(G, src, dst, cs, msv, tw, sp, direct, st); break;
-    case 256: run_box_group<T, 256>(G, src, dst, cs, msv, tw, sp, direct, st); break;
-    case 512: run_box_group<T, 512>(G, src, dst, cs, msv, tw, sp, direct, st); break;
-    case 1024: run_box_group<T, 1024>(G, src, dst, cs, msv, tw, sp, direct, st); break;
+void box_solve_group(const MultiGroupDesc &d, bool direct, hipStream_t st) {
+  switch (d.Mfft) {
+    case 16: run_box_group<T, 16>(d, direct, st); break;
+    case 32: run_box_group<T, 32>(d, direct, st); break;
+    case 64: run_box_group<T, 64>(d, direct, st); break;
+    case 128: run_box_group<T, 128>(d, direct, st); break;
+    case 256: run_box_group<T, 256>(d, direct, st); break;
+    case 512: run_box_group<T, 512>(d, direct, st); break;
+    case 1024: run_box_group<T, 1024>(d, direct, st); break;
     default: throw std::invalid_argument("unsupported grid size");
   }
 }
@@ -1752,7 +1768,7 @@ void box_solve_multi(const MultiGroupDesc *gd, int ng, hipStream_t st) {
   for (int k = 0; k < ng; ++k) order[k] = k;
   std::sort(order, order + ng, [&](int a, int b) { return gd[a].Mfft > gd[b].Mfft; });
   MultiX<T> x1{}, x2{};
-  int bx = 0;
+  int b1 = 0, b2 = 0;
   for (int j = 0; j < ng; ++j) {
     const MultiGroupDesc &d = gd[order[j]];
     const int M = d.Mfft, N = M - 1;
@@ -1763,25 +1779,25 @@ void box_solve_multi(const MultiGroupDesc *gd, int ng, hipStream_t st) {
     const C2<T> *tw = reinterpret_cast<const C2<T> *>(d.tw);
     const T *sp = static_cast<const T *>(d.sp);
     T *dst = static_cast<T *>(d.dst);
-    x1.g[j] = {static_cast<const T *>(d.src), dst, rows, tw, sp, M, bx};
-    x2.g[j] = {dst, dst, rows, tw, sp, M, bx};
-    bx += (int)((rows + tr - 1) / tr);
+    const int64_t n1 = d.in.list ? d.in.n : rows, n2 = d.out.list ? d.out.n : rows;
+    x1.g[j] = {static_cast<const T *>(d.src), dst, n1, d.in.list, tw, sp, M, b1};
+    x2.g[j] = {dst, dst, n2, d.out.list, tw, sp, M, b2};
+    b1 += (int)((n1 + tr - 1) / tr);
+    b2 += (int)((n2 + tr - 1) / tr);
   }
   x1.ng = x2.ng = ng;
   constexpr int NT = Shape<T, 64>::NT;
-  k_dst_x_multi<T><<<bx, NT, 0, st>>>(x1);
+  if (b1) k_dst_x_multi<T><<<b1, NT, 0, st>>>(x1);
   KFBI_HIP(hipGetLastError());
   last_axis_direct_multi<T>(gd, ng, st);
-  k_dst_x_multi<T><<<bx, NT, 0, st>>>(x2);
+  if (b2) k_dst_x_multi<T><<<b2, NT, 0, st>>>(x2);
   KFBI_HIP(hipGetLastError());
 }
 template void box_solve_multi<double>(const MultiGroupDesc *, int, hipStream_t);
 template void box_solve_multi<float>(const MultiGroupDesc *, int, hipStream_t);
 
-template void box_solve_group<double>(int, int, const double *, double *, int64_t, const ModeParams *,
-                                      const double *, const double *, bool, hipStream_t);
-template void box_solve_group<float>(int, int, const float *, float *, int64_t, const ModeParams *, const float *,
-                                     const float *, bool, hipStream_t);
+template void box_solve_group<double>(const MultiGroupDesc &, bool, hipStream_t);
+template void box_solve_group<float>(const MultiGroupDesc &, bool, hipStream_t);
 
 template <typename T>
 void box_solve(DevProblem &p, const T *src, bool src_plain, T *dst, bool dst_plain, hipStream_t st) {
@@ -1800,8 +1816,32 @@ void box_solve(DevProblem &p, const T *src, bool src_plain, T *dst, bool dst_pla
 template void box_solve<double>(DevProblem &, const double *, bool, double *, bool, hipStream_t);
 template void box_solve<float>(DevProblem &, const float *, bool, float *, bool, hipStream_t);
 
+// Whether a 2D product's passes take only the rows that matter.
+template <typename T>
+static bool rows2d_masked(const DevProblem &p) {
+  return p.sparse && p.direct && row_sets_pay(p.ncomp * p.comp_stride * (int64_t)sizeof(T));
+}
+
+template <typename T>
+static void box_rows2d(DevProblem &p, const T *src, const RowSet &in, const RowSet &out, hipStream_t st) {
+  switch (p.Mfft) {
+    case 16: run_box_rows2d<T, 16>(p, src, in, out, st); break;
+    case 32: run_box_rows2d<T, 32>(p, src, in, out, st); break;
+    case 64: run_box_rows2d<T, 64>(p, src, in, out, st); break;
+    case 128: run_box_rows2d<T, 128>(p, src, in, out, st); break;
+    case 256: run_box_rows2d<T, 256>(p, src, in, out, st); break;
+    case 512: run_box_rows2d<T, 512>(p, src, in, out, st); break;
+    case 1024: run_box_rows2d<T, 1024>(p, src, in, out, st); break;
+    default: throw std::invalid_argument("unsupported grid size");
+  }
+}
+
 template <typename T>
 void box_solve_stencils(DevProblem &p, const T *src, hipStream_t st) {
+  if (p.dim == 2 && rows2d_masked<T>(p)) {
+    box_rows2d<T>(p, src, RowSet{}, p.set_out(), st);
+    return;
+  }
   if (p.dim != 3 || !p.sparse) {
     box_solve<T>(p, src, false, p.tab<T>().work, false, st);
     return;
@@ -1847,6 +1887,10 @@ void bidomain_final_solve(DevProblem &p, const FhnArgs &a, bool fuse_be, hipStre
 
 template <typename T>
 void box_solve_matvec(DevProblem &p, hipStream_t st) {
+  if (p.dim == 2 && rows2d_masked<T>(p)) {
+    box_rows2d<T>(p, p.tab<T>().rhs, p.set_in(), p.set_out(), st);
+    return;
+  }
   if (p.dim != 3 || !p.sparse) {
     box_solve<T>(p, p.tab<T>().rhs, false, p.tab<T>().work, false, st);
     return;

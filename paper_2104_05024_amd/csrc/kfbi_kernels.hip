@@ -457,36 +457,37 @@ void upload_tables(DevProblem &p) {
   for (int64_t lin = 0; lin < (int64_t)t.inside.size(); ++lin) ins_pad[padpos(lin)] = t.inside[lin];
 
   // sparse matvec rows: irregular-node rows (right-hand side) and stencil rows (output)
-  if (d == 3) {
-    std::vector<uint8_t> min_(N * N, 0), mout(N * N, 0);
+  {
+    const int64_t planes = d == 3 ? N : 1, rows = planes * N;   // one plane in 2D
+    std::vector<uint8_t> min_(rows, 0), mout(rows, 0);
     for (int64_t lin : t.irregular) min_[lin / N] = 1;
     for (int64_t lin : t.st_lin) mout[lin / N] = 1;
     std::vector<int32_t> rin, rout;
     for (int c = 0; c < t.ncomp; ++c)
-      for (int64_t r = 0; r < N * N; ++r) {
-        if (min_[r]) rin.push_back((int32_t)(c * N * N + r));
-        if (mout[r]) rout.push_back((int32_t)(c * N * N + r));
+      for (int64_t r = 0; r < rows; ++r) {
+        if (min_[r]) rin.push_back((int32_t)(c * rows + r));
+        if (mout[r]) rout.push_back((int32_t)(c * rows + r));
       }
     p.n_rows_in = (int64_t)rin.size();
     p.n_rows_out = (int64_t)rout.size();
     p.rows_in = dupload(rin);
     p.rows_out = dupload(rout);
-    std::vector<uint64_t> bin((size_t)N * 16, 0), bout((size_t)N * 16, 0);
-    for (int64_t r = 0; r < N * N; ++r) {
+    std::vector<uint64_t> bin((size_t)planes * 16, 0), bout((size_t)planes * 16, 0);
+    for (int64_t r = 0; r < rows; ++r) {
       const int64_t z = r / N, y = r % N;
       if (min_[r]) bin[(size_t)z * 16 + (y >> 6)] |= uint64_t(1) << (y & 63);
       if (mout[r]) bout[(size_t)z * 16 + (y >> 6)] |= uint64_t(1) << (y & 63);
     }
     p.mask_in = dupload(bin);
     p.mask_out = dupload(bout);
-    std::vector<uint8_t> pin(N, 0), pout(N, 0);
-    for (int64_t r = 0; r < N * N; ++r) {
+    std::vector<uint8_t> pin(planes, 0), pout(planes, 0);
+    for (int64_t r = 0; r < rows; ++r) {
       if (min_[r]) pin[r / N] = 1;
       if (mout[r]) pout[r / N] = 1;
     }
     auto listed = [&](const std::vector<uint8_t> &f, int &n) {
       std::vector<int32_t> zs;
-      for (int64_t z = 0; z < N; ++z)
+      for (int64_t z = 0; z < planes; ++z)
         if (f[z]) zs.push_back((int32_t)z);
       n = (int)zs.size();
       return dupload(zs);
@@ -495,7 +496,7 @@ void upload_tables(DevProblem &p) {
     p.zlist_out = listed(pout, p.n_planes_out);
     p.planes_in_bits = PlaneBits{};
     p.planes_out_bits = PlaneBits{};
-    for (int64_t z = 0; z < N; ++z) {
+    for (int64_t z = 0; z < planes; ++z) {
       if (pin[z]) p.planes_in_bits.w[z >> 6] |= uint64_t(1) << (z & 63);
       if (pout[z]) p.planes_out_bits.w[z >> 6] |= uint64_t(1) << (z & 63);
     }

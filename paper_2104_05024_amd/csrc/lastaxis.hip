@@ -56,6 +56,11 @@ __device__ __forceinline__ uint32_t chunk_bits(const PlaneBits &b, int r0) {
   return (uint32_t)(w >> (r0 & 63));
 }
 
+// The same from a table of 16 words per problem (null: every row).
+__device__ __forceinline__ uint32_t chunk_bits(const uint64_t *__restrict__ bits, int problem, int r0) {
+  return bits ? (uint32_t)(bits[(int64_t)problem * 16 + (r0 >> 6)] >> (r0 & 63)) : ~0u;
+}
+
 // Rows of one component of a column tile, row i of the thread's chunk at base + i * RS.  Rows that a
 // thread does not have (masked planes, the row past the end, columns past the pad column) take an
 // offset beyond the buffer's range: such loads return zero and such stores are dropped, so that a
@@ -128,7 +133,7 @@ struct ColumnShared {
   double tot[2 * NC][XC];
 };
 
-// What one launch reads and writes (3D; the 2D pass is FORM 0):
+// What one launch reads and writes; ib / ob: the bits of the thread's chunk of rows in the sets (2D: forms 0 and 1):
 //   0 every row of every component in and out;
 //   1 rows in zin read (the others are zero), rows in zout written;
 //   2 every row read, rows in zout written;
@@ -137,10 +142,10 @@ struct ColumnShared {
 //   5 as 4 for the input (g, -g) plus the pair in ain2 on the rows in zin.
 template <typename T, int M, int NC, int DIM, int FORM, int XC>
 __device__ __forceinline__ void column_solve(const T *__restrict__ ain, T *__restrict__ a, int64_t P, int64_t cs,
-                                             const ModeParams &ms, int y, const PlaneBits &zin,
-                                             const PlaneBits &zout, const T *__restrict__ ain2, int x0,
+                                             const ModeParams &ms, int y, uint32_t ib, uint32_t ob,
+                                             const T *__restrict__ ain2, int x0,
                                              ColumnShared<NC, M / col_chunk(M), XC> &sh) {
-  constexpr int N = M - 1, LC = col_chunk(M), CH = M / LC, NW = (N + 63) / 64;
+  constexpr int N = M - 1, LC = col_chunk(M), CH = M / LC;
   const int xo = threadIdx.x % XC, c = threadIdx.x / XC, r0 = c * LC;
   const int x = x0 + xo;
   const bool in_row = M % XC == 0 || x < M;   // x = N is the pad column: zero in, zero out
@@ -148,9 +153,7 @@ __device__ __forceinline__ void column_solve(const T *__restrict__ ain, T *__res
   const int64_t base = (int64_t)r0 * RS + x;
   constexpr bool BUF = DIM == 2 || M <= 512;
   const int64_t bytes = (int64_t)N * RS * (int64_t)sizeof(T);
-  uint32_t ib = ~0u, ob = ~0u;
-  if constexpr (FORM == 1 || FORM == 5) ib = chunk_bits<NW>(zin, r0);
-  if constexpr (FORM >= 1 && FORM <= 3) ob = chunk_bits<NW>(zout, r0);
+  auto wants = [&](int i) { return FORM < 1 || FORM > 3 || ((ob >> i) & 1); };
   auto inside = [&](int i) { return in_row && (i < LC - 1 || c < CH - 1); };
   // all loads of the thread, in flight while the column's constants are computed
   double g[NC][LC];
@@ -305,7 +308,7 @@ __device__ __forceinline__ void column_solve(const T *__restrict__ ain, T *__res
 #pragma unroll
     for (int i = 0; i < LC; ++i) {
       const double u0 = B00 * g[0][i] + B10 * g[1][i], u1 = B01 * g[0][i] + B11 * g[1][i];
-      const bool wr = inside(i) && ((ob >> i) & 1);
+      const bool wr = inside(i) && wants(i);
       if constexpr (FORM >= 4) {
         o0.store(wr, base, i * RS, (T)(u0 - u1));
       } else {
@@ -315,7 +318,7 @@ __device__ __forceinline__ void column_solve(const T *__restrict__ ain, T *__res
     }
   } else {
 #pragma unroll
-    for (int i = 0; i < LC; ++i) o0.store(inside(i) && ((ob >> i) & 1), base, i * RS, (T)(s0 * g[0][i]));
+    for (int i = 0; i < LC; ++i) o0.store(inside(i) && wants(i), base, i * RS, (T)(s0 * g[0][i]));
   }
 }
 
@@ -325,13 +328,24 @@ constexpr int col_threads() { return M / col_chunk(M) * XC; }
 template <typename T, int M, int NC, int DIM, int FORM>
 __global__ __launch_bounds__((col_threads<M, col_width<T>(M)>())) void k_column(
     const T *ain, T *a, int64_t P, int64_t cs, ModeParams ms0, const ModeParams *__restrict__ msv, int64_t pstride,
-    PlaneBits zin, PlaneBits zout, const T *__restrict__ ain2) {
+    PlaneBits zin, PlaneBits zout, const uint64_t *__restrict__ bin, const uint64_t *__restrict__ bout,
+    const T *__restrict__ ain2) {
   constexpr int XC = col_width<T>(M);
   __shared__ ColumnShared<NC, M / col_chunk(M), XC> sh;
   const int by = blockIdx.y;
   const int64_t off = DIM == 3 ? (int64_t)by * P : (int64_t)by * pstride;
   const ModeParams ms = DIM == 2 && msv ? msv[by] : ms0;
-  column_solve<T, M, NC, DIM, FORM, XC>(ain + off, a + off, P, cs, ms, by, zin, zout, ain2 ? ain2 + off : nullptr,
+  constexpr int NW = (M + 62) / 64;
+  const int r0 = threadIdx.x / XC * col_chunk(M);
+  uint32_t ib = ~0u, ob = ~0u;
+  if constexpr (DIM == 3) {
+    if constexpr (FORM == 1 || FORM == 5) ib = chunk_bits<NW>(zin, r0);
+    if constexpr (FORM >= 1 && FORM <= 3) ob = chunk_bits<NW>(zout, r0);
+  } else if constexpr (FORM == 1) {
+    ib = chunk_bits(bin, by, r0);
+    ob = chunk_bits(bout, by, r0);
+  }
+  column_solve<T, M, NC, DIM, FORM, XC>(ain + off, a + off, P, cs, ms, by, ib, ob, ain2 ? ain2 + off : nullptr,
                                         blockIdx.x * XC, sh);
 }
 
@@ -341,15 +355,21 @@ void launch_form(const LastAxis<T> &l, hipStream_t st) {
   const dim3 g((M + XC - 1) / XC, DIM == 3 ? M - 1 : l.nprob);
   k_column<T, M, NC, DIM, FORM><<<g, col_threads<M, XC>(), 0, st>>>(
       l.in, l.out, M, l.cs, l.ms, l.msv, l.pstride, l.zin ? *l.zin : PlaneBits{}, l.zout ? *l.zout : PlaneBits{},
-      l.in2);
+      l.bin, l.bout, l.in2);
   KFBI_HIP(hipGetLastError());
 }
 
 template <typename T, int M>
 void launch_column(const LastAxis<T> &l, hipStream_t st) {
   if (l.dim == 2) {
-    if (l.ncomp == 2) launch_form<T, M, 2, 2, 0>(l, st);
-    else launch_form<T, M, 1, 2, 0>(l, st);
+    const bool masked = l.bin || l.bout;
+    if (l.ncomp == 2) {
+      if (masked) launch_form<T, M, 2, 2, 1>(l, st);
+      else launch_form<T, M, 2, 2, 0>(l, st);
+    } else {
+      if (masked) launch_form<T, M, 1, 2, 1>(l, st);
+      else launch_form<T, M, 1, 2, 0>(l, st);
+    }
     return;
   }
   if (l.form >= 3) {
@@ -378,6 +398,7 @@ struct MultiColumn {
     T *a;
     int64_t cs;
     const ModeParams *msv;
+    const uint64_t *bin, *bout;
     int M, begin, gx;
   } g[kMaxMultiGroups];
   int ng;
@@ -401,12 +422,13 @@ __global__ __launch_bounds__(kMultiThreads) void k_column_multi(MultiColumn<T> m
   const int b = (int)blockIdx.x - g.begin, pr = b / g.gx, bx = b - pr * g.gx;
   T *a = g.a + pr * g.cs;
   const ModeParams ms = g.msv[pr];
-  const PlaneBits none{};
+  auto bits = [&](const uint64_t *t, int M, int XC) { return chunk_bits(t, pr, (int)threadIdx.x / XC * col_chunk(M)); };
   switch (g.M) {
 #define KFBI_COLUMN_CASE(MM)                                                                                       \
     case MM:                                                                                                       \
-      column_solve<T, MM, 1, 2, 0, multi_width(MM)>(                                                               \
-          a, a, MM, 0, ms, 0, none, none, nullptr, bx * multi_width(MM),                                           \
+      column_solve<T, MM, 1, 2, 1, multi_width(MM)>(                                                               \
+          a, a, MM, 0, ms, 0, bits(g.bin, MM, multi_width(MM)), bits(g.bout, MM, multi_width(MM)), nullptr,        \
+          bx * multi_width(MM),                                                                                    \
           *reinterpret_cast<ColumnShared<1, MM / col_chunk(MM), multi_width(MM)> *>(lds));                         \
       break;
     KFBI_COLUMN_CASE(64) KFBI_COLUMN_CASE(128) KFBI_COLUMN_CASE(256) KFBI_COLUMN_CASE(512)
@@ -467,7 +489,7 @@ void last_axis_direct_multi(const MultiGroupDesc *gd, int ng, hipStream_t st) {
     if (M < 64 || M > 1024 || (M & (M - 1)) || gd[j].G < 1 || gd[j].cs != (int64_t)(M - 1) * M || !gd[j].msv)
       throw std::invalid_argument("merged passes: sizes 64..1024, padded groups");
     const int gx = (M + multi_width(M) - 1) / multi_width(M);
-    mp.g[j] = {static_cast<T *>(gd[j].dst), gd[j].cs, gd[j].msv, M, blocks, gx};
+    mp.g[j] = {static_cast<T *>(gd[j].dst), gd[j].cs, gd[j].msv, gd[j].in.bits, gd[j].out.bits, M, blocks, gx};
     blocks += gx * gd[j].G;
   }
   mp.ng = ng;
