@@ -135,7 +135,7 @@ __device__ __forceinline__ void dft(C2<T> *v) {
 #endif
 __device__ __forceinline__ int pad(int i) { return i + (i >> KFBI_LDS_PAD_SHIFT); }
 
-// Barrier for the LDS exchanges inside one pencil pair.  The M / 16 threads of a pair are
+// Barrier for the LDS exchanges inside one pencil pair.  The M / E threads (E values each) of a pair are
 // consecutive and M <= 1024, so a pair never straddles two wavefronts, and one wavefront's LDS
 // operations are carried out in program order: a wavefront-scope fence, which only stops the
 // compiler from moving LDS accesses across it, is enough.  Exchanges between pairs (the tile
@@ -147,22 +147,46 @@ __device__ __forceinline__ void pair_sync() {
 }
 
 
-template <typename T, int M>
+// W: wavefronts per workgroup; E: values of a pencil pair that one thread holds, M / E threads per pair.
+template <typename T, int M, int W, int E>
 struct Shape {
-  static constexpr int N = M - 1;
-  static constexpr int TPP = M / 16;                          // threads per pencil pair
+  static constexpr int N = M - 1, Ept = E;
+  static constexpr int TPP = M / E;        // threads per pencil pair
   static_assert(TPP <= 64 && 64 % TPP == 0, "a pencil pair must lie inside one wavefront");
-  static constexpr int NP = (sizeof(T) == 8 ? 2048 : 4096) / M;  // pencil pairs per workgroup
-  static constexpr int NT = NP * TPP;                         // threads per workgroup (128 / 256)
-  static constexpr int PADM = M + (M >> KFBI_LDS_PAD_SHIFT) + KFBI_LDS_PAIR_SKEW;                  // padded LDS length of one pair (odd:
-                                                              // pairs start on different banks)
+  static constexpr int NP = W * 64 / TPP;  // pencil pairs per workgroup
+  static constexpr int NT = 64 * W;
+  static constexpr int PADM = M + (M >> KFBI_LDS_PAD_SHIFT) + KFBI_LDS_PAIR_SKEW;   // padded LDS length of one pair
+                                                                                    // (odd: pairs start on
+                                                                                    // different banks)
 };
+// A transform is a serial chain per thread (pre-processing, log_E M stages, scan), about 4 us of it with 16
+// values a thread; with fewer, more threads share it, at more exchanges through LDS.  Rows: one wavefront
+// per workgroup (its barrier costs nothing and its loads and stores start when it is done: dense 256^3 coupled
+// FP64 113 -> 106 us), 4 values up to 64 cells, 8 up to 512, 16 at 1024 (the fewest that keep a pair in one
+// wavefront).  One 2D pass in FP64 with 16 / 8 / 4 values (us): 64 7.7 / 4.5 / 3.8, 128 7.1 / 5.0 / 4.0, 256 7.2 /
+// 4.9 / 4.1, 512 7.9 / 5.4; dense 3D scalar: 128 12.1 / 11.4 / 11.6, 256 59 / 54 / 63, 512 409 / 422.
+constexpr int row_values(int M) { return M <= 64 ? 4 : M <= 512 ? 8 : 16; }
+template <typename T, int M, int E = row_values(M)>
+using XShape = Shape<T, M, 1, E>;
+// Columns of a plane (y): as many wavefronts as make a tile's row segments 128 bytes or more (with 64: 47 -> 61 us
+// at 256^3), and fewer values only where the pass is short.  64^3 7.5 -> 5.2 us in FP64 and 10.9 -> 4.3 in FP32,
+// 128^3 13.7 -> 13.0 and 10.8 -> 8.7; 256 and up as fast with 16.
+constexpr int column_values(int M) { return M <= 64 ? 4 : M <= 128 ? 8 : 16; }
+template <typename T, int M>
+using YShape = Shape<T, M, M == 64 || M == 128 ? 4 : (sizeof(T) == 8 ? 2 : 4), column_values(M)>;
+// the bidomain step's x passes: 128 cells 11.1 -> 8.2 us (forward Euler) and 64^3 21.8 -> 9.6 (backward Euler);
+// at 256^3 the latter is slower with 8 values (154 against 142 us)
+template <int M>
+using FShape = Shape<double, M, 2, column_values(M)>;
+// the last axis as a fused transform pass
+template <typename T, int M>
+using LShape = Shape<T, M, sizeof(T) == 8 ? 2 : 4, 16>;
 
 // One Stockham stage of radix R after Ns points have been combined.
-template <typename T, int M, int R, int Ns>
+template <typename T, int M, int E, int R, int Ns>
 __device__ __forceinline__ void stage(C2<T> *buf, int lane, const C2<T> *__restrict__ tw) {
-  constexpr int NB = 16 / R, MR = M / R, TPP = M / 16;
-  C2<T> v[16];
+  constexpr int NB = E / R, MR = M / R, TPP = M / E;
+  C2<T> v[E];
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
     const int j = lane + TPP * b;
@@ -187,14 +211,14 @@ __device__ __forceinline__ void stage(C2<T> *buf, int lane, const C2<T> *__restr
   pair_sync();
 }
 
-template <typename T, int M, int Ns>
+template <typename T, int M, int E, int Ns>
 __device__ __forceinline__ void fft_stages(C2<T> *buf, int lane, const C2<T> *tw) {
   constexpr int rem = M / Ns;
-  if constexpr (rem > 16) {
-    stage<T, M, 16, Ns>(buf, lane, tw);
-    fft_stages<T, M, Ns * 16>(buf, lane, tw);
+  if constexpr (rem > E) {
+    stage<T, M, E, E, Ns>(buf, lane, tw);
+    fft_stages<T, M, E, Ns * E>(buf, lane, tw);
   } else {
-    stage<T, M, rem, Ns>(buf, lane, tw);
+    stage<T, M, E, rem, Ns>(buf, lane, tw);
   }
 }
 
@@ -209,28 +233,29 @@ struct NoHook {
   __device__ __forceinline__ void operator()(int, C2<T> &) const {}
 };
 
-// s_n = sin(pi n / M) at the positions n = 1 + lane + (M/16) i, i < 8, that one thread's
+// s_n = sin(pi n / M) at the positions n = 1 + lane + (M / E) i, i < E / 2, that one thread's
 // pre-processing combines, from a table in global memory or LDS.  Kernels load them from
 // memory with their tile, so that the pre-processing, which follows a barrier, does not wait
 // on memory (the last-axis pass reads them from an LDS copy instead, to hold no registers
 // across its forward transform).
-template <typename T, int M>
+template <typename T, int M, int E>
 struct Sines {
-  T s[8];
+  T s[E / 2];
   __device__ __forceinline__ Sines(const T *sp, int lane) {
+    constexpr int H = E / 2;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) s[i] = sp[1 + lane + (M / 16) * i];
+    for (int i = 0; i < H; ++i) s[i] = sp[1 + lane + (M / E) * i];
   }
 };
 
 // Pre-processing t_n = s_n (x_n + x_{M-n}) + (x_n - x_{M-n})/2: (n, M-n) pairs are owned by one
 // thread, so no barrier inside; the hook sees every input value (position m = 1..N) as it is
 // read.
-template <typename T, int M, typename Hook>
-__device__ __forceinline__ void dst_pre(C2<T> *buf, int lane, const Sines<T, M> &sn, const Hook &hook) {
-  constexpr int TPP = M / 16;
+template <typename T, int M, int E, typename Hook>
+__device__ __forceinline__ void dst_pre(C2<T> *buf, int lane, const Sines<T, M, E> &sn, const Hook &hook) {
+  constexpr int TPP = M / E, H = E / 2;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < H; ++i) {
     const int n = 1 + lane + TPP * i;
     C2<T> a = buf[pad(n)], b = buf[pad(M - n)];
     hook(n, a);
@@ -244,23 +269,23 @@ __device__ __forceinline__ void dst_pre(C2<T> *buf, int lane, const Sines<T, M> 
 }
 
 // Post-processing of the FFT of a pre-processed pencil pair held in buf (prefix scan over the odd
-// outputs): lane owns k in [8 lane, 8 lane + 8), so its outputs are the DST values at positions
-// 16 lane + q, q < 16, returned in y[q] (y[0] of lane 0, position 0, is not an output: zero).
-template <typename T, int M>
-__device__ __forceinline__ void dst_post(const C2<T> *buf, int lane, C2<T> (&y)[16]) {
-  constexpr int TPP = M / 16;
-  C2<T> ev[8], od[8];
+// outputs): lane owns k in [H lane, H lane + H), H = E / 2, so its outputs are the DST values at positions
+// E lane + q, q < E, returned in y[q] (y[0] of lane 0, position 0, is not an output: zero).
+template <typename T, int M, int E>
+__device__ __forceinline__ void dst_post(const C2<T> *buf, int lane, C2<T> (&y)[E]) {
+  constexpr int TPP = M / E, H = E / 2;
+  C2<T> ev[H], od[H];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int k = 8 * lane + i;
+  for (int i = 0; i < H; ++i) {
+    const int k = H * lane + i;
     const C2<T> zk = buf[pad(k)], zm = buf[pad((M - k) & (M - 1))];
     ev[i] = {(T)0.5 * (zm.y - zk.y), (T)0.5 * (zk.x - zm.x)};
     od[i] = {(T)0.5 * (zk.x + zm.x), (T)0.5 * (zk.y + zm.y)};
   }
   const C2<T> e0 = od[0];
 #pragma unroll
-  for (int i = 1; i < 8; ++i) od[i] = od[i] + od[i - 1];
-  const C2<T> tot = od[7];
+  for (int i = 1; i < H; ++i) od[i] = od[i] + od[i - 1];
+  const C2<T> tot = od[H - 1];
   C2<T> inc = tot;
 #pragma unroll
   for (int off = 1; off < TPP; off <<= 1) {
@@ -271,7 +296,7 @@ __device__ __forceinline__ void dst_post(const C2<T> *buf, int lane, C2<T> (&y)[
   const C2<T> E0 = {shfl_w(e0.x, 0, TPP), shfl_w(e0.y, 0, TPP)};
   const C2<T> half0 = (T)0.5 * E0;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < H; ++i) {
     y[2 * i] = (i > 0 || lane > 0) ? ev[i] : C2<T>{T(0), T(0)};
     y[2 * i + 1] = (excl + od[i]) - half0;
   }
@@ -280,15 +305,15 @@ __device__ __forceinline__ void dst_post(const C2<T> *buf, int lane, C2<T> (&y)[
 // The FFT of the pre-processed pencil pair and the post-processing; result at positions 1..N.
 // All threads of the workgroup must call it.  BLOCK: end with a workgroup barrier (the caller
 // reads other pairs' results next) rather than a pair one.
-template <typename T, int M, bool BLOCK = true>
+template <typename T, int M, int E, bool BLOCK = true>
 __device__ __forceinline__ void dst_rest(C2<T> *buf, int lane, const C2<T> *__restrict__ tw) {
-  fft_stages<T, M, 1>(buf, lane, tw);
-  C2<T> y[16];
-  dst_post<T, M>(buf, lane, y);
+    fft_stages<T, M, E, 1>(buf, lane, tw);
+  C2<T> y[E];
+  dst_post<T, M, E>(buf, lane, y);
   pair_sync();
 #pragma unroll
-  for (int q = 0; q < 16; ++q)
-    if (q > 0 || lane > 0) buf[pad(16 * lane + q)] = y[q];
+  for (int q = 0; q < E; ++q)
+    if (q > 0 || lane > 0) buf[pad(E * lane + q)] = y[q];
   if constexpr (BLOCK) __syncthreads();
   else pair_sync();
 }
@@ -296,12 +321,12 @@ __device__ __forceinline__ void dst_rest(C2<T> *buf, int lane, const C2<T> *__re
 // DST-I (unnormalised: y_k = sum_n x_n sin(pi n k / M)) of one pencil pair held in LDS as
 // complex values at positions 1..N; result at the same positions.  All threads of the
 // workgroup must call it (it contains barriers).
-template <typename T, int M, typename Hook = NoHook<T>>
+template <typename T, int M, int E, typename Hook = NoHook<T>>
 __device__ __forceinline__ void dst_pair(C2<T> *buf, int lane, const C2<T> *__restrict__ tw,
-                                         const Sines<T, M> &sn, const Hook &hook = Hook()) {
-  dst_pre<T, M>(buf, lane, sn, hook);
+                                         const Sines<T, M, E> &sn, const Hook &hook = Hook()) {
+  dst_pre<T, M, E>(buf, lane, sn, hook);
   pair_sync();
-  dst_rest<T, M>(buf, lane, tw);
+  dst_rest<T, M, E>(buf, lane, tw);
 }
 
 template <typename T>
@@ -326,17 +351,17 @@ struct alignas(16) V16 {
 // PIN / POUT: input / output in the padded layout (row pitch M) instead of pitch N.
 // One tile (2 NP rows, tile index blk) in the LDS buffer sbuf of NP * PADM values.
 // LIST (M >= 64): row i of the pass is row list[i] of both fields (row i itself where list is null).
-template <typename T, int M, bool PIN, bool POUT, bool LIST = false>
+template <typename T, int M, bool PIN, bool POUT, bool LIST = false, int E = row_values(M)>
 __device__ __forceinline__ void dst_x_tile(const T *__restrict__ in, T *__restrict__ out, int64_t nrows,
                                            const int32_t *__restrict__ list,
                                            const C2<T> *__restrict__ tw, const T *__restrict__ sp, C2<T> *sbuf,
                                            int64_t blk) {
-  using Sh = Shape<T, M>;
+  using Sh = XShape<T, M, E>;
   constexpr int N = Sh::N, NP = Sh::NP, NT = Sh::NT, PADM = Sh::PADM, VW = 16 / sizeof(T);
   constexpr int ROWS = 2 * NP;
   const int tid = threadIdx.x;
   const int64_t r0 = blk * ROWS;
-  const Sines<T, M> sn(sp, tid % Sh::TPP);
+  const Sines<T, M, Sh::Ept> sn(sp, tid % Sh::TPP);
   if constexpr (M >= 64) {
     // one pencil pair per wave at a time; a lane moves whole complex values (two 8-byte row
     // elements per 16-byte LDS word, unit stride: no LDS bank conflicts)
@@ -376,7 +401,7 @@ __device__ __forceinline__ void dst_x_tile(const T *__restrict__ in, T *__restri
         if (n < N) sbuf[(wv + NWV * pp) * PADM + pad(n + 1)] = v[pp][k];
       }
     __syncthreads();
-    dst_pair<T, M>(sbuf + (tid / Sh::TPP) * PADM, tid % Sh::TPP, tw, sn);
+    dst_pair<T, M, Sh::Ept>(sbuf + (tid / Sh::TPP) * PADM, tid % Sh::TPP, tw, sn);
 #pragma unroll
     for (int pp = 0; pp < PPW; ++pp) {
       const int rr = wv + NWV * pp;
@@ -440,7 +465,7 @@ __device__ __forceinline__ void dst_x_tile(const T *__restrict__ in, T *__restri
       }
     }
     __syncthreads();
-    dst_pair<T, M>(sbuf + (tid / Sh::TPP) * PADM, tid % Sh::TPP, tw, sn);
+    dst_pair<T, M, Sh::Ept>(sbuf + (tid / Sh::TPP) * PADM, tid % Sh::TPP, tw, sn);
     if constexpr (POUT) {
       constexpr int VPR = M / VW, NV = ROWS * VPR, PER = (NV + NT - 1) / NT;
       V16<T> reg[PER];
@@ -481,13 +506,13 @@ __device__ __forceinline__ void dst_x_tile(const T *__restrict__ in, T *__restri
   }
 }
 
-template <typename T, int M, bool PIN, bool POUT>
-__global__ __launch_bounds__((Shape<T, M>::NT)) void k_dst_x(const T *__restrict__ in, T *__restrict__ out,
+template <typename T, int M, bool PIN, bool POUT, int E>
+__global__ __launch_bounds__((XShape<T, M, E>::NT)) void k_dst_x(const T *__restrict__ in, T *__restrict__ out,
                                                              int64_t nrows, const C2<T> *__restrict__ tw,
                                                              const T *__restrict__ sp) {
-  using Sh = Shape<T, M>;
+  using Sh = XShape<T, M, E>;
   __shared__ C2<T> sbuf[Sh::NP * Sh::PADM];
-  dst_x_tile<T, M, PIN, POUT>(in, out, nrows, nullptr, tw, sp, sbuf, blockIdx.x);
+  dst_x_tile<T, M, PIN, POUT, false, E>(in, out, nrows, nullptr, tw, sp, sbuf, blockIdx.x);
 }
 
 // Row predicates of the strided tile mover: every row; rows in a bit set read once from memory
@@ -524,9 +549,8 @@ struct BitRows {
 // Tile mover for the strided passes: a tile is NR rows (stride RS elements) of TX consecutive
 // columns starting at column x0, for NC components (stride CS); element (row r, column xo,
 // component c) lives at LDS pair PAIR(xo, c), lane LANE(xo, c), position r + 1.
-template <typename T, int M, int TX, int NC>
+template <typename T, int M, int TX, int NC, typename Sh>
 struct StridedTile {
-  using Sh = Shape<T, M>;
   static constexpr int N = Sh::N, NT = Sh::NT, PADM = Sh::PADM, VW = 16 / sizeof(T);
   static constexpr bool VEC = (TX % VW == 0) && (TX <= M);
   static constexpr int NE = VEC ? N * NC * (TX / VW) : N * NC * TX;
@@ -606,7 +630,7 @@ struct StridedTile {
     if constexpr (!VEC) {
       load(base, RS, CS, x0, sbuf, tid, rows);
       __syncthreads();
-      dst_pre<T, M>(sbuf + (tid / Sh::TPP) * PADM, tid % Sh::TPP, Sines<T, M>(sp, tid % Sh::TPP), NoHook<T>());
+      dst_pre<T, M, Sh::Ept>(sbuf + (tid / Sh::TPP) * PADM, tid % Sh::TPP, Sines<T, M, Sh::Ept>(sp, tid % Sh::TPP), NoHook<T>());
     } else {
       constexpr int VPR = TX / VW, NPR = M / 2, NU = NPR * VPR, PU = (NU + NT - 1) / NT;
       V16<T> ra[PU][NC], rb[PU][NC];
@@ -748,23 +772,23 @@ struct StridedTile {
 // be zero on input are not read; only rows flagged on output are written.  planes (optional): the list of
 // planes to take, one per blockIdx.y; the others are neither read nor written.
 template <typename T, int M>
-__global__ __launch_bounds__((Shape<T, M>::NT)) void k_dst_y(const T *__restrict__ in, T *__restrict__ out,
+__global__ __launch_bounds__((YShape<T, M>::NT)) void k_dst_y(const T *__restrict__ in, T *__restrict__ out,
                                                                int64_t P, int64_t comp_stride,
                                                                const uint64_t *__restrict__ mask_in,
                                                                const uint64_t *__restrict__ mask_out,
                                                                const int32_t *__restrict__ planes,
                                                                const C2<T> *__restrict__ tw, const T *__restrict__ sp) {
-  using Sh = Shape<T, M>;
-  using Tl = StridedTile<T, M, 2 * Sh::NP, 1>;
+  using Sh = YShape<T, M>;
+  using Tl = StridedTile<T, M, 2 * Sh::NP, 1, Sh>;
   __shared__ C2<T> sbuf[Sh::NP * Sh::PADM];
   const int tid = threadIdx.x;
   const int x0 = blockIdx.x * 2 * Sh::NP, z = planes ? planes[blockIdx.y] : (int)blockIdx.y, c = blockIdx.z;
   const int64_t off = c * comp_stride + (int64_t)z * Sh::N * P;
   constexpr int NW = (Sh::N + 63) / 64;
-  const Sines<T, M> sn(sp, tid % Sh::TPP);
+  const Sines<T, M, Sh::Ept> sn(sp, tid % Sh::TPP);
   Tl::load(in + off, P, 0, x0, sbuf, tid, BitRowsMem<NW>(mask_in ? mask_in + (int64_t)z * 16 : nullptr));
   __syncthreads();
-  dst_pair<T, M>(sbuf + (tid / Sh::TPP) * Sh::PADM, tid % Sh::TPP, tw, sn);
+  dst_pair<T, M, Sh::Ept>(sbuf + (tid / Sh::TPP) * Sh::PADM, tid % Sh::TPP, tw, sn);
   Tl::store(out + off, P, 0, x0, sbuf, tid, BitRowsMem<NW>(mask_out ? mask_out + (int64_t)z * 16 : nullptr));
 }
 
@@ -820,11 +844,11 @@ __device__ __forceinline__ void dst_last_tile(const T *__restrict__ ain, T *__re
                                               const PlaneBits &zin, const PlaneBits &zout, C2<T> *sbuf, T *slam,
                                               T *ssin, int64_t id, int64_t total, int gx,
                                               const T *__restrict__ ain2 = nullptr) {
-  using Sh = Shape<T, M>;
+  using Sh = LShape<T, M>;
   constexpr int N = Sh::N, NP = Sh::NP, NT = Sh::NT, PADM = Sh::PADM;
   constexpr int TX = NC == 2 ? NP : 2 * NP;          // columns per tile
   constexpr int64_t LS = DIM == 3 ? (int64_t)N : 1;  // rows of the last axis step by LS * P
-  using Tl = StridedTile<T, M, TX, NC>;
+  using Tl = StridedTile<T, M, TX, NC, Sh>;
   const int tid = threadIdx.x;
   // A tile row of TX columns is half of a 128-byte line; the tile sharing the line is
   // given to the workgroup dispatched 8 later, i.e. on the same XCD (round-robin dispatch), so
@@ -848,7 +872,7 @@ __device__ __forceinline__ void dst_last_tile(const T *__restrict__ ain, T *__re
   __syncthreads();
   const int pr = tid / Sh::TPP, lane = tid % Sh::TPP;
   C2<T> *mine = sbuf + pr * PADM;
-  dst_rest<T, M, false>(mine, lane, tw);
+  dst_rest<T, M, Sh::Ept, false>(mine, lane, tw);
   // inverse transform with the mode solve applied as it reads the spectrum
   ModeHook<T, NC> mh;
   mh.slam = slam;
@@ -873,14 +897,14 @@ __device__ __forceinline__ void dst_last_tile(const T *__restrict__ ain, T *__re
   }
   mh.kap = (T)ms.kappa;
   mh.nrm = (T)ms.norm;
-  dst_pair<T, M>(mine, lane, tw, Sines<T, M>(ssin, lane), mh);
+  dst_pair<T, M, Sh::Ept>(mine, lane, tw, Sines<T, M, Sh::Ept>(ssin, lane), mh);
   if constexpr (ZM == 4 || ZM == 5) Tl::template store<true>(base, LS * P, comp_stride, x0, sbuf, tid);
   else if constexpr (ZM != 0) Tl::store(base, LS * P, comp_stride, x0, sbuf, tid, BitRows<NW>{zout});
   else Tl::store(base, LS * P, comp_stride, x0, sbuf, tid);
 }
 
 template <typename T, int M, int NC, int DIM, int ZM = 0>
-__global__ __launch_bounds__((Shape<T, M>::NT)) void k_dst_last(const T *__restrict__ ain, T *__restrict__ a,
+__global__ __launch_bounds__((LShape<T, M>::NT)) void k_dst_last(const T *__restrict__ ain, T *__restrict__ a,
                                                                      int64_t P, int64_t comp_stride,
                                                                   ModeScale ms0, const C2<T> *__restrict__ tw,
                                                                   const T *__restrict__ sp,
@@ -888,7 +912,7 @@ __global__ __launch_bounds__((Shape<T, M>::NT)) void k_dst_last(const T *__restr
                                                                   int64_t pstride = 0, PlaneBits zin = {},
                                                                   PlaneBits zout = {},
                                                                   const T *__restrict__ ain2 = nullptr) {
-  using Sh = Shape<T, M>;
+  using Sh = LShape<T, M>;
   __shared__ C2<T> sbuf[Sh::NP * Sh::PADM];
   __shared__ T slam[M];
   __shared__ T ssin[M / 2 + 1];
@@ -899,21 +923,21 @@ __global__ __launch_bounds__((Shape<T, M>::NT)) void k_dst_last(const T *__restr
 
 // DST along contiguous rows listed in `rows` (indices into the flattened [comp][..] row list),
 // padded layout in and out; used by the sparse passes of the matrix-vector product.
-template <typename T, int M>
-__global__ __launch_bounds__((Shape<T, M>::NT)) void k_dst_x_rows(const T *__restrict__ in, T *__restrict__ out,
+template <typename T, int M, int E>
+__global__ __launch_bounds__((XShape<T, M, E>::NT)) void k_dst_x_rows(const T *__restrict__ in, T *__restrict__ out,
                                                                     const int32_t *__restrict__ rows, int64_t nlist,
                                                                     const C2<T> *__restrict__ tw,
                                                                     const T *__restrict__ sp) {
-  using Sh = Shape<T, M>;
+  using Sh = XShape<T, M, E>;
   constexpr int N = Sh::N, NP = Sh::NP, NT = Sh::NT, PADM = Sh::PADM, VW = 16 / sizeof(T);
   constexpr int ROWS = 2 * NP, VPR = M / VW, NV = ROWS * VPR, PER = (NV + NT - 1) / NT;
   __shared__ C2<T> sbuf[NP * PADM];
   if constexpr (M >= 64) {
-    dst_x_tile<T, M, true, true, true>(in, out, nlist, rows, tw, sp, sbuf, blockIdx.x);
+    dst_x_tile<T, M, true, true, true, E>(in, out, nlist, rows, tw, sp, sbuf, blockIdx.x);
   } else {
     const int tid = threadIdx.x;
     const int64_t r0 = (int64_t)blockIdx.x * ROWS;
-    const Sines<T, M> sn(sp, tid % Sh::TPP);
+    const Sines<T, M, Sh::Ept> sn(sp, tid % Sh::TPP);
     V16<T> reg[PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
@@ -938,7 +962,7 @@ __global__ __launch_bounds__((Shape<T, M>::NT)) void k_dst_x_rows(const T *__res
       }
     }
     __syncthreads();
-    dst_pair<T, M>(sbuf + (tid / Sh::TPP) * PADM, tid % Sh::TPP, tw, sn);
+    dst_pair<T, M, Sh::Ept>(sbuf + (tid / Sh::TPP) * PADM, tid % Sh::TPP, tw, sn);
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int e = tid + i * NT;
@@ -979,12 +1003,12 @@ __global__ __launch_bounds__((Shape<T, M>::NT)) void k_dst_x_rows(const T *__res
 enum { FHN_FE = 0, FHN_SRC = 1, FHN_BE = 2 };
 
 template <int M, int MODE>
-__global__ __launch_bounds__((Shape<double, M>::NT)) void k_dst_x_fhn(FhnArgs a, double *__restrict__ work,
+__global__ __launch_bounds__((FShape<M>::NT)) void k_dst_x_fhn(FhnArgs a, double *__restrict__ work,
                                                                     const double *__restrict__ rhs,
                                                                     const uint64_t *__restrict__ mask, int64_t rows,
                                                                     int64_t cs, const C2<double> *__restrict__ tw,
                                                                     const double *__restrict__ sp) {
-  using Sh = Shape<double, M>;
+  using Sh = FShape<M>;
   using C = C2<double>;
   constexpr int N = Sh::N, NP = Sh::NP, NT = Sh::NT, PADM = Sh::PADM;
   constexpr int NE = NP * N, PER = (NE + NT - 1) / NT;
@@ -994,7 +1018,7 @@ __global__ __launch_bounds__((Shape<double, M>::NT)) void k_dst_x_fhn(FhnArgs a,
   double *__restrict__ V = a.V;
   double *__restrict__ q = a.q;
   const double *__restrict__ stim = a.stim;
-  const Sines<double, M> sn(sp, tid % Sh::TPP);
+  const Sines<double, M, Sh::Ept> sn(sp, tid % Sh::TPP);
   double va[PER], qa[PER];
   if constexpr (MODE == FHN_BE) {
     C u[PER];
@@ -1087,7 +1111,7 @@ __global__ __launch_bounds__((Shape<double, M>::NT)) void k_dst_x_fhn(FhnArgs a,
     }
   }
   __syncthreads();
-  dst_pair<double, M>(sbuf + (tid / Sh::TPP) * PADM, tid % Sh::TPP, tw, sn);
+  dst_pair<double, M, Sh::Ept>(sbuf + (tid / Sh::TPP) * PADM, tid % Sh::TPP, tw, sn);
   if constexpr (MODE == FHN_BE) {
     // V and q after the transform: fetched ahead of it they would be held across it in
     // registers (a second wave per SIMD would no longer fit)
@@ -1138,18 +1162,18 @@ __global__ __launch_bounds__((Shape<double, M>::NT)) void k_dst_x_fhn(FhnArgs a,
 // One pencil pair per wave at a time: a lane forms the values of both rows at one position and
 // writes them as one 16-byte LDS word.  M >= 64.
 template <int M>
-__global__ __launch_bounds__((Shape<double, M>::NT)) void k_dst_x_fe1(FhnArgs a, double *__restrict__ work,
+__global__ __launch_bounds__((XShape<double, M>::NT)) void k_dst_x_fe1(FhnArgs a, double *__restrict__ work,
                                                                     int64_t rows, const C2<double> *__restrict__ tw,
                                                                     const double *__restrict__ sp) {
   static_assert(M >= 64, "one pencil pair per wave needs M >= 64");
-  using Sh = Shape<double, M>;
+  using Sh = XShape<double, M>;
   using C = C2<double>;
   constexpr int N = Sh::N, NP = Sh::NP, NT = Sh::NT, PADM = Sh::PADM;
   constexpr int NWV = NT / 64, PPW = NP / NWV, KS = M / 64;
   __shared__ C sbuf[NP * PADM];
   const int tid = threadIdx.x;
   const int64_t r0 = (int64_t)blockIdx.x * 2 * NP;
-  const Sines<double, M> sn(sp, tid % Sh::TPP);
+  const Sines<double, M, Sh::Ept> sn(sp, tid % Sh::TPP);
   const int wv = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
   const double *__restrict__ V = a.V;
   const double *__restrict__ q = a.q;
@@ -1181,7 +1205,7 @@ __global__ __launch_bounds__((Shape<double, M>::NT)) void k_dst_x_fe1(FhnArgs a,
       }
     }
   __syncthreads();
-  dst_pair<double, M>(sbuf + (tid / Sh::TPP) * PADM, tid % Sh::TPP, tw, sn);
+  dst_pair<double, M, Sh::Ept>(sbuf + (tid / Sh::TPP) * PADM, tid % Sh::TPP, tw, sn);
 #pragma unroll
   for (int pp = 0; pp < PPW; ++pp) {
     const int rr = wv + NWV * pp;
@@ -1204,18 +1228,18 @@ __global__ __launch_bounds__((Shape<double, M>::NT)) void k_dst_x_fe1(FhnArgs a,
 // field, and this pass transforms its rows in pairs (as k_dst_x) before the pointwise update of
 // FHN_BE.  Half the pencils and a sixth less traffic than FHN_BE.  M >= 64.
 template <int M>
-__global__ __launch_bounds__((Shape<double, M>::NT)) void k_dst_x_be1(FhnArgs a, const double *__restrict__ work,
+__global__ __launch_bounds__((FShape<M>::NT)) void k_dst_x_be1(FhnArgs a, const double *__restrict__ work,
                                                                     int64_t rows, const C2<double> *__restrict__ tw,
                                                                     const double *__restrict__ sp) {
   static_assert(M >= 64, "one pencil pair per wave needs M >= 64");
-  using Sh = Shape<double, M>;
+  using Sh = FShape<M>;
   using C = C2<double>;
   constexpr int N = Sh::N, NP = Sh::NP, NT = Sh::NT, PADM = Sh::PADM;
   constexpr int NWV = NT / 64, PPW = NP / NWV, KS = M / 64;
   __shared__ C sbuf[NP * PADM];
   const int tid = threadIdx.x;
   const int64_t r0 = (int64_t)blockIdx.x * 2 * NP;
-  const Sines<double, M> sn(sp, tid % Sh::TPP);
+  const Sines<double, M, Sh::Ept> sn(sp, tid % Sh::TPP);
   const int wv = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
   double *__restrict__ V = a.V;
   double *__restrict__ q = a.q;
@@ -1241,7 +1265,7 @@ __global__ __launch_bounds__((Shape<double, M>::NT)) void k_dst_x_be1(FhnArgs a,
       }
   }
   __syncthreads();
-  dst_pair<double, M>(sbuf + (tid / Sh::TPP) * PADM, tid % Sh::TPP, tw, sn);
+  dst_pair<double, M, Sh::Ept>(sbuf + (tid / Sh::TPP) * PADM, tid % Sh::TPP, tw, sn);
   // V and q after the transform (fetched ahead of it they would be held across it), a thread's
   // elements in two chunks whose loads are all issued before the chunk's first store (V and q
   // are read and written through the same pointers, so loads are not moved across stores)
@@ -1278,22 +1302,51 @@ __global__ __launch_bounds__((Shape<double, M>::NT)) void k_dst_x_be1(FhnArgs a,
 // ---------------------------------------------------------------- launchers
 //
 // x pass over `rows` contiguous rows (padded in/out unless stated)
+// Values per thread of an x pass: 4 where it is short (2D, or few rows), 16 for the long ones of 512 cells; a batch's
+// group always takes row_values, as its passes merged with other groups' do.
+template <int M, typename F>
+void with_row_values(int64_t rows, bool group, const F &f) {
+  if constexpr (M == 128 || M == 256) {
+    if (!group && rows * M <= (1 << 20)) return f(std::integral_constant<int, 4>());
+  }
+  if constexpr (M == 512) {
+    if (!group && rows > 100000) return f(std::integral_constant<int, 16>());
+  }
+  f(std::integral_constant<int, row_values(M)>());
+}
+
 template <typename T, int M>
 void pass_x(const T *in, bool in_plain, T *out, bool out_plain, int64_t rows, const C2<T> *tw, const T *sp,
-            hipStream_t st) {
-  using Sh = Shape<T, M>;
-  const dim3 g((unsigned)((rows + 2 * Sh::NP - 1) / (2 * Sh::NP)));
-  if (in_plain) k_dst_x<T, M, false, true><<<g, Sh::NT, 0, st>>>(in, out, rows, tw, sp);
-  else if (out_plain) k_dst_x<T, M, true, false><<<g, Sh::NT, 0, st>>>(in, out, rows, tw, sp);
-  else k_dst_x<T, M, true, true><<<g, Sh::NT, 0, st>>>(in, out, rows, tw, sp);
-  KFBI_HIP(hipGetLastError());
+            hipStream_t st, bool group = false) {
+  with_row_values<M>(rows, group, [&](auto e) {
+    constexpr int E = decltype(e)::value;
+    using Sh = XShape<T, M, E>;
+    const dim3 g((unsigned)((rows + 2 * Sh::NP - 1) / (2 * Sh::NP)));
+    if (in_plain) k_dst_x<T, M, false, true, E><<<g, Sh::NT, 0, st>>>(in, out, rows, tw, sp);
+    else if (out_plain) k_dst_x<T, M, true, false, E><<<g, Sh::NT, 0, st>>>(in, out, rows, tw, sp);
+    else k_dst_x<T, M, true, true, E><<<g, Sh::NT, 0, st>>>(in, out, rows, tw, sp);
+    KFBI_HIP(hipGetLastError());
+  });
+}
+
+// x pass over listed rows
+template <typename T, int M>
+void pass_x_rows(const T *in, T *out, const int32_t *list, int64_t n, const C2<T> *tw, const T *sp, hipStream_t st,
+                 bool group = false) {
+  if (n < 1) return;
+  with_row_values<M>(n, group, [&](auto e) {
+    constexpr int E = decltype(e)::value;
+    using Sh = XShape<T, M, E>;
+    k_dst_x_rows<T, M, E><<<(unsigned)((n + 2 * Sh::NP - 1) / (2 * Sh::NP)), Sh::NT, 0, st>>>(in, out, list, n, tw, sp);
+    KFBI_HIP(hipGetLastError());
+  });
 }
 
 // y pass over every plane, or over the nz planes listed
 template <typename T, int M>
 void pass_y(const T *in, T *out, int64_t P, int64_t cs, int ncomp, const uint64_t *mask_in, const uint64_t *mask_out,
             const C2<T> *tw, const T *sp, hipStream_t st, const int32_t *planes = nullptr, int nz = -1) {
-  using Sh = Shape<T, M>;
+  using Sh = YShape<T, M>;
   if (nz == 0) return;
   const dim3 g((Sh::N + 2 * Sh::NP - 1) / (2 * Sh::NP), planes ? nz : Sh::N, ncomp);
   k_dst_y<T, M><<<g, Sh::NT, 0, st>>>(in, out, P, cs, mask_in, mask_out, planes, tw, sp);
@@ -1306,7 +1359,7 @@ void launch_last(const T *in, T *a, int dim, int ncomp, int64_t P, int64_t cs, c
                  const C2<T> *tw, const T *sp, const ModeScale *msv, int nprob, int64_t pstride, hipStream_t st,
                  const PlaneBits *zin = nullptr, const PlaneBits *zout = nullptr, int form = 0,
                  const T *in2 = nullptr) {
-  using Sh = Shape<T, M>;
+  using Sh = LShape<T, M>;
   const int tx = ncomp == 2 ? Sh::NP : 2 * Sh::NP;
   const dim3 g((Sh::N + tx - 1) / tx, dim == 3 ? Sh::N : nprob, 1);
   // form 3: antisymmetric source (needs zout); form 4: the difference of the pair (no masks);
@@ -1319,7 +1372,7 @@ void launch_last(const T *in, T *a, int dim, int ncomp, int64_t P, int64_t cs, c
     throw std::invalid_argument("the combined z pass takes the coupled 3D pair, a second input and its plane mask");
   if (dim == 3) {
     if (form >= 3) {
-      if constexpr (StridedTile<T, M, Sh::NP, 2>::VEC) {
+      if constexpr (StridedTile<T, M, Sh::NP, 2, Sh>::VEC) {
         if (form == 3) k_dst_last<T, M, 2, 3, 3><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp, nullptr, 0, {}, *zout);
         else if (form == 4) k_dst_last<T, M, 2, 3, 4><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp);
         else k_dst_last<T, M, 2, 3, 5><<<g, Sh::NT, 0, st>>>(in, a, P, cs, ms, tw, sp, nullptr, 0, *zin, {}, in2);
@@ -1430,7 +1483,6 @@ void run_box(DevProblem &p, const T *src, bool src_plain, T *dst, bool dst_plain
 template <typename T, int M>
 void run_box_stencils(DevProblem &p, const T *src, hipStream_t st, bool skip_x = false, bool anti = false) {
   constexpr int N = M - 1;
-  using Sh = Shape<T, M>;
   PrecTables<T> &tb = p.tab<T>();
   T *A = tb.work;
   const C2<T> *tw = reinterpret_cast<const C2<T> *>(tb.tw);
@@ -1467,16 +1519,15 @@ void run_box_stencils(DevProblem &p, const T *src, hipStream_t st, bool skip_x =
   tic(p.t_dst_y_sparse);
   pass_y<T, M>(A, A, P, cs, p.ncomp, nullptr, p.mask_out, tw, sp, st, p.zlist_out, p.n_planes_out);
   toc(p.t_dst_y_sparse);
-  const unsigned gout = (unsigned)((p.n_rows_out + 2 * Sh::NP - 1) / (2 * Sh::NP));
   tic(p.t_dst_x_rows);
-  if (gout) k_dst_x_rows<T, M><<<gout, Sh::NT, 0, st>>>(A, A, p.rows_out, p.n_rows_out, tw, sp);
+  pass_x_rows<T, M>(A, A, p.rows_out, p.n_rows_out, tw, sp, st);
   KFBI_HIP(hipGetLastError());
   toc(p.t_dst_x_rows);
 }
 
 template <int M, int MODE>
 void launch_x_fhn(DevProblem &p, const FhnArgs &a, hipStream_t st) {
-  using Sh = Shape<double, M>;
+  using Sh = FShape<M>;
   if (p.ncomp != 2 || p.P != M) throw std::invalid_argument("bidomain x pass: coupled pair in the padded layout");
   const int64_t rows = p.dim == 3 ? p.N * p.N : p.N;
   const unsigned g = (unsigned)((rows + Sh::NP - 1) / Sh::NP);
@@ -1495,7 +1546,7 @@ void launch_x_fhn(DevProblem &p, const FhnArgs &a, hipStream_t st) {
 // negative of the first (k_dst_x_fe1, dst_last_tile with ZM = 3).
 template <int M>
 void launch_x_fe1(DevProblem &p, const FhnArgs &a, hipStream_t st) {
-  using Sh = Shape<double, M>;
+  using Sh = XShape<double, M>;
   if (p.ncomp != 2 || p.P != M || p.dim != 3) throw std::invalid_argument("antisymmetric x pass: coupled 3D pair");
   const int64_t rows = p.N * p.N;
   const unsigned g = (unsigned)((rows + 2 * Sh::NP - 1) / (2 * Sh::NP));
@@ -1527,7 +1578,7 @@ void run_bidomain_final(DevProblem &p, const FhnArgs &a, bool fuse_be, hipStream
     if (p.dim == 3 && fuse_be) {
       // only Phi_i - Phi_e is needed: the z pass stores it, and the inverse y and x passes (the
       // latter with the backward Euler update) run over that one field
-      using Sh = Shape<double, M>;
+      using Sh = FShape<M>;
       PrecTables<double> &tb = p.f64;
       double *A = tb.work;
       const C2<double> *tw = reinterpret_cast<const C2<double> *>(tb.tw);
@@ -1536,9 +1587,8 @@ void run_bidomain_final(DevProblem &p, const FhnArgs &a, bool fuse_be, hipStream
         // f + C psi with f = (g, -g) antisymmetric: the volume solve left g's x-y transform in
         // gbuf, so only C psi is transformed, on the rows and planes holding irregular nodes as
         // in the product, and the z pass adds the two as it loads
-        const unsigned gin = (unsigned)((p.n_rows_in + 2 * Sh::NP - 1) / (2 * Sh::NP));
         p.t_dst_x_rows.tic(p.profile, st);
-        if (gin) k_dst_x_rows<double, M><<<gin, Sh::NT, 0, st>>>(tb.rhs, A, p.rows_in, p.n_rows_in, tw, tb.sp);
+        pass_x_rows<double, M>(tb.rhs, A, p.rows_in, p.n_rows_in, tw, tb.sp, st);
         KFBI_HIP(hipGetLastError());
         p.t_dst_x_rows.toc(p.profile, st);
         p.t_dst_y_sparse.tic(p.profile, st);
@@ -1584,7 +1634,6 @@ void run_bidomain_final(DevProblem &p, const FhnArgs &a, bool fuse_be, hipStream
 // 46.3 us, y passes 51.7 -> 48.5 us, and two fields less per problem and precision.
 template <typename T, int M>
 void run_box_sparse(DevProblem &p, hipStream_t st) {
-  using Sh = Shape<T, M>;
   PrecTables<T> &tb = p.tab<T>();
   T *A = tb.work;
   const C2<T> *tw = reinterpret_cast<const C2<T> *>(tb.tw);
@@ -1592,10 +1641,8 @@ void run_box_sparse(DevProblem &p, hipStream_t st) {
   const int64_t P = p.P, cs = p.comp_stride;
   auto tic = [&](Timer &t) { t.tic(p.profile, st); };
   auto toc = [&](Timer &t) { t.toc(p.profile, st); };
-  const unsigned gin = (unsigned)((p.n_rows_in + 2 * Sh::NP - 1) / (2 * Sh::NP));
-  const unsigned gout = (unsigned)((p.n_rows_out + 2 * Sh::NP - 1) / (2 * Sh::NP));
   tic(p.t_dst_x_rows);
-  if (gin) k_dst_x_rows<T, M><<<gin, Sh::NT, 0, st>>>(tb.rhs, A, p.rows_in, p.n_rows_in, tw, sp);
+  pass_x_rows<T, M>(tb.rhs, A, p.rows_in, p.n_rows_in, tw, sp, st);
   KFBI_HIP(hipGetLastError());
   toc(p.t_dst_x_rows);
   tic(p.t_dst_y_sparse);
@@ -1610,22 +1657,20 @@ void run_box_sparse(DevProblem &p, hipStream_t st) {
   pass_y<T, M>(A, A, P, cs, p.ncomp, nullptr, p.mask_out, tw, sp, st, p.zlist_out, p.n_planes_out);
   toc(p.t_dst_y_sparse);
   tic(p.t_dst_x_rows);
-  if (gout) k_dst_x_rows<T, M><<<gout, Sh::NT, 0, st>>>(A, A, p.rows_out, p.n_rows_out, tw, sp);
+  pass_x_rows<T, M>(A, A, p.rows_out, p.n_rows_out, tw, sp, st);
   KFBI_HIP(hipGetLastError());
   toc(p.t_dst_x_rows);
 }
 
 // x pass over the rows of a set (all `rows` rows where it has no list), padded in and out
 template <typename T, int M>
-void pass_x_set(const T *in, T *out, const RowSet &set, int64_t rows, const C2<T> *tw, const T *sp, hipStream_t st) {
-  using Sh = Shape<T, M>;
+void pass_x_set(const T *in, T *out, const RowSet &set, int64_t rows, const C2<T> *tw, const T *sp, hipStream_t st,
+                bool group = false) {
   if (!set.list) {
-    pass_x<T, M>(in, false, out, false, rows, tw, sp, st);
+    pass_x<T, M>(in, false, out, false, rows, tw, sp, st, group);
     return;
   }
-  const unsigned g = (unsigned)((set.n + 2 * Sh::NP - 1) / (2 * Sh::NP));
-  if (g) k_dst_x_rows<T, M><<<g, Sh::NT, 0, st>>>(in, out, set.list, set.n, tw, sp);
-  KFBI_HIP(hipGetLastError());
+  pass_x_rows<T, M>(in, out, set.list, set.n, tw, sp, st, group);
 }
 
 // Grouped 2D box solve of G one-component problems of equal size, stored at stride cs in
@@ -1639,7 +1684,7 @@ void run_box_group(const MultiGroupDesc &d, bool direct, hipStream_t st) {
   const int64_t rows = (int64_t)d.G * N;
   if (d.cs != (int64_t)N * M) throw std::invalid_argument("group stride");
   if (direct) {
-    pass_x_set<T, M>(src, dst, d.in, rows, tw, sp, st);
+    pass_x_set<T, M>(src, dst, d.in, rows, tw, sp, st, true);
     LastAxis<T> l;
     l.in = l.out = dst;
     l.dim = 2;
@@ -1650,11 +1695,11 @@ void run_box_group(const MultiGroupDesc &d, bool direct, hipStream_t st) {
     l.bin = d.in.bits;
     l.bout = d.out.bits;
     last_axis_direct<T>(l, st);
-    pass_x_set<T, M>(dst, dst, d.out, rows, tw, sp, st);
+    pass_x_set<T, M>(dst, dst, d.out, rows, tw, sp, st, true);
   } else {
-    pass_x<T, M>(src, false, dst, false, rows, tw, sp, st);
+    pass_x<T, M>(src, false, dst, false, rows, tw, sp, st, true);
     launch_last<T, M>(dst, dst, 2, 1, M, d.cs, ModeParams{}, tw, sp, d.msv, d.G, d.cs, st);
-    pass_x<T, M>(dst, false, dst, false, rows, tw, sp, st);
+    pass_x<T, M>(dst, false, dst, false, rows, tw, sp, st, true);
   }
 }
 
@@ -1689,8 +1734,7 @@ void run_box_rows2d(DevProblem &p, const T *src, const RowSet &in, const RowSet 
 //
 // One launch per pass over several size groups: the workgroups of group k are the block range
 // [begin_k, begin_{k+1}) and run that group's tile at its own size M (a switch on the uniform
-// size).  The workgroup size BASE / 16 is the same at every M, and so is the LDS tile buffer
-// up to a few hundred bytes, so one shape serves all sizes.
+// size).  The workgroup is one wavefront at every M, and the LDS tile buffer as large as the largest M needs.
 
 template <typename T>
 struct MultiX {
@@ -1709,9 +1753,9 @@ struct MultiX {
 // largest tile buffer over the sizes 64..1024 (NP * PADM, in complex values)
 template <typename T>
 constexpr int multi_sbuf() {
-  return std::max({Shape<T, 64>::NP * Shape<T, 64>::PADM, Shape<T, 128>::NP * Shape<T, 128>::PADM,
-                   Shape<T, 256>::NP * Shape<T, 256>::PADM, Shape<T, 512>::NP * Shape<T, 512>::PADM,
-                   Shape<T, 1024>::NP * Shape<T, 1024>::PADM});
+  return std::max({XShape<T, 64>::NP * XShape<T, 64>::PADM, XShape<T, 128>::NP * XShape<T, 128>::PADM,
+                   XShape<T, 256>::NP * XShape<T, 256>::PADM, XShape<T, 512>::NP * XShape<T, 512>::PADM,
+                   XShape<T, 1024>::NP * XShape<T, 1024>::PADM});
 }
 
 template <typename T, typename Mp>
@@ -1724,8 +1768,8 @@ __device__ __forceinline__ int multi_group(const Mp &mp) {
 }
 
 template <typename T>
-__global__ __launch_bounds__((Shape<T, 64>::NT)) void k_dst_x_multi(MultiX<T> mp) {
-  static_assert(Shape<T, 64>::NT == Shape<T, 1024>::NT, "one workgroup size for every M");
+__global__ __launch_bounds__((XShape<T, 64>::NT)) void k_dst_x_multi(MultiX<T> mp) {
+  static_assert(XShape<T, 64>::NT == XShape<T, 1024>::NT, "one workgroup size for every M");
   __shared__ C2<T> sbuf[multi_sbuf<T>()];
   const int k = multi_group<T>(mp);
   const auto &g = mp.g[k];
@@ -1742,7 +1786,13 @@ __global__ __launch_bounds__((Shape<T, 64>::NT)) void k_dst_x_multi(MultiX<T> mp
 
 template <typename T>
 int tile_rows(int M) {   // rows per x-pass tile
-  return 2 * ((sizeof(T) == 8 ? 2048 : 4096) / M);
+  switch (M) {
+    case 64: return 2 * XShape<T, 64>::NP;
+    case 128: return 2 * XShape<T, 128>::NP;
+    case 256: return 2 * XShape<T, 256>::NP;
+    case 512: return 2 * XShape<T, 512>::NP;
+    default: return 2 * XShape<T, 1024>::NP;
+  }
 }
 
 }  // namespace
@@ -1786,7 +1836,7 @@ void box_solve_multi(const MultiGroupDesc *gd, int ng, hipStream_t st) {
     b2 += (int)((n2 + tr - 1) / tr);
   }
   x1.ng = x2.ng = ng;
-  constexpr int NT = Shape<T, 64>::NT;
+  constexpr int NT = XShape<T, 64>::NT;
   if (b1) k_dst_x_multi<T><<<b1, NT, 0, st>>>(x1);
   KFBI_HIP(hipGetLastError());
   last_axis_direct_multi<T>(gd, ng, st);
