@@ -361,7 +361,6 @@ __device__ __forceinline__ void dst_x_tile(const T *__restrict__ in, T *__restri
   constexpr int ROWS = 2 * NP;
   const int tid = threadIdx.x;
   const int64_t r0 = blk * ROWS;
-  const Sines<T, M, Sh::Ept> sn(sp, tid % Sh::TPP);
   if constexpr (M >= 64) {
     // one pencil pair per wave at a time; a lane moves whole complex values (two 8-byte row
     // elements per 16-byte LDS word, unit stride: no LDS bank conflicts)
@@ -381,27 +380,65 @@ __device__ __forceinline__ void dst_x_tile(const T *__restrict__ in, T *__restri
       if constexpr (LIST) return __builtin_amdgcn_readlane(held, 2 * pp + h);
       else return r0 + 2 * (wv + NWV * pp) + h;
     };
-    C2<T> v[PPW][KS];
+    if constexpr (M >= 128) {
+      // a lane loads x_n and x_{M-n} (n = 1 + lane + 64 k, element n - 1) and writes the pre-processed values
+      // (dst_pre): one trip through LDS, which bounds the pass with memory, instead of two: dense 256^3 FP64 scalar
+      // 54.4 -> 52.6 and 51.0 -> 46.7 us, 2D 1024 9.0 -> 8.2
+      constexpr int KC = KS / 2;
+      C2<T> va[PPW][KC], vb[PPW][KC];
+      T sk[KC];
 #pragma unroll
-    for (int pp = 0; pp < PPW; ++pp) {
-      const int64_t ia = r0 + 2 * (wv + NWV * pp);
-      const bool oka = ia < nrows, okb = ia + 1 < nrows;
-      const T *ra = in + row_of(pp, 0) * PI, *rb = in + row_of(pp, 1) * PI;
+      for (int k = 0; k < KC; ++k) sk[k] = sp[1 + lane + 64 * k];
 #pragma unroll
-      for (int k = 0; k < KS; ++k) {
-        const int n = lane + 64 * k;
-        v[pp][k] = {oka && n < N ? ra[n] : T(0), okb && n < N ? rb[n] : T(0)};
+      for (int pp = 0; pp < PPW; ++pp) {
+        const int64_t ia = r0 + 2 * (wv + NWV * pp);
+        const bool oka = ia < nrows, okb = ia + 1 < nrows;
+        const T *ra = in + row_of(pp, 0) * PI, *rb = in + row_of(pp, 1) * PI;
+#pragma unroll
+        for (int k = 0; k < KC; ++k) {
+          const int e = lane + 64 * k, f = M - 2 - e;
+          va[pp][k] = {oka ? ra[e] : T(0), okb ? rb[e] : T(0)};
+          vb[pp][k] = {oka ? ra[f] : T(0), okb ? rb[f] : T(0)};
+        }
       }
+#pragma unroll
+      for (int pp = 0; pp < PPW; ++pp) {
+        C2<T> *q = sbuf + (wv + NWV * pp) * PADM;
+#pragma unroll
+        for (int k = 0; k < KC; ++k) {
+          const int n = 1 + lane + 64 * k;
+          const C2<T> sum = sk[k] * (va[pp][k] + vb[pp][k]), dif = (T)0.5 * (va[pp][k] - vb[pp][k]);
+          q[pad(n)] = sum + dif;
+          q[pad(M - n)] = sum - dif;
+        }
+        if (lane == 0) q[pad(0)] = {T(0), T(0)};
+      }
+      __syncthreads();
+      dst_rest<T, M, Sh::Ept>(sbuf + (tid / Sh::TPP) * PADM, tid % Sh::TPP, tw);
+    } else {
+      const Sines<T, M, Sh::Ept> sn(sp, tid % Sh::TPP);
+      C2<T> v[PPW][KS];
+#pragma unroll
+      for (int pp = 0; pp < PPW; ++pp) {
+        const int64_t ia = r0 + 2 * (wv + NWV * pp);
+        const bool oka = ia < nrows, okb = ia + 1 < nrows;
+        const T *ra = in + row_of(pp, 0) * PI, *rb = in + row_of(pp, 1) * PI;
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+          const int n = lane + 64 * k;
+          v[pp][k] = {oka && n < N ? ra[n] : T(0), okb && n < N ? rb[n] : T(0)};
+        }
+      }
+#pragma unroll
+      for (int pp = 0; pp < PPW; ++pp)
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+          const int n = lane + 64 * k;
+          if (n < N) sbuf[(wv + NWV * pp) * PADM + pad(n + 1)] = v[pp][k];
+        }
+      __syncthreads();
+      dst_pair<T, M, Sh::Ept>(sbuf + (tid / Sh::TPP) * PADM, tid % Sh::TPP, tw, sn);
     }
-#pragma unroll
-    for (int pp = 0; pp < PPW; ++pp)
-#pragma unroll
-      for (int k = 0; k < KS; ++k) {
-        const int n = lane + 64 * k;
-        if (n < N) sbuf[(wv + NWV * pp) * PADM + pad(n + 1)] = v[pp][k];
-      }
-    __syncthreads();
-    dst_pair<T, M, Sh::Ept>(sbuf + (tid / Sh::TPP) * PADM, tid % Sh::TPP, tw, sn);
 #pragma unroll
     for (int pp = 0; pp < PPW; ++pp) {
       const int rr = wv + NWV * pp;
@@ -419,6 +456,7 @@ __device__ __forceinline__ void dst_x_tile(const T *__restrict__ in, T *__restri
       }
     }
   } else {
+    const Sines<T, M, Sh::Ept> sn(sp, tid % Sh::TPP);
     if constexpr (PIN) {
       constexpr int VPR = M / VW, NV = ROWS * VPR, PER = (NV + NT - 1) / NT;
       V16<T> reg[PER];
@@ -785,10 +823,20 @@ __global__ __launch_bounds__((YShape<T, M>::NT)) void k_dst_y(const T *__restric
   const int x0 = blockIdx.x * 2 * Sh::NP, z = planes ? planes[blockIdx.y] : (int)blockIdx.y, c = blockIdx.z;
   const int64_t off = c * comp_stride + (int64_t)z * Sh::N * P;
   constexpr int NW = (Sh::N + 63) / 64;
-  const Sines<T, M, Sh::Ept> sn(sp, tid % Sh::TPP);
-  Tl::load(in + off, P, 0, x0, sbuf, tid, BitRowsMem<NW>(mask_in ? mask_in + (int64_t)z * 16 : nullptr));
-  __syncthreads();
-  dst_pair<T, M, Sh::Ept>(sbuf + (tid / Sh::TPP) * Sh::PADM, tid % Sh::TPP, tw, sn);
+  const BitRowsMem<NW> rin(mask_in ? mask_in + (int64_t)z * 16 : nullptr);
+  C2<T> *mine = sbuf + (tid / Sh::TPP) * Sh::PADM;
+  // pre-processing as the tile is loaded saves a trip through LDS (128^3 FP64 13.3 -> 12.5 us), but its registers
+  // cost a workgroup in flight at 256 (58.8 -> 70.3) and below 64 there is no vector path
+  if constexpr (M == 64 || M == 128) {
+    Tl::load_pre(in + off, P, 0, x0, sbuf, tid, sp, rin);
+    __syncthreads();
+    dst_rest<T, M, Sh::Ept>(mine, tid % Sh::TPP, tw);
+  } else {
+    const Sines<T, M, Sh::Ept> sn(sp, tid % Sh::TPP);
+    Tl::load(in + off, P, 0, x0, sbuf, tid, rin);
+    __syncthreads();
+    dst_pair<T, M, Sh::Ept>(mine, tid % Sh::TPP, tw, sn);
+  }
   Tl::store(out + off, P, 0, x0, sbuf, tid, BitRowsMem<NW>(mask_out ? mask_out + (int64_t)z * 16 : nullptr));
 }
 
