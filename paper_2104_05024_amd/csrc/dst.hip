@@ -350,12 +350,13 @@ struct alignas(16) V16 {
 // DST along contiguous rows: pairs of consecutive rows of the flattened [comp][..][x] list.
 // PIN / POUT: input / output in the padded layout (row pitch M) instead of pitch N.
 // One tile (2 NP rows, tile index blk) in the LDS buffer sbuf of NP * PADM values.
-// LIST (M >= 64): row i of the pass is row list[i] of both fields (row i itself where list is null).
+// LIST (M >= 64): row i of the pass is row list[i] of both fields (row i itself where list is null); cin / cout
+// (M >= 128): M / 64 words per listed row, the columns that may be non-zero on input / that are wanted (null: all).
 template <typename T, int M, bool PIN, bool POUT, bool LIST = false, int E = row_values(M)>
 __device__ __forceinline__ void dst_x_tile(const T *__restrict__ in, T *__restrict__ out, int64_t nrows,
-                                           const int32_t *__restrict__ list,
-                                           const C2<T> *__restrict__ tw, const T *__restrict__ sp, C2<T> *sbuf,
-                                           int64_t blk) {
+                                           const int32_t *__restrict__ list, const uint64_t *__restrict__ cin,
+                                           const uint64_t *__restrict__ cout, const C2<T> *__restrict__ tw,
+                                           const T *__restrict__ sp, C2<T> *sbuf, int64_t blk) {
   using Sh = XShape<T, M, E>;
   constexpr int N = Sh::N, NP = Sh::NP, NT = Sh::NT, PADM = Sh::PADM, VW = 16 / sizeof(T);
   constexpr int ROWS = 2 * NP;
@@ -380,6 +381,13 @@ __device__ __forceinline__ void dst_x_tile(const T *__restrict__ in, T *__restri
       if constexpr (LIST) return __builtin_amdgcn_readlane(held, 2 * pp + h);
       else return r0 + 2 * (wv + NWV * pp) + h;
     };
+    // whether column e of listed row i is in a set
+    auto has = [&](const uint64_t *set, int64_t i, bool ok, int e) -> bool {
+      if constexpr (LIST && M >= 128) {
+        if (set && ok) return (set[i * KS + (e >> 6)] >> (e & 63)) & 1;
+      }
+      return ok;
+    };
     if constexpr (M >= 128) {
       // a lane loads x_n and x_{M-n} (n = 1 + lane + 64 k, element n - 1) and writes the pre-processed values
       // (dst_pre): one trip through LDS, which bounds the pass with memory, instead of two: dense 256^3 FP64 scalar
@@ -397,8 +405,8 @@ __device__ __forceinline__ void dst_x_tile(const T *__restrict__ in, T *__restri
 #pragma unroll
         for (int k = 0; k < KC; ++k) {
           const int e = lane + 64 * k, f = M - 2 - e;
-          va[pp][k] = {oka ? ra[e] : T(0), okb ? rb[e] : T(0)};
-          vb[pp][k] = {oka ? ra[f] : T(0), okb ? rb[f] : T(0)};
+          va[pp][k] = {has(cin, ia, oka, e) ? ra[e] : T(0), has(cin, ia + 1, okb, e) ? rb[e] : T(0)};
+          vb[pp][k] = {has(cin, ia, oka, f) ? ra[f] : T(0), has(cin, ia + 1, okb, f) ? rb[f] : T(0)};
         }
       }
 #pragma unroll
@@ -450,8 +458,8 @@ __device__ __forceinline__ void dst_x_tile(const T *__restrict__ in, T *__restri
         const int n = lane + 64 * k;   // n = N: the pad column of the padded layout, zero
         if (POUT || n < N) {
           const C2<T> c = n < N ? sbuf[rr * PADM + pad(n + 1)] : C2<T>{T(0), T(0)};
-          if (oka) oa[n] = c.x;
-          if (okb) ob[n] = c.y;
+          if (has(cout, ia, oka, n)) oa[n] = c.x;
+          if (has(cout, ia + 1, okb, n)) ob[n] = c.y;
         }
       }
     }
@@ -550,7 +558,7 @@ __global__ __launch_bounds__((XShape<T, M, E>::NT)) void k_dst_x(const T *__rest
                                                              const T *__restrict__ sp) {
   using Sh = XShape<T, M, E>;
   __shared__ C2<T> sbuf[Sh::NP * Sh::PADM];
-  dst_x_tile<T, M, PIN, POUT, false, E>(in, out, nrows, nullptr, tw, sp, sbuf, blockIdx.x);
+  dst_x_tile<T, M, PIN, POUT, false, E>(in, out, nrows, nullptr, nullptr, nullptr, tw, sp, sbuf, blockIdx.x);
 }
 
 // Row predicates of the strided tile mover: every row; rows in a bit set read once from memory
@@ -974,6 +982,8 @@ __global__ __launch_bounds__((LShape<T, M>::NT)) void k_dst_last(const T *__rest
 template <typename T, int M, int E>
 __global__ __launch_bounds__((XShape<T, M, E>::NT)) void k_dst_x_rows(const T *__restrict__ in, T *__restrict__ out,
                                                                     const int32_t *__restrict__ rows, int64_t nlist,
+                                                                    const uint64_t *__restrict__ cin,
+                                                                    const uint64_t *__restrict__ cout,
                                                                     const C2<T> *__restrict__ tw,
                                                                     const T *__restrict__ sp) {
   using Sh = XShape<T, M, E>;
@@ -981,7 +991,7 @@ __global__ __launch_bounds__((XShape<T, M, E>::NT)) void k_dst_x_rows(const T *_
   constexpr int ROWS = 2 * NP, VPR = M / VW, NV = ROWS * VPR, PER = (NV + NT - 1) / NT;
   __shared__ C2<T> sbuf[NP * PADM];
   if constexpr (M >= 64) {
-    dst_x_tile<T, M, true, true, true, E>(in, out, nlist, rows, tw, sp, sbuf, blockIdx.x);
+    dst_x_tile<T, M, true, true, true, E>(in, out, nlist, rows, cin, cout, tw, sp, sbuf, blockIdx.x);
   } else {
     const int tid = threadIdx.x;
     const int64_t r0 = (int64_t)blockIdx.x * ROWS;
@@ -1377,15 +1387,17 @@ void pass_x(const T *in, bool in_plain, T *out, bool out_plain, int64_t rows, co
   });
 }
 
-// x pass over listed rows
+// x pass over the listed rows of a set.  last: the pass that ends a solve, of which only the set's columns are wanted;
+// else the one that begins it, whose input is zero outside them.
 template <typename T, int M>
-void pass_x_rows(const T *in, T *out, const int32_t *list, int64_t n, const C2<T> *tw, const T *sp, hipStream_t st,
+void pass_x_rows(const T *in, T *out, const RowSet &set, bool last, const C2<T> *tw, const T *sp, hipStream_t st,
                  bool group = false) {
-  if (n < 1) return;
-  with_row_values<M>(n, group, [&](auto e) {
+  if (set.n < 1) return;
+  with_row_values<M>(set.n, group, [&](auto e) {
     constexpr int E = decltype(e)::value;
     using Sh = XShape<T, M, E>;
-    k_dst_x_rows<T, M, E><<<(unsigned)((n + 2 * Sh::NP - 1) / (2 * Sh::NP)), Sh::NT, 0, st>>>(in, out, list, n, tw, sp);
+    k_dst_x_rows<T, M, E><<<(unsigned)((set.n + 2 * Sh::NP - 1) / (2 * Sh::NP)), Sh::NT, 0, st>>>(
+        in, out, set.list, set.n, last ? nullptr : set.cols, last ? set.cols : nullptr, tw, sp);
     KFBI_HIP(hipGetLastError());
   });
 }
@@ -1568,7 +1580,7 @@ void run_box_stencils(DevProblem &p, const T *src, hipStream_t st, bool skip_x =
   pass_y<T, M>(A, A, P, cs, p.ncomp, nullptr, p.mask_out, tw, sp, st, p.zlist_out, p.n_planes_out);
   toc(p.t_dst_y_sparse);
   tic(p.t_dst_x_rows);
-  pass_x_rows<T, M>(A, A, p.rows_out, p.n_rows_out, tw, sp, st);
+  pass_x_rows<T, M>(A, A, p.set_out(), true, tw, sp, st);
   KFBI_HIP(hipGetLastError());
   toc(p.t_dst_x_rows);
 }
@@ -1636,7 +1648,7 @@ void run_bidomain_final(DevProblem &p, const FhnArgs &a, bool fuse_be, hipStream
         // gbuf, so only C psi is transformed, on the rows and planes holding irregular nodes as
         // in the product, and the z pass adds the two as it loads
         p.t_dst_x_rows.tic(p.profile, st);
-        pass_x_rows<double, M>(tb.rhs, A, p.rows_in, p.n_rows_in, tw, tb.sp, st);
+        pass_x_rows<double, M>(tb.rhs, A, p.set_in(), false, tw, tb.sp, st);
         KFBI_HIP(hipGetLastError());
         p.t_dst_x_rows.toc(p.profile, st);
         p.t_dst_y_sparse.tic(p.profile, st);
@@ -1690,7 +1702,7 @@ void run_box_sparse(DevProblem &p, hipStream_t st) {
   auto tic = [&](Timer &t) { t.tic(p.profile, st); };
   auto toc = [&](Timer &t) { t.toc(p.profile, st); };
   tic(p.t_dst_x_rows);
-  pass_x_rows<T, M>(tb.rhs, A, p.rows_in, p.n_rows_in, tw, sp, st);
+  pass_x_rows<T, M>(tb.rhs, A, p.set_in(), false, tw, sp, st);
   KFBI_HIP(hipGetLastError());
   toc(p.t_dst_x_rows);
   tic(p.t_dst_y_sparse);
@@ -1705,20 +1717,20 @@ void run_box_sparse(DevProblem &p, hipStream_t st) {
   pass_y<T, M>(A, A, P, cs, p.ncomp, nullptr, p.mask_out, tw, sp, st, p.zlist_out, p.n_planes_out);
   toc(p.t_dst_y_sparse);
   tic(p.t_dst_x_rows);
-  pass_x_rows<T, M>(A, A, p.rows_out, p.n_rows_out, tw, sp, st);
+  pass_x_rows<T, M>(A, A, p.set_out(), true, tw, sp, st);
   KFBI_HIP(hipGetLastError());
   toc(p.t_dst_x_rows);
 }
 
 // x pass over the rows of a set (all `rows` rows where it has no list), padded in and out
 template <typename T, int M>
-void pass_x_set(const T *in, T *out, const RowSet &set, int64_t rows, const C2<T> *tw, const T *sp, hipStream_t st,
+void pass_x_set(const T *in, T *out, const RowSet &set, bool last, int64_t rows, const C2<T> *tw, const T *sp, hipStream_t st,
                 bool group = false) {
   if (!set.list) {
     pass_x<T, M>(in, false, out, false, rows, tw, sp, st, group);
     return;
   }
-  pass_x_rows<T, M>(in, out, set.list, set.n, tw, sp, st, group);
+  pass_x_rows<T, M>(in, out, set, last, tw, sp, st, group);
 }
 
 // Grouped 2D box solve of G one-component problems of equal size, stored at stride cs in
@@ -1732,7 +1744,7 @@ void run_box_group(const MultiGroupDesc &d, bool direct, hipStream_t st) {
   const int64_t rows = (int64_t)d.G * N;
   if (d.cs != (int64_t)N * M) throw std::invalid_argument("group stride");
   if (direct) {
-    pass_x_set<T, M>(src, dst, d.in, rows, tw, sp, st, true);
+    pass_x_set<T, M>(src, dst, d.in, false, rows, tw, sp, st, true);
     LastAxis<T> l;
     l.in = l.out = dst;
     l.dim = 2;
@@ -1743,7 +1755,7 @@ void run_box_group(const MultiGroupDesc &d, bool direct, hipStream_t st) {
     l.bin = d.in.bits;
     l.bout = d.out.bits;
     last_axis_direct<T>(l, st);
-    pass_x_set<T, M>(dst, dst, d.out, rows, tw, sp, st, true);
+    pass_x_set<T, M>(dst, dst, d.out, true, rows, tw, sp, st, true);
   } else {
     pass_x<T, M>(src, false, dst, false, rows, tw, sp, st, true);
     launch_last<T, M>(dst, dst, 2, 1, M, d.cs, ModeParams{}, tw, sp, d.msv, d.G, d.cs, st);
@@ -1759,7 +1771,7 @@ void run_box_rows2d(DevProblem &p, const T *src, const RowSet &in, const RowSet 
   const C2<T> *tw = reinterpret_cast<const C2<T> *>(tb.tw);
   const int64_t rows = (int64_t)p.ncomp * (M - 1);
   p.t_dst_x.tic(p.profile, st);
-  pass_x_set<T, M>(src, tb.work, in, rows, tw, tb.sp, st);
+  pass_x_set<T, M>(src, tb.work, in, false, rows, tw, tb.sp, st);
   p.t_dst_x.toc(p.profile, st);
   p.t_dst_last.tic(p.profile, st);
   LastAxis<T> l;
@@ -1774,7 +1786,7 @@ void run_box_rows2d(DevProblem &p, const T *src, const RowSet &in, const RowSet 
   last_axis_direct<T>(l, st);
   p.t_dst_last.toc(p.profile, st);
   p.t_dst_x.tic(p.profile, st);
-  pass_x_set<T, M>(tb.work, tb.work, out, rows, tw, tb.sp, st);
+  pass_x_set<T, M>(tb.work, tb.work, out, true, rows, tw, tb.sp, st);
   p.t_dst_x.toc(p.profile, st);
 }
 
@@ -1825,7 +1837,8 @@ __global__ __launch_bounds__((XShape<T, 64>::NT)) void k_dst_x_multi(MultiX<T> m
   switch (g.M) {
 #define KFBI_MULTI_ROWS(MM)                                                                       \
     case MM:                                                                                      \
-      dst_x_tile<T, MM, true, true, true>(g.in, g.out, g.rows, g.list, g.tw, g.sp, sbuf, b);      \
+      dst_x_tile<T, MM, true, true, true>(g.in, g.out, g.rows, g.list, nullptr, nullptr, g.tw, g.sp, \
+                                          sbuf, b);                                               \
       break;
     KFBI_MULTI_ROWS(64) KFBI_MULTI_ROWS(128) KFBI_MULTI_ROWS(256) KFBI_MULTI_ROWS(512) KFBI_MULTI_ROWS(1024)
 #undef KFBI_MULTI_ROWS

@@ -472,6 +472,22 @@ void upload_tables(DevProblem &p) {
     p.n_rows_out = (int64_t)rout.size();
     p.rows_in = dupload(rin);
     p.rows_out = dupload(rout);
+    auto columns = [&](const std::vector<int32_t> &list, const std::vector<int64_t> &nodes) -> uint64_t * {
+      if (d != 3 || p.Mfft < 256) return nullptr;
+      const size_t KS = (size_t)p.Mfft / 64;
+      std::vector<int64_t> at((size_t)rows, -1);   // place of each row of one component in the list
+      const size_t per = list.size() / (size_t)t.ncomp;
+      for (size_t i = 0; i < per; ++i) at[(size_t)list[i]] = (int64_t)i;
+      std::vector<uint64_t> bits(list.size() * KS, 0);
+      for (int64_t lin : nodes) {
+        const int64_t x = lin % N, i = at[(size_t)(lin / N)];
+        for (int c = 0; c < t.ncomp; ++c)
+          bits[((size_t)c * per + (size_t)i) * KS + (size_t)(x >> 6)] |= uint64_t(1) << (x & 63);
+      }
+      return dupload(bits);
+    };
+    p.cols_in = columns(rin, t.irregular);
+    p.cols_out = columns(rout, t.st_lin);
     std::vector<uint64_t> bin((size_t)planes * 16, 0), bout((size_t)planes * 16, 0);
     for (int64_t r = 0; r < rows; ++r) {
       const int64_t z = r / N, y = r % N;
@@ -530,7 +546,7 @@ void free_tables(DevProblem &p) {
     *q = nullptr;
   }
   p.itab.n_slots = 0;
-  uint64_t **bp[] = {&p.mask_in, &p.mask_out};
+  uint64_t **bp[] = {&p.mask_in, &p.mask_out, &p.cols_in, &p.cols_out};
   for (uint64_t **q : bp) {
     if (*q) (void)hipFree(*q);
     *q = nullptr;
