@@ -38,6 +38,7 @@ template <>
 inline float *Group::work<float>() const { return work32; }
 
 struct Batch {
+  int64_t longest = 0;                         // entries of the longest density
   static constexpr int kMaxRestart = 64;
   int np = 0;
   std::vector<std::unique_ptr<DevProblem>> probs;
@@ -54,7 +55,7 @@ struct Batch {
   double *V = nullptr, *vin = nullptr, *w = nullptr, *r = nullptr, *d = nullptr, *t = nullptr, *gp = nullptr;
   double *x = nullptr, *dx = nullptr;
   double *hcols = nullptr, *hhost = nullptr, *ydev = nullptr, *sdev = nullptr, *nrm = nullptr;
-  int *jdev = nullptr, *jhost = nullptr;
+  int *jdev = nullptr;
   int *seqdev = nullptr, *seqhost = nullptr;   // step counter polled by the host (as the solver's)
   int seq_next = 0;
   void host_wait(hipStream_t st);

@@ -9,6 +9,7 @@
 #include <stdexcept>
 #include <vector>
 
+#include "arnoldi.h"
 #include "solver.h"
 
 namespace kfbi {
@@ -158,10 +159,9 @@ __global__ __launch_bounds__(kB) void k_normalize(double *V, int64_t ldv, const 
   if (vnext) vnext[i] = v;
 }
 
-// j <- j + 1 (when given), and the step counter: seq <- seq + 1, also stored to the host's copy
-__global__ void k_inc_j(int *j, int *seq, int *seq_host) {
+// the step counter: seq <- seq + 1, also stored to the host's copy
+__global__ void k_count(int *seq, int *seq_host) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
-    if (j) *j += 1;
     const int s = *seq + 1;
     *seq = s;
     __threadfence_system();
@@ -189,90 +189,24 @@ __global__ __launch_bounds__(kB) void k_finish_host(const double *__restrict__ p
   }
 }
 
-// The orthogonalisation of one Arnoldi step for short vectors (n <= 1024 E), by one workgroup: both
-// classical Gram-Schmidt passes of w against V_0..V_j, the norm, V_{j+1} = w / ||w|| (also into vnext),
-// and the Hessenberg column straight into pinned host memory ([pass][kMaxRestart + 2], then
-// ||w||^2).  With seq it also ends the captured step: j <- j + 1 and the step counter.
+// The orthogonalisation of one Arnoldi step for short vectors (n <= 1024 E), by one workgroup
+// (orthogonalise_block), and the Hessenberg column straight into pinned host memory
+// ([pass][kMaxRestart + 2], then ||w||^2).  With seq it also ends the captured step: j <- j + 1 and the step counter.
 // Seven launches of 2-4 us each (and the gaps between them) become one: 8.7 us instead of 20 for the
-// 256 densities of a 128^2 pair, 18.0 instead of 27 for the 4,098 of a 64^3 one.  Bound by latency, then
-// by what one workgroup reads (the basis four times): at 10 basis vectors and about 5,000
-// entries it meets the many-block kernels.  With few vectors several wavefronts share one; only one
+// 256 densities of a 128^2 pair, 18.0 instead of 27 for the 4,098 of a 64^3 one.  At 10 basis vectors and about
+// 5,000 entries it meets the many-block kernels.  With few vectors several wavefronts share one; only one
 // wavefront stores to the host and fences, since a system fence writes back the L2 (10.5 us with all).
-constexpr int kSmallThreads = 1024, kSmallMax = 5 * kSmallThreads;
 template <int E>
 __global__ __launch_bounds__(kSmallThreads) void k_orthogonalise_small(double *V, const double *w_in, int64_t n,
                                                                        int *jdev, int jh, double *vnext,
                                                                        double *__restrict__ host, int *seq,
                                                                        int *seq_host) {
-  constexpr int NT = kSmallThreads, NW = NT / 64, HS = Solver::kMaxRestart + 2;
-  __shared__ double ws[E * NT];
-  __shared__ double hp[HS + NW];   // partial dots: P parts of each of the K vectors
-  __shared__ double hcol[2][HS];
-  __shared__ double red[NW];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int HS = Solver::kMaxRestart + 2;
+  static_assert(HS == kSmallColumn);
+  __shared__ double hcol[2][kSmallColumn];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int j = jdev ? *jdev : jh, K = j + 1;
-  double w[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int i = tid + NT * e;
-    w[e] = i < n ? w_in[i] : 0.0;
-    ws[i] = w[e];
-  }
-  const int P = K < NW ? NW / K : 1;   // wavefronts sharing one vector
-  for (int pass = 0; pass < 2; ++pass) {
-    __syncthreads();
-    for (int t = wave; t < K * P; t += NW) {
-      const int k = t / P, part = t - k * P;
-      const double *v = V + (int64_t)k * n;
-      double acc = 0;
-#pragma unroll 16
-      for (int i = lane + 64 * part; i < n; i += 64 * P) acc += v[i] * ws[i];
-      for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-      if (lane == 0) hp[t] = acc;
-    }
-    __syncthreads();
-    if (tid < K) {
-      double h = hp[tid * P];
-      for (int part = 1; part < P; ++part) h += hp[tid * P + part];
-      hcol[pass][tid] = h;
-    }
-    __syncthreads();
-    double acc[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) acc[e] = 0;
-#pragma unroll 4
-    for (int k = 0; k < K; ++k) {
-      const double h = hcol[pass][k];
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const int i = tid + NT * e;
-        acc[e] += i < n ? h * V[(int64_t)k * n + i] : 0.0;
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      w[e] -= acc[e];
-      if (pass == 0) ws[tid + NT * e] = w[e];
-    }
-  }
-  double sq = 0;
-#pragma unroll
-  for (int e = 0; e < E; ++e) sq += w[e] * w[e];
-  for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
-  if (lane == 0) red[wave] = sq;
-  __syncthreads();
-  double nrm2 = 0;
-#pragma unroll
-  for (int k = 0; k < NW; ++k) nrm2 += red[k];
-  const double sc = nrm2 > 0 ? 1.0 / sqrt(nrm2) : 0.0;
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int i = tid + NT * e;
-    if (i < n) {
-      V[(int64_t)K * n + i] = w[e] * sc;
-      if (vnext) vnext[i] = w[e] * sc;
-    }
-  }
+  const double nrm2 = orthogonalise_block<E>(V, n, w_in, n, K, vnext, hcol);
   if (wave > 0) return;   // one wavefront stores and fences: a system fence writes back the L2
   for (int k = lane; k < K; k += 64) {
     host[k] = hcol[0][k];
@@ -516,7 +450,8 @@ void Solver::finish_host(int K, hipStream_t st) {
 }
 
 // Both Gram-Schmidt passes of w against V_0..V_j, the norm and V_{j+1} (also into vnext), the Hessenberg column
-// on its way to hhost.  j from device memory when jd is given (the captured step).
+// in hdev.  j from device memory when jd is given (the captured step, which k_end_step ends: 4.5 us instead of the
+// 11 of a copy and a counter kernel); otherwise the column is also on its way to hhost.
 void Solver::orthogonalise(double *w, const int *jd, int j, int m, double *vnext, hipStream_t st) {
   const int K = jd ? m : j + 1;
   for (int pass = 0; pass < 2; ++pass) {
@@ -526,7 +461,7 @@ void Solver::orthogonalise(double *w, const int *jd, int j, int m, double *vnext
   }
   k_normalize<<<nblk(L), kB, 0, st>>>(V, L, w, npart, (int)nblk(L), hdev + 2 * (kMaxRestart + 2), jd, j, vnext, L);
   KFBI_HIP(hipGetLastError());
-  KFBI_HIP(hipMemcpyAsync(hhost, hdev, 3 * (kMaxRestart + 2) * sizeof(double), hipMemcpyDeviceToHost, st));
+  if (!jd) KFBI_HIP(hipMemcpyAsync(hhost, hdev, 3 * (kMaxRestart + 2) * sizeof(double), hipMemcpyDeviceToHost, st));
 }
 
 // The same for short vectors in one launch; step: also the end of the captured step.
@@ -554,12 +489,12 @@ void Solver::arnoldi_step(DevProblem &p, int prec, int m, hipStream_t st) {
     return;
   }
   orthogonalise(wv, jdev, 0, m, vin, st);
-  k_inc_j<<<1, 1, 0, st>>>(jdev, seqdev, seqhost);
+  k_end_step<<<1, 64, 0, st>>>(hdev, hhost, kMaxRestart + 2, 1, jdev, seqdev, seqhost);
   KFBI_HIP(hipGetLastError());
 }
 
 void Solver::host_wait(hipStream_t st) {
-  k_inc_j<<<1, 1, 0, st>>>(nullptr, seqdev, seqhost);
+  k_count<<<1, 1, 0, st>>>(seqdev, seqhost);
   KFBI_HIP(hipGetLastError());
   wait_step(st);
 }
