@@ -88,6 +88,9 @@ struct InterfaceTables {
   int64_t n_slots = 0;                               // arms of the irregular nodes, padded to 64s
   int32_t *arm_idx = nullptr, *arm_head = nullptr;   // density points [K][slot]; (position, arms of the node) [slot]
   double *arm_w = nullptr;                           // [comp][K][slot]
+  // for the row pass that forms the correction itself: the listed row of each slot, the first slot of each listed
+  // row of one component (and the end)
+  int32_t *arm_row = nullptr, *row_slot = nullptr;
   int32_t *st_pos = nullptr, *q_idx = nullptr;       // grid and density points of the nodes [M][S], [M][Kn]
   double *st_nw = nullptr, *q_w = nullptr;           // their weights [comp][M][S], [comp][M][Kn]
 };
@@ -195,8 +198,8 @@ void box_solve(DevProblem &p, const T *src, bool src_plain, T *dst, bool dst_pla
 
 // Box solve of the matrix-vector product: rhs (padded, sparse) -> work (padded); only the
 // extrapolation-stencil values of work are meaningful afterwards.
-template <typename T>
-void box_solve_matvec(DevProblem &p, hipStream_t st);
+template <typename T, typename TP>
+void box_solve_matvec(DevProblem &p, const TP *psi, hipStream_t st);
 
 // Box solve of src (padded) into work when only the extrapolation-stencil values of the result
 // are read afterwards (identical there to box_solve).

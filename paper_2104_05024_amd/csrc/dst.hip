@@ -1040,6 +1040,90 @@ __global__ __launch_bounds__((XShape<T, M, E>::NT)) void k_dst_x_rows(const T *_
   }
 }
 
+// The first row pass of a product with the correction formed in it (M >= 64): the listed rows hold zeros but for
+// the irregular nodes' values, each the sum of its arms' terms (arm slots are sorted by node, so a tile's slots are
+// one range per component; the arms of a node lie within 64 slots and their first adds up the others', as where the
+// correction is a launch of its own).  The field of corrections is neither written nor read, and a launch goes.
+// Bound by the arms' tables (240 bytes an arm of a coupled 3D pair) and LDS.  Correction and row pass / fused: coupled
+// 256^3 shell FP64 product 219.3 -> 212.5 us, 2D star 128 22.6 -> 17.2, coupled 2D 512 26.2 -> 25.0; alike at 128^3.
+template <typename T, typename TP, int M, int E, int D, int K>
+__global__ __launch_bounds__(64) void k_dst_x_correct(InterfaceTables t, const TP *__restrict__ psi, int64_t nd,
+                                                      T *__restrict__ out, const int32_t *__restrict__ rows, int per,
+                                                      int ncomp, const C2<T> *__restrict__ tw,
+                                                      const T *__restrict__ sp) {
+  using Sh = XShape<T, M, E>;
+  constexpr int N = Sh::N, NP = Sh::NP, PADM = Sh::PADM, ROWS = 2 * NP;
+  static_assert(ROWS <= 64, "a lane per row of the tile");
+  __shared__ C2<T> sbuf[NP * PADM];
+  const int lane = threadIdx.x, r0 = blockIdx.x * ROWS, nrows = per * ncomp;
+  const int32_t held = lane < ROWS && r0 + lane < nrows ? rows[r0 + lane] : 0;
+  for (int i = lane; i < NP * PADM; i += 64) sbuf[i] = {T(0), T(0)};
+  const Sines<T, M, E> sn(sp, lane % Sh::TPP);
+  __syncthreads();
+  const int64_t ns = t.n_slots;
+  for (int c = 0; c < ncomp; ++c) {
+    const int lo = max(r0 - c * per, 0), hi = min(r0 + ROWS - c * per, per);
+    if (lo >= hi) continue;
+    const int s0 = t.row_slot[lo], s1 = t.row_slot[hi];
+    const double *w = t.arm_w + (int64_t)c * K * ns;
+    const TP *ps = psi + c * nd;
+    // U groups of 64 slots at a time (n_slots is a multiple of 64; a group past the range repeats the first): two
+    // where the wait for them is what the pass takes (64^3 7.4 -> 6.7 us, 128^3 9.3 -> 8.5; 256^3 43.9 / 44.6)
+    constexpr int U = M <= 128 ? 2 : 1;
+    for (int sb = s0 & ~63; sb < s1; sb += 64 * U) {
+      int s[U];
+      int32_t j[U][K], row[U];
+      int2 head[U];
+      double v[U], f[U][K];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        s[u] = sb + 64 * u + lane;
+        const int q = sb + 64 * u < s1 ? s[u] : sb + lane;
+#pragma unroll
+        for (int k = 0; k < K; ++k) j[u][k] = t.arm_idx[k * ns + q];
+#pragma unroll
+        for (int k = 0; k < K; ++k) f[u][k] = w[k * ns + q];
+        head[u] = reinterpret_cast<const int2 *>(t.arm_head)[q];
+        row[u] = t.arm_row[q];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        v[u] = 0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[u] += f[u][k] * (double)ps[j[u][k]];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        double sum = v[u];
+#pragma unroll
+        for (int i = 1; i < 2 * D; ++i) {
+          const double o = __shfl_down(v[u], i, 64);
+          sum += i < head[u].y ? o : 0.0;
+        }
+        if (s[u] >= s0 && s[u] < s1 && head[u].y > 0) {
+          const int li = row[u] + c * per - r0;
+          lane_of(sbuf[(li >> 1) * PADM + pad((head[u].x & (M - 1)) + 1)], li & 1) = (T)sum;
+        }
+      }
+    }
+  }
+  __syncthreads();
+  dst_pair<T, M, E>(sbuf + (lane / Sh::TPP) * PADM, lane % Sh::TPP, tw, sn);
+#pragma unroll
+  for (int pp = 0; pp < NP; ++pp) {
+    const bool oka = r0 + 2 * pp < nrows, okb = r0 + 2 * pp + 1 < nrows;
+    T *oa = out + (int64_t)__builtin_amdgcn_readlane(held, 2 * pp) * M;
+    T *ob = out + (int64_t)__builtin_amdgcn_readlane(held, 2 * pp + 1) * M;
+#pragma unroll
+    for (int k = 0; k < M / 64; ++k) {
+      const int n = lane + 64 * k;   // n = N: the pad column, zero
+      const C2<T> v = n < N ? sbuf[pp * PADM + pad(n + 1)] : C2<T>{T(0), T(0)};
+      if (oka) oa[n] = v.x;
+      if (okb) ob[n] = v.y;
+    }
+  }
+}
+
 // ---------------------------------------------------------------- bidomain x passes
 //
 // The x passes of a coupled bidomain step pair row r of component 0 with row r of component 1
@@ -1402,6 +1486,32 @@ void pass_x_rows(const T *in, T *out, const RowSet &set, bool last, const C2<T> 
   });
 }
 
+// first row pass of a product, correction included
+template <typename T, typename TP, int M>
+void pass_x_correct(DevProblem &p, const TP *psi, hipStream_t st) {
+  if constexpr (M >= 64) {
+    const int64_t n = p.n_rows_in;
+    if (n < 1) return;
+    PrecTables<T> &tb = p.tab<T>();
+    const C2<T> *tw = reinterpret_cast<const C2<T> *>(tb.tw);
+    const int per = (int)(n / p.ncomp);
+    with_row_values<M>(n, false, [&](auto e) {
+      // FP32 at 256^3: more rows to a tile and its 64-slot groups fuller, 25.4 -> 23.7 us (FP64 43.2 / 44.7)
+      constexpr int E0 = decltype(e)::value, E = sizeof(T) == 4 && M == 256 && E0 == 8 ? 16 : E0;
+      using Sh = XShape<T, M, E>;
+      const unsigned g = (unsigned)((n + 2 * Sh::NP - 1) / (2 * Sh::NP));
+      if (p.dim == 2)
+        k_dst_x_correct<T, TP, M, E, 2, 4><<<g, 64, 0, st>>>(p.itab, psi, p.M, tb.work, p.rows_in, per, p.ncomp, tw, tb.sp);
+      else
+        k_dst_x_correct<T, TP, M, E, 3, kLsqNodes><<<g, 64, 0, st>>>(p.itab, psi, p.M, tb.work, p.rows_in, per, p.ncomp,
+                                                                     tw, tb.sp);
+      KFBI_HIP(hipGetLastError());
+    });
+  } else {
+    throw std::logic_error("rows below 64 cells form no correction");
+  }
+}
+
 // y pass over every plane, or over the nz planes listed
 template <typename T, int M>
 void pass_y(const T *in, T *out, int64_t P, int64_t cs, int ncomp, const uint64_t *mask_in, const uint64_t *mask_out,
@@ -1692,8 +1802,8 @@ void run_bidomain_final(DevProblem &p, const FhnArgs &a, bool fuse_be, hipStream
 // needs no zeros.  One field instead of one per pass keeps a product of the 256^3 pair (63 MB of
 // right-hand-side rows, 136 MB of planes) inside the 256 MB memory-side cache: last axis 66.4 ->
 // 46.3 us, y passes 51.7 -> 48.5 us, and two fields less per problem and precision.
-template <typename T, int M>
-void run_box_sparse(DevProblem &p, hipStream_t st) {
+template <typename T, typename TP, int M>
+void run_box_sparse(DevProblem &p, const TP *psi, hipStream_t st) {
   PrecTables<T> &tb = p.tab<T>();
   T *A = tb.work;
   const C2<T> *tw = reinterpret_cast<const C2<T> *>(tb.tw);
@@ -1702,7 +1812,8 @@ void run_box_sparse(DevProblem &p, hipStream_t st) {
   auto tic = [&](Timer &t) { t.tic(p.profile, st); };
   auto toc = [&](Timer &t) { t.toc(p.profile, st); };
   tic(p.t_dst_x_rows);
-  pass_x_rows<T, M>(tb.rhs, A, p.set_in(), false, tw, sp, st);
+  if (psi) pass_x_correct<T, TP, M>(p, psi, st);
+  else pass_x_rows<T, M>(tb.rhs, A, p.set_in(), false, tw, sp, st);
   KFBI_HIP(hipGetLastError());
   toc(p.t_dst_x_rows);
   tic(p.t_dst_y_sparse);
@@ -1765,13 +1876,14 @@ void run_box_group(const MultiGroupDesc &d, bool direct, hipStream_t st) {
 
 // 2D box solve whose right-hand side is zero outside the rows of `in` and whose result is read only on the rows
 // of `out` (sets without a list: every row), padded, into work: the other rows are neither read nor written.
-template <typename T, int M>
-void run_box_rows2d(DevProblem &p, const T *src, const RowSet &in, const RowSet &out, hipStream_t st) {
+template <typename T, typename TP, int M>
+void run_box_rows2d(DevProblem &p, const T *src, const TP *psi, const RowSet &in, const RowSet &out, hipStream_t st) {
   PrecTables<T> &tb = p.tab<T>();
   const C2<T> *tw = reinterpret_cast<const C2<T> *>(tb.tw);
   const int64_t rows = (int64_t)p.ncomp * (M - 1);
   p.t_dst_x.tic(p.profile, st);
-  pass_x_set<T, M>(src, tb.work, in, false, rows, tw, tb.sp, st);
+  if (psi) pass_x_correct<T, TP, M>(p, psi, st);
+  else pass_x_set<T, M>(src, tb.work, in, false, rows, tw, tb.sp, st);
   p.t_dst_x.toc(p.profile, st);
   p.t_dst_last.tic(p.profile, st);
   LastAxis<T> l;
@@ -1933,16 +2045,16 @@ static bool rows2d_masked(const DevProblem &p) {
   return p.sparse && p.direct && row_sets_pay(p.ncomp * p.comp_stride * (int64_t)sizeof(T));
 }
 
-template <typename T>
-static void box_rows2d(DevProblem &p, const T *src, const RowSet &in, const RowSet &out, hipStream_t st) {
+template <typename T, typename TP>
+static void box_rows2d(DevProblem &p, const T *src, const TP *psi, const RowSet &in, const RowSet &out, hipStream_t st) {
   switch (p.Mfft) {
-    case 16: run_box_rows2d<T, 16>(p, src, in, out, st); break;
-    case 32: run_box_rows2d<T, 32>(p, src, in, out, st); break;
-    case 64: run_box_rows2d<T, 64>(p, src, in, out, st); break;
-    case 128: run_box_rows2d<T, 128>(p, src, in, out, st); break;
-    case 256: run_box_rows2d<T, 256>(p, src, in, out, st); break;
-    case 512: run_box_rows2d<T, 512>(p, src, in, out, st); break;
-    case 1024: run_box_rows2d<T, 1024>(p, src, in, out, st); break;
+    case 16: run_box_rows2d<T, TP, 16>(p, src, psi, in, out, st); break;
+    case 32: run_box_rows2d<T, TP, 32>(p, src, psi, in, out, st); break;
+    case 64: run_box_rows2d<T, TP, 64>(p, src, psi, in, out, st); break;
+    case 128: run_box_rows2d<T, TP, 128>(p, src, psi, in, out, st); break;
+    case 256: run_box_rows2d<T, TP, 256>(p, src, psi, in, out, st); break;
+    case 512: run_box_rows2d<T, TP, 512>(p, src, psi, in, out, st); break;
+    case 1024: run_box_rows2d<T, TP, 1024>(p, src, psi, in, out, st); break;
     default: throw std::invalid_argument("unsupported grid size");
   }
 }
@@ -1950,7 +2062,7 @@ static void box_rows2d(DevProblem &p, const T *src, const RowSet &in, const RowS
 template <typename T>
 void box_solve_stencils(DevProblem &p, const T *src, hipStream_t st) {
   if (p.dim == 2 && rows2d_masked<T>(p)) {
-    box_rows2d<T>(p, src, RowSet{}, p.set_out(), st);
+    box_rows2d<T, double>(p, src, nullptr, RowSet{}, p.set_out(), st);
     return;
   }
   if (p.dim != 3 || !p.sparse) {
@@ -1996,10 +2108,11 @@ void bidomain_final_solve(DevProblem &p, const FhnArgs &a, bool fuse_be, hipStre
   }
 }
 
-template <typename T>
-void box_solve_matvec(DevProblem &p, hipStream_t st) {
-  if (p.dim == 2 && rows2d_masked<T>(p)) {
-    box_rows2d<T>(p, p.tab<T>().rhs, p.set_in(), p.set_out(), st);
+// psi given: the first pass forms the correction from it; else it is in rhs.
+template <typename T, typename TP>
+void box_solve_matvec(DevProblem &p, const TP *psi, hipStream_t st) {
+  if (p.dim == 2 && (psi || rows2d_masked<T>(p))) {
+    box_rows2d<T, TP>(p, p.tab<T>().rhs, psi, p.set_in(), rows2d_masked<T>(p) ? p.set_out() : RowSet{}, st);
     return;
   }
   if (p.dim != 3 || !p.sparse) {
@@ -2007,17 +2120,18 @@ void box_solve_matvec(DevProblem &p, hipStream_t st) {
     return;
   }
   switch (p.Mfft) {
-    case 16: run_box_sparse<T, 16>(p, st); break;
-    case 32: run_box_sparse<T, 32>(p, st); break;
-    case 64: run_box_sparse<T, 64>(p, st); break;
-    case 128: run_box_sparse<T, 128>(p, st); break;
-    case 256: run_box_sparse<T, 256>(p, st); break;
-    case 512: run_box_sparse<T, 512>(p, st); break;
-    case 1024: run_box_sparse<T, 1024>(p, st); break;
+    case 16: run_box_sparse<T, TP, 16>(p, psi, st); break;
+    case 32: run_box_sparse<T, TP, 32>(p, psi, st); break;
+    case 64: run_box_sparse<T, TP, 64>(p, psi, st); break;
+    case 128: run_box_sparse<T, TP, 128>(p, psi, st); break;
+    case 256: run_box_sparse<T, TP, 256>(p, psi, st); break;
+    case 512: run_box_sparse<T, TP, 512>(p, psi, st); break;
+    case 1024: run_box_sparse<T, TP, 1024>(p, psi, st); break;
     default: throw std::invalid_argument("unsupported grid size");
   }
 }
-template void box_solve_matvec<double>(DevProblem &, hipStream_t);
-template void box_solve_matvec<float>(DevProblem &, hipStream_t);
+template void box_solve_matvec<double, double>(DevProblem &, const double *, hipStream_t);
+template void box_solve_matvec<float, double>(DevProblem &, const double *, hipStream_t);
+template void box_solve_matvec<float, float>(DevProblem &, const float *, hipStream_t);
 
 }  // namespace kfbi

@@ -486,6 +486,17 @@ void upload_tables(DevProblem &p) {
       }
       return dupload(bits);
     };
+    // listed row of each arm slot, first slot of each listed row (of one component: the same in the other)
+    const size_t per = rin.size() / (size_t)t.ncomp;
+    std::vector<int32_t> place((size_t)rows, 0), arm_row((size_t)ns, 0), row_slot(per + 1, (int32_t)ns);
+    for (size_t i = 0; i < per; ++i) place[(size_t)rin[i]] = (int32_t)i;
+    for (size_t r = t.irregular.size(); r-- > 0;) {
+      const int32_t i = place[(size_t)(t.irregular[r] / N)];
+      for (size_t a = 0; a < arms_of[r].size(); ++a) arm_row[(size_t)slot_of[r] + a] = i;
+      row_slot[(size_t)i] = (int32_t)slot_of[r];
+    }
+    p.itab.arm_row = dupload(arm_row);
+    p.itab.row_slot = dupload(row_slot);
     p.cols_in = columns(rin, t.irregular);
     p.cols_out = columns(rout, t.st_lin);
     std::vector<uint64_t> bin((size_t)planes * 16, 0), bout((size_t)planes * 16, 0);
@@ -539,6 +550,7 @@ void upload_tables(DevProblem &p) {
 
 void free_tables(DevProblem &p) {
   int32_t **ip[] = {&p.itab.arm_idx, &p.itab.arm_head, &p.itab.st_pos, &p.itab.q_idx,
+                    &p.itab.arm_row, &p.itab.row_slot,
                     &p.rows_in,      &p.rows_out,      &p.zlist_in,    &p.zlist_out};
   double **wp[] = {&p.itab.arm_w, &p.itab.st_nw, &p.itab.q_w};
   for (double **q : wp) {
