@@ -579,6 +579,17 @@ void Batch::gmres(int prec, const double *b, double *xv, bool x_zero, const std:
       k_seg_update<<<nb(L), kB, 0, st>>>(xv, V, L, ydev, pid, np, jmax);
       KFBI_HIP(hipGetLastError());
     }
+    // An FP32 inner solve ends on its Arnoldi-relation residual, as the single solver's does: the refinement takes
+    // the FP64 residual itself, and a check by an FP32 product, near its rounding for large coupled or fine
+    // problems, restarts by luck (64 problems: 19 or 54 FP32 products, from one problem alone).
+    if (prec == 1) {
+      for (int p = 0; p < np; ++p) {
+        if (!active[p] || jend[p] == 0) continue;
+        beta[p] = std::fabs(g[(size_t)p * (m + 1) + jend[p]]);
+        active[p] = beta[p] > tol[p];
+      }
+      if (std::none_of(active.begin(), active.end(), [](char a) { return a; })) break;
+    }
     // true residual
     apply_vec(prec, xv, t, st);
     ++matvecs;

@@ -12,12 +12,12 @@
 //   T = FFT_M(t):  y_{2k} = -Im T_k,  y_{2k+1} = y_{2k-1} + Re T_k,  y_1 = Re T_0 / 2,
 // and the two real pencils ride in the real and imaginary parts of t.  The prefix sum
 // over the odd outputs is a chunked scan across the lanes that own the pencil pair.
-// The FFT is a Stockham radix-16 (then 2/4/8/16) transform in LDS: every thread holds
-// exactly 16 complex values per stage.
+// The FFT is a Stockham transform in LDS: every thread holds exactly E = 4, 8 or 16 complex
+// values per stage (row_values, column_values), the radix of every stage but the last.
 //
 // Passes (3D, fields in the padded [comp][z][y][x] layout with row pitch P = M):
-//   x (contiguous rows) -> y (tiles of columns, one z-plane) -> z fused with the mode
-//   scaling and the inverse z transform -> y inverse -> x inverse.
+//   x (contiguous rows) -> y (tiles of columns, one z-plane) -> z (solved directly, lastaxis.hip, or
+//   a pass here fused with the mode scaling and the inverse z transform) -> y inverse -> x inverse.
 // Each pass reads and writes its tile once; y and z passes work in place.
 #include <algorithm>
 
