@@ -128,8 +128,8 @@ __device__ __forceinline__ double decay_add(double p, double d, double g) { retu
 template <int NC, int CH, int XC>
 struct ColumnShared {
   double fs[CH][XC][NC], bs[CH][XC][NC];
-  double A[NC * NC][XC];            // into the decoupled variables; its transpose leads back
-  double d[NC][XC], mu[NC][XC], wk[NC][XC], inv_mu[NC][XC];   // wk = 1 / (1 - mu^2)
+  double A[NC * NC][XC];            // into the decoupled variables (the pair's last: A11 - A10); its transpose leads back
+  double d[NC][XC], mu[NC][XC], wk[NC][XC], inv_mu[NC][XC];   // mu: times the pair's weight; wk = 1 / (1 - mu^2)
   double tot[2 * NC][XC];
 };
 
@@ -176,27 +176,48 @@ __device__ __forceinline__ void column_solve(const T *__restrict__ ain, T *__res
   if (c == 0) {
     const double h2 = ms.h2;
     const double lx = ms.lam[x < N ? x : N - 1], ly = DIM == 3 ? ms.lam[y] : 0.0;
-    double s[NC];
+    double s[NC], wt[2] = {1.0, 1.0};
     if constexpr (NC == 2) {
       const double b0 = ms.D0[0] * lx + ms.D0[1] * ly, b1 = ms.D1[0] * lx + ms.D1[1] * ly, kap = ms.kappa;
-      const double i0 = recip(ms.D0[DIM - 1]), i1 = recip(ms.D1[DIM - 1]);
-      const double q0 = sqrt(i0), q1 = sqrt(i1);
-      const double p = (b0 + kap) * i0, q = (b1 + kap) * i1, cc = kap * q0 * q1;
-      const double hd = 0.5 * (p - q), rr = sqrt(hd * hd + cc * cc);
+      const double dz0 = ms.D0[DIM - 1], dz1 = ms.D1[DIM - 1], i0 = recip(dz0), i1 = recip(dz1);
+      const double p = (b0 + kap) * i0, q = (b1 + kap) * i1;
+      // X = dz1 b0 - dz0 b1, exactly 0 where the conductivities are proportional
+      auto cross = [&](int ax) {
+        const double t = dz0 * ms.D1[ax];
+        return fma(dz1, ms.D0[ax], -t) + fma(-dz0, ms.D1[ax], t);
+      };
+      const double X = lx * cross(0) + (DIM == 3 ? ly * cross(1) : 0.0);
+      // (p - q) / 2 and half the eigenvalues' difference, of [[p, -c], [-c, q]] with c^2 = kappa^2 / (dz0 dz1)
+      const double hd = 0.5 * (X + kap * (dz1 - dz0)) * (i0 * i1), rr = sqrt(hd * hd + kap * i0 * (kap * i1));
       const double l1 = 0.5 * (p + q) + rr;
       // the eigenvalues' product without cancellation: det = b0 b1 + kappa (b0 + b1)
       const double l2 = (b0 * b1 + kap * (b0 + b1)) * i0 * i1 * recip(l1);
-      // largest eigenvalue's vector (cos, sin) of [[p, -cc], [-cc, q]]: cos 2a = hd / rr
-      double big = 1.0, small = 0.0;
+      // Rows (1, r) or (r, 1) into the decoupled variables, the larger entry 1, and weights w on the way back (squares
+      // of the normalised rows' larger entries: no square roots, whose rounding would be one and the same everywhere).
+      // rho: the smaller entry of the small eigenvalue's row.  That row is applied as A10 (f0 + f1) + (A11 - A10) f1:
+      // sources near (g, -g), a step's among them, cancel in it, and 1 / l2 magnifies what is left (by l1 / l2, about
+      // kappa over the mode sums), so the difference is taken without cancellation from
+      //   rho = 1 - 2 X / (S + X + R) where hd >= 0, 1 + 2 X / (S - X + R) where hd < 0,
+      // S = kappa (dz0 + dz1), R = 2 dz0 dz1 rr (S +- X > 0 there).
+      const bool first = hd >= 0.0;   // the large eigenvalue's row has its larger entry at component 0
+      double big2 = 1.0, rho = 0.0, rel = first ? 1.0 : -1.0;
       if (rr > 0.0) {
-        big = sqrt(0.5 + 0.5 * (fabs(hd) * recip(rr)));
-        small = 0.5 * cc * recip(rr * big);
+        const double ir = recip(rr);
+        big2 = 0.5 + 0.5 * (fabs(hd) * ir);
+        rel = 2.0 * X * recip(kap * (dz0 + dz1) + (first ? X : -X) + 2.0 * dz0 * dz1 * rr);
+        if (fabs(rel) < 0.5) {
+          rho = first ? 1.0 - rel : 1.0 + rel;
+        } else {
+          rho = 0.5 * kap * (first ? i0 : i1) * (ir * recip(big2));
+          rel = first ? 1.0 - rho : rho - 1.0;
+        }
       }
-      const double ca = hd >= 0.0 ? big : small, sa = hd >= 0.0 ? -small : -big;
-      sh.A[0][xo] = ca * q0;
-      sh.A[1][xo] = sa * q1;
-      sh.A[2][xo] = -sa * q0;
-      sh.A[3][xo] = ca * q1;
+      sh.A[0][xo] = first ? 1.0 : -rho * dz1 * i0;
+      sh.A[1][xo] = first ? -rho * dz0 * i1 : 1.0;
+      sh.A[2][xo] = first ? rho : 1.0;
+      sh.A[3][xo] = rel;
+      wt[0] = big2 * (first ? i0 : i1);
+      wt[1] = big2 * (first ? i1 : i0);
       s[0] = h2 * l1;
       s[1] = h2 * l2;
     } else {
@@ -208,7 +229,7 @@ __device__ __forceinline__ void column_solve(const T *__restrict__ ain, T *__res
     for (int k = 0; k < NC; ++k) {
       const Decay dk(s[k]);
       sh.d[k][xo] = dk.d;
-      sh.mu[k][xo] = dk.mu;
+      sh.mu[k][xo] = wt[k] * dk.mu;
       sh.wk[k][xo] = dk.inv_mu * dk.inv_rho;
       sh.inv_mu[k][xo] = dk.inv_mu;
     }
@@ -218,18 +239,21 @@ __device__ __forceinline__ void column_solve(const T *__restrict__ ain, T *__res
 #pragma unroll
   for (int k = 0; k < NC; ++k) d[k] = sh.d[k][xo];
   if constexpr (NC == 2) {
-    const double A00 = sh.A[0][xo], A01 = sh.A[1][xo], A10 = sh.A[2][xo], A11 = sh.A[3][xo];
+    const double A00 = sh.A[0][xo], A01 = sh.A[1][xo], A10 = sh.A[2][xo], A11m = sh.A[3][xo];
 #pragma unroll
     for (int i = 0; i < LC; ++i) {
-      double f0 = (double)f[0][i], f1;
+      double f0 = (double)f[0][i], f1, both;
       if constexpr (FORM == 3 || FORM == 5) f1 = -f0;
       else f1 = (double)f[1][i];
       if constexpr (FORM == 5) {
+        both = (double)f2[0][i] + (double)f2[1][i];
         f0 += (double)f2[0][i];
         f1 += (double)f2[1][i];
+      } else {
+        both = f0 + f1;
       }
       g[0][i] = A00 * f0 + A01 * f1;
-      g[1][i] = A10 * f0 + A11 * f1;
+      g[1][i] = A10 * both + A11m * f1;
     }
   } else {
     const double A00 = sh.A[0][xo];
@@ -304,7 +328,7 @@ __device__ __forceinline__ void column_solve(const T *__restrict__ ain, T *__res
   const double s0 = scale * sh.mu[0][xo];
   if constexpr (NC == 2) {
     const double s1 = scale * sh.mu[1][xo];
-    const double B00 = s0 * sh.A[0][xo], B01 = s0 * sh.A[1][xo], B10 = s1 * sh.A[2][xo], B11 = s1 * sh.A[3][xo];
+    const double B00 = s0 * sh.A[0][xo], B01 = s0 * sh.A[1][xo], B10 = s1 * sh.A[2][xo], B11 = B10 + s1 * sh.A[3][xo];
 #pragma unroll
     for (int i = 0; i < LC; ++i) {
       const double u0 = B00 * g[0][i] + B10 * g[1][i], u1 = B01 * g[0][i] + B11 * g[1][i];
