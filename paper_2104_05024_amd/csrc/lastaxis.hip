@@ -128,7 +128,7 @@ __device__ __forceinline__ double decay_add(double p, double d, double g) { retu
 template <int NC, int CH, int XC>
 struct ColumnShared {
   double fs[CH][XC][NC], bs[CH][XC][NC];
-  double A[NC * NC][XC];            // into the decoupled variables (the pair's last: A11 - A10); its transpose leads back
+  double A[NC * NC][XC];            // into the decoupled variables (the pair's last in FP64: A11 - A10); its transpose leads back
   double d[NC][XC], mu[NC][XC], wk[NC][XC], inv_mu[NC][XC];   // mu: times the pair's weight; wk = 1 / (1 - mu^2)
   double tot[2 * NC][XC];
 };
@@ -152,6 +152,9 @@ __device__ __forceinline__ void column_solve(const T *__restrict__ ain, T *__res
   const int64_t RS = DIM == 3 ? (int64_t)N * P : P;
   const int64_t base = (int64_t)r0 * RS + x;
   constexpr bool BUF = DIM == 2 || M <= 512;
+  // The small eigenvalue's row as A10 (f0 + f1) + (A11 - A10) f1 (see below); FP32 values carry 2^29 times the rounding
+  // that this is there for
+  constexpr bool SUM = sizeof(T) == 8;
   const int64_t bytes = (int64_t)N * RS * (int64_t)sizeof(T);
   auto wants = [&](int i) { return FORM < 1 || FORM > 3 || ((ob >> i) & 1); };
   auto inside = [&](int i) { return in_row && (i < LC - 1 || c < CH - 1); };
@@ -215,7 +218,7 @@ __device__ __forceinline__ void column_solve(const T *__restrict__ ain, T *__res
       sh.A[0][xo] = first ? 1.0 : -rho * dz1 * i0;
       sh.A[1][xo] = first ? -rho * dz0 * i1 : 1.0;
       sh.A[2][xo] = first ? rho : 1.0;
-      sh.A[3][xo] = rel;
+      sh.A[3][xo] = SUM ? rel : sh.A[2][xo] + rel;
       wt[0] = big2 * (first ? i0 : i1);
       wt[1] = big2 * (first ? i1 : i0);
       s[0] = h2 * l1;
@@ -239,21 +242,21 @@ __device__ __forceinline__ void column_solve(const T *__restrict__ ain, T *__res
 #pragma unroll
   for (int k = 0; k < NC; ++k) d[k] = sh.d[k][xo];
   if constexpr (NC == 2) {
-    const double A00 = sh.A[0][xo], A01 = sh.A[1][xo], A10 = sh.A[2][xo], A11m = sh.A[3][xo];
+    const double A00 = sh.A[0][xo], A01 = sh.A[1][xo], A10 = sh.A[2][xo], A11 = sh.A[3][xo];
 #pragma unroll
     for (int i = 0; i < LC; ++i) {
-      double f0 = (double)f[0][i], f1, both;
+      double f0 = (double)f[0][i], f1, both = f0;
       if constexpr (FORM == 3 || FORM == 5) f1 = -f0;
       else f1 = (double)f[1][i];
       if constexpr (FORM == 5) {
         both = (double)f2[0][i] + (double)f2[1][i];
         f0 += (double)f2[0][i];
         f1 += (double)f2[1][i];
-      } else {
+      } else if constexpr (SUM) {
         both = f0 + f1;
       }
       g[0][i] = A00 * f0 + A01 * f1;
-      g[1][i] = A10 * both + A11m * f1;
+      g[1][i] = A10 * both + A11 * f1;
     }
   } else {
     const double A00 = sh.A[0][xo];
@@ -328,7 +331,8 @@ __device__ __forceinline__ void column_solve(const T *__restrict__ ain, T *__res
   const double s0 = scale * sh.mu[0][xo];
   if constexpr (NC == 2) {
     const double s1 = scale * sh.mu[1][xo];
-    const double B00 = s0 * sh.A[0][xo], B01 = s0 * sh.A[1][xo], B10 = s1 * sh.A[2][xo], B11 = B10 + s1 * sh.A[3][xo];
+    const double B00 = s0 * sh.A[0][xo], B01 = s0 * sh.A[1][xo], B10 = s1 * sh.A[2][xo],
+                 B11 = (SUM ? B10 : 0.0) + s1 * sh.A[3][xo];
 #pragma unroll
     for (int i = 0; i < LC; ++i) {
       const double u0 = B00 * g[0][i] + B10 * g[1][i], u1 = B01 * g[0][i] + B11 * g[1][i];
@@ -349,8 +353,13 @@ __device__ __forceinline__ void column_solve(const T *__restrict__ ain, T *__res
 template <int M, int XC>
 constexpr int col_threads() { return M / col_chunk(M) * XC; }
 
+// Waves per SIMD that the register allocation has to leave: four for 3D FP32 pairs (masked 256^3 pair 36 us; with 130
+// registers, so three waves, 49).
+template <typename T, int M, int NC, int DIM>
+constexpr int col_waves() { return sizeof(T) == 4 && NC == 2 && DIM == 3 && M <= 512 ? 4 : 1; }
+
 template <typename T, int M, int NC, int DIM, int FORM>
-__global__ __launch_bounds__((col_threads<M, col_width<T>(M)>())) void k_column(
+__global__ __launch_bounds__((col_threads<M, col_width<T>(M)>()), (col_waves<T, M, NC, DIM>())) void k_column(
     const T *ain, T *a, int64_t P, int64_t cs, ModeParams ms0, const ModeParams *__restrict__ msv, int64_t pstride,
     PlaneBits zin, PlaneBits zout, const uint64_t *__restrict__ bin, const uint64_t *__restrict__ bout,
     const T *__restrict__ ain2) {
