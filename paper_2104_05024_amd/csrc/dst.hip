@@ -178,9 +178,13 @@ using YShape = Shape<T, M, M == 64 || M == 128 ? 4 : (sizeof(T) == 8 ? 2 : 4), c
 // at 256^3 the latter is slower with 8 values (154 against 142 us)
 template <int M>
 using FShape = Shape<double, M, 2, column_values(M)>;
-// the last axis as a fused transform pass
+// The last axis as a fused transform pass (boxes that are not solved by columns): values per thread as for the columns of
+// a plane, and in FP64 tiles of four wavefronts at 128 and 1024 cells, where two leave row segments of 32 bytes (1024) or
+// wait longer (128).  2 wavefronts of 16 values / this, box solves (us): FP64 2D 64 17.0 / 13.4, 2D 1024 41.3 / 37.5,
+// its pair 59.9 / 50.6, 64^3 28.9 / 25.1, 128^3 68.6 / 66.1; FP32 64^3 25.9 / 20.3, pair of 128^3 63.0 / 57.6.  At 256
+// and 512 four lose (FP32 pair of 256^3 258 -> 265).
 template <typename T, int M>
-using LShape = Shape<T, M, sizeof(T) == 8 ? 2 : 4, 16>;
+using LShape = Shape<T, M, sizeof(T) == 4 || M == 64 || M == 128 || M == 1024 ? 4 : 2, column_values(M)>;
 
 // One Stockham stage of radix R after Ns points have been combined.
 template <typename T, int M, int E, int R, int Ns>
@@ -817,14 +821,13 @@ struct StridedTile {
 // may alias.  mask_in / mask_out (optional, [z][16] bit rows, bit y of plane z): rows known to
 // be zero on input are not read; only rows flagged on output are written.  planes (optional): the list of
 // planes to take, one per blockIdx.y; the others are neither read nor written.
-template <typename T, int M>
-__global__ __launch_bounds__((YShape<T, M>::NT)) void k_dst_y(const T *__restrict__ in, T *__restrict__ out,
+template <typename T, int M, typename Sh = YShape<T, M>>
+__global__ __launch_bounds__(Sh::NT) void k_dst_y(const T *__restrict__ in, T *__restrict__ out,
                                                                int64_t P, int64_t comp_stride,
                                                                const uint64_t *__restrict__ mask_in,
                                                                const uint64_t *__restrict__ mask_out,
                                                                const int32_t *__restrict__ planes,
                                                                const C2<T> *__restrict__ tw, const T *__restrict__ sp) {
-  using Sh = YShape<T, M>;
   using Tl = StridedTile<T, M, 2 * Sh::NP, 1, Sh>;
   __shared__ C2<T> sbuf[Sh::NP * Sh::PADM];
   const int tid = threadIdx.x;
@@ -1446,10 +1449,15 @@ __global__ __launch_bounds__((FShape<M>::NT)) void k_dst_x_be1(FhnArgs a, const 
 // x pass over `rows` contiguous rows (padded in/out unless stated)
 // Values per thread of an x pass: 4 where it is short (2D, or few rows), 16 for the long ones of 512 cells; a batch's
 // group always takes row_values, as its passes merged with other groups' do.
-template <int M, typename F>
-void with_row_values(int64_t rows, bool group, const F &f) {
+// Long dense passes of 256 cells in FP32 take 16 as well (inverse pass of a 256^3 pair 53.1 -> 47.8 us), listed rows do
+// not (the coupled FP32 product would take 143 us, not 129.7).
+template <typename T, int M, typename F>
+void with_row_values(int64_t rows, bool group, bool dense, const F &f) {
   if constexpr (M == 128 || M == 256) {
     if (!group && rows * M <= (1 << 20)) return f(std::integral_constant<int, 4>());
+  }
+  if constexpr (M == 256 && sizeof(T) == 4) {
+    if (!group && dense) return f(std::integral_constant<int, 16>());
   }
   if constexpr (M == 512) {
     if (!group && rows > 100000) return f(std::integral_constant<int, 16>());
@@ -1460,7 +1468,7 @@ void with_row_values(int64_t rows, bool group, const F &f) {
 template <typename T, int M>
 void pass_x(const T *in, bool in_plain, T *out, bool out_plain, int64_t rows, const C2<T> *tw, const T *sp,
             hipStream_t st, bool group = false) {
-  with_row_values<M>(rows, group, [&](auto e) {
+  with_row_values<T, M>(rows, group, true, [&](auto e) {
     constexpr int E = decltype(e)::value;
     using Sh = XShape<T, M, E>;
     const dim3 g((unsigned)((rows + 2 * Sh::NP - 1) / (2 * Sh::NP)));
@@ -1477,7 +1485,7 @@ template <typename T, int M>
 void pass_x_rows(const T *in, T *out, const RowSet &set, bool last, const C2<T> *tw, const T *sp, hipStream_t st,
                  bool group = false) {
   if (set.n < 1) return;
-  with_row_values<M>(set.n, group, [&](auto e) {
+  with_row_values<T, M>(set.n, group, false, [&](auto e) {
     constexpr int E = decltype(e)::value;
     using Sh = XShape<T, M, E>;
     k_dst_x_rows<T, M, E><<<(unsigned)((set.n + 2 * Sh::NP - 1) / (2 * Sh::NP)), Sh::NT, 0, st>>>(
@@ -1495,7 +1503,7 @@ void pass_x_correct(DevProblem &p, const TP *psi, hipStream_t st) {
     PrecTables<T> &tb = p.tab<T>();
     const C2<T> *tw = reinterpret_cast<const C2<T> *>(tb.tw);
     const int per = (int)(n / p.ncomp);
-    with_row_values<M>(n, false, [&](auto e) {
+    with_row_values<T, M>(n, false, false, [&](auto e) {
       // FP32 at 256^3: more rows to a tile and its 64-slot groups fuller, 25.4 -> 23.7 us (FP64 43.2 / 44.7)
       constexpr int E0 = decltype(e)::value, E = sizeof(T) == 4 && M == 256 && E0 == 8 ? 16 : E0;
       using Sh = XShape<T, M, E>;
@@ -1512,15 +1520,23 @@ void pass_x_correct(DevProblem &p, const TP *psi, hipStream_t st) {
   }
 }
 
-// y pass over every plane, or over the nz planes listed
+// y pass over every plane, or over the nz planes listed.  wide (the dense scalar FP64 pass of 128 cells beside the fused
+// last axis): tiles of 64 columns with 16 values per thread, 12.6 us there against 14.3; beside the columns, which leave
+// the cache in another state, they are slower (box solve 53.5 / 56.4), so those keep the narrow ones.
 template <typename T, int M>
 void pass_y(const T *in, T *out, int64_t P, int64_t cs, int ncomp, const uint64_t *mask_in, const uint64_t *mask_out,
-            const C2<T> *tw, const T *sp, hipStream_t st, const int32_t *planes = nullptr, int nz = -1) {
-  using Sh = YShape<T, M>;
+            const C2<T> *tw, const T *sp, hipStream_t st, const int32_t *planes = nullptr, int nz = -1, bool wide = false) {
   if (nz == 0) return;
-  const dim3 g((Sh::N + 2 * Sh::NP - 1) / (2 * Sh::NP), planes ? nz : Sh::N, ncomp);
-  k_dst_y<T, M><<<g, Sh::NT, 0, st>>>(in, out, P, cs, mask_in, mask_out, planes, tw, sp);
-  KFBI_HIP(hipGetLastError());
+  auto go = [&](auto sh) {
+    using Sh = decltype(sh);
+    const dim3 g((Sh::N + 2 * Sh::NP - 1) / (2 * Sh::NP), planes ? nz : Sh::N, ncomp);
+    k_dst_y<T, M, Sh><<<g, Sh::NT, 0, st>>>(in, out, P, cs, mask_in, mask_out, planes, tw, sp);
+    KFBI_HIP(hipGetLastError());
+  };
+  if constexpr (M == 128 && sizeof(T) == 8) {
+    if (wide) return go(Shape<T, M, 4, 16>());
+  }
+  go(YShape<T, M>());
 }
 
 // fused last-axis pass; nprob > 1 only in 2D (batched groups with per-problem msv)
@@ -1620,6 +1636,7 @@ void run_box(DevProblem &p, const T *src, bool src_plain, T *dst, bool dst_plain
   const int64_t rows = (int64_t)p.ncomp * (p.dim == 3 ? (int64_t)N * N : N);
   auto tic = [&](Timer &t) { t.tic(p.profile, st); };
   auto toc = [&](Timer &t) { t.toc(p.profile, st); };
+  const bool wide = !p.direct && p.ncomp == 1;
   if (!(skip & 1)) {
     tic(p.t_dst_x);
     pass_x<T, M>(src, src_plain, A, false, rows, tw, sp, st);
@@ -1627,7 +1644,7 @@ void run_box(DevProblem &p, const T *src, bool src_plain, T *dst, bool dst_plain
   }
   if (p.dim == 3) {
     tic(p.t_dst_y);
-    pass_y<T, M>(A, A, P, cs, p.ncomp, nullptr, nullptr, tw, sp, st);
+    pass_y<T, M>(A, A, P, cs, p.ncomp, nullptr, nullptr, tw, sp, st, nullptr, -1, wide);
     toc(p.t_dst_y);
   }
   tic(p.t_dst_last);
@@ -1635,7 +1652,7 @@ void run_box(DevProblem &p, const T *src, bool src_plain, T *dst, bool dst_plain
   toc(p.t_dst_last);
   if (p.dim == 3) {
     tic(p.t_dst_y);
-    pass_y<T, M>(A, A, P, cs, p.ncomp, nullptr, nullptr, tw, sp, st);
+    pass_y<T, M>(A, A, P, cs, p.ncomp, nullptr, nullptr, tw, sp, st, nullptr, -1, wide);
     toc(p.t_dst_y);
   }
   if (!(skip & 2)) {
