@@ -343,12 +343,13 @@ struct LastAxis {
   int form = 0;
   const T *in2 = nullptr;
 };
-// Whether the columns are solved directly: where the slowest mode decays across the box,
-// s M^2 >= 2 (the isotropic boxes have 9.9 in 2D and 19.7 in 3D).  Below that the direct solve's
-// starting values come out of a difference of nearly equal sums (relative error in the lowest
-// mode about 2e-15 at s M^2 = 2 and 6e-14 at 0.1, against the DST's 5e-16), so boxes whose
-// conductivity along the last axis is more than five (2D) or ten (3D) times the others' keep the
-// DST; so do reaction terms so large (s >= 1e12) that mu drops out of the recursions.
+// Whether the columns are solved directly: where the slowest mode decays across the box, s M^2 >= 6 (the isotropic boxes
+// have 9.9 in 2D and 19.7 in 3D, more with a reaction term).  Below that the starting values come out of a difference of
+// nearly equal sums, and on small grids the error exceeds the sine transforms' (root mean square over seeded smooth
+// sources, columns / transforms: s M^2 2.2 1.25 and 1.24 at 16^2 and 32^2, 3 1.21 and 1.35, 4 1.13 and 1.24, 5 1.06 and
+// 1.04, 6.5 0.93 and 1.00; 0.7 to 1.0 from 128 cells on at any of them).  So boxes whose last axis conducts more than
+// 1.6 (2D) or 3.3 (3D) times the others keep the transforms (64^3 FP64 25.1 us against 23.5), as do reaction terms so large
+// (s >= 1e12) that mu drops out of the recursions.
 bool column_direct(int dim, int ncomp, int M, double h, const double D[2][3], double kappa);
 template <typename T>
 void last_axis_direct(const LastAxis<T> &l, hipStream_t st);

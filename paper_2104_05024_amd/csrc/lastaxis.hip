@@ -489,7 +489,7 @@ bool column_direct(int dim, int ncomp, int M, double h, const double D[2][3], do
     l = (b[0] * b[1] + kappa * (b[0] + b[1])) / (dz[0] * dz[1]) / big;
   }
   const double s = l * h * h;
-  return s * M * M >= 2.0 && s < 1e12;
+  return s * M * M >= 6.0 && s < 1e12;
 }
 
 template <typename T>
