@@ -21,7 +21,7 @@ struct Group {
   double *rhs64 = nullptr, *fpad64 = nullptr, *work64 = nullptr;
   float *rhs32 = nullptr, *fpad32 = nullptr, *work32 = nullptr;
   ModeParams *msv = nullptr;   // per-slot mode parameters (device)
-  bool direct = true;                          // every member's last axis is solved directly
+  bool direct = true;                          // the members' last axis is solved directly
   RowSet rows_in, rows_out;                    // rows of the members that hold irregular / stencil nodes
   template <typename T>
   T *rhs() const;
@@ -60,10 +60,9 @@ struct Batch {
   int seq_next = 0;
   void host_wait(hipStream_t st);
   bool use_graph = true;
-  // box solves of all size groups as one launch per pass (box_solve_multi) when every group's
-  // size is 64..1024; otherwise, or when switched off, one launch per group and pass
+  // box solves of the groups of one kind of last axis as one launch per pass (box_solve_multi) for the sizes
+  // 64..1024; smaller ones, or all when switched off, one launch per group and pass
   bool merged = true;
-  bool mergeable() const;
   template <typename T>
   // every group: src (rhs, or fpad if from_fpad) -> work; stencils: only the rows holding stencil nodes are
   // read afterwards.  rhs is zero outside the rows holding irregular nodes.

@@ -1,9 +1,10 @@
 // Batched two-dimensional Neumann problems (many interfaces of uneven grid sizes at once).
 //
 // Every problem keeps its own setup tables; the batch adds
-//   * size groups: problems with the same grid size share padded field buffers (stride
-//     N * M), so each DST pass of a group is one launch (blockIdx.y = problem for the fused
-//     last-axis pass, with per-problem mode parameters);
+//   * groups: problems with the same grid size and kind of last axis (columns or the fused
+//     transform pass) share padded field buffers (stride N * M), so each pass of a group is one
+//     launch (blockIdx.y = problem on the last axis, with per-problem mode parameters), or one
+//     launch over all groups of a kind from 64 cells on;
 //   * work lists: the correction and gather kernels of all problems run as one launch
 //     each, a table naming the problem of every block;
 //   * GMRES(m) for all problems in lockstep on concatenated vectors [problem][M_p]: per-problem
@@ -189,20 +190,22 @@ void Batch::init(int n, const kfbi_interface *ifaces, const kfbi_grid *grids, co
     upload_tables(*probs[i]);
     probs[i]->on_device = true;
   }
-  // size groups
-  std::vector<int> sizes;
-  for (auto &p : probs) sizes.push_back((int)p->Mfft);
-  std::sort(sizes.begin(), sizes.end());
-  sizes.erase(std::unique(sizes.begin(), sizes.end()), sizes.end());
+  // groups by size and by kind of last axis: a member whose last axis is not solved by columns leaves the others'
+  // passes as they are
+  std::vector<std::pair<int, bool>> kinds;
+  for (auto &p : probs) kinds.emplace_back((int)p->Mfft, p->direct);
+  std::sort(kinds.begin(), kinds.end());
+  kinds.erase(std::unique(kinds.begin(), kinds.end()), kinds.end());
   group_of.assign(n, 0);
   slot_of.assign(n, 0);
-  for (int s : sizes) {
+  for (const auto &[s, direct] : kinds) {
     Group g;
     g.Mfft = s;
+    g.direct = direct;
     g.N = s - 1;
     g.cs = (int64_t)g.N * s;
     for (int i = 0; i < n; ++i)
-      if (probs[i]->Mfft == s) {
+      if (probs[i]->Mfft == s && probs[i]->direct == direct) {
         group_of[i] = (int)groups.size();
         slot_of[i] = (int)g.members.size();
         g.members.push_back(i);
@@ -223,7 +226,6 @@ void Batch::init(int n, const kfbi_interface *ifaces, const kfbi_grid *grids, co
       m.kappa = p.kappa;
       m.norm = p.lam_scale;
       m.h2 = p.h * p.h;
-      g.direct = g.direct && p.direct;
       ms.push_back(m);
     }
     // rows of the members that matter to a product: the members' lists at their slots, their bits in slot order
@@ -365,13 +367,6 @@ void Batch::release() {
   probs.clear();
 }
 
-bool Batch::mergeable() const {
-  if (groups.empty() || (int)groups.size() > kMaxMultiGroups) return false;
-  for (const Group &g : groups)
-    if (g.Mfft < 64 || g.Mfft > 1024 || !g.direct) return false;
-  return true;
-}
-
 void Batch::drop_graphs() {
   for (int k = 0; k < 2; ++k)
     if (graph[k]) {
@@ -391,19 +386,21 @@ void Batch::box_all(bool from_fpad, bool stencils, hipStream_t st) {
     const T *src;
     if constexpr (sizeof(T) == 8) src = from_fpad ? g.fpad64 : g.rhs64;
     else src = from_fpad ? g.fpad32 : g.rhs32;
-    return MultiGroupDesc{g.Mfft,   (int)g.members.size(), g.cs,
-                          src,      g.work<T>(),           g.msv,
-                          tb.tw,    tb.sp,                 !from_fpad && sets ? g.rows_in : RowSet{},
-                          stencils && sets ? g.rows_out : RowSet{}};
+    const bool listed = g.direct && sets;
+    return MultiGroupDesc{g.Mfft, (int)g.members.size(), g.direct, g.cs, src, g.work<T>(), g.msv, tb.tw, tb.sp,
+                          !from_fpad && listed ? g.rows_in : RowSet{}, stencils && listed ? g.rows_out : RowSet{}};
   };
-  if (merged && mergeable()) {
+  for (bool direct : {true, false}) {
     MultiGroupDesc d[kMaxMultiGroups];
     int k = 0;
-    for (const Group &g : groups) d[k++] = desc(g);
-    box_solve_multi<T>(d, k, st);
-    return;
+    for (const Group &g : groups) {
+      if (g.direct != direct) continue;
+      if (merged && g.Mfft >= 64) d[k++] = desc(g);   // at most the five sizes 64..1024
+      else box_solve_group<T>(desc(g), st);
+    }
+    if (k > 1) box_solve_multi<T>(d, k, st);
+    else if (k == 1) box_solve_group<T>(d[0], st);
   }
-  for (const Group &g : groups) box_solve_group<T>(desc(g), g.direct, st);
 }
 
 template <typename T, typename TP>

@@ -309,9 +309,10 @@ void launch_batch_gather(const BatchItem<T> *items, const BatchBlocks &b, const 
 // outside which the source is zero and the rows the result is read on (row sets of the whole group).
 // Merged: several such groups (each with its own size) in one launch per pass, so the tiles of small grids
 // run beside those of large ones instead of in launches of their own that cannot fill the GPU.
-// Sizes 64..1024, last axis direct; the groups are those of one precision.  Same results.
+// Sizes 64..1024, all direct or none; the groups are those of one precision.  Same results.
 struct MultiGroupDesc {
   int Mfft = 0, G = 0;
+  bool direct = true;
   int64_t cs = 0;
   const void *src = nullptr;
   void *dst = nullptr;
@@ -321,7 +322,7 @@ struct MultiGroupDesc {
 };
 constexpr int kMaxMultiGroups = 8;
 template <typename T>
-void box_solve_group(const MultiGroupDesc &d, bool direct, hipStream_t st);
+void box_solve_group(const MultiGroupDesc &d, hipStream_t st);
 template <typename T>
 void box_solve_multi(const MultiGroupDesc *groups, int ngroups, hipStream_t st);
 

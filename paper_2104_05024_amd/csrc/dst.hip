@@ -895,7 +895,7 @@ struct ModeHook {
 // component 0 plus the pair read from ain2 on the planes in zin.
 // One tile of the pass: tile number id of total (gx tiles per row of the grid of tiles), LDS
 // buffers sbuf (NP * PADM values), slam (M) and ssin (M / 2 + 1).
-template <typename T, int M, int NC, int DIM, int ZM = 0>
+template <typename T, int M, int NC, int DIM, int ZM = 0, typename Sh = LShape<T, M>>
 __device__ __forceinline__ void dst_last_tile(const T *__restrict__ ain, T *__restrict__ a, int64_t P,
                                               int64_t comp_stride, const ModeScale &ms0,
                                               const C2<T> *__restrict__ tw, const T *__restrict__ sp,
@@ -903,7 +903,6 @@ __device__ __forceinline__ void dst_last_tile(const T *__restrict__ ain, T *__re
                                               const PlaneBits &zin, const PlaneBits &zout, C2<T> *sbuf, T *slam,
                                               T *ssin, int64_t id, int64_t total, int gx,
                                               const T *__restrict__ ain2 = nullptr) {
-  using Sh = LShape<T, M>;
   constexpr int N = Sh::N, NP = Sh::NP, NT = Sh::NT, PADM = Sh::PADM;
   constexpr int TX = NC == 2 ? NP : 2 * NP;          // columns per tile
   constexpr int64_t LS = DIM == 3 ? (int64_t)N : 1;  // rows of the last axis step by LS * P
@@ -1864,14 +1863,14 @@ void pass_x_set(const T *in, T *out, const RowSet &set, bool last, int64_t rows,
 // Grouped 2D box solve of G one-component problems of equal size, stored at stride cs in
 // padded layout: one launch per pass for the whole group.
 template <typename T, int M>
-void run_box_group(const MultiGroupDesc &d, bool direct, hipStream_t st) {
+void run_box_group(const MultiGroupDesc &d, hipStream_t st) {
   constexpr int N = M - 1;
   const C2<T> *tw = static_cast<const C2<T> *>(d.tw);
   const T *sp = static_cast<const T *>(d.sp), *src = static_cast<const T *>(d.src);
   T *dst = static_cast<T *>(d.dst);
   const int64_t rows = (int64_t)d.G * N;
   if (d.cs != (int64_t)N * M) throw std::invalid_argument("group stride");
-  if (direct) {
+  if (d.direct) {
     pass_x_set<T, M>(src, dst, d.in, false, rows, tw, sp, st, true);
     LastAxis<T> l;
     l.in = l.out = dst;
@@ -1974,6 +1973,64 @@ __global__ __launch_bounds__((XShape<T, 64>::NT)) void k_dst_x_multi(MultiX<T> m
   }
 }
 
+// The last axis of groups that are not solved by columns: the fused transform pass with one workgroup size for every M
+// (the values per thread are those of a group's own launch, so the results are the same).
+template <typename T>
+struct MultiLast {
+  struct G {
+    T *a;
+    int64_t cs;
+    const ModeScale *msv;
+    const C2<T> *tw;
+    const T *sp;
+    int M, begin, gx, nprob;
+  } g[kMaxMultiGroups];
+  int ng;
+};
+
+template <typename T, int M>
+using MLShape = Shape<T, M, sizeof(T) == 8 ? 2 : 4, column_values(M)>;
+
+template <typename T>
+constexpr int multi_last_sbuf() {
+  return std::max({MLShape<T, 64>::NP * MLShape<T, 64>::PADM, MLShape<T, 128>::NP * MLShape<T, 128>::PADM,
+                   MLShape<T, 256>::NP * MLShape<T, 256>::PADM, MLShape<T, 512>::NP * MLShape<T, 512>::PADM,
+                   MLShape<T, 1024>::NP * MLShape<T, 1024>::PADM});
+}
+
+template <typename T>
+__global__ __launch_bounds__((MLShape<T, 64>::NT)) void k_dst_last_multi(MultiLast<T> mp) {
+  static_assert(MLShape<T, 64>::NT == MLShape<T, 1024>::NT, "one workgroup size for every M");
+  __shared__ C2<T> sbuf[multi_last_sbuf<T>()];
+  __shared__ T slam[1024];
+  __shared__ T ssin[1024 / 2 + 1];
+  const int k = multi_group<T>(mp);
+  const auto &g = mp.g[k];
+  const int64_t b = (int64_t)blockIdx.x - g.begin, total = (int64_t)g.gx * g.nprob;
+  const ModeScale none{};
+  const PlaneBits nob{};
+  switch (g.M) {
+#define KFBI_MULTI_LAST(MM)                                                                                     \
+    case MM:                                                                                                    \
+      dst_last_tile<T, MM, 1, 2, 0, MLShape<T, MM>>(g.a, g.a, MM, g.cs, none, g.tw, g.sp, g.msv, g.cs, nob, nob, \
+                                                    sbuf, slam, ssin, b, total, g.gx);                          \
+      break;
+    KFBI_MULTI_LAST(64) KFBI_MULTI_LAST(128) KFBI_MULTI_LAST(256) KFBI_MULTI_LAST(512) KFBI_MULTI_LAST(1024)
+#undef KFBI_MULTI_LAST
+  }
+}
+
+template <typename T>
+int tile_columns(int M) {   // columns per tile of the merged last-axis pass
+  switch (M) {
+    case 64: return 2 * MLShape<T, 64>::NP;
+    case 128: return 2 * MLShape<T, 128>::NP;
+    case 256: return 2 * MLShape<T, 256>::NP;
+    case 512: return 2 * MLShape<T, 512>::NP;
+    default: return 2 * MLShape<T, 1024>::NP;
+  }
+}
+
 template <typename T>
 int tile_rows(int M) {   // rows per x-pass tile
   switch (M) {
@@ -1988,15 +2045,15 @@ int tile_rows(int M) {   // rows per x-pass tile
 }  // namespace
 
 template <typename T>
-void box_solve_group(const MultiGroupDesc &d, bool direct, hipStream_t st) {
+void box_solve_group(const MultiGroupDesc &d, hipStream_t st) {
   switch (d.Mfft) {
-    case 16: run_box_group<T, 16>(d, direct, st); break;
-    case 32: run_box_group<T, 32>(d, direct, st); break;
-    case 64: run_box_group<T, 64>(d, direct, st); break;
-    case 128: run_box_group<T, 128>(d, direct, st); break;
-    case 256: run_box_group<T, 256>(d, direct, st); break;
-    case 512: run_box_group<T, 512>(d, direct, st); break;
-    case 1024: run_box_group<T, 1024>(d, direct, st); break;
+    case 16: run_box_group<T, 16>(d, st); break;
+    case 32: run_box_group<T, 32>(d, st); break;
+    case 64: run_box_group<T, 64>(d, st); break;
+    case 128: run_box_group<T, 128>(d, st); break;
+    case 256: run_box_group<T, 256>(d, st); break;
+    case 512: run_box_group<T, 512>(d, st); break;
+    case 1024: run_box_group<T, 1024>(d, st); break;
     default: throw std::invalid_argument("unsupported grid size");
   }
 }
@@ -2008,12 +2065,15 @@ void box_solve_multi(const MultiGroupDesc *gd, int ng, hipStream_t st) {
   for (int k = 0; k < ng; ++k) order[k] = k;
   std::sort(order, order + ng, [&](int a, int b) { return gd[a].Mfft > gd[b].Mfft; });
   MultiX<T> x1{}, x2{};
-  int b1 = 0, b2 = 0;
+  MultiLast<T> la{};
+  int b1 = 0, b2 = 0, bl = 0;
   for (int j = 0; j < ng; ++j) {
     const MultiGroupDesc &d = gd[order[j]];
     const int M = d.Mfft, N = M - 1;
     if (M < 64 || M > 1024 || (M & (M - 1)) || d.G < 1 || d.cs != (int64_t)N * M)
       throw std::invalid_argument("merged passes: sizes 64..1024, padded groups");
+    if (d.direct != gd[0].direct || (!d.direct && (d.in.list || d.out.list || d.in.bits || d.out.bits)))
+      throw std::invalid_argument("merged passes: one kind of last axis; row sets need columns");
     const int64_t rows = (int64_t)d.G * N;
     const int tr = tile_rows<T>(M);
     const C2<T> *tw = reinterpret_cast<const C2<T> *>(d.tw);
@@ -2024,20 +2084,25 @@ void box_solve_multi(const MultiGroupDesc *gd, int ng, hipStream_t st) {
     x2.g[j] = {dst, dst, n2, d.out.list, tw, sp, M, b2};
     b1 += (int)((n1 + tr - 1) / tr);
     b2 += (int)((n2 + tr - 1) / tr);
+    const int tc = tile_columns<T>(M), gx = (N + tc - 1) / tc;
+    la.g[j] = {dst, d.cs, d.msv, tw, sp, M, bl, gx, d.G};
+    bl += gx * d.G;
   }
-  x1.ng = x2.ng = ng;
+  x1.ng = x2.ng = la.ng = ng;
   constexpr int NT = XShape<T, 64>::NT;
   if (b1) k_dst_x_multi<T><<<b1, NT, 0, st>>>(x1);
   KFBI_HIP(hipGetLastError());
-  last_axis_direct_multi<T>(gd, ng, st);
+  if (gd[0].direct) last_axis_direct_multi<T>(gd, ng, st);
+  else k_dst_last_multi<T><<<bl, MLShape<T, 64>::NT, 0, st>>>(la);
+  KFBI_HIP(hipGetLastError());
   if (b2) k_dst_x_multi<T><<<b2, NT, 0, st>>>(x2);
   KFBI_HIP(hipGetLastError());
 }
 template void box_solve_multi<double>(const MultiGroupDesc *, int, hipStream_t);
 template void box_solve_multi<float>(const MultiGroupDesc *, int, hipStream_t);
 
-template void box_solve_group<double>(const MultiGroupDesc &, bool, hipStream_t);
-template void box_solve_group<float>(const MultiGroupDesc &, bool, hipStream_t);
+template void box_solve_group<double>(const MultiGroupDesc &, hipStream_t);
+template void box_solve_group<float>(const MultiGroupDesc &, hipStream_t);
 
 template <typename T>
 void box_solve(DevProblem &p, const T *src, bool src_plain, T *dst, bool dst_plain, hipStream_t st) {

@@ -157,3 +157,22 @@ def test_batch():
         for v in sols:
             assert err(v[t], u) < 1e-9
     b.close()
+
+
+def test_batch_members_keep_their_own_route():
+    """A member that needs transforms leaves the others' passes as they are (their products stay the same bits), and
+    merged launches give what one launch per group gives, for both kinds of groups, in FP64 and FP32."""
+    probs = members()
+    free = [i for i, (_, _, co) in enumerate(probs) if co is not ONE2]
+    both, alone = K.Batch(probs), K.Batch([probs[i] for i in free])
+    psi = np.random.default_rng(14).uniform(-1, 1, size=both.L)
+    pick = np.concatenate([psi[both.ioff[i]:both.ioff[i] + both.M[i]] for i in free])
+    for dtype in (torch.float64, torch.float32):
+        a, b = both.apply(dev(psi, dtype)), alone.apply(dev(pick, dtype))
+        for k, i in enumerate(free):
+            assert torch.equal(a[both.ioff[i]:both.ioff[i] + both.M[i]], b[alone.ioff[k]:alone.ioff[k] + alone.M[k]]), i
+        both.merge(False)
+        assert torch.equal(both.apply(dev(psi, dtype)), a)
+        both.merge(True)
+    both.close()
+    alone.close()
