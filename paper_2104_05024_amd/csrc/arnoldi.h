@@ -10,6 +10,16 @@ namespace {
 constexpr int kSmallThreads = 1024, kSmallMax = 5 * kSmallThreads;
 constexpr int kSmallColumn = 66;   // room of a Hessenberg column
 
+// Whether one workgroup orthogonalises a step against K basis vectors of n entries: it reads the basis four times by
+// itself, so from K n = 24,576 on the many-block kernels are faster.  One iteration of a 128^2 problem, one workgroup /
+// many blocks (us): 1,025 entries, 19 vectors 39.5 / 41.1, 30 48.2 / 42.2; 2,049, 7 36.2 / 38.9, 15 45.2 / 40.3; 4,097,
+// 3 35.9 / 38.6, 11 52.8 / 39.1, 56 149 / 54; 513 entries never lose.  batch: one workgroup for each problem, against
+// kernels whose work grows with the problems too: 36,864 entries of the longest (1 problem of 5,120 entries, 7 vectors
+// 48.8 / 47.1; 16 of 2,049, 19 56.9 / 64.3, 30 72.9 / 64.9; 64 of 2,049, 15 68.6 / 68.3, 46 160 / 114).
+constexpr bool one_workgroup(int64_t n, int K, bool batch) {
+  return n <= kSmallMax && (n <= 512 || K * n <= (batch ? 36 : 24) * 1024);
+}
+
 // Both classical Gram-Schmidt passes of w_in against V_0..V_{K-1} (stride ldv), the norm and V_K = w / ||w|| (also
 // into vnext) for n <= 1024 E entries, by one workgroup; the passes' coefficients in hcol.  Returns ||w||^2.
 // Bound by latency, then by what one workgroup reads (the basis four times).

@@ -69,8 +69,8 @@ struct Batch {
   void box_all(bool from_fpad, bool stencils, hipStream_t st);
   void drop_graphs();                              // the captured steps are captured again when next used
   hipStream_t cap = nullptr;           // capture stream (the caller's stream may be the null stream)
-  hipGraphExec_t graph[2] = {nullptr, nullptr};
-  int graph_m[2] = {0, 0};
+  hipGraphExec_t graph[2][2] = {};     // captured steps (precision, one workgroup per problem orthogonalises)
+  int graph_m[2][2] = {};
 
   void init(int n, const kfbi_interface *ifaces, const kfbi_grid *grids, const kfbi_coeffs *coeffs);
   void release();
@@ -82,8 +82,8 @@ struct Batch {
   void matvec(const TP *in, TP *out, hipStream_t st);
   void apply_vec(int prec, const double *in, double *out, hipStream_t st);
   void seg_norms(const double *v, std::vector<double> &out, hipStream_t st);
-  void arnoldi_step(int prec, int m, hipStream_t st);
-  void run_step(int prec, int m, hipStream_t st);
+  void arnoldi_step(int prec, bool small, int m, hipStream_t st);
+  void run_step(int prec, bool small, int m, hipStream_t st);
   void gmres(int prec, const double *b, double *x, bool x_zero, const std::vector<double> &tol, int restart,
              int maxit, std::vector<int> &its, int &matvecs, std::vector<double> &res, hipStream_t st);
   void pack(const double *plain, int which, bool to_padded, hipStream_t st);

@@ -338,11 +338,7 @@ void Batch::init(int n, const kfbi_interface *ifaces, const kfbi_grid *grids, co
 }
 
 void Batch::release() {
-  for (int k = 0; k < 2; ++k)
-    if (graph[k]) {
-      (void)hipGraphExecDestroy(graph[k]);
-      graph[k] = nullptr;
-    }
+  drop_graphs();
   for (Group &g : groups) {
     void *ps[] = {g.rhs64, g.fpad64, g.work64, g.rhs32, g.fpad32, g.work32, g.msv,
                   const_cast<int32_t *>(g.rows_in.list),   const_cast<uint64_t *>(g.rows_in.bits),
@@ -368,11 +364,10 @@ void Batch::release() {
 }
 
 void Batch::drop_graphs() {
-  for (int k = 0; k < 2; ++k)
-    if (graph[k]) {
-      (void)hipGraphExecDestroy(graph[k]);
-      graph[k] = nullptr;
-      graph_m[k] = 0;
+  for (auto &kind : graph)
+    for (hipGraphExec_t &e : kind) {
+      if (e) (void)hipGraphExecDestroy(e);
+      e = nullptr;
     }
 }
 
@@ -427,10 +422,10 @@ void Batch::seg_norms(const double *v, std::vector<double> &out, hipStream_t st)
   for (int p = 0; p < np; ++p) out[p] = std::sqrt(std::max(0.0, hhost[p]));
 }
 
-void Batch::arnoldi_step(int prec, int m, hipStream_t st) {
+void Batch::arnoldi_step(int prec, bool small, int m, hipStream_t st) {
   const int ld = kMaxRestart + 1;
   apply_vec(prec, vin, w, st);
-  if (longest <= kSmallMax) {
+  if (small) {
     switch ((longest + kSmallThreads - 1) / kSmallThreads) {
 #define KFBI_SMALL(EE)                                                                                           \
   case EE:                                                                                                       \
@@ -460,31 +455,32 @@ void Batch::host_wait(hipStream_t st) {
   seq_next = poll_step_counter(seqhost, seq_next + 1, st);
 }
 
-void Batch::run_step(int prec, int m, hipStream_t st) {
+void Batch::run_step(int prec, bool small, int m, hipStream_t st) {
   if (!use_graph) {
-    arnoldi_step(prec, m, st);
+    arnoldi_step(prec, small, m, st);
     return;
   }
-  if (!graph[prec] || graph_m[prec] != m) {
-    if (graph[prec]) (void)hipGraphExecDestroy(graph[prec]);
-    graph[prec] = nullptr;
+  hipGraphExec_t &exec = graph[prec][small];
+  if (!exec || graph_m[prec][small] != m) {
+    if (exec) (void)hipGraphExecDestroy(exec);
+    exec = nullptr;
     // captured on the batch's own stream, replayed on the caller's
     hipGraph_t g = nullptr;
     KFBI_HIP(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
     try {
-      arnoldi_step(prec, m, cap);
+      arnoldi_step(prec, small, m, cap);
     } catch (...) {
       (void)hipStreamEndCapture(cap, &g);
       if (g) (void)hipGraphDestroy(g);
       throw;
     }
     KFBI_HIP(hipStreamEndCapture(cap, &g));
-    const hipError_t e = hipGraphInstantiate(&graph[prec], g, nullptr, nullptr, 0);
+    const hipError_t e = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
     KFBI_HIP(e);
-    graph_m[prec] = m;
+    graph_m[prec][small] = m;
   }
-  KFBI_HIP(hipGraphLaunch(graph[prec], st));
+  KFBI_HIP(hipGraphLaunch(exec, st));
 }
 
 // GMRES(m) on A x = b for every problem at once; tol[p] absolute; x updated in place.
@@ -521,7 +517,7 @@ void Batch::gmres(int prec, const double *b, double *xv, bool x_zero, const std:
     k_seg_scale<<<nb(L), kB, 0, st>>>(r, sdev, pid, V, vin, jdev, L);
     KFBI_HIP(hipGetLastError());
     for (int j = 0; j < m && total < maxit; ++j) {
-      run_step(prec, m, st);
+      run_step(prec, one_workgroup(longest, j + 1, true), m, st);
       ++matvecs;
       ++total;
       seq_next = poll_step_counter(seqhost, seq_next + 1, st);   // the step ends with the counter

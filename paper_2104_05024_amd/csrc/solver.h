@@ -21,7 +21,8 @@ struct Solver {
   double *meandev = nullptr;   // gauge mean of the last solve
   int64_t n_inside = 0;
   int8_t *inside_plain = nullptr;
-  // captured Arnoldi step (per precision of the product), replayed every GMRES iteration
+  // captured Arnoldi steps (by precision of the product, and whether one workgroup orthogonalises), replayed every
+  // GMRES iteration
   bool use_graph = true;
   double *vin = nullptr, *wv = nullptr;
   int *jdev = nullptr;
@@ -34,13 +35,13 @@ struct Solver {
   // kernel, polled; errors are reported through the stream synchronisation it falls back to)
   void host_wait(hipStream_t st);
   hipStream_t cap = nullptr;
-  hipGraphExec_t graph[2] = {nullptr, nullptr};
-  int graph_m[2] = {0, 0};
-  void arnoldi_step(DevProblem &p, int prec, int m, hipStream_t st);
+  hipGraphExec_t graph[2][2] = {};
+  int graph_m[2][2] = {};
+  void arnoldi_step(DevProblem &p, int prec, bool small, int m, hipStream_t st);
   void orthogonalise(double *w, const int *jd, int j, int m, double *vnext, hipStream_t st);
   void orthogonalise_small(const double *w, bool step, int j, double *vnext, hipStream_t st);
   void finish_host(int K, hipStream_t st);
-  void run_step(DevProblem &p, int prec, int m, hipStream_t st);
+  void run_step(DevProblem &p, int prec, bool small, int m, hipStream_t st);
 
   void init(DevProblem &p);
   void release();

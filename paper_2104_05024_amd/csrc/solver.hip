@@ -387,10 +387,10 @@ void Solver::init(DevProblem &p) {
 }
 
 void Solver::release() {
-  for (int k = 0; k < 2; ++k)
-    if (graph[k]) {
-      (void)hipGraphExecDestroy(graph[k]);
-      graph[k] = nullptr;
+  for (auto &kind : graph)
+    for (hipGraphExec_t &e : kind) {
+      if (e) (void)hipGraphExecDestroy(e);
+      e = nullptr;
     }
   if (cap) (void)hipStreamDestroy(cap);
   cap = nullptr;
@@ -487,9 +487,9 @@ void Solver::orthogonalise_small(const double *w, bool step, int j, double *vnex
 // One Arnoldi step with j read from device memory (so one captured graph serves every j):
 // w = A v for v = V_j (held in vin), two classical Gram-Schmidt passes against V_0..V_j, the
 // norm, V_{j+1} (also into vin), the Hessenberg column to pinned host memory, j <- j + 1.
-void Solver::arnoldi_step(DevProblem &p, int prec, int m, hipStream_t st) {
+void Solver::arnoldi_step(DevProblem &p, int prec, bool small, int m, hipStream_t st) {
   apply_vec(p, prec, vin, wv, st);
-  if (L <= kSmallMax) {
+  if (small) {
     orthogonalise_small(wv, true, 0, vin, st);
     return;
   }
@@ -518,26 +518,27 @@ int poll_step_counter(const int *seq_host, int expect, hipStream_t st) {
 void Solver::wait_step(hipStream_t st) { seq_next = poll_step_counter(seqhost, seq_next + 1, st); }
 
 // Replays the captured Arnoldi step (captured on first use on the solver's own stream).
-void Solver::run_step(DevProblem &p, int prec, int m, hipStream_t st) {
-  if (!graph[prec] || graph_m[prec] != m) {
-    if (graph[prec]) (void)hipGraphExecDestroy(graph[prec]);
-    graph[prec] = nullptr;
+void Solver::run_step(DevProblem &p, int prec, bool small, int m, hipStream_t st) {
+  hipGraphExec_t &exec = graph[prec][small];
+  if (!exec || graph_m[prec][small] != m) {
+    if (exec) (void)hipGraphExecDestroy(exec);
+    exec = nullptr;
     hipGraph_t g = nullptr;
     KFBI_HIP(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
     try {
-      arnoldi_step(p, prec, m, cap);
+      arnoldi_step(p, prec, small, m, cap);
     } catch (...) {
       (void)hipStreamEndCapture(cap, &g);
       if (g) (void)hipGraphDestroy(g);
       throw;
     }
     KFBI_HIP(hipStreamEndCapture(cap, &g));
-    const hipError_t e = hipGraphInstantiate(&graph[prec], g, nullptr, nullptr, 0);
+    const hipError_t e = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
     KFBI_HIP(e);
-    graph_m[prec] = m;
+    graph_m[prec][small] = m;
   }
-  KFBI_HIP(hipGraphLaunch(graph[prec], st));
+  KFBI_HIP(hipGraphLaunch(exec, st));
 }
 
 int Solver::gmres(DevProblem &p, const double *b, double bnorm, double *x, bool x_zero, double tol_abs, int restart,
@@ -587,13 +588,14 @@ int Solver::gmres(DevProblem &p, const double *b, double bnorm, double *x, bool 
       // relaxed: FP32 products once the current (Givens) residual is below sw_abs
       const int pj = a.relax ? (std::fabs(g[j]) <= a.sw_abs ? 1 : 0) : a.prec;
       any32 = any32 || pj == 1;
+      const bool small = one_workgroup(L, j + 1, false);
       if (graphed) {
-        run_step(p, pj, m, st);
+        run_step(p, pj, small, m, st);
       } else {
         const double *vj = V + (int64_t)j * L;
         double *vn = V + (int64_t)(j + 1) * L;
         apply_vec(p, pj, vj, vn, st);
-        if (L <= kSmallMax) orthogonalise_small(vn, false, j, nullptr, st);
+        if (small) orthogonalise_small(vn, false, j, nullptr, st);
         else orthogonalise(vn, nullptr, j, m, nullptr, st);
       }
       count(pj);
