@@ -502,13 +502,14 @@ void Batch::gmres(int prec, const double *b, double *xv, bool x_zero, const std:
   for (int p = 0; p < np; ++p) active[p] = beta[p] > tol[p];
   std::vector<double> H((size_t)np * (m + 1) * m), cs((size_t)np * m), sn((size_t)np * m), g((size_t)np * (m + 1));
   std::vector<int> jend(np);
-  std::vector<char> done(np);
+  std::vector<char> done(np), broke(np);   // broke: the last column gave nothing (breakdown)
   std::vector<double> s(np), yh((size_t)m * np);
   int total = 0;
   while (total < maxit && std::any_of(active.begin(), active.end(), [](char a) { return a; })) {
     for (int p = 0; p < np; ++p) {
       s[p] = active[p] ? 1.0 / beta[p] : 0.0;
       done[p] = !active[p];
+      broke[p] = 0;
       jend[p] = 0;
       std::fill(&g[(size_t)p * (m + 1)], &g[(size_t)p * (m + 1)] + m + 1, 0.0);
       g[(size_t)p * (m + 1)] = active[p] ? beta[p] : 0.0;
@@ -545,7 +546,8 @@ void Batch::gmres(int prec, const double *b, double *xv, bool x_zero, const std:
         gp_[j] = c_[j] * gp_[j];
         jend[p] = j + 1;
         its[p] += 1;
-        if (std::fabs(gp_[j + 1]) <= tol[p] || den == 0.0) done[p] = 1;
+        broke[p] = den == 0.0;
+        if (std::fabs(gp_[j + 1]) <= tol[p] || broke[p]) done[p] = 1;
         else all = false;
       }
       if (all) break;
@@ -574,10 +576,11 @@ void Batch::gmres(int prec, const double *b, double *xv, bool x_zero, const std:
     }
     // An FP32 inner solve ends on its Arnoldi-relation residual, as the single solver's does: the refinement takes
     // the FP64 residual itself, and a check by an FP32 product, near its rounding for large coupled or fine
-    // problems, restarts by luck (64 problems: 19 or 54 FP32 products, from one problem alone).
+    // problems, restarts by luck (64 problems: 19 or 54 FP32 products, from one problem alone).  After a breakdown
+    // the relation's residual is zero for a column that was left out, so those problems are checked.
     if (prec == 1) {
       for (int p = 0; p < np; ++p) {
-        if (!active[p] || jend[p] == 0) continue;
+        if (!active[p] || jend[p] == 0 || broke[p]) continue;
         beta[p] = std::fabs(g[(size_t)p * (m + 1) + jend[p]]);
         active[p] = beta[p] > tol[p];
       }
