@@ -289,9 +289,9 @@ def variant_kwargs(name, a):
     }[name]
 
 
-KERNELS = ("dst_x", "dst_y", "dst_last", "dst_x_rows", "dst_y_sparse", "dst_last_sparse", "dst_last_out",
-           "dst_x_fhn", "dst_x_fe1", "dst_y1", "dst_last_anti", "dst_last_diff", "dst_last_comb", "dst_x_be1", "jumps",
-           "correct", "gather")
+KERNELS = ("dst_x", "dst_y", "dst_last", "dst_x_correct", "dst_x_rows", "dst_y_sparse", "dst_last_sparse",
+           "dst_last_out", "dst_x_fhn", "dst_x_fe1", "dst_y1", "dst_last_anti", "dst_last_diff", "dst_last_comb",
+           "dst_x_be1", "correct", "gather")
 
 
 def main():
@@ -408,10 +408,12 @@ def main():
     # passes (dst_x, dst_y, dst_last) read and write the whole coupled field.  The matvec's z pass
     # (dst_last_sparse) reads only the z planes holding irregular nodes and writes only those holding
     # extrapolation-stencil nodes; the volume solve's z pass (dst_last_out) reads every plane and
-    # writes the stencil planes.  The row-list x pass (dst_x_rows) reads and writes the rows holding
-    # irregular nodes (forward) or stencil nodes (inverse); the masked y pass (dst_y_sparse) reads the
+    # writes the stencil planes.  A product's first row pass (dst_x_correct) reads the arms' tables (12
+    # density indices and positions, 10 weights per component) and writes the rows holding irregular nodes; the
+    # row-list x pass (dst_x_rows) reads and writes the rows holding stencil nodes, in the final solve of a step
+    # also those holding irregular nodes (priced by how many of each ran); the masked y pass (dst_y_sparse) reads the
     # irregular rows and writes whole planes that hold any (forward), or reads whole stencil planes
-    # and writes the stencil rows (inverse); each is priced per launch as the mean of its two forms.
+    # and writes the stencil rows (inverse), priced per launch as the mean of the two.
     # The x passes of a step's box solves that carry the reaction (dst_x_fhn) are priced as the mean
     # of: forward Euler + source (V, q read, the pair written), source + correction (V, q and the
     # correction rows read, the pair written) and inverse + backward Euler (the pair, V and q read,
@@ -432,10 +434,12 @@ def main():
     stl = prob.table("st_lin")
     planes_in, planes_out = len(np.unique(irr // (N * N))), len(np.unique(stl // (N * N)))
     rows_in, rows_out = nc * len(np.unique(irr // N)), nc * len(np.unique(stl // N))
+    n_cross, n_fwd, n_rows = prob.n_crossings, kt[ref]["dst_last_comb"][1], kt[ref]["dst_x_rows"][1]
     algo_of = {"dst_x": 2.0 * field_bytes, "dst_y": 2.0 * field_bytes, "dst_last": 2.0 * field_bytes,
                "dst_last_sparse": float(nc * N * N * 8 * (planes_in + planes_out)),
                "dst_last_out": float(field_bytes + nc * N * N * 8 * planes_out),
-               "dst_x_rows": float((rows_in + rows_out) * N * 8),
+               "dst_x_correct": float(2 * n_cross * (12 * 4 + nc * 10 * 8) + rows_in * N * 8),
+               "dst_x_rows": float((2 * rows_out + n_fwd / max(n_rows, 1) * 2 * (rows_in - rows_out)) * N * 8),
                "dst_y_sparse": float(((rows_in * N + planes_in * nc * N * N) + (planes_out * nc * N * N + rows_out * N))
                                      * 8 / 2),
                "dst_x_fe1": 1.5 * field_bytes, "dst_y1": float(field_bytes),
@@ -487,7 +491,6 @@ def main():
         if "plain" in results else None,
         "roofline": roof,
         "setup_s": round(setup_s, 2),
-        "autotuned_tile_widths": {"f64": list(prob.tiles(K.KFBI_F64)), "f32": list(prob.tiles(K.KFBI_F32))},
     }
     prob.close()
     if not a.no_batch and not a.profile_run:

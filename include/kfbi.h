@@ -364,8 +364,9 @@ const char *kfbi_last_error(void);
 
 /* Timing of the kernel launches on the problem's stream since profiling was enabled, measured
  * with HIP events around each launch: average microseconds and launch count for the named
- * kernel class ("dst_x", "dst_y", "dst_last" (dense passes), "dst_x_rows", "dst_y_sparse",
- * "dst_last_sparse" (row- and plane-masked passes of the matrix-vector product), "dst_last_out"
+ * kernel class ("dst_x", "dst_y", "dst_last" (dense passes; the last axis by columns or
+ * transforms), "dst_x_correct", "dst_x_rows", "dst_y_sparse", "dst_last_sparse" (a product's first
+ * row pass, which forms the correction, and its row- and plane-masked passes), "dst_last_out"
  * (the z pass of the volume solve whose result is read only at the interface stencils: every
  * plane read, stencil planes written), "dst_x_fhn" (the x passes of a bidomain step's box solves
  * that also carry its reaction half steps), "dst_x_fe1", "dst_y1", "dst_last_anti" (the volume
@@ -376,12 +377,15 @@ const char *kfbi_last_error(void);
  * update over that one field; its inverse y pass counts under "dst_y1"), "dst_last_comb" (that
  * z pass when the step also has no stimulus current: it adds the transform of C psi, taken
  * through the masked row and plane passes, to the volume solve's transform of kappa V1 as it
- * loads), "correct", "gather", "jumps" (no launches: the jumps are part of "correct" and "gather")).
+ * loads), "correct" (products below 64 cells, whose correction is a launch of its own), "gather",
+ * "jumps" (no launches: the jumps are part of the correction and of "gather")).  Profiling launches
+ * GMRES steps directly instead of replaying captured ones; the kernels and their results are the
+ * same.
  * Returns KFBI_EINVAL if the name is unknown. */
 int kfbi_kernel_time(kfbi_problem p, const char *kernel, double *avg_us, int64_t *launches);
 /* DST tile widths (1 or 2) of the x, y and last-axis passes for dtype KFBI_F64 / KFBI_F32: 1 after
- * setup, or what kfbi_set_tiles stored.  Every pass has one tile shape (the wider one was within 3%
- * of it at best), so the widths have no effect. */
+ * setup, or what kfbi_set_tiles stored.  Every pass has one tile shape at each size and type, so the
+ * widths have no effect. */
 int kfbi_get_tiles(kfbi_problem p, int32_t dtype, int32_t widths[3]);
 /* GMRES iterations of kfbi_solve_neumann / bidomain_step replay one captured Arnoldi step
  * (a hipGraph holding the product, both Gram-Schmidt passes, the norm and the next basis

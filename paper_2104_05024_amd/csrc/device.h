@@ -152,7 +152,7 @@ struct DevProblem {
   int tile_w[2][3] = {{1, 1, 1}, {1, 1, 1}};
 
   bool profile = false;
-  Timer t_dst_x, t_dst_y, t_dst_last, t_correct, t_gather, t_jumps, t_dst_x_rows, t_dst_y_sparse, t_dst_last_sparse,
+  Timer t_dst_x, t_dst_y, t_dst_last, t_correct, t_gather, t_dst_x_correct, t_dst_x_rows, t_dst_y_sparse, t_dst_last_sparse,
       t_dst_last_out, t_dst_x_fhn, t_dst_x_fe1, t_dst_y1, t_dst_last_anti, t_dst_last_diff, t_dst_x_be1,
       t_dst_last_comb;
   hipStream_t stream = nullptr;

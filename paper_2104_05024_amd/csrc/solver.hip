@@ -414,9 +414,8 @@ void Solver::release() {
 
 template <typename T, typename TP>
 void Solver::apply(DevProblem &p, const TP *psi, TP *out, hipStream_t st) {
-  // The first row pass forms the correction itself.  With profiling on the two are launched apart, each timed as
-  // its own class; a grid or last axis without the row lists' passes takes them apart too.
-  const bool fused = !p.profile && p.sparse && p.Mfft >= 64 && (p.dim == 3 || p.direct);
+  // The first row pass forms the correction itself, but on grids and last axes without the row lists' passes.
+  const bool fused = p.sparse && p.Mfft >= 64 && (p.dim == 3 || p.direct);
   if (!fused) {
     p.t_correct.tic(p.profile, st);
     launch_correct<T, TP>(p, psi, st);

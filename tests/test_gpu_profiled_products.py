@@ -1,0 +1,49 @@
+"""Profiling times the kernels that a product runs: switching it on changes no bit of the product.  And the FP32 product
+of the kernels that hold the correction, against the FP64 product of the same density, at every size and component
+count (256^3 and the coupled 512^2 among them).  FP32 tolerance: 6e-8 of the largest value from the rounding of the grid
+values, which the extrapolated gradient's differences over h magnify in proportion to the cells: 6e-8 times the cells."""
+import numpy as np
+import pytest
+
+from paper_2104_05024_amd import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2104_05024_amd import kfbi as K  # noqa: E402
+
+PAIR2 = W.bidomain_coeffs(2, W.BidomainParams(), 0.01)
+PAIR3 = W.Coeffs(2, [[3.0, 0.5, 0.5], [2.0, 1.0, 1.0]], 200.0)
+CASES = {
+    "2d_32": (W.circle2d(0.6, 31), W.box(2, 32), PAIR2, "correct"),
+    "2d_64": (W.circle2d(0.6, 63), W.box(2, 64), W.scalar_coeffs(2, 1.0, 50.0), "dst_x_correct"),
+    "2d_256": (W.star2d(n_nodes=301), W.box(2, 256), W.scalar_coeffs(2, 1.0, 400.0), "dst_x_correct"),
+    "2d_512_pair": (W.circle2d(0.5, 333), W.box(2, 512), PAIR2, "dst_x_correct"),
+    "2d_1024": (W.circle2d(0.4, 301), W.box(2, 1024), W.scalar_coeffs(2, 1.0, 400.0), "dst_x_correct"),
+    "3d_64_pair": (W.sphere(0.6, 997), W.box(3, 64), PAIR3, "dst_x_correct"),
+    "3d_128": (W.sphere(0.7, 997), W.box(3, 128), W.scalar_coeffs(3, 1.0, 400.0), "dst_x_correct"),
+    "3d_256": (W.sphere(0.4, 997), W.box(3, 256), W.scalar_coeffs(3, 1.0, 400.0), "dst_x_correct"),
+    "3d_256_pair": (W.sphere(0.3, 997), W.box(3, 256), PAIR3, "dst_x_correct"),
+    "last_axis_64": (W.sphere(0.6, 997), W.box(3, 64), W.Coeffs(1, [[1.0, 1.0, 6.0]], 0.5), "dst_x_correct"),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_product(name):
+    iface, grid, co, kernel = CASES[name]
+    print(f"[profiled products] {name}", flush=True)
+    p = K.Problem(iface, grid, co)
+    psi = torch.tensor(np.random.default_rng(9).uniform(-1, 1, size=(co.ncomp, p.M)), device="cuda")
+    out = {}
+    for x in (psi, psi.float()):
+        out[x.dtype] = p.apply(x)
+        p.profile(True)
+        timed = p.apply(x)
+        launches = p.kernel_time(kernel)[1]
+        p.profile(False)
+        assert launches == 1 and torch.equal(timed, out[x.dtype]), x.dtype
+    ref = out[torch.float64]
+    assert float((out[torch.float32].double() - ref).abs().max()) <= 6e-8 * grid.cells * float(ref.abs().max())
+    p.close()
