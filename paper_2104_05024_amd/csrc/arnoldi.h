@@ -98,7 +98,9 @@ __device__ __forceinline__ double orthogonalise_block(double *V, int64_t ldv, co
 
 // End of an Arnoldi step whose coefficients are in device memory ([pass][ld][np], then np squared norms): those of
 // the j + 1 vectors into pinned host memory, j <- j + 1, the step counter.  One wavefront, since a system fence by
-// many writes the L2 back many times.
+// many writes the L2 back many times.  Its time grows with problems and vectors; against a copy of the whole array and a
+// counter kernel an iteration of 1,024 problems takes 72 us, not 156 (6 vectors), 132, not 196 (61), of 2,048 225, not 418
+// (61).
 __global__ __launch_bounds__(64) void k_end_step(const double *__restrict__ h, double *__restrict__ host, int ld,
                                                  int np, int *j, int *seq, int *seq_host) {
   const int K = *j + 1, lane = threadIdx.x;

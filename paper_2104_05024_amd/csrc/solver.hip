@@ -282,7 +282,7 @@ __global__ __launch_bounds__(kB) void k_recycled_resid(double *__restrict__ r, c
 // End of a bidomain step: g'^{n-1} <- g'^n, the density history shifts by one step, the context
 // keeps its own copy of the new density, and the mismatch flag of the next recycled residual is
 // cleared.
-__global__ __launch_bounds__(kB) void k_end_step(double *__restrict__ gp_prev, const double *__restrict__ gp,
+__global__ __launch_bounds__(kB) void k_end_bidomain_step(double *__restrict__ gp_prev, const double *__restrict__ gp,
                                                  double *__restrict__ hist2, double *__restrict__ hist1,
                                                  double *__restrict__ psi_last, const double *__restrict__ psi,
                                                  int *__restrict__ bad, int64_t n) {
@@ -1138,7 +1138,7 @@ int bidomain_s::step(bidomain_state &s, double dt, kfbi_solve_info &info, hipStr
     if (params.warm_start == 4) mlp_note_cost(this, info.matvecs_fp64 + 0.5 * info.matvecs_fp32, learned_dir);
   }
   ++steps_done;
-  k_end_step<<<nblk(L), kB, 0, st>>>(gp_prev, sv.gp, hist2, hist1, psi_last, psi0, r0_bad_dev, L);
+  k_end_bidomain_step<<<nblk(L), kB, 0, st>>>(gp_prev, sv.gp, hist2, hist1, psi_last, psi0, r0_bad_dev, L);
   KFBI_HIP(hipGetLastError());
   sv.host_wait(st);
   have_prev = true;
