@@ -1046,8 +1046,9 @@ __global__ __launch_bounds__((XShape<T, M, E>::NT)) void k_dst_x_rows(const T *_
 // the irregular nodes' values, each the sum of its arms' terms (arm slots are sorted by node, so a tile's slots are
 // one range per component; the arms of a node lie within 64 slots and their first adds up the others', as where the
 // correction is a launch of its own).  The field of corrections is neither written nor read, and a launch goes.
-// Bound by the arms' tables (240 bytes an arm of a coupled 3D pair) and LDS.  Correction and row pass / fused: coupled
-// 256^3 shell FP64 product 219.3 -> 212.5 us, 2D star 128 22.6 -> 17.2, coupled 2D 512 26.2 -> 25.0; alike at 128^3.
+// Bound by memory: at the coupled 256^3 shell 152 MB read (212 bytes an arm; a tile reads whole groups of 64, about 1.8
+// times its own) and 63 MB of rows written in 42 us, 5.1 TB/s.  Correction and row pass apart / together: that FP64
+// product 219.3 / 212.5 us, 2D star 128 22.6 / 18.8, coupled 2D 512 26.2 / 25.0; alike at 128^3.
 template <typename T, typename TP, int M, int E, int D, int K>
 __global__ __launch_bounds__(64) void k_dst_x_correct(InterfaceTables t, const TP *__restrict__ psi, int64_t nd,
                                                       T *__restrict__ out, const int32_t *__restrict__ rows, int per,
@@ -1448,8 +1449,8 @@ __global__ __launch_bounds__((FShape<M>::NT)) void k_dst_x_be1(FhnArgs a, const 
 // x pass over `rows` contiguous rows (padded in/out unless stated)
 // Values per thread of an x pass: 4 where it is short (2D, or few rows), 16 for the long ones of 512 cells; a batch's
 // group always takes row_values, as its passes merged with other groups' do.
-// Long dense passes of 256 cells in FP32 take 16 as well (inverse pass of a 256^3 pair 53.1 -> 47.8 us), listed rows do
-// not (the coupled FP32 product would take 143 us, not 129.7).
+// Long dense passes of 256 cells in FP32 take 16 as well (box solve of a 256^3 pair 239 -> 231 us), listed rows do not
+// (scalar FP32 product 81.7 us, 83.4 with 16).
 template <typename T, int M, typename F>
 void with_row_values(int64_t rows, bool group, bool dense, const F &f) {
   if constexpr (M == 128 || M == 256) {

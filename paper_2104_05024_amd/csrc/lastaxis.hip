@@ -17,13 +17,12 @@
 //    through LDS, one thread per system and direction turns them into the values entering the
 //    chunks, and every thread runs the two recursions over its rows in registers.
 //
-// What bounds it: memory for the dense form, one read and one write (256^3 pair FP64: 531 MB in
-// 82.8 us, 6.4 TB/s, where the fused DST pass took 141.9 us); about half and half memory and FP64
-// issue for the masked one (272.6 MB in 66.4 us, DST 142.4 us), 16 rows and some 1,300 instructions
-// per thread.  The column's constants and the values entering its chunks are worked out once per
-// column, not by every chunk's thread (72.4 us before).  16 rows per thread: the pair's rows take
-// 64 registers, four waves fit a SIMD, and 16 columns by 16 chunks are a workgroup of 256 threads
-// over whole 128-byte lines.  FP32, scalar 256^3, masked: 38.5 -> 19.4 us.
+// What bounds it: memory, one read and one write.  256^3 pair in FP64: dense 531 MB in 84 us (6.3 TB/s; the fused
+// transform pass took 142), masked 273 MB in 46 us (5.9 TB/s; 130, and 66 here before a product's passes worked in one
+// field).  The masked form issues 685 vector instructions per wavefront in 14% of its cycles, and waits for memory in
+// 35%.  The column's constants and the values entering its chunks are worked out once per column, not by every chunk's
+// thread (15% slower).  16 rows per thread: the pair's rows take 64 registers, four waves fit a SIMD, and 16 columns by
+// 16 chunks are a workgroup of 256 threads over whole 128-byte lines.  FP32, scalar 256^3, masked: 38.5 -> 19.4 us.
 //
 // The recursions use delta = 1 - mu (from s without cancellation; mu^n likewise through
 // 1 - mu^{2n} = delta_n (2 - delta_n)): with mu itself, its rounding alone would cost M eps in the
