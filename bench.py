@@ -122,9 +122,9 @@ def measured_traffic(kernel):
     source has changed since the counters were taken."""
     import hashlib
     path = os.path.join(ROOT, "profiles", "pmc_traffic_dst_fp64_shell256.txt")
-    src = os.path.join(ROOT, "paper_2104_05024_amd", "csrc", "dst.hip")
+    src = [os.path.join(ROOT, "paper_2104_05024_amd", "csrc", f) for f in ("dst.hip", "lastaxis.hip")]
     try:
-        sha = hashlib.sha256(open(src, "rb").read()).hexdigest()
+        sha = hashlib.sha256(b"".join(open(f, "rb").read() for f in src)).hexdigest()
         for line in open(path):
             f = line.split()
             if len(f) == 5 and f[0] == "bench-traffic" and f[1] == kernel:
