@@ -352,7 +352,7 @@ int kfbi_batch_graph(kfbi_batch b, int32_t enable);
 /* enable != 0 (default): each pass of the box solves is one launch over all groups of 64..1024
  * cells together (the tiles of small grids run beside those of large ones), one for the problems
  * whose last axis is solved by columns and one for those that need transforms (a last axis that
- * conducts more than about 1.6 times the other); 0: one launch per group and pass.  Results are
+ * conducts more than about five times the other); 0: one launch per group and pass.  Results are
  * identical.  Waits for the batch's capture stream; the captured Arnoldi steps are captured again
  * at their next use. */
 int kfbi_batch_merge(kfbi_batch b, int32_t enable);

@@ -21,7 +21,7 @@ struct Group {
   double *rhs64 = nullptr, *fpad64 = nullptr, *work64 = nullptr;
   float *rhs32 = nullptr, *fpad32 = nullptr, *work32 = nullptr;
   ModeParams *msv = nullptr;   // per-slot mode parameters (device)
-  bool direct = true;                          // the members' last axis is solved directly
+  ColumnRule columns;                          // whether the members' last axis is solved by columns
   RowSet rows_in, rows_out;                    // rows of the members that hold irregular / stencil nodes
   template <typename T>
   T *rhs() const;

@@ -10,8 +10,8 @@
 //   * GMRES(m) for all problems in lockstep on concatenated vectors [problem][M_p]: per-problem
 //     dot products, Gram-Schmidt (two passes), norms and basis updates are segment kernels;
 //     the Givens least-squares updates run on the host, one synchronisation per iteration.
-//     One Arnoldi step (copy of v_j, the batched product, both Gram-Schmidt passes, the norm,
-//     v_{j+1}, the copy of the new Hessenberg column to pinned host memory and j <- j + 1)
+//     One Arnoldi step (the batched product, both Gram-Schmidt passes, the norm, v_{j+1}, the
+//     new Hessenberg column to pinned host memory and j <- j + 1)
 //     reads j from device memory, so a single hipGraph serves every iteration; it is
 //     captured on first use and replayed.
 //   * mixed precision as for one problem: FP64 residuals and refinement, FP32-operator inner
@@ -192,20 +192,20 @@ void Batch::init(int n, const kfbi_interface *ifaces, const kfbi_grid *grids, co
   }
   // groups by size and by kind of last axis: a member whose last axis is not solved by columns leaves the others'
   // passes as they are
-  std::vector<std::pair<int, bool>> kinds;
-  for (auto &p : probs) kinds.emplace_back((int)p->Mfft, p->direct);
+  std::vector<std::pair<int, ColumnRule>> kinds;
+  for (auto &p : probs) kinds.emplace_back((int)p->Mfft, p->columns);
   std::sort(kinds.begin(), kinds.end());
   kinds.erase(std::unique(kinds.begin(), kinds.end()), kinds.end());
   group_of.assign(n, 0);
   slot_of.assign(n, 0);
-  for (const auto &[s, direct] : kinds) {
+  for (const auto &[s, columns] : kinds) {
     Group g;
     g.Mfft = s;
-    g.direct = direct;
+    g.columns = columns;
     g.N = s - 1;
     g.cs = (int64_t)g.N * s;
     for (int i = 0; i < n; ++i)
-      if (probs[i]->Mfft == s && probs[i]->direct == direct) {
+      if (probs[i]->Mfft == s && probs[i]->columns == columns) {
         group_of[i] = (int)groups.size();
         slot_of[i] = (int)g.members.size();
         g.members.push_back(i);
@@ -381,16 +381,16 @@ void Batch::box_all(bool from_fpad, bool stencils, hipStream_t st) {
     const T *src;
     if constexpr (sizeof(T) == 8) src = from_fpad ? g.fpad64 : g.rhs64;
     else src = from_fpad ? g.fpad32 : g.rhs32;
-    const bool listed = g.direct && sets;
-    return MultiGroupDesc{g.Mfft, (int)g.members.size(), g.direct, g.cs, src, g.work<T>(), g.msv, tb.tw, tb.sp,
+    const bool direct = g.columns.of<T>(), listed = direct && sets;
+    return MultiGroupDesc{g.Mfft, (int)g.members.size(), direct, g.cs, src, g.work<T>(), g.msv, tb.tw, tb.sp,
                           !from_fpad && listed ? g.rows_in : RowSet{}, stencils && listed ? g.rows_out : RowSet{}};
   };
   for (bool direct : {true, false}) {
     MultiGroupDesc d[kMaxMultiGroups];
     int k = 0;
     for (const Group &g : groups) {
-      if (g.direct != direct) continue;
-      if (merged && g.Mfft >= 64) d[k++] = desc(g);   // at most the five sizes 64..1024
+      if (g.columns.of<T>() != direct) continue;
+      if (merged && g.Mfft >= 64) d[k++] = desc(g);   // at most the five sizes 64..1024 (one rule for both types)
       else box_solve_group<T>(desc(g), st);
     }
     if (k > 1) box_solve_multi<T>(d, k, st);

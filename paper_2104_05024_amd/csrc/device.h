@@ -111,6 +111,17 @@ struct RowSet {
 // A batch of 64 (64..1024 cells): x pass 38 -> 30 us and last axis 45 -> 37 in FP32, 72 -> 61 and 60 -> 54 in FP64.
 inline bool row_sets_pay(int64_t bytes) { return bytes >= 4000000; }
 
+// Whether box solves take the last axis as tridiagonal columns (column_direct), by type.
+struct ColumnRule {
+  bool f64 = false, f32 = false;
+  template <typename T>
+  bool of() const {
+    return sizeof(T) == 8 ? f64 : f32;
+  }
+  bool operator==(const ColumnRule &o) const { return f64 == o.f64 && f32 == o.f32; }
+  bool operator<(const ColumnRule &o) const { return f64 != o.f64 ? f64 < o.f64 : f32 < o.f32; }
+};
+
 struct DevProblem {
   HostTables ht;
   bool on_device = false;
@@ -127,7 +138,7 @@ struct DevProblem {
   // sparse matvec box solve: rows of the flattened [comp][z][y] row list that carry irregular
   // nodes (in) / extrapolation-stencil nodes (out), and their [z][y] bits
   bool sparse = true;
-  bool direct = false;         // last axis as tridiagonal systems (column_direct) instead of DSTs
+  ColumnRule columns;          // whether the last axis is solved as tridiagonal systems instead of by DSTs
   int32_t *rows_in = nullptr, *rows_out = nullptr;
   int64_t n_rows_in = 0, n_rows_out = 0;
   // columns of each listed row, in 3D from 256 cells on: there about half of a row pass's traffic goes.  Smaller
@@ -344,14 +355,15 @@ struct LastAxis {
   int form = 0;
   const T *in2 = nullptr;
 };
-// Whether the columns are solved directly: where the slowest mode decays across the box, s M^2 >= 6 (the isotropic boxes
-// have 9.9 in 2D and 19.7 in 3D, more with a reaction term).  Below that the starting values come out of a difference of
-// nearly equal sums, and on small grids the error exceeds the sine transforms' (root mean square over seeded smooth
-// sources, columns / transforms: s M^2 2.2 1.25 and 1.24 at 16^2 and 32^2, 3 1.21 and 1.35, 4 1.13 and 1.24, 5 1.06 and
-// 1.04, 6.5 0.93 and 1.00; 0.7 to 1.0 from 128 cells on at any of them).  So boxes whose last axis conducts more than
-// 1.6 (2D) or 3.3 (3D) times the others keep the transforms (64^3 FP64 25.1 us against 23.5), as do reaction terms so large
-// (s >= 1e12) that mu drops out of the recursions.
-bool column_direct(int dim, int ncomp, int M, double h, const double D[2][3], double kappa);
+// Whether the columns are solved directly: where the slowest mode decays across the box, s M^2 >= 2 (the isotropic boxes
+// have 9.9 in 2D and 19.7 in 3D, more with a reaction term), and from 6 on in FP64 up to 32 cells.  Below that the
+// starting values come out of a difference of nearly equal sums, whose error the transforms' exceeds on larger grids
+// and in FP32 only.  Root mean square over seeded smooth sources, columns / transforms: FP64 at s M^2 2.1, 3 and 5,
+// 16^2 2.45, 1.20 and 1.11, 32^2 1.24, 1.20 and 0.98, 32^3 1.18, 1.14 and 1.02; 64^2 0.96, 0.91 and 0.87, 64^3 0.92, 0.88
+// and 0.90, 256^2 0.81, 0.73 and 0.73; FP32 0.55 to 0.82 at any size and s M^2.  So boxes whose last axis conducts more
+// than five (2D) or ten (3D) times the others keep the transforms (FP64 up to 32 cells 1.6 and 3.3 times), as do
+// reaction terms so large (s >= 1e12) that mu drops out of the recursions.
+ColumnRule column_direct(int dim, int ncomp, int M, double h, const double D[2][3], double kappa);
 template <typename T>
 void last_axis_direct(const LastAxis<T> &l, hipStream_t st);
 template <typename T>

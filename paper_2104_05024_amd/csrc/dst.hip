@@ -1603,7 +1603,7 @@ template <typename T, int M>
 void solve_last(DevProblem &p, T *a, hipStream_t st, const T *in = nullptr, const PlaneBits *zin = nullptr,
                 const PlaneBits *zout = nullptr, int form = 0, const T *in2 = nullptr) {
   PrecTables<T> &tb = p.tab<T>();
-  if (p.direct) {
+  if (p.columns.of<T>()) {
     LastAxis<T> l;
     l.in = in ? in : a;
     l.out = a;
@@ -1636,7 +1636,7 @@ void run_box(DevProblem &p, const T *src, bool src_plain, T *dst, bool dst_plain
   const int64_t rows = (int64_t)p.ncomp * (p.dim == 3 ? (int64_t)N * N : N);
   auto tic = [&](Timer &t) { t.tic(p.profile, st); };
   auto toc = [&](Timer &t) { t.toc(p.profile, st); };
-  const bool wide = !p.direct && p.ncomp == 1;
+  const bool wide = !p.columns.of<T>() && p.ncomp == 1;
   if (!(skip & 1)) {
     tic(p.t_dst_x);
     pass_x<T, M>(src, src_plain, A, false, rows, tw, sp, st);
@@ -2127,7 +2127,7 @@ template void box_solve<float>(DevProblem &, const float *, bool, float *, bool,
 // Whether a 2D product's passes take only the rows that matter.
 template <typename T>
 static bool rows2d_masked(const DevProblem &p) {
-  return p.sparse && p.direct && row_sets_pay(p.ncomp * p.comp_stride * (int64_t)sizeof(T));
+  return p.sparse && p.columns.of<T>() && row_sets_pay(p.ncomp * p.comp_stride * (int64_t)sizeof(T));
 }
 
 template <typename T, typename TP>

@@ -337,7 +337,7 @@ void upload_tables(DevProblem &p) {
     for (int a = 0; a < 3; ++a) p.D[c][a] = t.D[c < nc_ ? c : 0][a < d ? a : 0];
   p.lam_scale = 1.0;
   for (int a = 0; a < d; ++a) p.lam_scale *= 2.0 / (double)t.cells;
-  p.direct = column_direct(d, nc_, t.cells, t.h, p.D, t.kappa);
+  p.columns = column_direct(d, nc_, t.cells, t.h, p.D, t.kappa);
   const int64_t N = p.N, M = p.M, nc = t.nc, P = p.P, K = t.K, Kn = t.Kn, S = t.S;
   auto padpos = [&](int64_t lin) { return (lin % N) + P * (lin / N); };
   if (padpos(N * (d == 3 ? N * N : N) - 1) >= (int64_t)1 << 31) throw std::invalid_argument("grid too large");

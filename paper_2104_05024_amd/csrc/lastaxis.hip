@@ -473,7 +473,7 @@ __global__ __launch_bounds__(kMultiThreads) void k_column_multi(MultiColumn<T> m
 
 // Smallest s M^2 over the columns (the lowest modes of the other axes): how many times e the
 // slowest solution decays across the box, squared.
-bool column_direct(int dim, int ncomp, int M, double h, const double D[2][3], double kappa) {
+ColumnRule column_direct(int dim, int ncomp, int M, double h, const double D[2][3], double kappa) {
   const double sn = std::sin(0.5 * M_PI / M), lam = 4.0 / (h * h) * sn * sn;
   double b[2], dz[2];
   for (int c = 0; c < 2; ++c) {
@@ -488,7 +488,8 @@ bool column_direct(int dim, int ncomp, int M, double h, const double D[2][3], do
     l = (b[0] * b[1] + kappa * (b[0] + b[1])) / (dz[0] * dz[1]) / big;
   }
   const double s = l * h * h;
-  return s * M * M >= 6.0 && s < 1e12;
+  const bool f32 = s * M * M >= 2.0 && s < 1e12;
+  return {f32 && (M > 32 || s * M * M >= 6.0), f32};
 }
 
 template <typename T>

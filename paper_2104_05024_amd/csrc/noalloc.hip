@@ -86,7 +86,7 @@ void solve(const kfbi_grid &g, const kfbi_coeffs &co, const T *f, T *u, unsigned
     for (int a = 0; a < 3; ++a) p.D[c][a] = co.D[c < co.ncomp ? c : 0][a < d ? a : 0];
   p.lam_scale = 1.0;
   for (int a = 0; a < d; ++a) p.lam_scale *= 2.0 / (double)M;
-  p.direct = column_direct(d, p.ncomp, M, p.h, p.D, p.kappa);
+  p.columns = column_direct(d, p.ncomp, M, p.h, p.D, p.kappa);
   const size_t field = align256((size_t)p.ncomp * p.comp_stride * sizeof(T));
   const size_t twb = align256((size_t)2 * M * sizeof(T)), spb = align256((size_t)(M / 2 + 1) * sizeof(T));
   PrecTables<T> &tb = p.tab<T>();

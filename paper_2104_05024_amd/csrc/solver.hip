@@ -415,7 +415,7 @@ void Solver::release() {
 template <typename T, typename TP>
 void Solver::apply(DevProblem &p, const TP *psi, TP *out, hipStream_t st) {
   // The first row pass forms the correction itself, but on grids and last axes without the row lists' passes.
-  const bool fused = p.sparse && p.Mfft >= 64 && (p.dim == 3 || p.direct);
+  const bool fused = p.sparse && p.Mfft >= 64 && (p.dim == 3 || p.columns.of<T>());
   if (!fused) {
     p.t_correct.tic(p.profile, st);
     launch_correct<T, TP>(p, psi, st);

@@ -26,7 +26,7 @@ CASES = {
     "3d_128": (W.sphere(0.7, 997), W.box(3, 128), W.scalar_coeffs(3, 1.0, 400.0), "dst_x_correct"),
     "3d_256": (W.sphere(0.4, 997), W.box(3, 256), W.scalar_coeffs(3, 1.0, 400.0), "dst_x_correct"),
     "3d_256_pair": (W.sphere(0.3, 997), W.box(3, 256), PAIR3, "dst_x_correct"),
-    "last_axis_64": (W.sphere(0.6, 997), W.box(3, 64), W.Coeffs(1, [[1.0, 1.0, 6.0]], 0.5), "dst_x_correct"),
+    "last_axis_64": (W.sphere(0.6, 997), W.box(3, 64), W.Coeffs(1, [[1.0, 1.0, 16.0]], 0.5), "dst_x_correct"),
 }
 
 
